@@ -205,10 +205,10 @@ def run_config(cfg, steps, warmup, ntok, workers_arg, decode_only, cpu_heads, ca
         "reorder_quantize_us": None if decode_only else float(rq_us.mean()),
         "reorder_quantize_bytes": rq_bytes,
         "reorder_quantize_gbps": None if decode_only else rq_bytes / (float(rq_us.mean()) * 1e-6) / 1e9,
-        "kernel": "decode_quads_kernel" if int(plan.sizes.v_layout) == 1 else "decode_attention_kernel",
-        "kernel_family": ("four query heads per wave on 4x4x4 matrix instructions"
-                          + (", two waves per workgroup sharing their K/V units through shared memory"
-                             if w.num_q_heads // w.num_kv_heads > 4 else "")) if int(plan.sizes.v_layout) == 1
+        "kernel": "decode_attention_kernel" if int(plan.sizes.v_layout) != 1 else
+                  "decode_tiles_kernel" if w.num_q_heads // w.num_kv_heads > 4 else "decode_quads_kernel",
+        "kernel_family": ("up to eight query heads per wave on 16x16x32 matrix instructions" if w.num_q_heads // w.num_kv_heads > 4
+                          else "four query heads per wave on 4x4x4 matrix instructions") if int(plan.sizes.v_layout) == 1
                          else "one query head per wave on the vector ALU (no matrix instructions)",
         "cache_copies": ncopies, "distinct_layers": len(src), "steps": steps, "decode_calls_per_step": ntok,
     }

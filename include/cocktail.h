@@ -266,8 +266,8 @@ int cocktail_reorder_quantize_paged(const cocktail_shape* shape, const cocktail_
  * two calls on the same inputs agree to fp32 summation order, not bit for bit
  * (shapes with Hq/Hkv > 4 use no pools and are reproducible bit for bit, and so is any plan made with
  * cocktail_plan_options::reproducible).  Shapes with Hq = Hkv run one query head per wave on the vector
- * ALU; 2 <= Hq/Hkv <= 8 run four query heads per wave on 4x4x4 matrix instructions (V in token quads), unless
- * the plan asks for the vector ALU only; for larger ratios (up to COCKTAIL_MAX_Q_PER_KV) the query heads of a kv
+ * ALU; 2 <= Hq/Hkv <= 8 run all query heads of a kv head in one wave on matrix instructions (4x4x4 up to four heads,
+ * 16x16x32 beyond; V in token quads), unless the plan asks for the vector ALU only; for larger ratios (up to COCKTAIL_MAX_Q_PER_KV) the query heads of a kv
  * head are cut into equal sets of up to 8 that each read the kv head's blocks (one head per wave if no such set size
  * divides the ratio).
  *
@@ -414,8 +414,7 @@ int cocktail_chunk_bitwidths(int32_t batch, int32_t embed_dim, int32_t total_chu
 
 /*
  * Number of decode workgroups that fills the current HIP device for this shape
- * (compute units x resident waves per unit / waves per workgroup; a workgroup is two waves for
- * 5 <= Hq/Hkv <= 8 and one wave otherwise).  Needs a GPU: EHIP otherwise.
+ * (compute units x resident waves per unit; a workgroup is one wave).  Needs a GPU: EHIP otherwise.
  */
 int cocktail_default_workers(const cocktail_shape* shape, int32_t* num_workers);
 

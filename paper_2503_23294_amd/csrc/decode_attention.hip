@@ -122,13 +122,7 @@ extern "C" int cocktail_default_workers(const cocktail_shape* shape, int32_t* nu
     (void)hipGetLastError();
     return fail(COCKTAIL_EHIP, "no HIP device available");
   }
-  const int rep = shape->num_q_heads / shape->num_kv_heads;
-  const int waves_per_cu = 8;   // two waves per SIMD at <= 256 VGPRs
-  const int wrep = work_rep_of(rep, false);
-  // one-wave workgroups: eight per compute unit; two-wave workgroups (which share their K/V units through 32 KB
-  // of shared memory each): four
-  const int per_cu = uses_token_quads(wrep) ? waves_per_cu / quad_waves(wrep) : waves_per_cu;
-  *num_workers = prop.multiProcessorCount * per_cu;
+  *num_workers = prop.multiProcessorCount * 8;   // one-wave workgroups, two waves per SIMD at <= 256 VGPRs
   return COCKTAIL_OK;
 }
 
@@ -257,7 +251,10 @@ int decode_enqueue(const cocktail_shape* shape, const PlanHeader* hd, const void
                                      : (hd->work_rep == hd->rep && hd->packed_bytes >= kNonTemporalMinBytes);
     const bool int8 = hd->class_blocks[2] > 0;
     const bool d64 = shape->head_dim == 64;
-    const hipError_t e = quads ? (d64 ? launch_decode_quads<64>(p, shape->group_size, nt, int8, int(grid.x), st)
+    const bool tiles = quads && uses_tiles(p.rep);
+    const hipError_t e = tiles ? (d64 ? launch_decode_tiles<64>(p, shape->group_size, nt, int8, int(grid.x), st)
+                                      : launch_decode_tiles<128>(p, shape->group_size, nt, int8, int(grid.x), st))
+                       : quads ? (d64 ? launch_decode_quads<64>(p, shape->group_size, nt, int8, int(grid.x), st)
                                       : launch_decode_quads<128>(p, shape->group_size, nt, int8, int(grid.x), st))
                                : (d64 ? launch_decode_heads<64>(p, shape->group_size, nt, int8, int(grid.x), st)
                                       : launch_decode_heads<128>(p, shape->group_size, nt, int8, int(grid.x), st));

@@ -78,7 +78,6 @@ __device__ __forceinline__ rsrc_t make_rsrc(const char* base, uint32_t bytes) {
 // MI355X is worth 10 % of HBM throughput); shapes in which several workgroups walk the blocks of one kv head,
 // and small caches that stay resident between calls, use the default policy.
 constexpr int kAuxDefault = 0, kAuxNonTemporal = 2;
-typedef __attribute__((address_space(3))) char* lds_ptr_t;   // a wave-uniform address in shared memory
 constexpr int64_t kNonTemporalMinBytes = int64_t(64) << 20;   // packed K+V bytes of one call
 template <int AUX>
 __device__ __forceinline__ u32x4 load16(rsrc_t rs, uint32_t voff, uint32_t soff) {
@@ -168,28 +167,6 @@ struct QuantClass {
     } else {
       s.meta[0] = __builtin_amdgcn_raw_buffer_load_b32(rs, vm, moff, AUX);
     }
-  }
-
-  // The same unit fetched into shared memory instead (workgroups whose waves share their K/V units): the
-  // image is what the lanes of one wave would hold in registers, piece p of lane l at p*1024 + l*16 and
-  // scale/zero dword g of lane l at PH*1024 + g*256 + l*4; the loads write it without passing through registers.
-  static constexpr int LDS_UNIT = PH * 1024 + NGH * 256;
-  template <int AUX>
-  __device__ static __forceinline__ void load_lds(lds_ptr_t dst, rsrc_t rs, int u, uint32_t vc, uint32_t vm) {
-    const uint32_t boff = uint32_t(u / UPB) * BLOCKB;
-    const uint32_t sub = uint32_t(u % UPB);
-#pragma unroll
-    for (int p = 0; p < PH; ++p)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst + p * 1024, 16, vc, boff + sub * (UT * 16) + p * (kTB * 16), 0, AUX);
-    const uint32_t moff = boff + kTB * ROWB + sub * (UT * 4 * NG);
-#pragma unroll
-    for (int g = 0; g < NGH; ++g) __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst + PH * 1024 + g * 256, 4, vm + g * 4, moff, 0, AUX);
-  }
-  __device__ static __forceinline__ void read_lds(Stage& s, const char* src, int lane) {
-#pragma unroll
-    for (int p = 0; p < PH; ++p) s.pc[p] = *reinterpret_cast<const u32x4*>(src + p * 1024 + lane * 16);
-#pragma unroll
-    for (int g = 0; g < NGH; ++g) s.meta[g] = *reinterpret_cast<const uint32_t*>(src + PH * 1024 + g * 256 + lane * 4);
   }
 
   // this lane's half of q.k^ (natural units, before the softmax scale)
@@ -286,18 +263,6 @@ struct HalfClass {
     const uint32_t boff = uint32_t(u / UPB) * BLOCKB + uint32_t(u % UPB) * (UT * 16);
 #pragma unroll
     for (int p = 0; p < PH; ++p) s.pc[p] = load16<AUX>(rs, vc, boff + p * (kTB * 16));
-  }
-
-  static constexpr int LDS_UNIT = PH * 1024;   // see QuantClass::load_lds
-  template <int AUX>
-  __device__ static __forceinline__ void load_lds(lds_ptr_t dst, rsrc_t rs, int u, uint32_t vc, uint32_t) {
-    const uint32_t boff = uint32_t(u / UPB) * BLOCKB + uint32_t(u % UPB) * (UT * 16);
-#pragma unroll
-    for (int p = 0; p < PH; ++p) __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst + p * 1024, 16, vc, boff + p * (kTB * 16), 0, AUX);
-  }
-  __device__ static __forceinline__ void read_lds(Stage& s, const char* src, int lane) {
-#pragma unroll
-    for (int p = 0; p < PH; ++p) s.pc[p] = *reinterpret_cast<const u32x4*>(src + p * 1024 + lane * 16);
   }
 
   __device__ static __forceinline__ float half_logit(const Stage& s, const uint32_t (&q)[DH / 2],
@@ -495,10 +460,11 @@ __device__ __forceinline__ AppendSlice append_slice(int idx) {
   const int b = a.bh / kp->num_kv_heads;
   const int first = sl * kAppendSliceBlocks;
   a.tokens = uni(min(max(appended_count(b) - first * kTB, 0), kAppendSliceBlocks * kTB));
-  a.blocks = min(kAppendSliceBlocks, kp->app_blocks - first);
+  // (the divisions are done on the vector unit: back to scalars, or every load would loop over its buffer resource)
+  a.blocks = uni(min(kAppendSliceBlocks, kp->app_blocks - first));
   // the append buffers are laid out by (sequence, kv head of the cache)
-  a.first_block = (b * (kp->num_kv_heads / kp->kv_share) + (a.bh % kp->num_kv_heads) / kp->kv_share) * kp->app_blocks + first;
-  a.qrow = b * kp->num_q_heads + (a.bh % kp->num_kv_heads) * kp->rep;
+  a.first_block = uni((b * (kp->num_kv_heads / kp->kv_share) + (a.bh % kp->num_kv_heads) / kp->kv_share) * kp->app_blocks + first);
+  a.qrow = uni(b * kp->num_q_heads + (a.bh % kp->num_kv_heads) * kp->rep);
   a.pid = uni(kp->bh_off[a.bh + 1]) - slices + sl;
   return a;
 }
@@ -513,12 +479,14 @@ __device__ __forceinline__ void write_neutral(int slot, int r, int lane) {
   for (int i = 0; i < HD / 64; ++i) out[kPartialFloats + 64 * i + lane] = 0.f;
 }
 
-// Launch the partial-state kernels for head_dim HD (one translation unit per head_dim and kernel family):
-// one query head per wave on the vector ALU; 2 to 8 query heads per kv head on matrix instructions, `grid`
-// workgroups of one wave (up to 4 heads) or two waves (5 to 8).  int8: the cache has an INT8 class.
+// Launch the partial-state kernels for head_dim HD (one translation unit per head_dim and kernel family), `grid`
+// workgroups of one wave: one query head per wave on the vector ALU; 2 to 4 query heads per wave on 4x4x4 matrix
+// instructions, 5 to 8 on 16x16x32 ones.  int8: the cache has an INT8 class.
 template <int HD>
 hipError_t launch_decode_heads(const DecodeParams& p, int group_size, bool non_temporal, bool int8, int grid, hipStream_t st);
 template <int HD>
 hipError_t launch_decode_quads(const DecodeParams& p, int group_size, bool non_temporal, bool int8, int grid, hipStream_t st);
+template <int HD>
+hipError_t launch_decode_tiles(const DecodeParams& p, int group_size, bool non_temporal, bool int8, int grid, hipStream_t st);
 
 }  // namespace cocktail

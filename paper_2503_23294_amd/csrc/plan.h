@@ -35,11 +35,11 @@ constexpr int kMaxPoolSegments = 32;           // segments one pool may touch (a
 // blocks of append capacity (one partial state each), so a long generation does not hang on a single wave.
 constexpr int kAppendSliceBlocks = 8;
 constexpr int kCounterStride = 32;             // uint32 slots between two pool counters (one 128-byte line each)
-// Query heads per kv head for which a wave serves four of them at a time with matrix instructions and V is
-// stored in token quads: 2 to 4 heads take one wave per workgroup, 5 to 8 two waves (one per head quad).
+// Query heads per kv head for which one wave serves all of them with matrix instructions and V is stored in token quads.
 constexpr int kQuadMinRep = 2, kQuadMaxRep = 8;
 __host__ __device__ inline bool uses_token_quads(int rep) { return rep >= kQuadMinRep && rep <= kQuadMaxRep; }
-__host__ __device__ inline int quad_waves(int rep) { return (rep + 3) / 4; }
+// Of these, 5 to 8 heads run on the kernel with eight heads per wave (16x16x32 instructions), 2 to 4 on the one with four.
+__host__ __device__ inline bool uses_tiles(int rep) { return rep > 4 && rep <= kQuadMaxRep; }
 // Query heads one workgroup serves when rep = Hq / Hkv heads share a kv head: all of them up to kQuadMaxRep; beyond
 // that the heads of a kv head are cut into equal sets (the largest divisor of rep that the matrix kernel takes),
 // each walking the kv head's blocks by itself; 1 (a wave per query head, vector ALU) if there is no such divisor

@@ -288,9 +288,7 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
   Tuning tune = read_tuning();
   int pool_percent = tune.pool_percent;
   const int rep = shape->num_q_heads / Hkv;
-  // 2 to 4 query heads per kv head are served by one wave (token-quad form of V); beyond that the query
-  // heads run as two or more waves of one workgroup on the same blocks, where a pool would need a ticket
-  // shared by those waves, so those shapes keep the purely static split
+  // 5 to 8 query heads per kv head keep the purely static split: their calls are reproducible bit for bit
   // Up to eight query heads of a kv head are served by one workgroup.  Where more of them share a kv head they are
   // cut into equal sets, and with one wave per query head (the vector-ALU kernel, on request) every head is a set
   // of its own: each set walks the blocks of its kv head as if they were its own.
@@ -301,7 +299,7 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
   if (quads && !tune.weight_set)
     for (int c = 0; c < NC; ++c) tune.weight[c] = kQuadCostWeight[c];
   const int64_t* weight = tune.weight;
-  if ((wrep > 1 && !(quads && quad_waves(wrep) == 1)) || reproducible) pool_percent = 0;
+  if ((wrep > 1 && !(quads && !uses_tiles(wrep))) || reproducible) pool_percent = 0;
 
   // ---- physical runs of the class buffers: (class, b, h) order, each a contiguous run of blocks ----
   struct Run {
@@ -354,7 +352,7 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
     // scale every worker's share by the measured relative speed of its class next to its mate's class.
     std::vector<double> wcap(P, 1.0), gfrac(NGR + 1, 0.0);
     const bool pair_speed = pair_speed_on && !layout && P % 2 == 0 && P >= 2 * group_workers &&
-                            (wrep == 1 || (tune.pair_table_set && quads && quad_waves(wrep) == 1));
+                            (wrep == 1 || (tune.pair_table_set && quads));
     for (int round = 0; round < (pair_speed ? 4 : 1); ++round) {
       double total_cap = 0.0;
       for (int w = 0; w < P; ++w) total_cap += wcap[w];

@@ -181,6 +181,20 @@ def test_head_dim_64_long_sequences_with_pools(rep, workers):
     ck.cocktail_decode_check(c.cache)
 
 
+@pytest.mark.parametrize("rep,head_dim,group", [(5, 128, 32), (8, 128, 64), (7, 128, 128), (8, 64, 32), (6, 64, 64)])
+def test_eight_heads_per_wave_at_the_edges_of_its_tiles(rep, head_dim, group):
+    """Runs of every class whose lengths lie around the 16-token sets, the 32-token granules, the 64-token blocks and
+    the iteration sizes of the kernel for five to eight query heads, on many and on few workers."""
+    lens = [1, 15, 16, 17, 31, 33, 64, 65, 127, 129, 255, 257]
+    for mix in ((0, 0, 0, 1), (0, 0, 1, 0), (0, 1, 0, 0), (1, 0, 0, 0), (0.25, 0.25, 0.25, 0.25)):
+        w = workloads.small(f"tiles_r{rep}", len(lens), 2 * rep, 2, lens, 1, group, mix=mix, head_dim=head_dim, seed_offset=900 + rep)
+        _announce(f"{w.name} d{head_dim} g{group} mix={mix}")
+        for workers in (2, 64):
+            c = Case(w, workers=workers)
+            c.check_all()
+            ck.cocktail_decode_check(c.cache)
+
+
 @pytest.mark.parametrize("mix", [(1, 0, 0), (0, 1, 0), (0, 0, 1), (0.5, 0, 0.5), (0, 1, 0, 0), (0.3, 0.3, 0, 0.4),
                                  (0, 0.5, 0.5, 0), (0.25, 0.25, 0.25, 0.25)])
 def test_single_class_and_missing_class(mix):

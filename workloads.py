@@ -82,7 +82,7 @@ def config(n: int) -> Workload:
                         (1 / 3, 1 / 3, 1 / 3), dirichlet=True)
     if n == 6:
         # not one of the benchmark's five: a Llama-3-70B-shaped layer (8 query heads per kv head), the shape the
-        # two-wave grouped-query kernel is profiled on
+        # kernel for five to eight query heads is profiled on
         return Workload("x6_gqa_64q_8kv_128k_b4", 6, 4, 64, 8, 128, 256, 32, (131072,) * 4, (0.15, 0.35, 0.5))
     if n == 7:
         # extra: head_dim 64 (64 heads of 64 channels, one query head per kv head), 128K context
