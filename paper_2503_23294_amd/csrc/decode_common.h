@@ -116,6 +116,84 @@ __device__ __forceinline__ Segment uni(const Segment& x) {
 // Zero-instruction anchor: the value must exist in a VGPR at this point of the program order.
 __device__ __forceinline__ void pin(float& x) { asm volatile("" : "+v"(x)); }
 
+// Sum (maximum) over the sixteen lanes of a row; every lane gets it.
+template <int N>
+__device__ __forceinline__ float row_ror(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x120 + N, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float row_sum(float x) {
+  x += row_ror<8>(x), x += row_ror<4>(x), x += row_ror<2>(x);
+  return x + row_ror<1>(x);
+}
+__device__ __forceinline__ float row_max(float x) {
+  x = fmaxf(x, row_ror<8>(x)), x = fmaxf(x, row_ror<4>(x)), x = fmaxf(x, row_ror<2>(x));
+  return fmaxf(x, row_ror<1>(x));
+}
+// (x of lanes 0-31, y of lanes 0-31) and (x of lanes 32-63, y of lanes 32-63)
+__device__ __forceinline__ void swap_halves(float x, float y, float& lo, float& hi) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, y), false, false);
+  lo = __builtin_bit_cast(float, uint32_t(r[0])), hi = __builtin_bit_cast(float, uint32_t(r[1]));
+}
+// Sum (maximum) of a lane's value and that of the lane 32 further on; every lane gets it.
+__device__ __forceinline__ float both_halves(float x, bool maximum) {
+  float lo, hi;
+  swap_halves(x, x, lo, hi);
+  return maximum ? fmaxf(lo, hi) : lo + hi;
+}
+
+// The same for the two rows of each half of the wave.
+__device__ __forceinline__ void swap_rows(float x, float y, float& even, float& odd) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, y), false, false);
+  even = __builtin_bit_cast(float, uint32_t(r[0])), odd = __builtin_bit_cast(float, uint32_t(r[1]));
+}
+// Sum over the lanes that hold different tokens in the flushes: the 32 lanes of a half (UT = 32) or all 64.
+template <int UT>
+__device__ __forceinline__ float token_sum(float x) {
+  float a, b;
+  x = row_sum(x);
+  swap_rows(x, x, a, b);
+  x = a + b;
+  return UT == 64 ? both_halves(x, false) : x;
+}
+
+// Halving steps of a sum over lanes.  Lane pairs that differ in one bit of their position add up two values: the lane with
+// the bit clear ends up with x's sum, the other one with y's, so every step halves the number of values a lane holds.
+__device__ __forceinline__ float fold32(float x, float y) {
+  float a, b;
+  swap_halves(x, y, a, b);
+  return a + b;
+}
+__device__ __forceinline__ float fold16(float x, float y) {
+  float a, b;
+  swap_rows(x, y, a, b);
+  return a + b;
+}
+// (an operand read from another lane needs two wait states after the instruction that wrote it; the compiler does not see
+// into the asm)
+#define COCKTAIL_FOLD(NAME, X, XBANKS, Y, YBANKS)                                                   \
+  __device__ __forceinline__ float NAME(float x, float y) {                                       \
+    float r;                                                                                      \
+    asm("s_nop 1\n\tv_add_f32_dpp %0, %1, %1 " X " row_mask:0xf bank_mask:" XBANKS                 \
+        "\n\tv_add_f32_dpp %0, %2, %2 " Y " row_mask:0xf bank_mask:" YBANKS                        \
+        : "=&v"(r)                                                                                \
+        : "v"(x), "v"(y));                                                                        \
+    return r;                                                                                     \
+  }
+COCKTAIL_FOLD(fold8, "row_ror:8", "0xf", "row_ror:8", "0xc")               // lane and lane ^ 8
+COCKTAIL_FOLD(fold4, "row_shl:4", "0x5", "row_shr:4", "0xa")               // lane and lane ^ 4
+COCKTAIL_FOLD(fold7, "row_half_mirror", "0xf", "row_half_mirror", "0xa")   // lane and lane ^ 7, by bit 2
+#undef COCKTAIL_FOLD
+template <int CTRL>
+__device__ __forceinline__ float quad_lane(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float fold2(float x, float y, bool bit) {   // lane and lane ^ 2
+  return (bit ? y : x) + quad_lane<0x4E>(bit ? x : y);
+}
+__device__ __forceinline__ float fold1(float x, float y, bool bit) {   // lane and lane ^ 1
+  return (bit ? y : x) + quad_lane<0xB1>(bit ? x : y);
+}
+
 template <int NGH>
 struct LaneState {
   float acc[DH];       // sum_t p_t * (scale * code | value) for this lane's 64 channels

@@ -38,7 +38,6 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 
 constexpr float kTopExp = 15.0f;     // p * scale stays below 2^kTopExp (fp16 holds up to 2^16 - 32)
 constexpr float kHeadroom = 4.0f;    // log2 units left to grow into when the reference is moved
-constexpr int kRedStride = 36;      // floats per lane in the reduction tile (32 + padding, 16-byte aligned rows)
 
 __device__ __forceinline__ f4 mfma4(u32x2 a, u32x2 b, f4 c) {
   return __builtin_amdgcn_mfma_f32_4x4x4f16(__builtin_bit_cast(h4, a), __builtin_bit_cast(h4, b), c, 0, 0, 0);
@@ -253,55 +252,68 @@ __device__ __forceinline__ void softmax_quads(const f4 (&s)[J], const float (&ev
   }
 }
 
-// Writes the partial states `pid` of the wave's query heads: (m, l, o[HD]) per head, reduced over the lanes.
+// Writes the partial states `pid` of the wave's query heads: (m, l, tokens, o[HD]) per head, summed over the lanes in
+// registers (decode_common.h: the fold steps).
 template <int HD, class CLS, int NGH, int GL>
-__device__ __forceinline__ void flush_quads(const QuadState<NGH>& st, float* red, int pid, int lane, int tokens) {
+__device__ __forceinline__ void flush_quads(const QuadState<NGH>& st, int pid, int lane, int tokens) {
   constexpr int UT = Geo<HD>::UT;
+  constexpr int STRIDE = HD + kPartialFloats;
   kparams_t prm = kparams();
   const int rep = prm->rep;
-  // quantities kept per token lane: add up the lanes that hold different tokens (at head_dim 128 the 32 lanes
-  // of each half; both halves hold the same p)
-  f4 l = st.l;
-  f4 z[NGH];
+  // quantities kept per token lane: the lanes that hold different tokens (at head_dim 128 the 32 lanes of each half;
+  // both halves hold the same p)
+  f4 l, z[NGH];
 #pragma unroll
-  for (int g = 0; g < NGH; ++g) z[g] = st.zacc[g];
+  for (int i = 0; i < 4; ++i) {
+    l[i] = token_sum<UT>(st.l[i]);
 #pragma unroll
-  for (int o = UT / 2; o > 0; o >>= 1) {
-    l += shfl_xor4(l, o);
-#pragma unroll
-    for (int g = 0; g < NGH; ++g) z[g] += shfl_xor4(z[g], o);
+    for (int g = 0; g < NGH; ++g) z[g][i] = token_sum<UT>(st.zacc[g][i]);
   }
-  constexpr int STRIDE = HD + kPartialFloats;
   float* out = prm->ws + int64_t(pid) * rep * STRIDE;
   if (lane < rep) {
     out[lane * STRIDE] = pick(st.m, lane);
     out[lane * STRIDE + 1] = pick(l, lane);
     out[lane * STRIDE + 2] = __int_as_float(tokens);
   }
-  // channel accumulators: lane 32h + 4b + j holds the sum over the tokens of quad b for 16 channels of half h
-  // (head_dim 64: one half, sixteen quads over the 64 lanes); the quads are added through a shared-memory
-  // tile, eight of the sixteen channels at a time.
-  // Reader lane (h, head i, x) adds up, for j = 0..3, channel 64h + 32ps + 8j + x of head i.
-  constexpr int NQ = UT / 4;   // token quads per unit
-  const int hh = HD == 64 ? 0 : lane >> 5, ii = (lane >> 3) & 3, xx = lane & 7;
-  const bool reader = HD == 128 || lane < 32;
+  // channel accumulators: lane 32h + 4b + j (head_dim 64: 4b + j) holds the sum over the tokens of quad b for its channels
+  // e = 0..15.  The steps over the bits of b leave four consecutive channels e = 8 e3 + 4 e2 + {0..3} and two heads (one)
+  // per lane; the factor of a channel depends on e % 4 only.
+  const f4 zz = NGH == 2 ? (lane & (HD == 64 ? 32 : 16) ? z[NGH - 1] : z[0]) : z[0];   // by e3: the half of 32 channels
+  f4 o[2];
 #pragma unroll
-  for (int ps = 0; ps < 2; ++ps) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+  for (int e = 0; e < 4; ++e) {
 #pragma unroll
-    for (int e8 = 0; e8 < 8; ++e8)
-      *reinterpret_cast<f4*>(red + lane * kRedStride + e8 * 4) = st.acc[ps * 8 + e8] * CLS::fac(ps * 8 + e8);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const float zv = pick(z[(32 * ps) / GL < NGH ? (32 * ps) / GL : 0], ii);
+    for (int i = 0; i < 2; ++i) {
+      float w[2];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      float sum = 0.f;
+      for (int x = 0; x < 2; ++x) {
+        const int hd = i + 2 * x;
+        if constexpr (HD == 64)
+          w[x] = fold16(fold32(st.acc[e][hd], st.acc[e + 8][hd]), fold32(st.acc[e + 4][hd], st.acc[e + 12][hd]));
+        else
+          w[x] = fold8(fold16(st.acc[e][hd], st.acc[e + 8][hd]), fold16(st.acc[e + 4][hd], st.acc[e + 12][hd]));
+      }
+      o[i][e] = HD == 64 ? fold8(w[0], w[1]) : fold4(w[0], w[1]);
+      sched_fence();   // one after the other: the register stages of the next piece leave little room
+    }
+  }
+  const int j = lane & 3;
+  if constexpr (HD == 64) {
 #pragma unroll
-      for (int b = 0; b < NQ; ++b) sum += red[(32 * hh + 4 * b + j) * kRedStride + xx * 4 + ii];
-      if (reader && ii < rep) out[ii * STRIDE + kPartialFloats + 64 * hh + 32 * ps + 8 * j + xx] = sum + zv;
+    for (int e = 0; e < 4; ++e) o[0][e] = fold4(o[0][e], o[1][e]);
+    const int head = 2 * ((lane >> 3) & 1) + ((lane >> 2) & 1), ch = 32 * (lane >> 5) + 8 * j + 4 * ((lane >> 4) & 1);
+    const float zh = pick(zz, head);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[0][e] = o[0][e] * CLS::fac(e) + zh;
+    if (head < rep) *reinterpret_cast<f4*>(out + head * STRIDE + kPartialFloats + ch) = o[0];
+  } else {
+    const int head0 = 2 * ((lane >> 2) & 1), ch = 64 * (lane >> 5) + 32 * ((lane >> 4) & 1) + 8 * j + 4 * ((lane >> 3) & 1);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const float zh = lane & 4 ? zz[2 + i] : zz[i];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[i][e] = o[i][e] * CLS::fac(e) + zh;
+      if (head0 + i < rep) *reinterpret_cast<f4*>(out + (head0 + i) * STRIDE + kPartialFloats + ch) = o[i];
     }
   }
 }
@@ -342,7 +354,7 @@ __device__ __forceinline__ void begin_quads(int qrow, int h, int lane, QuadState
 
 // The quad kernel's version of the one-head kernel's run_class: same pipeline, four heads per wave.
 template <int HD, class CLS, int CID, int G, int AUX>
-__device__ __forceinline__ void run_quads(Stream<HD>& sm, Piece& cur, float* red, int lane, bool app = false) {
+__device__ __forceinline__ void run_quads(Stream<HD>& sm, Piece& cur, int lane, bool app = false) {
   constexpr int NGH = CLS::NGH;
   constexpr int GL = G < DH ? G : DH;
   constexpr int J = CLS::J;
@@ -411,7 +423,7 @@ __device__ __forceinline__ void run_quads(Stream<HD>& sm, Piece& cur, float* red
       CLS::template load<AUX>(vs[jj], vrs, jj < rn ? ru + jj : roob, vc, vm);
       sched_fence();
     }
-    if (!more || nxt.fresh) flush_quads<HD, CLS, NGH, GL>(st, red, pid, lane, covered);
+    if (!more || nxt.fresh) flush_quads<HD, CLS, NGH, GL>(st, pid, lane, covered);
     if (!more) break;
     if (nxt.fresh) {
       pid = nxt.pid;
@@ -432,7 +444,7 @@ __device__ __forceinline__ void write_neutral_heads(int slot, int lane) {
 }
 
 template <int HD, int G, int AUX>
-__device__ __forceinline__ void appended_tokens_quads(int idx, float* red, int lane) {
+__device__ __forceinline__ void appended_tokens_quads(int idx, int lane) {
   const AppendSlice a = append_slice(idx);
   if (a.tokens <= 0) {
     write_neutral_heads<HD>(a.pid, lane);
@@ -441,19 +453,18 @@ __device__ __forceinline__ void appended_tokens_quads(int idx, float* red, int l
   Stream<HD> sm;
   sm.init_run(kFp16Class, a.tokens, a.first_block, a.blocks, a.qrow, a.pid);
   Piece cur = sm.next(lane);
-  if (cur.nu > 0) run_quads<HD, QuadHalf<HD, G>, kFp16Class, G, AUX>(sm, cur, red, lane, true);
+  if (cur.nu > 0) run_quads<HD, QuadHalf<HD, G>, kFp16Class, G, AUX>(sm, cur, lane, true);
 }
 
 // One single-wave workgroup per worker.
 template <int HD, int G, int AUX, bool INT8>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void decode_quads_kernel(DecodeParams) {
-  __shared__ __attribute__((aligned(16))) float red[64 * kRedStride];   // the reduction tile of a flush
   const int lane = threadIdx.x;
 #ifdef COCKTAIL_TRACE
   const uint64_t t_start = __builtin_amdgcn_s_memrealtime();
 #endif
   if (int(blockIdx.x) >= kparams()->num_workers) {
-    appended_tokens_quads<HD, G, AUX>(int(blockIdx.x) - kparams()->num_workers, red, lane);
+    appended_tokens_quads<HD, G, AUX>(int(blockIdx.x) - kparams()->num_workers, lane);
     return;
   }
   Stream<HD> sm;
@@ -461,13 +472,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void de
   Piece cur = sm.next(lane);
   while (cur.nu > 0) {
     if (cur.cls == 0) {
-      run_quads<HD, QuadQuant<HD, 2, G>, 0, G, AUX>(sm, cur, red, lane);
+      run_quads<HD, QuadQuant<HD, 2, G>, 0, G, AUX>(sm, cur, lane);
     } else if (cur.cls == 1) {
-      run_quads<HD, QuadQuant<HD, 4, G>, 1, G, AUX>(sm, cur, red, lane);
+      run_quads<HD, QuadQuant<HD, 4, G>, 1, G, AUX>(sm, cur, lane);
     } else if (INT8 && cur.cls == 2) {
-      if constexpr (INT8) run_quads<HD, QuadQuant<HD, 8, G>, 2, G, AUX>(sm, cur, red, lane);
+      if constexpr (INT8) run_quads<HD, QuadQuant<HD, 8, G>, 2, G, AUX>(sm, cur, lane);
     } else {
-      run_quads<HD, QuadHalf<HD, G>, kFp16Class, G, AUX>(sm, cur, red, lane);
+      run_quads<HD, QuadHalf<HD, G>, kFp16Class, G, AUX>(sm, cur, lane);
     }
   }
   for (int i = 0; i < sm.nps; ++i) {

@@ -42,31 +42,6 @@ __device__ __forceinline__ f4 mfma16(u32x4 a, u32x4 b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h8, b), c, 0, 0, 0);
 }
 
-// Sum (maximum) over the sixteen lanes of a row; every lane gets it.
-template <int N>
-__device__ __forceinline__ float row_ror(float x) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x120 + N, 0xf, 0xf, false));
-}
-__device__ __forceinline__ float row_sum(float x) {
-  x += row_ror<8>(x), x += row_ror<4>(x), x += row_ror<2>(x);
-  return x + row_ror<1>(x);
-}
-__device__ __forceinline__ float row_max(float x) {
-  x = fmaxf(x, row_ror<8>(x)), x = fmaxf(x, row_ror<4>(x)), x = fmaxf(x, row_ror<2>(x));
-  return fmaxf(x, row_ror<1>(x));
-}
-// (x of lanes 0-31, y of lanes 0-31) and (x of lanes 32-63, y of lanes 32-63)
-__device__ __forceinline__ void swap_halves(float x, float y, float& lo, float& hi) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, y), false, false);
-  lo = __builtin_bit_cast(float, uint32_t(r[0])), hi = __builtin_bit_cast(float, uint32_t(r[1]));
-}
-// The values of this token over the lanes that hold other tokens of the same heads: both halves of the wave.
-__device__ __forceinline__ float both_halves(float x, bool maximum) {
-  float lo, hi;
-  swap_halves(x, x, lo, hi);
-  return maximum ? fmaxf(lo, hi) : lo + hi;
-}
-
 // N dwords at a lane's offset, in the widest loads that fit; more than 16 bytes continue in the next piece of the row
 template <int N>
 struct Words {
