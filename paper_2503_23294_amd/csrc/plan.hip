@@ -503,6 +503,7 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
       }
       // own ranges: [G0, Gp) in k parts of equal cost
       const int64_t cp = cost_at(Gp, sGp);
+      const int64_t own_q = (cp - c0) / k, own_r = (cp - c0) % k;
       int sc = sG0;
       int32_t prev = G0;
       int sprev = sG0;
@@ -512,7 +513,7 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
         if (r == k - 1) {
           nb = Gp, snb = sGp;
         } else {
-          nb = block_at(c0 + static_cast<int64_t>((static_cast<__int128>(cp - c0) * (r + 1)) / k), sc);
+          nb = block_at(c0 + own_q * (r + 1) + own_r * (r + 1) / k, sc);   // c0 + (cp - c0) (r + 1) / k without 128-bit arithmetic
           snb = sc;
           if (nb > Gp) nb = Gp, snb = sGp;
           if (nb < prev) nb = prev, snb = sprev;
@@ -587,44 +588,50 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
     }
   }
 
-  // ---- reorder+quantize records: one per block of the class buffers ----
+  // reorder+quantize records, one per block of the class buffers: the largest array of a plan by far (2.6 MB for 40 heads of
+  // 128K tokens), so they are written straight into the blob, and not at all when only the sizes are asked for
+  const int64_t num_items = int64_t(v_blk_base[NC * B + 0]) + v_blk_base[NC * B + 1] + v_blk_base[NC * B + 2] + v_blk_base[NC * B + 3];
   // (blocks of an FP16 run that are only room to grow get a record without valid rows: they are written as zeros)
-  std::vector<RQItem> rq_items;
-  rq_items.reserve(v_blk_base[NC * B + 0] + v_blk_base[NC * B + 1] + v_blk_base[NC * B + 2] + v_blk_base[NC * B + 3]);
-  for (int c = 0; c < NC; ++c)
-    for (int b = 0; b < B; ++b) {
-      const int nb = v_cap[NC * b + c], ntok = v_ct[NC * b + c];
-      if (nb == 0) continue;
-      const int n = seq_lens[b] / C;
-      const int32_t* pb = v_perm.data() + v_chunk_off[b];
-      const int cc0 = v_cc0[NC * b + c];
-      const int tail = seq_lens[b] - n * C;
-      const int chunk_tokens = c == kFp16Class ? ntok - tail : ntok;
-      auto src_token = [&](int r) {   // source token of row r of the class (Alg. 1 order; tail after the FP16 chunks)
-        if (r < chunk_tokens) return pb[cc0 + r / C] * C + r % C;
-        return n * C + (r - chunk_tokens);
-      };
-      std::vector<RQItem> head_items(nb);
-      for (int j = 0; j < nb; ++j) {
-        RQItem& it = head_items[j];
-        std::memset(&it, 0, sizeof(it));
-        const int r0 = j * kTB;
-        const int nvalid = ntok - r0 < kTB ? (ntok > r0 ? ntok - r0 : 0) : kTB;
-        it.b = b, it.j = j;
-        it.cls_nvalid = c | (nvalid << 8);
-        if (nvalid == 0) continue;   // room to grow: t0 = 0, nothing is read
-        const int t0 = src_token(r0);
-        // rows are consecutive tokens iff the last one is (chunks keep their order, so tokens in between are too)
-        it.t0 = src_token(r0 + nvalid - 1) == t0 + nvalid - 1 ? t0 : -1;
-      }
-      for (int h = 0; h < Hkv; ++h)
+  auto write_items = [&](RQItem* out) {
+    for (int c = 0; c < NC; ++c)
+      for (int b = 0; b < B; ++b) {
+        const int nb = v_cap[NC * b + c], ntok = v_ct[NC * b + c];
+        if (nb == 0) continue;
+        const int n = seq_lens[b] / C;
+        const int32_t* pb = v_perm.data() + v_chunk_off[b];
+        const int cc0 = v_cc0[NC * b + c];
+        const int tail = seq_lens[b] - n * C;
+        const int chunk_tokens = c == kFp16Class ? ntok - tail : ntok;
+        auto src_token = [&](int r) {   // source token of row r of the class (Alg. 1 order; tail after the FP16 chunks)
+          if (r < chunk_tokens) return pb[cc0 + r / C] * C + r % C;
+          return n * C + (r - chunk_tokens);
+        };
+        const int64_t row0 = v_cum[b] * Hkv;   // first source row of the sequence in the ragged layout
         for (int j = 0; j < nb; ++j) {
-          RQItem it = head_items[j];
-          it.h = h;
-          it.ragged_row = (v_cum[b] * Hkv + int64_t(h) * seq_lens[b]) + (it.t0 >= 0 ? it.t0 : 0);
-          rq_items.push_back(it);
+          RQItem it;
+          std::memset(&it, 0, sizeof(it));
+          const int r0 = j * kTB;
+          const int nvalid = ntok - r0 < kTB ? (ntok > r0 ? ntok - r0 : 0) : kTB;
+          it.b = b, it.j = j;
+          it.cls_nvalid = c | (nvalid << 8);
+          if (nvalid > 0) {   // else room to grow: t0 = 0, nothing is read
+            const int t0 = src_token(r0);
+            // rows are consecutive tokens iff the last one is (chunks keep their order, so tokens in between are too)
+            it.t0 = src_token(r0 + nvalid - 1) == t0 + nvalid - 1 ? t0 : -1;
+          }
+          it.ragged_row = row0 + (it.t0 >= 0 ? it.t0 : 0);
+          out[j] = it;
         }
-    }
+        for (int h = 1; h < Hkv; ++h)   // the other heads: the same rows, seq_lens[b] further on each
+          for (int j = 0; j < nb; ++j) {
+            RQItem it = out[j];
+            it.h = h;
+            it.ragged_row += int64_t(h) * seq_lens[b];
+            out[int64_t(h) * nb + j] = it;
+          }
+        out += int64_t(Hkv) * nb;
+      }
+  };
 
   // ---- sizes and blob layout ----
   PlanHeader hd;
@@ -668,7 +675,7 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
   place(hd.off_worker_rec, int64_t(sizeof(WorkerRec)) * P);
   place(hd.off_group_rec, int64_t(sizeof(GroupRec)) * NG);
   place(hd.off_pool_seg, int64_t(sizeof(PoolSeg)) * NPS);
-  place(hd.off_rq_items, int64_t(sizeof(RQItem)) * int64_t(rq_items.size()));
+  place(hd.off_rq_items, int64_t(sizeof(RQItem)) * num_items);
   off = (off + 127) & ~int64_t(127);
   place(hd.off_counters, int64_t(4 * kCounterStride) * NG);
   if (too_large || off >= (int64_t(1) << 31)) return fail(COCKTAIL_EUNSUPPORTED, "plan larger than 2 GiB");
@@ -697,7 +704,9 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
       return fail(COCKTAIL_ENOSPACE, "plan buffer holds %zu bytes, %lld needed", plan_capacity,
                   (long long)hd.plan_bytes);
     char* p = static_cast<char*>(plan_host);
-    std::memset(p, 0, hd.plan_bytes);
+    std::memset(p, 0, hd.off_rq_items);   // the records fill their part themselves
+    const int64_t items_end = hd.off_rq_items + int64_t(sizeof(RQItem)) * num_items;
+    std::memset(p + items_end, 0, hd.plan_bytes - items_end);
     std::memcpy(p, &hd, sizeof(hd));
     auto put = [&](int32_t o, const void* src, size_t bytes) {
       if (bytes) std::memcpy(p + o, src, bytes);
@@ -713,8 +722,7 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
     put(hd.off_run_blocks, v_cap.data(), 4 * NC * size_t(B));
     put(hd.off_segments, segs.data(), sizeof(Segment) * size_t(S));
     put(hd.off_bh_off, bh_off.data(), 4 * bh_off.size());
-    std::vector<WorkerRec> recs(P);
-    std::memset(recs.data(), 0, sizeof(WorkerRec) * recs.size());
+    WorkerRec* const recs = reinterpret_cast<WorkerRec*>(p + hd.off_worker_rec);   // zero so far
     // Which workgroup id runs which range.  Workgroup ids are handed to the compute units in order
     // (round-robin over the XCDs), and when P fills the chip twice, workgroup i shares a SIMD with
     // workgroup i + P/2, which was dispatched later and loses every issue arbitration against it.
@@ -740,10 +748,9 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
       rc.ngran = groups[items[w].group].ngran, rc.pseg0 = groups[items[w].group].pseg0;
       if (items[w].g0 < items[w].g1) rc.first = segs[items[w].seg0];
     }
-    put(hd.off_worker_rec, recs.data(), sizeof(WorkerRec) * recs.size());
     put(hd.off_group_rec, groups.data(), sizeof(GroupRec) * groups.size());
     put(hd.off_pool_seg, psegs.data(), sizeof(PoolSeg) * psegs.size());
-    put(hd.off_rq_items, rq_items.data(), sizeof(RQItem) * rq_items.size());
+    write_items(reinterpret_cast<RQItem*>(p + hd.off_rq_items));
   }
   g_err[0] = 0;
   return COCKTAIL_OK;

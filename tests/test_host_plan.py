@@ -234,6 +234,21 @@ def test_work_split_of_random_small_shapes(seed):
         _check_work_split(plan, w, workers, seed)
 
 
+def test_plan_is_the_same_whatever_the_buffer_it_is_written_to():
+    """One pass into a buffer of any content and spare room gives the bytes of a size query followed by an exact fit."""
+    import ctypes as C
+    for w, workers in ((workloads.config(1), 2048), (workloads.small("b", 3, 16, 2, [700, 0, 65], 32, 32, seed_offset=4), 33)):
+        plan, bits = _plan(w, workers)
+        sl, flat = np.asarray(w.seq_lens, np.int32), np.concatenate(bits)
+        args = (C.byref(plan.shape), sl.ctypes.data_as(C.POINTER(C.c_int32)), flat.ctypes.data_as(C.POINTER(C.c_uint8)), workers)
+        sizes = _lib.Sizes()
+        assert _lib.lib().cocktail_plan(*args, C.byref(sizes), None, 0, None, None) == 0
+        exact = np.full(int(sizes.plan_bytes), 0xAB, np.uint8)
+        assert _lib.lib().cocktail_plan(*args, C.byref(sizes), exact.ctypes.data, exact.size, None, None) == 0
+        assert np.array_equal(plan.blob, exact)
+        assert _lib.lib().cocktail_plan(*args, C.byref(sizes), exact.ctypes.data, exact.size - 1, None, None) == _lib.ENOSPACE
+
+
 def test_plan_handles_empty_sequences_and_tail_only():
     sh = ck.make_shape(3, 2, 2, 128, 16, 32)
     plan = ck.cocktail_plan(sh, [0, 5, 16], [4], 8)
