@@ -196,7 +196,12 @@ __device__ __forceinline__ void quantize_rows(LoadRow load_row, char* lds, int r
   }
 }
 
-template <int D, int G, bool PAGED>
+// UNIFORM: the rows of a pass (16 at head_dim 128, 32 at 64) are consecutive source tokens in every block, and lie in
+// one page: chunk size (and page size) are multiples of a pass.  Token, page and base address of a pass are then
+// scalars, whatever the order of the chunks and pages.  Looking rows up one by one costs a division, a table look-up and a
+// 64-bit product per row and thread (16-token pages, 4 ragged sequences, 8 kv heads, 803 MB: 155 -> 133 us; 32-token
+// chunks, 53K tokens, 273 MB: 54 -> 51 us).
+template <int D, int G, bool PAGED, bool UNIFORM>
 __global__ __launch_bounds__(256) void reorder_quantize_kernel(RQParams p) {
   static_assert(D == 64 || D == 128, "a row is 8 or 16 lanes of 8 channels");
   static_assert(D % G == 0, "a group lies inside a row");
@@ -213,7 +218,12 @@ __global__ __launch_bounds__(256) void reorder_quantize_kernel(RQParams p) {
   const int t0 = item.t0, j = item.j, b = item.b, h = item.h;
   const _Float16* src;       // row 0 of the block (consecutive rows) or token 0 of the head (row by row)
   bool per_row = t0 < 0;     // rows are looked up one by one
-  if constexpr (PAGED) {
+  if constexpr (UNIFORM) {
+    // token 0 of the head (paged: the head inside a page); the passes add their first token
+    src = p.src[which] + (PAGED      ? h * p.stride_h
+                          : p.ragged ? (item.ragged_row - (t0 >= 0 ? t0 : 0)) * p.stride_t
+                                     : b * p.stride_b + h * p.stride_h);
+  } else if constexpr (PAGED) {
     src = p.src[which] + h * p.stride_h;     // the head inside a page; page and slot are added per block or per row
     const int last = t0 + (item.cls_nvalid >> 8) - 1;
     const int pg = t0 < 0 ? 0 : p.page_shift >= 0 ? t0 >> p.page_shift : t0 / p.page_size;
@@ -233,7 +243,41 @@ __global__ __launch_bounds__(256) void reorder_quantize_kernel(RQParams p) {
   const PlanHeader* hd = static_cast<const PlanHeader*>(p.plan);
   int C = 1, N = 0, cc0 = 0, chunk_tokens = 0;
   const int32_t* perm = nullptr;
-  if (t0 < 0) {
+  const _Float16* pass_src[PASSES] = {};   // UNIFORM: first row of every pass (nullptr: its rows read as zeros)
+  if constexpr (UNIFORM) {
+    int slot = 0, off = 0;
+    if (t0 < 0) {
+      C = load_record(&hd->chunk_size);
+      const int32_t* chunk_off = plan_array<int32_t>(p.plan, load_record(&hd->off_chunk_off));
+      const int c0 = load_record(chunk_off + b);
+      N = load_record(chunk_off + b + 1) - c0;
+      perm = plan_array<int32_t>(p.plan, load_record(&hd->off_perm)) + c0 +
+             load_record(plan_array<int32_t>(p.plan, load_record(&hd->off_class_chunk0)) + kNumClasses * b + cls);
+      const int ntok = load_record(plan_array<int32_t>(p.plan, load_record(&hd->off_class_tokens)) + kNumClasses * b + cls);
+      const int T = load_record(plan_array<int32_t>(p.plan, load_record(&hd->off_seq_len)) + b);
+      chunk_tokens = (cls == kFp16Class) ? ntok - (T - N * C) : ntok;
+      slot = __builtin_amdgcn_readfirstlane(j * kTB / C), off = j * kTB - slot * C;
+    }
+#pragma unroll
+    for (int pass = 0; pass < PASSES; ++pass) {
+      if (pass * RPP >= nvalid) break;
+      int t = t0 + pass * RPP;
+      if (t0 < 0) {
+        const int r = j * kTB + pass * RPP;
+        t = r < chunk_tokens ? load_record(perm + slot) * C + off : N * C + (r - chunk_tokens);
+        off += RPP;
+        if (off >= C) off -= C, ++slot;   // C is a multiple of RPP
+      }
+      if constexpr (PAGED) {
+        const int pg = p.page_shift >= 0 ? t >> p.page_shift : __builtin_amdgcn_readfirstlane(t / p.page_size);
+        const int page = load_record(p.page_table + int64_t(b) * p.table_stride + pg);
+        if (uint32_t(page) < uint32_t(p.num_pages))
+          pass_src[pass] = src + int64_t(page) * p.stride_page + int64_t(t - pg * p.page_size) * p.stride_t;
+      } else {
+        pass_src[pass] = src + int64_t(t) * p.stride_t;
+      }
+    }
+  } else if (t0 < 0) {
     C = hd->chunk_size;
     const int32_t* chunk_off = plan_array<int32_t>(p.plan, hd->off_chunk_off);
     N = chunk_off[b + 1] - chunk_off[b];
@@ -267,7 +311,7 @@ __global__ __launch_bounds__(256) void reorder_quantize_kernel(RQParams p) {
   // paged source, rows one by one: the page ids of this thread's four rows are fetched up front, so that
   // the four row loads do not each wait for a table look-up first (-1: not a page of the pool)
   int row_page[PASSES] = {};
-  if constexpr (PAGED) {
+  if constexpr (PAGED && !UNIFORM) {
     if (per_row) {
 #pragma unroll
       for (int pass = 0; pass < PASSES; ++pass) {
@@ -282,9 +326,14 @@ __global__ __launch_bounds__(256) void reorder_quantize_kernel(RQParams p) {
       }
     }
   }
+  const uint32_t row_off = uint32_t(row) * uint32_t(p.stride_t) + seg * 8;   // UNIFORM: inside a pass
   auto load_row = [&](int pass) {
     const int i = pass * RPP + row;
     u32x4 v = {0u, 0u, 0u, 0u};
+    if constexpr (UNIFORM) {
+      if (i < nvalid && pass_src[pass]) v = RQ_LOAD(reinterpret_cast<const u32x4*>(pass_src[pass] + row_off));
+      return v;
+    }
     if (i < nvalid) {
       const _Float16* ptr = row_ptr + pass * pass_step;
       if (per_row) {
@@ -423,12 +472,22 @@ int launch_reorder_quantize(const cocktail_shape* shape, const cocktail_cache* c
   }
   if (tot == 0) return COCKTAIL_OK;
   const dim3 grid(static_cast<unsigned>(tot), 2, 1), block(256, 1, 1);
-#define COCKTAIL_RQ_LAUNCH(D, G)                                                                 \
-  if (paged) hipLaunchKernelGGL((reorder_quantize_kernel<D, G, true>), grid, block, 0, st, p);  \
-  else hipLaunchKernelGGL((reorder_quantize_kernel<D, G, false>), grid, block, 0, st, p)
+  // Scalar addresses per pass where a pass (256 threads: this many rows) never crosses a chunk or page (and offsets inside
+  // a pass fit 32 bits), but blocks of 64 rows do: chunks and pages of whole blocks have one address per block in the other
+  // kernel, which is 1 % faster there (128K tokens, 40 heads, 512-token chunks: 548 against 554 us).
+  const int rows = 256 / (shape->head_dim / 8);
+  const bool whole_blocks = hd->chunk_size % kTB == 0 && (!paged || p.page_size % kTB == 0);
+  const bool uniform = !whole_blocks && hd->chunk_size % rows == 0 && (!paged || p.page_size % rows == 0) &&
+                       p.stride_t < (int64_t(1) << 24);
+#define COCKTAIL_RQ_LAUNCH2(D, G, P)                                                                      \
+  if (uniform) hipLaunchKernelGGL((reorder_quantize_kernel<D, G, P, true>), grid, block, 0, st, p);      \
+  else hipLaunchKernelGGL((reorder_quantize_kernel<D, G, P, false>), grid, block, 0, st, p)
+#define COCKTAIL_RQ_LAUNCH(D, G)                  \
+  if (paged) { COCKTAIL_RQ_LAUNCH2(D, G, true); } \
+  else { COCKTAIL_RQ_LAUNCH2(D, G, false); }
   if (shape->head_dim == 64) {
-    if (shape->group_size == 32) COCKTAIL_RQ_LAUNCH(64, 32);
-    else COCKTAIL_RQ_LAUNCH(64, 64);
+    if (shape->group_size == 32) { COCKTAIL_RQ_LAUNCH(64, 32) }
+    else { COCKTAIL_RQ_LAUNCH(64, 64) }
   } else {
     switch (shape->group_size) {
       case 32: COCKTAIL_RQ_LAUNCH(128, 32); break;
@@ -437,6 +496,7 @@ int launch_reorder_quantize(const cocktail_shape* shape, const cocktail_cache* c
     }
   }
 #undef COCKTAIL_RQ_LAUNCH
+#undef COCKTAIL_RQ_LAUNCH2
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(COCKTAIL_EHIP, "reorder_quantize launch failed: %s", hipGetErrorString(e));
   return COCKTAIL_OK;

@@ -322,6 +322,64 @@ def test_paged_source(page_size, head_major, rep, head_dim, room):
             assert err.max() <= TOL
 
 
+@pytest.mark.parametrize("head_dim,chunk,page_size", [(128, 16, 0), (128, 48, 0), (128, 80, 16), (128, 64, 48), (128, 128, 16),
+                                                      (64, 32, 0), (64, 96, 32), (64, 64, 96), (128, 24, 16), (64, 16, 32)])
+@pytest.mark.parametrize("rep", [1, 4])
+def test_blocks_that_cross_chunks_and_pages(head_dim, chunk, page_size, rep):
+    """Chunks and pages that are multiples of a pass of reorder+quantize (16 rows at head_dim 128, 32 at 64) but not of a
+    block, and some that are not: ragged, dense and paged sources give the oracle's class buffers byte for byte.  A page id
+    outside the pool reads as zeros in either kernel."""
+    lens = [chunk * 9 + 21, 5, 0, 700, chunk * 4]
+    w = workloads.small(f"cross{chunk}_{page_size}", len(lens), 2 * rep, 2, lens, chunk, 32, mix=(0.3, 0.2, 0.25, 0.25),
+                        head_dim=head_dim, seed_offset=chunk + page_size)
+    _announce(f"{w.name} d{head_dim} rep={rep}")
+    dev = _dev()
+    shape = ck.make_shape(w.batch, w.num_q_heads, w.num_kv_heads, w.head_dim, w.chunk_size, w.group_size)
+    bits = workloads.chunk_bits(w)
+    plan = ck.cocktail_plan(shape, w.seq_lens, np.concatenate(bits), 8)
+    tmax, v_quads = max(lens), int(plan.sizes.v_layout) == 1
+    ks, vs = zip(*[[np.stack(x) for x in zip(*[workloads.kv_head(w, 0, b, h) for h in range(2)])] for b in range(w.batch)])
+    dense = [np.zeros((w.batch, 2, tmax, head_dim), np.float16) for _ in range(2)]
+    for b, t in enumerate(lens):
+        dense[0][b, :, :t], dense[1][b, :, :t] = ks[b], vs[b]
+
+    def check(cache, ks, vs):
+        oc = O.reorder_quantize(list(ks), list(vs), bits, w.chunk_size, w.group_size)
+        for c in range(O.NUM_CLASSES):
+            assert np.array_equal(cache.k[c].cpu().numpy(), O.pack_class_buffer(oc, c, "k")), f"K class {c}"
+            assert np.array_equal(cache.v[c].cpu().numpy(), O.pack_class_buffer(oc, c, "v", v_quads=v_quads)), f"V class {c}"
+
+    if not page_size:
+        cache = ck.PackedCache(plan, dev)
+        flat = [torch.from_numpy(np.concatenate([x.reshape(-1) for x in side])).to(dev) for side in (ks, vs)]
+        ck.cocktail_reorder_quantize(cache, *flat, ragged=True)
+        check(cache, ks, vs)
+        cache = ck.PackedCache(plan, dev)
+        ck.cocktail_reorder_quantize(cache, *[torch.from_numpy(x).to(dev) for x in dense])
+        check(cache, ks, vs)
+        return
+    need = [-(-t // page_size) for t in lens]
+    ids = np.random.default_rng(1).permutation(sum(need))
+    table = np.full((w.batch, max(need)), -1, np.int32)
+    pools = [np.zeros((sum(need), 2, page_size, head_dim), np.float16) for _ in range(2)]
+    pos = 0
+    for b, t in enumerate(lens):
+        table[b, :need[b]] = ids[pos:pos + need[b]]
+        pos += need[b]
+        for pool, src in zip(pools, (ks[b], vs[b])):
+            for i in range(need[b]):
+                rows = src[:, i * page_size:(i + 1) * page_size]
+                pool[table[b, i], :, :rows.shape[1]] = rows
+    table[0, 1] = sum(need) + 7                              # not a page of the pool
+    gone = [x.copy() for x in (ks[0], vs[0])]
+    for x in gone:
+        x[:, page_size:2 * page_size] = 0
+    cache = ck.PackedCache(plan, dev)
+    ck.cocktail_reorder_quantize_paged(cache, torch.from_numpy(pools[0]).to(dev), torch.from_numpy(pools[1]).to(dev),
+                                       torch.from_numpy(table).to(dev))
+    check(cache, (gone[0],) + ks[1:], (gone[1],) + vs[1:])
+
+
 def test_more_workers_than_blocks_and_repeatability():
     w = workloads.small("tiny", 1, 1, 1, [70], 16, 32, seed_offset=2)
     _announce(w.name)
