@@ -305,7 +305,7 @@ int cocktail_decode_attention_marked(const cocktail_shape* shape, const void* q,
  * cocktail_decode_attention for callers that cannot allocate device memory or hand over a workspace: code
  * that runs under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments,
  * same two kernels and same results, but the partial states go to a workspace built into the library: a
- * static device array of COCKTAIL_STATIC_WORKSPACE_BYTES that every GPU the library runs on holds until the
+ * static device array of COCKTAIL_STATIC_WORKSPACE_BYTES_TILES that every GPU the library runs on holds until the
  * process ends.  The call allocates and frees nothing, on the device or through any library.
  *
  * Every call on a GPU shares that GPU's array, so calls that overlap in time on one GPU (two streams, two
@@ -313,9 +313,11 @@ int cocktail_decode_attention_marked(const cocktail_shape* shape, const void* q,
  * on the first call on each device (with that device current): make that call outside a graph capture.
  *
  * Errors: as cocktail_decode_attention, and ENOSPACE if the plan's workspace_bytes exceeds
- * COCKTAIL_STATIC_WORKSPACE_BYTES (the five benchmark shapes need 0.1 to 5.2 MB).
+ * COCKTAIL_STATIC_WORKSPACE_BYTES (the five benchmark shapes need 0.1 to 5.2 MB), or
+ * COCKTAIL_STATIC_WORKSPACE_BYTES_TILES where one wave serves five to eight query heads (more and larger partial states).
  */
 #define COCKTAIL_STATIC_WORKSPACE_BYTES (16u << 20)
+#define COCKTAIL_STATIC_WORKSPACE_BYTES_TILES (24u << 20)
 int cocktail_decode_attention_static(const cocktail_shape* shape, const void* q, const cocktail_cache* cache,
                                      float sm_scale, void* out, float* lse, void* stream);
 

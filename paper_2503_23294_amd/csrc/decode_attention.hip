@@ -128,8 +128,13 @@ extern "C" int cocktail_default_workers(const cocktail_shape* shape, int32_t* nu
 
 // Scratch of the entry point that allocates nothing: the partial softmax states and the status words of one
 // decode call.  In host code this name is only a handle; the device address comes from hipGetSymbolAddress.
-constexpr size_t kStaticWorkspaceBytes = size_t(COCKTAIL_STATIC_WORKSPACE_BYTES);
-static __device__ __align__(256) unsigned char scratch[kStaticWorkspaceBytes];
+static __device__ __align__(256) unsigned char scratch[COCKTAIL_STATIC_WORKSPACE_BYTES_TILES];
+// What a plan may need of it.  The kernel with eight heads per wave has twice the workers of a kernel with two waves per
+// workgroup, up to 1024 more partial states of 8 x 132 floats (4.3 MB): its plans may go that much beyond the common limit.
+size_t static_workspace_limit(const PlanHeader* hd) {
+  return hd->v_layout == COCKTAIL_V_TOKEN_QUADS && uses_tiles(hd->work_rep) ? size_t(COCKTAIL_STATIC_WORKSPACE_BYTES_TILES)
+                                                                           : size_t(COCKTAIL_STATIC_WORKSPACE_BYTES);
+}
 
 namespace {
 
@@ -306,10 +311,10 @@ extern "C" int cocktail_decode_attention_static(const cocktail_shape* shape, con
   const PlanHeader* hd = nullptr;
   if (int rc = check_plan_matches(shape, cache, &hd)) return rc;
   if (!q || !out) return fail(COCKTAIL_EINVAL, "q and out must not be NULL");
-  if (static_cast<size_t>(hd->workspace_bytes) > kStaticWorkspaceBytes)
+  if (static_cast<size_t>(hd->workspace_bytes) > static_workspace_limit(hd))
     return fail(COCKTAIL_ENOSPACE, "this plan needs a workspace of %lld bytes, the built-in one holds %zu: use "
                 "cocktail_decode_attention with a caller-supplied workspace", (long long)hd->workspace_bytes,
-                kStaticWorkspaceBytes);
+                static_workspace_limit(hd));
   void* ws = nullptr;
   if (int rc = static_workspace(&ws)) return rc;
   return decode_enqueue(shape, hd, q, cache, sm_scale, out, lse, ws, stream);
@@ -321,7 +326,7 @@ extern "C" int cocktail_decode_check(const cocktail_shape* shape, const cocktail
   if (int rc = check_plan_matches(shape, cache, &hd)) return rc;
   void* ws = const_cast<void*>(workspace);
   if (!ws) {
-    if (static_cast<size_t>(hd->workspace_bytes) > kStaticWorkspaceBytes)
+    if (static_cast<size_t>(hd->workspace_bytes) > static_workspace_limit(hd))
       return fail(COCKTAIL_ENOSPACE, "this plan does not fit the built-in workspace");
     if (int rc = static_workspace(&ws)) return rc;
   }

@@ -73,3 +73,21 @@ def test_static_workspace_entry_point_rejects_plans_beyond_its_size():
     assert L.cocktail_decode_attention_static(C.byref(sh), 16, C.byref(cache), 0.0, 16, None, None) == _lib.ENOSPACE
     assert b"built-in" in L.cocktail_last_error()
     assert L.cocktail_decode_attention_static(C.byref(sh), None, C.byref(cache), 0.0, 16, None, None) == _lib.EINVAL
+
+
+@pytest.mark.parametrize("rep,accepted", [(8, True), (4, False)])
+def test_static_workspace_holds_the_partial_states_of_eight_heads_per_wave(rep, accepted):
+    """Plans with eight heads per wave have 2048 workers, 1024 more than their workspace was sized for at first: what needs
+    up to 24 MiB is not refused.  q is misaligned, so that the call ends with an error in any case, also on a GPU."""
+    import ctypes as C
+    sh = ck.make_shape(84, 8 * rep, 8, 128, 64, 32)
+    bits = np.tile(np.repeat(np.array([2, 4, 8, 16], np.uint8), 4), sh.batch)
+    plan = ck.cocktail_plan(sh, [16 * 64] * sh.batch, bits, 2048 if rep == 8 else 8192)
+    need = int(plan.sizes.workspace_bytes)
+    assert _lib.STATIC_WORKSPACE_BYTES < need <= 24 << 20, need
+    cache = _lib.Cache()
+    cache.plan_host = plan.blob.ctypes.data
+    cache.plan_dev = 4096
+    L = _lib.lib()
+    rc = L.cocktail_decode_attention_static(C.byref(sh), 8, C.byref(cache), 0.0, 16, None, None)
+    assert rc != 0 and (rc != _lib.ENOSPACE) == accepted, rc
