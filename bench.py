@@ -78,7 +78,7 @@ def oracle_sample(w, layer_of, bits, q_of, gpu_out_of, heads):
 def measured_traffic(workload_name):
     """HBM bytes per decode call and the file they come from: the committed rocprofv3 counter summary of this
     workload under profiles/ ((None, None) if there is none).  Not measured in this run."""
-    for kernel in ("decode_attention", "decode_quads"):
+    for kernel in ("decode_attention", "decode_quads", "decode_tiles"):
         name = f"{kernel}_{workload_name}_hbm_traffic.txt"
         try:
             with open(os.path.join(ROOT, "profiles", name)) as f:
@@ -381,9 +381,7 @@ def main():
                    "group_size": w.group_size,
                    "class_tokens_int2_int4_int8_fp16": d["class_tokens"],
                    "decode_workgroups": d["workers"], "decode_calls_per_step": ntok, "cache_copies": head["cache_copies"],
-                   "kernel_family": "one query head per wave on the vector ALU (no matrix instructions)"
-                   if head["kernel"] == "decode_attention_kernel" else
-                   "four query heads per wave on 4x4x4 matrix instructions (grouped-query shapes)",
+                   "kernel_family": head["kernel_family"],
                    "step": "reorder+quantize once, then one decode-attention call per output token"
                    if not args.decode_only else "decode attention only"},
         "decode_us_median_step": head["decode_us_median_step"], "decode_us_min_step": head["decode_us_min_step"],
