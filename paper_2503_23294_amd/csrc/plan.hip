@@ -48,6 +48,7 @@ constexpr int64_t kQuadCostWeight[kNumClasses] = {1300, 1250, 950, 450};
 // ranges (8 a hair ahead at 128K), 5 to 6 clearly best on short ones (32K: 33.2 against 35.9 us); the
 // grouped-query kernel likes 4.
 constexpr int kGroupWorkers = 8, kGroupWorkersShort = 6, kQuadGroupWorkers = 4;
+constexpr int kXcds = 8;   // workgroups are handed to the XCDs round robin
 constexpr int kLongRangeBlocks = 24;   // average blocks per worker from which a range counts as long
 // The share of a group's cost that goes into its shared pool.
 constexpr int kPoolPercent = 25;
@@ -326,6 +327,17 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
   const int group_workers = tune.group_workers > 0 ? tune.group_workers
                             : quads                ? kQuadGroupWorkers
                             : tot_blocks >= int64_t(kLongRangeBlocks) * P ? kGroupWorkers : kGroupWorkersShort;
+  // Where a kv head has several sets of query heads (ratios above eight on the matrix kernels), each set walks the same
+  // blocks.  `sets` consecutive groups take the same stripe of blocks, one set each, worker by worker, and the workers
+  // of a stripe get workgroup ids that differ by multiples of kXcds: they run on one XCD, start together, and all but the first find
+  // the blocks in its L2.  (In run order the sets lay half a class apart and every byte was fetched once per set:
+  // 8 ragged contexts up to 64K, 64 q / 4 kv heads, 61 -> 52 us per call;
+  // 4 x 128K, 128 q / 8 kv heads, 235 -> 167.)  Workers beyond whole units of kXcds * share stay without work: taken where
+  // they are at most 1/32 of all.
+  const int unit = kXcds * share;
+  const bool twins = quads && share > 1 && !tune.layout && tune.pair_mode < 2 && kXcds % group_workers == 0 &&
+                     P >= unit && int64_t(P % unit) * 32 <= P;
+  const int sets = twins ? share : 1;
 
   // ---- global order and segments ----
   // The workers form groups of `group_workers`; group j works on one stripe [cut[c][j], cut[c][j+1]) of
@@ -334,7 +346,9 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
   //   layout 0: the class-major order INT2 | INT4 | INT8 | FP16 is cut into NGR parts of equal cost, so a
   //             group works on one class (two where it straddles a class boundary);
   //   layout 1: every group receives the same share of every class (FP16 stripe, then INT2, INT4, INT8).
-  const int NGR = (P + group_workers - 1) / group_workers;
+  const int NGR = (P + group_workers - 1) / group_workers, NST = twins ? P / unit * (kXcds / group_workers) : NGR;   // groups, stripes
+  if (twins)
+    for (int c = 0; c < NC; ++c) class_nblk[c] /= sets;   // blocks of one set
   const bool pair_speed_on = tune.pair_speed;
   const int layout = tune.layout;
   const int class_order[NC] = {layout ? 3 : 0, layout ? 0 : 1, layout ? 1 : 2, layout ? 2 : 3};
@@ -352,7 +366,7 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
     // scale every worker's share by the measured relative speed of its class next to its mate's class.
     std::vector<double> wcap(P, 1.0), gfrac(NGR + 1, 0.0);
     const bool pair_speed = pair_speed_on && !layout && P % 2 == 0 && P >= 2 * group_workers &&
-                            (wrep == 1 || (tune.pair_table_set && quads));
+                            (wrep == 1 || (tune.pair_table_set && quads && !twins));
     for (int round = 0; round < (pair_speed ? 4 : 1); ++round) {
       double total_cap = 0.0;
       for (int w = 0; w < P; ++w) total_cap += wcap[w];
@@ -362,6 +376,8 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
         for (int w = j * group_workers; w < P && w < (j + 1) * group_workers; ++w) acc += wcap[w];
       }
       gfrac[NGR] = 1.0;
+      if (twins)
+        for (int j = 0; j <= NST; ++j) gfrac[j] = double(j) / NST;
       if (!pair_speed || round == 3) break;
       std::vector<int> wclass(P);
       for (int w = 0; w < P; ++w) {
@@ -371,7 +387,7 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
       }
       for (int w = 0; w < P; ++w) wcap[w] = tune.pair_table[wclass[w]][wclass[(w + P / 2) % P]];
     }
-    for (int j = 0; j <= NGR; ++j) {
+    for (int j = 0; j <= NST; ++j) {
       for (int c = 0; c < NC; ++c) {
         if (layout) {
           const int w_lo = j * group_workers < P ? j * group_workers : P;
@@ -383,23 +399,27 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
         }
       }
     }
-    for (int c = 0; c < NC; ++c) cut[c][0] = 0, cut[c][NGR] = class_nblk[c];
+    for (int c = 0; c < NC; ++c) cut[c][0] = 0, cut[c][NST] = class_nblk[c];
   }
   std::vector<Segment> segs;
   std::vector<int64_t> seg_cost0;   // cumulative cost (weighted bytes of K+V) at the start of each segment
   std::vector<int32_t> group_g0(NGR + 1, 0), group_s0(NGR + 1, 0);
   int64_t gblk = 0, cost = 0;
   {
-    std::vector<Run> by_class[NC];
-    for (const Run& r : runs) by_class[r.cls].push_back(r);
-    size_t cur_run[NC] = {};      // run holding the next block of each class
-    int64_t run_first[NC] = {};   // class-local index of that run's first block
+    struct Walk {
+      std::vector<Run> by_class[NC];
+      size_t cur_run[NC] = {};      // run holding the next block of each class
+      int64_t run_first[NC] = {};   // index of that run's first block among the set's blocks of the class
+    };
+    std::vector<Walk> walks(sets);
+    for (const Run& r : runs) walks[r.h % sets].by_class[r.cls].push_back(r);
     for (int j = 0; j < NGR; ++j) {
+      auto& [by_class, cur_run, run_first] = walks[j % sets];
       group_g0[j] = static_cast<int32_t>(gblk), group_s0[j] = static_cast<int32_t>(segs.size());
       for (int ci = 0; ci < NC; ++ci) {
         const int c = class_order[ci];
-        int64_t lo = cut[c][j];
-        const int64_t hi = cut[c][j + 1];
+        int64_t lo = j < NST * sets ? cut[c][j / sets] : 0;
+        const int64_t hi = j < NST * sets ? cut[c][j / sets + 1] : 0;
         while (lo < hi) {
           while (run_first[c] + by_class[c][cur_run[c]].nb <= lo) run_first[c] += by_class[c][cur_run[c]++].nb;
           const Run& r = by_class[c][cur_run[c]];
@@ -731,6 +751,7 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
     //           memory pipeline busy.
     //   mode 2: rank r of group j becomes workgroup (r odd ? P/2 : 0) + j*k/2 + (r/2 + j) mod (k/2):
     //           SIMD mates are neighbouring ranks of one group.  Mode 3: mates are ranks r and r + k/2.
+    // With twins the groups of a unit are dealt out so that the workers of a stripe are kXcds apart.
     const int pair_mode = tune.pair_mode;
     const bool spread = pair_mode >= 2 && group_workers % 2 == 0 && P % group_workers == 0;
     for (int w = 0; w < P; ++w) {
@@ -739,6 +760,10 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
         const int hk = group_workers / 2, j = items[w].group, r = items[w].rank;
         id = pair_mode == 2 ? (r & 1) * (P / 2) + j * hk + ((r >> 1) + j) % hk
                             : (r / hk) * (P / 2) + j * hk + (r % hk + j) % hk;
+      }
+      if (twins && w < P - P % unit) {   // group g of a unit: set g % sets of stripe g / sets
+        const int r = w % unit, g = r / group_workers;
+        id = w - r + g % sets * kXcds + g / sets * group_workers + r % group_workers;
       }
       WorkerRec& rc = recs[id];
       rc.g0 = items[w].g0, rc.g1 = items[w].g1;

@@ -540,3 +540,42 @@ def test_fold_rejects_plans_that_do_not_belong_together():
     # a plan without append buffers cannot be folded from
     desc.plan_host = plan(w.seq_lens, bits, max_seq_lens=most).blob.ctypes.data
     assert fold(good) == _lib.EINVAL
+
+
+@pytest.mark.parametrize("rep,sets", [(9, 3), (10, 2), (16, 2), (24, 3), (32, 4), (64, 8), (8, 1), (11, 1)])
+@pytest.mark.parametrize("workers,capacity", [(2048, 0), (2048, 1500), (64, 0), (100, 70)])
+def test_the_sets_of_a_kv_head_have_twin_workers(rep, sets, workers, capacity):
+    """Sets of query heads that walk the blocks of one kv head: the workers of the sets take the same blocks, segment by
+    segment, and their workgroup ids differ by multiples of eight (one XCD); no partial state is shared."""
+    w = workloads.small(f"twin{rep}", 3, 2 * rep, 2, (40 * 64 + 17, 0, 12345), 64, 32, mix=(0.2, 0.4, 0.4), seed_offset=rep)
+    sh = ck.make_shape(w.batch, w.num_q_heads, w.num_kv_heads, w.head_dim, w.chunk_size, w.group_size)
+    plan = ck.cocktail_plan(sh, w.seq_lens, np.concatenate(workloads.chunk_bits(w)), workers, append_capacity=capacity)
+    h = _parse(plan)
+    if not capacity:
+        _check_work_split(plan, w, workers)
+    whole = h["workers"] - h["workers"] % (8 * sets)
+    if sets == 1 or (h["workers"] - whole) * 32 > h["workers"]:   # more than 1/32 of the workers would have no work
+        return
+    segs = _arr(plan.blob, h["off"]["segments"], np.int32, 8 * h["segments"]).reshape(-1, 8)
+    recs = _arr(plan.blob, h["off"]["worker_rec"], np.int32, 16 * h["workers"]).reshape(-1, 16)
+
+    def pieces(rec):   # (segment without its set, blocks) and the set of every segment of a worker's own range
+        g, g1, s = rec[:3]
+        out = []
+        while g < g1:
+            sg = segs[s]
+            end = min(sg[6] + sg[5], g1)
+            out.append(((sg[0], sg[1] // sets, sg[2], sg[3], sg[4] + g - sg[6], end - g), sg[1] % sets))
+            g, s = end, s + 1
+        return out
+    work = 0
+    assert all(r[0] == r[1] for r in recs[whole:])
+    for i in range(whole):
+        if i // 8 % sets:
+            continue
+        first = pieces(recs[i])
+        work += len(first)
+        for k in range(sets):
+            other = pieces(recs[i + 8 * k])
+            assert [x[0] for x in other] == [x[0] for x in first] and all(x[1] == k for x in other)
+    assert work > 0
