@@ -255,12 +255,30 @@ __device__ __forceinline__ void begin_tiles(int qrow, int lane, TileState<T>& st
   }
 #pragma unroll
   for (int g = 0; g < T::NM; ++g) st.zacc[g] = splat(0.f);
-  st.l = splat(0.f);
   st.m = splat(0.f);
   const int g = lane >> 4, head = lane & 7;
   const bool real = head < kparams()->rep;                  // rows of heads that do not exist are zero
   const bool mine = real && ((lane >> 3) & 1) == (g >> 1);  // the row's half and the half the lane group's channels lie in
   const u32x4* qp = reinterpret_cast<const u32x4*>(kparams()->q + int64_t(qrow + (real ? head : 0)) * (HD / 2));
+  // A head whose query is not finite must not reach the others, which share the products of tile_accumulate with it (0 times
+  // a NaN weight): its row becomes zero, and its l NaN, which no weight changes any more.  (0.1 to 0.25 us of the calls named
+  // at the top; by the sums of the matrix unit and a branch it was 0.4 to 0.6.)
+  typedef uint16_t us2 __attribute__((ext_vector_type(2)));
+  us2 top = {0, 0};
+#pragma unroll
+  for (int r = 0; r < T::NR; ++r)
+#pragma unroll
+    for (int m = 0; m < T::CPL; ++m) {
+      const u32x4 v = qp[T::chunk0(r, g) + m];
+      qa[r * T::CPL + m] = v;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) top = __builtin_elementwise_max(top, __builtin_bit_cast(us2, v[w] & 0x7FFF7FFFu));
+    }
+  uint64_t bad = __builtin_amdgcn_ballot_w64(mine && max(top.x, top.y) >= 0x7C00);
+  bad |= bad >> 32, bad |= bad >> 16, bad |= bad >> 8;      // one bit per head
+  const bool keep = mine && !(uint32_t(bad) >> head & 1u);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) st.l[i] = uint32_t(bad) >> (4 * (g & 1) + i) & 1u ? __builtin_nanf("") : 0.f;
   u32x4 ones;
   ones.x = ones.y = ones.z = ones.w = 0x3C003C00u;
 #pragma unroll
@@ -268,8 +286,8 @@ __device__ __forceinline__ void begin_tiles(int qrow, int lane, TileState<T>& st
     qs[r] = splat(0.f);
 #pragma unroll
     for (int m = 0; m < T::CPL; ++m) {
-      u32x4 v = qp[T::chunk0(r, g) + m];
-      v.x = mine ? v.x : 0u, v.y = mine ? v.y : 0u, v.z = mine ? v.z : 0u, v.w = mine ? v.w : 0u;
+      u32x4 v = qa[r * T::CPL + m];
+      v.x = keep ? v.x : 0u, v.y = keep ? v.y : 0u, v.z = keep ? v.z : 0u, v.w = keep ? v.w : 0u;
       if constexpr (T::QUANT) {
         // the sum of the query channels of the half, which the zero is multiplied with
         qs[r] = mfma16(v, ones, qs[r]);

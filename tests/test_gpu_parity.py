@@ -195,6 +195,34 @@ def test_eight_heads_per_wave_at_the_edges_of_its_tiles(rep, head_dim, group):
             ck.cocktail_decode_check(c.cache)
 
 
+@pytest.mark.parametrize("value", [float("nan"), float("inf"), float("-inf")])
+@pytest.mark.parametrize("rep,head_dim,bad", [(5, 128, 4), (8, 128, 5), (16, 128, 9), (7, 64, 0), (8, 64, 7)])
+def test_a_query_that_is_not_finite_stays_in_its_head(rep, head_dim, bad, value):
+    """Heads that share a wave share matrix products: a NaN or an infinity in the query of one of them leaves the bits of all
+    others as they are, in every class and in the appended tokens, and its own row is not an answer."""
+    w = workloads.small(f"bad_r{rep}", 2, 2 * rep, 2, [64 * 40 + 17, 700], 32, 32, mix=(0.2, 0.25, 0.25, 0.3), head_dim=head_dim,
+                        seed_offset=60 + rep)
+    _announce(f"{w.name} d{head_dim} {value}")
+    dev = _dev()
+    sh = ck.make_shape(w.batch, w.num_q_heads, w.num_kv_heads, w.head_dim, w.chunk_size, w.group_size)
+    cache = ck.PackedCache(ck.cocktail_plan(sh, w.seq_lens, np.concatenate(workloads.chunk_bits(w)), 24, append_capacity=70), dev)
+    k, v = (torch.from_numpy(x).to(dev) for x in workloads.kv_flat(w, 0))
+    ck.cocktail_reorder_quantize(cache, k, v, ragged=True)
+    for i in range(3):
+        ck.cocktail_append_fp16(cache, *(x.view(-1, head_dim)[i:i + 4].reshape(2, 2, head_dim).contiguous() for x in (k, v)))
+    q = torch.from_numpy(workloads.query(w, 0)).to(dev)
+    out, lse = ck.cocktail_decode_attention(cache, q)
+    other = torch.ones(w.batch, w.num_q_heads, dtype=torch.bool)
+    other[1, rep + bad] = False
+    q[1, rep + bad, head_dim - 3] = value
+    got, got_lse = ck.cocktail_decode_attention(cache, q)
+    assert torch.isfinite(lse).all() and torch.isfinite(out).all()
+    assert torch.equal(got.cpu()[other], out.cpu()[other]) and torch.equal(got_lse.cpu()[other], lse.cpu()[other])
+    assert not torch.isfinite(got_lse[1, rep + bad])
+    again, again_lse = ck.cocktail_decode_attention(cache, torch.from_numpy(workloads.query(w, 0)).to(dev))
+    assert torch.equal(again, out) and torch.equal(again_lse, lse)
+
+
 @pytest.mark.parametrize("mix", [(1, 0, 0), (0, 1, 0), (0, 0, 1), (0.5, 0, 0.5), (0, 1, 0, 0), (0.3, 0.3, 0, 0.4),
                                  (0, 0.5, 0.5, 0), (0.25, 0.25, 0.25, 0.25)])
 def test_single_class_and_missing_class(mix):
