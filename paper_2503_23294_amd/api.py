@@ -67,13 +67,13 @@ def cocktail_plan(shape: Shape, seq_lens: Sequence[int], chunk_bits: Sequence[in
         ml = np.ascontiguousarray(np.asarray(max_seq_lens, dtype=np.int32))
         if ml.shape != (shape.batch,):
             raise ValueError("max_seq_lens must have one entry per sequence")
-        opt.max_seq_lens = ml.ctypes.data_as(C.POINTER(C.c_int32))   # `ml` stays alive until both calls below return
+        opt.max_seq_lens = ml.ctypes.data_as(C.POINTER(C.c_int32))   # `ml` stays alive until the calls below return
     # one pass: into a buffer that is large enough for any split of the work (pages nothing is written to cost nothing); should
     # it not be, the library says how much it takes
     ct = np.zeros((shape.batch, _lib.NUM_CLASSES), dtype=np.int32)
     perm = np.zeros(max(cb.size, 1), dtype=np.int32)
     longest = sl if max_seq_lens is None else np.maximum(sl, ml)
-    nbytes = _plan_bytes_bound(shape, int(longest.astype(np.int64).sum()) if sl.size else 0, cb.size, num_workers, append_capacity)
+    nbytes = _plan_bytes_bound(shape, int(longest.astype(np.int64).sum()) if sl.size else 0, cb.size, num_workers)
     for _ in range(2):
         blob = np.empty(nbytes, dtype=np.uint8)
         rc = lib().cocktail_plan_ex(C.byref(shape), slp, cbp, num_workers, C.byref(opt), C.byref(sizes), blob.ctypes.data,
@@ -85,16 +85,17 @@ def cocktail_plan(shape: Shape, seq_lens: Sequence[int], chunk_bits: Sequence[in
     return Plan(shape, sizes, blob[:nbytes], ct, perm[:int(sizes.total_chunks)], sl)
 
 
-def _plan_bytes_bound(shape: Shape, tokens: int, chunks: int, num_workers: int, append_capacity: int) -> int:
+def _plan_bytes_bound(shape: Shape, tokens: int, chunks: int, num_workers: int) -> int:
     """Bytes a plan blob takes at most, about: a 32-byte record per 64-token block and kv head, one per segment and pool part
-    (a run of every class, sequence and head, cut where groups of workers meet), the workers' records and counters."""
-    if min(shape.batch, shape.num_q_heads, shape.num_kv_heads) < 1 or num_workers < 1:
-        return 4096                                          # the library refuses these
+    (a run of every class, sequence and head, cut where groups of workers meet), the workers' records and counters.  The
+    arguments are not checked yet, so the figure is kept to what can always be allocated: the library refuses the bad ones, and
+    says how much a plan takes that does not fit."""
     runs = _lib.NUM_CLASSES * shape.batch
     blocks = shape.num_kv_heads * (tokens // _lib.TOKENS_PER_BLOCK + 2 * runs)
     workers = min(num_workers, 2 * shape.num_q_heads * (tokens // _lib.TOKENS_PER_BLOCK + 2 * runs) + 64)
     segments = runs * shape.num_q_heads + 8 * workers
-    return 8192 + 32 * blocks + 4 * chunks + 64 * runs + 4 * shape.batch * (shape.num_q_heads + 8) + 64 * segments + 256 * workers
+    need = 8192 + 32 * blocks + 4 * chunks + 64 * runs + 4 * shape.batch * (shape.num_q_heads + 8) + 64 * segments + 256 * workers
+    return min(max(need, 4096), 64 << 20)
 
 
 def cocktail_plan_field(plan: Plan, name: str, index: int = 0) -> int:

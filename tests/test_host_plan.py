@@ -274,6 +274,34 @@ def test_plan_rejects_bad_arguments(kwargs, code):
     assert _lib.lib().cocktail_last_error() != b""
 
 
+@pytest.mark.parametrize("lens,shape,workers,code,text", [
+    ([-10**6], (1, 2, 2, 128, 8, 32), 2048, _lib.EINVAL, "negative"),
+    ([64, -10**5], (2, 2, 2, 128, 64, 32), 2048, _lib.EINVAL, "negative"),
+    ([2**31 - 1], (1, 64, 64, 128, 1 << 20, 32), 2048, _lib.EUNSUPPORTED, "4 GiB"),
+    ([2**31 - 1], (1, 256, 256, 64, 1 << 20, 32), 2048, _lib.EUNSUPPORTED, "4 GiB"),
+    ([16], (1, 2, 2, 128, 8, 32), -10**6, _lib.EINVAL, "num_workers"),
+    ([16], (1, 2, 2, 128, 8, 32), 2**31 - 1, _lib.EINVAL, "num_workers"),
+    ([16], (1, 2, 0, 128, 8, 32), 64, _lib.EINVAL, ">= 1"),
+    ([16], (1, -2**31, 2, 128, 8, 32), 64, _lib.EINVAL, ">= 1"),
+])
+def test_plan_binding_hands_on_what_the_library_says(lens, shape, workers, code, text):
+    """The buffer the binding makes before the library has looked at the arguments neither fails nor hides the error."""
+    bits = np.full(sum(t // shape[4] for t in lens if t >= 0), 4, np.uint8)
+    with pytest.raises(ck.CocktailError, match=text) as e:
+        ck.cocktail_plan(ck.make_shape(*shape), lens, bits, workers)
+    assert e.value.code == code
+
+
+def test_plan_that_is_larger_than_the_first_buffer(monkeypatch):
+    """A plan that does not fit the buffer made for it is written to one of its size."""
+    w = workloads.small("large", 3, 16, 2, [700, 0, 65], 32, 32, seed_offset=4)
+    want, _ = _plan(w, 33)
+    monkeypatch.setattr(ck.api, "_plan_bytes_bound", lambda *a: 4096)
+    got, _ = _plan(w, 33)
+    assert want.blob.size > 4096 and np.array_equal(got.blob, want.blob) and np.array_equal(got.perm, want.perm)
+    assert np.array_equal(got.class_tokens, want.class_tokens)
+
+
 def test_plan_capacity_and_null_checks():
     sh = ck.make_shape(1, 2, 2, 128, 8, 32)
     lens = np.array([16], dtype=np.int32)
