@@ -314,7 +314,8 @@ int cocktail_decode_attention_marked(const cocktail_shape* shape, const void* q,
  *
  * Errors: as cocktail_decode_attention, and ENOSPACE if the plan's workspace_bytes exceeds
  * COCKTAIL_STATIC_WORKSPACE_BYTES (the five benchmark shapes need 0.1 to 5.2 MB), or
- * COCKTAIL_STATIC_WORKSPACE_BYTES_TILES where one wave serves five to eight query heads (more and larger partial states).
+ * COCKTAIL_STATIC_WORKSPACE_BYTES_TILES where one wave serves five to eight query heads (more and larger partial states) or
+ * the query heads of a kv head are cut into sets on matrix instructions (Hq/Hkv > 8: more partial states).
  */
 #define COCKTAIL_STATIC_WORKSPACE_BYTES (16u << 20)
 #define COCKTAIL_STATIC_WORKSPACE_BYTES_TILES (24u << 20)

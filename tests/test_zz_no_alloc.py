@@ -91,3 +91,21 @@ def test_static_workspace_holds_the_partial_states_of_eight_heads_per_wave(rep, 
     L = _lib.lib()
     rc = L.cocktail_decode_attention_static(C.byref(sh), 8, C.byref(cache), 0.0, 16, None, None)
     assert rc != 0 and (rc != _lib.ENOSPACE) == accepted, rc
+
+
+@pytest.mark.parametrize("rep,kv_heads,accepted", [(62, 32, True), (13, 32, False)])
+def test_static_workspace_holds_the_partial_states_of_twin_sets(rep, kv_heads, accepted):
+    """Sets of query heads that are planned as twins have more partial states than sets that are cut one after the other (62
+    heads in sets of two: 12.7 MiB then, 17 MiB as twins): such a plan is not refused.  A ratio without sets keeps the common
+    limit.  q is misaligned, so that the call ends with an error in any case, also on a GPU."""
+    import ctypes as C
+    sh = ck.make_shape(8 if accepted else 6, kv_heads * rep, kv_heads, 128, 256, 32)
+    plan = ck.cocktail_plan(sh, [50] * sh.batch if accepted else [50 * 64] * sh.batch,
+                            [] if accepted else np.full(12 * sh.batch, 4, np.uint8), 2048 if accepted else 1 << 15)
+    need = int(plan.sizes.workspace_bytes)
+    assert _lib.STATIC_WORKSPACE_BYTES < need <= 24 << 20, need
+    cache = _lib.Cache()
+    cache.plan_host = plan.blob.ctypes.data
+    cache.plan_dev = 4096
+    rc = _lib.lib().cocktail_decode_attention_static(C.byref(sh), 8, C.byref(cache), 0.0, 16, None, None)
+    assert rc != 0 and (rc != _lib.ENOSPACE) == accepted, rc
