@@ -592,7 +592,13 @@ __device__ __forceinline__ void run_tiles(Stream<HD>& sm, Piece& cur, int lane, 
 // ---------------------------------------------------------------- INT2 and INT4: staged through shared memory
 // Loads that write shared memory: 16 (4) bytes per lane from `rs` at voff + soff, to lds + 16 (4) * lane.  Written as
 // assembly because the compiler would otherwise wait for all of them before any read of shared memory; the caller waits
-// (wait_newest) for the ones it needs.  No register is written, the address registers are read when it issues.
+// (wait_newest) for the ones it needs.  No register but m0 is written (the compiler warns that m0 is reserved: it is named so that
+// nothing is kept there); the address registers are read when the load issues.  The compiler does not see a load inside and so does
+// not keep the five wait states a vector-memory instruction needs after a vector instruction wrote one of its scalar operands (a
+// read of a lane, also the reload of a spilled scalar): fetch_block takes them once for the loads of a block, and a test looks in
+// the built library for such a write between them.  (One wait for a block costs up to 0.3 %, one per load up to 1.6 %.  All loads of
+// a block in one statement with the offset of the instruction: 4 x 128K 129.5 -> 127.5 us, but append 49.0 -> 50.0 and sixteen
+// heads 52.0 -> 52.6.)
 struct LdsRsrc {
   u32x4 w;
 };
@@ -602,18 +608,21 @@ __device__ __forceinline__ LdsRsrc lds_rsrc(const char* base, uint32_t bytes) {
   r.w.x = uint32_t(b), r.w.y = uint32_t(b >> 32) & 0xffffu, r.w.z = bytes, r.w.w = 0x00020000u;
   return r;
 }
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 template <int AUX, bool WIDE>
 __device__ __forceinline__ void load_to_lds(uint32_t lds, const LdsRsrc& rs, uint32_t voff, uint32_t soff) {
   // (one wait state between the write of m0 and the load that reads it)
   if constexpr (WIDE && AUX == kAuxNonTemporal)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds" ::"s"(lds), "v"(voff), "s"(rs.w), "s"(soff) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds" ::"s"(lds), "v"(voff), "s"(rs.w), "s"(soff) : "memory", "m0");
   else if constexpr (WIDE)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rs.w), "s"(soff) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rs.w), "s"(soff) : "memory", "m0");
   else if constexpr (AUX == kAuxNonTemporal)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen nt lds" ::"s"(lds), "v"(voff), "s"(rs.w), "s"(soff) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen nt lds" ::"s"(lds), "v"(voff), "s"(rs.w), "s"(soff) : "memory", "m0");
   else
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rs.w), "s"(soff) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rs.w), "s"(soff) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 // Until all but the newest N vector-memory operations of this wave are complete (they complete in order; operations the
 // caller has not counted only make the wait longer).
 template <int N>
@@ -625,7 +634,8 @@ __device__ __forceinline__ void wait_newest() {
 template <class T, int AUX>
 __device__ __forceinline__ void fetch_block(uint32_t lds, const LdsRsrc& rs, int blk, int lane) {
   const uint32_t off = uint32_t(blk) * T::BLOCKB;
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // what is still being read out of the image has been read
+  // what is still being read out of the image has been read; the wait states of the loads
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_nop 4" ::"s"(rs.w), "s"(off) : "memory");
 #pragma unroll
   for (int i = 0; i < T::BLOCKB / 1024; ++i) load_to_lds<AUX, true>(lds + i * 1024, rs, lane * 16, off + i * 1024);
 #pragma unroll
