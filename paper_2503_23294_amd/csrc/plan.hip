@@ -612,7 +612,8 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
   // 128K tokens), so they are written straight into the blob, and not at all when only the sizes are asked for
   const int64_t num_items = int64_t(v_blk_base[NC * B + 0]) + v_blk_base[NC * B + 1] + v_blk_base[NC * B + 2] + v_blk_base[NC * B + 3];
   // (blocks of an FP16 run that are only room to grow get a record without valid rows: they are written as zeros)
-  auto write_items = [&](RQItem* out) {
+  // (by copies, as everything in the blob: the caller's buffer need not be aligned)
+  auto write_items = [&](char* out) {
     for (int c = 0; c < NC; ++c)
       for (int b = 0; b < B; ++b) {
         const int nb = v_cap[NC * b + c], ntok = v_ct[NC * b + c];
@@ -640,16 +641,17 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
             it.t0 = src_token(r0 + nvalid - 1) == t0 + nvalid - 1 ? t0 : -1;
           }
           it.ragged_row = row0 + (it.t0 >= 0 ? it.t0 : 0);
-          out[j] = it;
+          std::memcpy(out + int64_t(j) * sizeof(it), &it, sizeof(it));
         }
         for (int h = 1; h < Hkv; ++h)   // the other heads: the same rows, seq_lens[b] further on each
           for (int j = 0; j < nb; ++j) {
-            RQItem it = out[j];
+            RQItem it;
+            std::memcpy(&it, out + int64_t(j) * sizeof(it), sizeof(it));
             it.h = h;
             it.ragged_row += int64_t(h) * seq_lens[b];
-            out[int64_t(h) * nb + j] = it;
+            std::memcpy(out + (int64_t(h) * nb + j) * sizeof(it), &it, sizeof(it));
           }
-        out += int64_t(Hkv) * nb;
+        out += int64_t(Hkv) * nb * sizeof(RQItem);
       }
   };
 
@@ -742,7 +744,6 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
     put(hd.off_run_blocks, v_cap.data(), 4 * NC * size_t(B));
     put(hd.off_segments, segs.data(), sizeof(Segment) * size_t(S));
     put(hd.off_bh_off, bh_off.data(), 4 * bh_off.size());
-    WorkerRec* const recs = reinterpret_cast<WorkerRec*>(p + hd.off_worker_rec);   // zero so far
     // Which workgroup id runs which range.  Workgroup ids are handed to the compute units in order
     // (round-robin over the XCDs), and when P fills the chip twice, workgroup i shares a SIMD with
     // workgroup i + P/2, which was dispatched later and loses every issue arbitration against it.
@@ -765,17 +766,18 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
         const int r = w % unit, g = r / group_workers;
         id = w - r + g % sets * kXcds + g / sets * group_workers + r % group_workers;
       }
-      WorkerRec& rc = recs[id];
+      WorkerRec rc = {};
       rc.g0 = items[w].g0, rc.g1 = items[w].g1;
       rc.seg0 = items[w].seg0, rc.pid0 = items[w].pid0;
       rc.group = items[w].group;
       rc.rank_nps = items[w].rank | (groups[items[w].group].nps << 16);
       rc.ngran = groups[items[w].group].ngran, rc.pseg0 = groups[items[w].group].pseg0;
       if (items[w].g0 < items[w].g1) rc.first = segs[items[w].seg0];
+      std::memcpy(p + hd.off_worker_rec + int64_t(id) * sizeof(rc), &rc, sizeof(rc));
     }
     put(hd.off_group_rec, groups.data(), sizeof(GroupRec) * groups.size());
     put(hd.off_pool_seg, psegs.data(), sizeof(PoolSeg) * psegs.size());
-    write_items(reinterpret_cast<RQItem*>(p + hd.off_rq_items));
+    write_items(p + hd.off_rq_items);
   }
   g_err[0] = 0;
   return COCKTAIL_OK;

@@ -49,6 +49,14 @@ static void check_plan(const cocktail_shape& sh, const std::vector<int32_t>& len
   rc = cocktail_plan_ex(&sh, lens.data(), bits.empty() ? nullptr : bits.data(), workers, &opt, &sz, blob.data(),
                         blob.size(), ct.data(), perm.data());
   REQUIRE(rc == COCKTAIL_OK);
+  // the same bytes in a buffer of any alignment
+  if (blob.size() < 40000) {
+    const size_t shift = 1 + size_t(workers) % 15;
+    std::vector<char> odd(blob.size() + shift);
+    REQUIRE(cocktail_plan_ex(&sh, lens.data(), bits.empty() ? nullptr : bits.data(), workers, &opt, &sz, odd.data() + shift,
+                             blob.size(), nullptr, nullptr) == COCKTAIL_OK);
+    REQUIRE(std::memcmp(odd.data() + shift, blob.data(), blob.size()) == 0);
+  }
   const PlanHeader& hd = *view<PlanHeader>(blob, 0, 1);
   REQUIRE(hd.magic == kPlanMagic && hd.plan_bytes == int64_t(blob.size()));
   const int B = sh.batch, Hkv = sh.num_kv_heads, C = sh.chunk_size, P = hd.num_workers;
