@@ -47,8 +47,9 @@
  *   Tokens past n_{b,c} in the last block of a head are zero bytes.
  *   (At head_dim 64 a row is half as long, everything else is the same; group_size is then 32 or 64.)
  *   V in token quads (cocktail_sizes::v_layout == COCKTAIL_V_TOKEN_QUADS; chosen
- *   wherever the matrix kernel runs (Hq/Hkv >= 2 unless the plan is vector-ALU-only or Hq/Hkv > 8 is prime), where a wave serves four query heads of a kv head
- *   with matrix instructions and needs four tokens of a channel side by side):
+ *   wherever a matrix kernel runs (Hq/Hkv >= 2 unless the plan is vector-ALU-only or Hq/Hkv > 8 has no divisor from
+ *   2 to 8), where a wave serves several query heads of a kv head with matrix instructions and needs four tokens of a
+ *   channel side by side):
  *   same block size, piece addressing and meta as above, but the 16-byte piece at
  *   slot sl no longer holds one token.  With n = 16/bits values per half-word,
  *   token i of the block and channel c are found at
@@ -264,12 +265,13 @@ int cocktail_reorder_quantize_paged(const cocktail_shape* shape, const cocktail_
  * up gets NaN in out and lse and a non-zero status word (cocktail_decode_check);
  * the call after it finds the counters at zero again.  Which worker takes which pool piece differs from call to call, so
  * two calls on the same inputs agree to fp32 summation order, not bit for bit
- * (shapes with Hq/Hkv > 4 use no pools and are reproducible bit for bit, and so is any plan made with
- * cocktail_plan_options::reproducible).  Shapes with Hq = Hkv run one query head per wave on the vector
- * ALU; 2 <= Hq/Hkv <= 8 run all query heads of a kv head in one wave on matrix instructions (4x4x4 up to four heads,
- * 16x16x32 beyond; V in token quads), unless the plan asks for the vector ALU only; for larger ratios (up to COCKTAIL_MAX_Q_PER_KV) the query heads of a kv
- * head are cut into equal sets of up to 8 that each read the kv head's blocks (one head per wave if no such set size
- * divides the ratio).
+ * (plans made with cocktail_plan_options::reproducible use no pools and are reproducible bit for bit, and so are
+ * plans on matrix instructions whose workgroups serve five to eight query heads: Hq/Hkv of 5 to 8, and the larger
+ * ratios whose largest divisor up to 8 is at least 5, such as 10, 12 and 16 but not 9, 11 or 13).  Shapes with
+ * Hq = Hkv run one query head per wave on the vector ALU; 2 <= Hq/Hkv <= 8 run all query heads of a kv head in one
+ * wave on matrix instructions (4x4x4 up to four heads, 16x16x32 beyond; V in token quads), unless the plan asks for
+ * the vector ALU only; for larger ratios (up to COCKTAIL_MAX_Q_PER_KV) the query heads of a kv head are cut into equal
+ * sets, of as many heads as that divisor, that each read the kv head's blocks (one head per wave if it is 1).
  *
  *   cache      the appended tokens (num_appended of every sequence, or appended_dev[b] of sequence b) are
  *              attended to after the context

@@ -289,7 +289,7 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
   Tuning tune = read_tuning();
   int pool_percent = tune.pool_percent;
   const int rep = shape->num_q_heads / Hkv;
-  // 5 to 8 query heads per kv head keep the purely static split: their calls are reproducible bit for bit
+  // Workgroups of five to eight query heads keep the purely static split: their calls are reproducible bit for bit.
   // Up to eight query heads of a kv head are served by one workgroup.  Where more of them share a kv head they are
   // cut into equal sets, and with one wave per query head (the vector-ALU kernel, on request) every head is a set
   // of its own: each set walks the blocks of its kv head as if they were its own.

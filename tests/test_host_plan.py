@@ -473,6 +473,23 @@ def test_v_layout_follows_the_query_to_kv_head_ratio(rep, quads, valu):
     _check_work_split(plan, w, 16)
 
 
+@pytest.mark.parametrize("rep", list(range(1, 17)) + [18, 20, 22, 27, 33, 62, 64])
+def test_which_plans_have_no_pools(rep):
+    """The header promises calls that repeat bit for bit, hence no pools, for plans whose workgroups serve five to eight query
+    heads and for reproducible ones; all others have pools where the context is long enough."""
+    sh = ck.make_shape(1, 8 * rep, 8, 128, 64, 32)
+    bits = np.tile(np.array([2, 4, 16, 2], np.uint8), 256)
+    per_group = max([d for d in range(1, 9) if rep % d == 0])
+    assert (per_group >= 5) == (rep in (5, 6, 7, 8, 10, 12, 14, 15, 16, 18, 20, 64))
+    for kw, static in ((dict(), per_group >= 5), (dict(reproducible=True), True), (dict(vector_alu_only=True), False)):
+        plan = ck.cocktail_plan(sh, [65536], bits, 256, **kw)
+        h = _parse(plan)
+        assert h["work_rep"] == (1 if kw.get("vector_alu_only") else per_group)
+        groups = _arr(plan.blob, h["off"]["group_rec"], np.int32, 8 * h["groups"]).reshape(-1, 8)
+        recs = _arr(plan.blob, h["off"]["worker_rec"], np.int32, 16 * h["workers"]).reshape(-1, 16)
+        assert (groups[:, 0] == 0).all() == static and (recs[:, 14] == 0).all() == static
+
+
 def test_room_to_grow_keeps_the_cache_layout_from_plan_to_plan():
     """cocktail_plan_options::max_seq_lens: FP16 runs are laid out for the length a sequence may reach, so the plan
     of a longer context (more FP16 tokens at the end, Sec. III-A) describes the same buffers."""
