@@ -115,7 +115,7 @@ def _check_work_split(plan, w, workers, seed=0):
         assert all(recs[x, 13] >> 16 == nps and recs[x, 14] == ngran and recs[x, 15] == pseg0 for x in ws)
         assert 0 <= nps <= 32 and counter == gi
         if h["work_rep"] > 4:
-            assert ngran == 0                                # two waves on the same blocks: static split only
+            assert ngran == 0                                # five to eight heads per workgroup: static split only
         # tickets are handed out in ascending order to whichever worker asks next
         hand = sorted(rng.integers(0, nworkers, size=ngran).tolist()) if ngran else []
         tickets = {r: [] for r in range(nworkers)}
@@ -172,6 +172,11 @@ def _check_work_split(plan, w, workers, seed=0):
                     seg, slot0 = psegs[pseg0 + pi, 0], psegs[pseg0 + pi, 4]
                     assert slot0 + r not in pid_owner
                     pid_owner[slot0 + r] = (segs[seg, 2], segs[seg, 0] * h["work_heads"] + segs[seg, 1], 1)
+    # the appended tokens of a (sequence, work head): the last ids of its range, one per slice
+    for bh in range(BH):
+        for pid in range(bh_off[bh + 1] - f(plan, "append_slices"), bh_off[bh + 1]):
+            assert pid not in pid_owner
+            pid_owner[pid] = (_lib.NUM_CLASSES - 1, bh, 2)
     assert (seen == 1).all()
     assert sorted(pid_owner) == list(range(h["partials"])) and h["partials"] == plan.sizes.num_partials
     assert bh_off[0] == 0 and bh_off[BH] == h["partials"] and (np.diff(bh_off) >= 0).all()
@@ -588,21 +593,27 @@ def test_fold_rejects_plans_that_do_not_belong_together():
 
 
 @pytest.mark.parametrize("rep,sets", [(9, 3), (10, 2), (16, 2), (24, 3), (32, 4), (64, 8), (8, 1), (11, 1)])
-@pytest.mark.parametrize("workers,capacity", [(2048, 0), (2048, 1500), (64, 0), (100, 70)])
+@pytest.mark.parametrize("workers,capacity", [(2048, 0), (2048, 1500), (64, 0), (96, 70), (100, 70), (100, 0)])
 def test_the_sets_of_a_kv_head_have_twin_workers(rep, sets, workers, capacity):
     """Sets of query heads that walk the blocks of one kv head: the workers of the sets take the same blocks, segment by
-    segment, and their workgroup ids differ by multiples of eight (one XCD); no partial state is shared."""
+    segment, and their workgroup ids differ by multiples of eight (one XCD); no partial state is shared.  Where that would leave
+    more than 1/32 of the workers without work (100 workers), and without sets, the split is the plain one: every block of
+    every work head once, by workers that all have some."""
     w = workloads.small(f"twin{rep}", 3, 2 * rep, 2, (40 * 64 + 17, 0, 12345), 64, 32, mix=(0.2, 0.4, 0.4), seed_offset=rep)
     sh = ck.make_shape(w.batch, w.num_q_heads, w.num_kv_heads, w.head_dim, w.chunk_size, w.group_size)
     plan = ck.cocktail_plan(sh, w.seq_lens, np.concatenate(workloads.chunk_bits(w)), workers, append_capacity=capacity)
     h = _parse(plan)
-    if not capacity:
-        _check_work_split(plan, w, workers)
-    whole = h["workers"] - h["workers"] % (8 * sets)
-    if sets == 1 or (h["workers"] - whole) * 32 > h["workers"]:   # more than 1/32 of the workers would have no work
-        return
+    _check_work_split(plan, w, workers)
+    workers = h["workers"]                                  # at most one per unit of work: 960 for two sets of this context
+    whole = workers - workers % (8 * sets)
+    twins = sets > 1 and whole and (workers - whole) * 32 <= workers
+    assert twins == (sets > 1 and (workers >= 960 or workers == 64 and sets != 3 or workers == 96 and sets != 8))
     segs = _arr(plan.blob, h["off"]["segments"], np.int32, 8 * h["segments"]).reshape(-1, 8)
     recs = _arr(plan.blob, h["off"]["worker_rec"], np.int32, 16 * h["workers"]).reshape(-1, 16)
+
+    if not twins:
+        assert (recs[:, 0] < recs[:, 1]).sum() > 0.95 * min(workers, h["gblocks"])
+        return
 
     def pieces(rec):   # (segment without its set, blocks) and the set of every segment of a worker's own range
         g, g1, s = rec[:3]

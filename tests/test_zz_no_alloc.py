@@ -26,7 +26,7 @@ def _prepare(w, workers, dev):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("rep", [1, 4])
+@pytest.mark.parametrize("rep", [1, 4, 8, 16])
 def test_static_workspace_entry_point_matches_the_regular_one(rep):
     assert torch.cuda.is_available(), "this test needs the MI355X"
     dev = torch.device("cuda:0")
@@ -58,6 +58,32 @@ def test_static_workspace_entry_point_matches_the_regular_one(rep):
         torch.cuda.synchronize()
         err = ((again.float() - b).abs().amax(dim=2) / b.abs().amax(dim=2)).max().item()
         assert err <= TOL
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rep,kv_heads,batch,tokens,chunk", [(8, 8, 128, 64, 16), (62, 32, 8, 50, 256)])
+def test_static_workspace_beyond_16_mib_is_as_good_as_the_callers(rep, kv_heads, batch, tokens, chunk):
+    """Plans that need more than COCKTAIL_STATIC_WORKSPACE_BYTES and are accepted (five to eight heads per wave: no
+    pools, the same bits; twin sets, with pools): the same as on a workspace of the caller's, in calls that follow each other."""
+    dev = torch.device("cuda:0")
+    w = workloads.small(f"static_r{rep}", batch, rep * kv_heads, kv_heads, [tokens] * batch, chunk, 32,
+                        mix=(0.25, 0.25, 0.25, 0.25), seed_offset=820 + rep)
+    print(f"[no-alloc] {w.name}", flush=True)
+    shape = ck.make_shape(w.batch, w.num_q_heads, w.num_kv_heads, w.head_dim, w.chunk_size, w.group_size)
+    bits = np.tile(np.array([2, 4, 8, 16], np.uint8), batch) if tokens == 4 * chunk else np.zeros(0, np.uint8)
+    cache = ck.PackedCache(ck.cocktail_plan(shape, w.seq_lens, bits, 2048), dev)
+    assert _lib.STATIC_WORKSPACE_BYTES < int(cache.plan.sizes.workspace_bytes) <= 24 << 20, cache.plan.sizes.workspace_bytes
+    ck.cocktail_reorder_quantize(cache, *(torch.from_numpy(x).to(dev) for x in workloads.kv_flat(w, 0, threads=8)), ragged=True)
+    q = torch.from_numpy(workloads.query(w, 0)).to(dev)
+    ref, ref_lse = ck.cocktail_decode_attention(cache, q)
+    for _ in range(2):
+        out, lse = torch.full_like(ref, float("nan")), torch.full_like(ref_lse, float("nan"))
+        ck.cocktail_decode_attention_static(cache, q, 0.0, out, lse)
+        ck.cocktail_decode_check(cache, static_workspace=True)
+        assert torch.isfinite(lse).all() and torch.allclose(lse, ref_lse, rtol=0, atol=1e-4 * max(1.0, float(ref_lse.abs().max())))
+        a, b = out.float(), ref.float()
+        assert ((a - b).abs().amax(dim=2) / b.abs().amax(dim=2)).max().item() <= TOL
+        assert rep != 8 or torch.equal(out, ref) and torch.equal(lse, ref_lse)
 
 
 def test_static_workspace_entry_point_rejects_plans_beyond_its_size():
