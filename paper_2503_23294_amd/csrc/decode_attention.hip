@@ -3,8 +3,8 @@
 //
 // This file holds the exact merge of the partial softmax states and the host side of the decode entry points;
 // the partial-state kernels are templates (decode_heads_impl.h: one query head per kv head, vector ALU;
-// decode_quads_impl.h: grouped-query shapes, 4x4x4 matrix instructions) instantiated per head_dim in their
-// own translation units.
+// decode_quads_impl.h: two to four query heads per wave, 4x4x4 matrix instructions; decode_tiles_impl.h: five to eight,
+// 16x16x32 matrix instructions) instantiated per head_dim in their own translation units.
 #include <hip/hip_runtime.h>
 
 #include <cmath>

@@ -29,8 +29,9 @@
 //    reference maximum grows by more than 2^8, then the V pass.  (m, l, o[D])
 //    partials go to the workspace and a second small kernel merges them exactly
 //    (the softmax-weighted sum does not depend on how tokens are grouped, Eq. 4-5).
-//  * This kernel serves shapes with one query head per kv head; grouped-query shapes run on the
-//    kernel of decode_quads.hip, which shares the pieces, pools and register stages with this one.
+//  * This kernel serves one query head per wave (one query head per kv head; ratios above eight without a divisor from
+//    2 to 8; plans for the vector ALU only); the other grouped-query shapes run on the kernels of decode_quads_impl.h and
+//    decode_tiles_impl.h, which share the pieces and the buffer loads with this one, the former its pools too.
 #pragma once
 #include <hip/hip_runtime.h>
 

@@ -24,10 +24,12 @@
 // fp16 subnormals (exact), scale and zero are applied to 32-bit sums, and what the rounding of p * scale loses is fed
 // back around the middle of the code range (sum of the rounded weights: a product with a column of ones).
 //
-// Bound by memory and, for the INT2 class, by the vector ALU (busy 90 % of a call on INT2 blocks of G 32): 180 vector and 22
-// matrix instructions per 32 INT2 tokens and eight heads, where a pair of waves with four heads each took 280 + 64.
-// 4 x 128K tokens, 64 query / 8 kv heads (759 MB): 182.5 -> 129 us per call; 8 ragged sequences, 64 q / 4 kv heads (two
-// sets per kv head): 92 -> 60 us; 8 x 16K tokens and 300 appended, 64 q / 8 kv heads: 66.5 -> 50 us.
+// Bound by memory and, for the INT2 class, by the vector ALU (busy 90 % of a call on INT2 blocks of G 32): 190 vector and 22
+// matrix instructions per 32 INT2 tokens and eight heads at G 32 (151 and 19 at G 64; the loop of the built kernel without its
+// rescale), where a pair of waves with four heads each took 280 + 64.
+// 4 x 128K tokens, 64 query / 8 kv heads (759 MB): 182.5 -> 130 us per call; 8 ragged sequences, 64 q / 4 kv heads (two
+// sets per kv head): 92 -> 60 us, 52 with the sets as twins (plan.hip); 8 x 16K tokens and 300 appended, 64 q / 8 kv heads:
+// 66.5 -> 49.5 us.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -97,7 +99,8 @@ struct TileClass {
   // Where the lowest field of a byte is put before it is masked.  The matrix unit aligns the 32 products of an
   // instruction to the largest by their nominal exponents, in which a subnormal counts as 2^-14 however many leading zeros
   // it has, and cuts off below: fields at bit 2 instead of 0 keep two more bits of every product.  (Error of `out` against
-  // 64 bits, 128K tokens, INT4, G 32, worse of two seeds: 3.6e-4 at bit 0; 2.8e-4 for instructions over 4 products.)
+  // 64 bits, 64 query / 8 kv heads, 128K tokens, INT4, G 32, worse of two seeds: 3.6e-4 at bit 0, 2.3e-4 at bit 2; 2.8e-4 for
+  // instructions over 4 products with the fields at bit 0.)
   static constexpr int POS0 = BITS <= 4 ? 2 : 0;
   static constexpr uint32_t MASK0 = BITS == 2 ? 0x000C000Cu : BITS == 4 ? 0x003C003Cu : 0x00FF00FFu;
   static constexpr float UNIT = QUANT ? float(1 << (24 - POS0)) : 1.0f;   // what a product with such a field has to be scaled by

@@ -42,7 +42,10 @@ int check_shape(const cocktail_shape* s) {
 }
 
 constexpr int64_t kCostWeight[kNumClasses] = {1150, 1300, 1100, 530};
-// The same for the kernel that serves four query heads per wave: its arithmetic runs on the matrix unit.
+// The same for the kernels on the matrix unit, fitted with four query heads per wave.  With eight the optimum is flat around
+// them (us; 4 x 128K at 8 heads | ragged at 16 | 8 x 16K at 8 and 300 appended): 132 | 52.8 | 51.9; INT2 at 1150 130.4 | 52.9 |
+// 51.8, at 1450 131.6 | 51.3 | 51.4; INT4 at 1100 132.4 | 52.3 | 52.4, at 1400 129.7 | 53.2 | 51.9; FP16 at 400 130.1 | 51.2 |
+// 51.1, at 500 132.5 | 52.9 | 51.9, at 550 134.2 | 54.6 | 51.8 (one run; two of the present weights differ by up to 1.3).
 constexpr int64_t kQuadCostWeight[kNumClasses] = {1300, 1250, 950, 450};
 // Workers per group.  Measured on MI355X: with one query head per kv head 4 to 8 are equal on long
 // ranges (8 a hair ahead at 128K), 5 to 6 clearly best on short ones (32K: 33.2 against 35.9 us); the
