@@ -402,18 +402,63 @@ __device__ __forceinline__ void tile_accumulate(const typename T::VStage& s, int
   }
 }
 
+// Another reference for the lane's head i: what has been summed up is multiplied with alpha = 2^(old - new).
+template <class T>
+__device__ __forceinline__ void tile_rescale(TileState<T>& st, int i, float m, float alpha) {
+  st.m[i] = m;
+  st.l[i] *= alpha;
+#pragma unroll
+  for (int g = 0; g < T::NM; ++g) st.zacc[g][i] *= alpha;
+#pragma unroll
+  for (int a = 0; a < T::NA; ++a) {
+    st.ones[a][i] *= alpha;
+#pragma unroll
+    for (int e = 0; e < T::ES; ++e) st.acc[a][e][i] *= alpha;
+  }
+}
+
 // Online softmax over N granules: p holds q.k^ (in units of 1 / UNIT) and becomes the weights; c turns it into
 // log2 units, ev = exponents of the V scales.  `first`: the state is empty, its reference comes from these granules.
+//
+// `far`: some reference of the state is 2^24 or more, where binary32 holds no fractions.  p c - m of the unrounded product is then
+// off by up to half a unit of m, which at 2^31 is more than the weights' whole range: all of them may vanish, and equal logits of
+// different pieces get different weights.  So the logits are rounded first there, and the reference is one of the rounded values,
+// without headroom (it could not be held): the largest weight is 1, and with it the largest product a V scale.  Decided once
+// per state and when a reference is raised; the common path pays for a branch (4 x 128K at eight heads 129.65 -> 129.5 us, sixteen
+// heads 52.15 -> 52.3; the unrounded logits kept for a second pass instead took 48 bytes of scratch: 145 us).
+constexpr float kFar = 16777216.0f;
 template <class T, int N>
-__device__ __forceinline__ void tile_softmax(f4 (&p)[N], const float (&ev)[N], float c, bool first, TileState<T>& st) {
+__device__ __forceinline__ void tile_softmax(f4 (&p)[N], const float (&ev)[N], float c, bool first, bool& far, TileState<T>& st) {
+  constexpr float kRoom = kTopExp - kHeadroom;
   if (first) {
+    bool any = false;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       float tmax = kNegBig;
 #pragma unroll
       for (int n = 0; n < N; ++n) tmax = fmaxf(tmax, __builtin_fmaf(p[n][i], c, ev[n]));
-      st.m[i] = both_halves(row_max(tmax), true) - (kTopExp - kHeadroom);
+      tmax = both_halves(row_max(tmax), true);
+      any |= !(__builtin_fabsf(tmax) < kFar);
+      st.m[i] = tmax - kRoom;
     }
+    far = __builtin_amdgcn_ballot_w64(any) != 0;
+  }
+  if (__builtin_expect(far, 0)) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float tmax = kNegBig;
+#pragma unroll
+      for (int n = 0; n < N; ++n) {
+        float s = p[n][i] * c;
+        pin(s);   // rounded: no product inside the subtraction below
+        p[n][i] = s;
+        tmax = fmaxf(tmax, s + ev[n]);
+      }
+      tmax = both_halves(row_max(tmax), true);
+      const float m = first || tmax > st.m[i] + kTopExp ? tmax : st.m[i];
+      tile_rescale(st, i, m, first ? 1.f : __builtin_amdgcn_exp2f(st.m[i] - m));
+    }
+    c = 1.f;
   }
   float top = -INFINITY;
 #pragma unroll
@@ -423,26 +468,25 @@ __device__ __forceinline__ void tile_softmax(f4 (&p)[N], const float (&ev)[N], f
     top = fmaxf(top, fmaxf(fmaxf(p[n][0], p[n][1]), fmaxf(p[n][2], p[n][3])) + ev[n]);
   }
   if (__builtin_expect(__builtin_amdgcn_ballot_w64(top > kTopExp) != 0, 0)) {
+    f4 up;
+    bool any = false;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       float tmax = -INFINITY;
 #pragma unroll
       for (int n = 0; n < N; ++n) tmax = fmaxf(tmax, p[n][i] + ev[n]);
-      tmax = both_halves(row_max(tmax), true);
-      const float up = tmax > kTopExp ? tmax - (kTopExp - kHeadroom) : 0.f;
-      const float alpha = __builtin_amdgcn_exp2f(-up);
-      st.m[i] += up;
-      st.l[i] *= alpha;
+      up[i] = both_halves(row_max(tmax), true);
+      any |= up[i] > kTopExp && !(__builtin_fabsf(st.m[i] + up[i]) < kFar);
+    }
+    far = far || __builtin_amdgcn_ballot_w64(any) != 0;
 #pragma unroll
-      for (int g = 0; g < T::NM; ++g) st.zacc[g][i] *= alpha;
+    for (int i = 0; i < 4; ++i) {
+      // the reference as binary32 holds it, and the step that was really made
+      const float m = up[i] > kTopExp ? st.m[i] + (up[i] - (far ? 0.f : kRoom)) : st.m[i];
+      const float step = m - st.m[i];
+      tile_rescale(st, i, m, __builtin_amdgcn_exp2f(-step));
 #pragma unroll
-      for (int a = 0; a < T::NA; ++a) {
-        st.ones[a][i] *= alpha;
-#pragma unroll
-        for (int e = 0; e < T::ES; ++e) st.acc[a][e][i] *= alpha;
-      }
-#pragma unroll
-      for (int n = 0; n < N; ++n) p[n][i] -= up;
+      for (int n = 0; n < N; ++n) p[n][i] -= step;
     }
   }
 #pragma unroll
@@ -537,7 +581,7 @@ __device__ __forceinline__ void run_tiles(Stream<HD>& sm, Piece& cur, int lane, 
   begin_tiles<HD, T>(sm.qrow, lane, st, qa, qs);
   int valid = cur.valid;
   int covered = 0;
-  bool first = true;                                 // the partial state is empty
+  bool first = true, far = false;                    // the partial state is empty; see tile_softmax
   const int tpos = 16 * (lane >> 5) + (lane & 15);   // the token of a granule the lane makes p for
   Piece nxt = sm.next(lane);
 #pragma unroll 1
@@ -568,7 +612,7 @@ __device__ __forceinline__ void run_tiles(Stream<HD>& sm, Piece& cur, int lane, 
     float ev[J * GR];
 #pragma unroll
     for (int n = 0; n < J * GR; ++n) ev[n] = tile_exponent<T>(vs[n / GR], n % GR);
-    tile_softmax<T, J * GR>(p, ev, c, first, st);
+    tile_softmax<T, J * GR>(p, ev, c, first, far, st);
     first = false;
 #pragma unroll
     for (int jj = 0; jj < J; ++jj) {
@@ -684,7 +728,7 @@ __device__ __forceinline__ void run_tiles_lds(Stream<HD>& sm, Piece& cur, char* 
   begin_tiles<HD, T>(sm.qrow, lane, st, qa, qs);
   int valid = cur.valid;
   int covered = 0;
-  bool first = true;
+  bool first = true, far = false;
   const int tpos = 16 * (lane >> 5) + (lane & 15);
   Piece nxt = sm.next(lane);
 #pragma unroll 1
@@ -724,7 +768,7 @@ __device__ __forceinline__ void run_tiles_lds(Stream<HD>& sm, Piece& cur, char* 
       T::read_v_meta(vs[n], lds + vimg(n / 2), n % 2, off);
       ev[n] = tile_exponent<T>(vs[n], 0);
     }
-    tile_softmax<T, NG>(p, ev, c, first, st);
+    tile_softmax<T, NG>(p, ev, c, first, far, st);
     first = false;
 #pragma unroll
     for (int j = 0; j < JB; ++j) {

@@ -223,6 +223,48 @@ def test_a_query_that_is_not_finite_stays_in_its_head(rep, head_dim, bad, value)
     assert torch.equal(again, out) and torch.equal(again_lse, lse)
 
 
+@pytest.mark.parametrize("rep,head_dim", [(1, 128), (5, 128), (8, 128), (16, 128), (8, 64)])
+@pytest.mark.parametrize("bits", [2, 4, 8, 16])
+@pytest.mark.parametrize("qscale,kscale", [(200.0, 100.0), (3.0e3, 2.0e3), (1.5e4, 1.5e4)])
+def test_logits_far_beyond_the_binary32_integers(rep, head_dim, bits, qscale, kscale):
+    """Queries and keys up to the fp16 limit: logits of 1e4 to 1e9 log2 units, which binary32 holds to 2^-10 to 64.  The weight
+    goes to the largest logit, and tokens with the same key share it equally, whatever pieces and workers they are on."""
+    hkv, tokens, chunk = 2, 1024, 64
+    dev, g = _dev(), torch.Generator().manual_seed(rep + bits)
+    _announce(f"large logits rep={rep} d={head_dim} bits={bits} q {qscale} k {kscale}")
+    sh = ck.make_shape(1, rep * hkv, hkv, head_dim, chunk, 32)
+    plan = ck.cocktail_plan(sh, [tokens], np.full(tokens // chunk, bits, np.uint8), 7)
+    q = (torch.randn(1, rep * hkv, head_dim, generator=g) * qscale).half()
+    v = torch.randn(1, hkv, tokens, head_dim, generator=g).half()
+    one = (torch.randn(1, hkv, 1, head_dim, generator=g) * kscale).half()
+    # all keys alike, or one key and multiples of it, so that the order of the logits is known and each is far from the next: eight
+    # multiples, 128 tokens each; small ones first and then 512 different ones, the reference has to follow over many powers of two
+    for pattern in ("same", "levels", "rise"):
+        factor = torch.ones(tokens)
+        if pattern == "levels":
+            factor = 0.25 + 0.75 * (torch.randperm(tokens, generator=g) // 128).float() / 8
+        elif pattern == "rise":
+            factor = torch.cat([torch.full((tokens // 2,), 2.0 ** -12), 0.5 + torch.randperm(tokens // 2, generator=g).float() / tokens])
+        k = (one.float() * factor.view(1, 1, -1, 1)).half()
+        cache = ck.PackedCache(plan, dev)
+        ck.cocktail_reorder_quantize(cache, k.to(dev), v.to(dev))
+        out, lse = ck.cocktail_decode_attention(cache, q.to(dev))
+        ck.cocktail_decode_check(cache)
+        bit_list = [np.full(tokens // chunk, bits, np.uint8)]
+        for h in range(hkv):
+            oc = O.reorder_quantize([k[0, h:h + 1].numpy()], [v[0, h:h + 1].numpy()], bit_list, chunk, 32)
+            for r in range(rep):
+                hq = h * rep + r
+                ref, rl = O.decode_attention(q[:, hq:hq + 1].numpy(), oc)
+                got = out[0, hq].double().cpu().numpy()
+                # binary32 sums of products whose magnitudes may cancel: some 2^-17 of what they add up to
+                terms = np.abs(q[0, hq].double().numpy()) @ np.abs(k[0, h].double().numpy()).max(0) / head_dim ** 0.5
+                assert abs(float(lse[0, hq]) - rl[0, 0]) <= 2.0 ** -17 * terms + 1e-4, (pattern, hq, float(lse[0, hq]), rl[0, 0])
+                # the mean of many values is small: the weights are rounded to fp16, 2^-11 of the largest value at most
+                err = np.abs(got - ref[0, 0]).max()
+                assert err <= 2.0 ** -11 * float(v.abs().max()), (pattern, hq, err)
+
+
 @pytest.mark.parametrize("mix", [(1, 0, 0), (0, 1, 0), (0, 0, 1), (0.5, 0, 0.5), (0, 1, 0, 0), (0.3, 0.3, 0, 0.4),
                                  (0, 0.5, 0.5, 0), (0.25, 0.25, 0.25, 0.25)])
 def test_single_class_and_missing_class(mix):
