@@ -38,6 +38,7 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 
 constexpr float kTopExp = 15.0f;     // p * scale stays below 2^kTopExp (fp16 holds up to 2^16 - 32)
 constexpr float kHeadroom = 4.0f;    // log2 units left to grow into when the reference is moved
+constexpr float kFar = 16777216.0f;  // 2^24: references that are treated on their own
 
 __device__ __forceinline__ f4 mfma4(u32x2 a, u32x2 b, f4 c) {
   return __builtin_amdgcn_mfma_f32_4x4x4f16(__builtin_bit_cast(h4, a), __builtin_bit_cast(h4, b), c, 0, 0, 0);
@@ -234,7 +235,10 @@ __device__ __forceinline__ void softmax_quads(const f4 (&s)[J], const float (&ev
     f4 alpha;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float mnew = tmax[i] > st.m[i] + kTopExp ? tmax[i] - (kTopExp - kHeadroom) : st.m[i];
+      // (from 2^24 on binary32 holds no fractions: a reference below a logit is rounded to one 16 below it, for which fp16 has no
+      // room; the logit itself leaves a weight of 1 and a V scale as the largest product)
+      const float room = __builtin_fabsf(tmax[i]) < kFar ? kTopExp - kHeadroom : 0.f;
+      const float mnew = tmax[i] > st.m[i] + kTopExp ? tmax[i] - room : st.m[i];
       alpha[i] = __builtin_amdgcn_exp2f(st.m[i] - mnew);
       st.m[i] = mnew;
     }

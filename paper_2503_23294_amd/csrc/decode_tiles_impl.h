@@ -426,7 +426,6 @@ __device__ __forceinline__ void tile_rescale(TileState<T>& st, int i, float m, f
 // without headroom (it could not be held): the largest weight is 1, and with it the largest product a V scale.  Decided once
 // per state and when a reference is raised; the common path pays for a branch (4 x 128K at eight heads 129.65 -> 129.5 us, sixteen
 // heads 52.15 -> 52.3; the unrounded logits kept for a second pass instead took 48 bytes of scratch: 145 us).
-constexpr float kFar = 16777216.0f;
 template <class T, int N>
 __device__ __forceinline__ void tile_softmax(f4 (&p)[N], const float (&ev)[N], float c, bool first, bool& far, TileState<T>& st) {
   constexpr float kRoom = kTopExp - kHeadroom;

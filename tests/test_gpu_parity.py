@@ -223,7 +223,7 @@ def test_a_query_that_is_not_finite_stays_in_its_head(rep, head_dim, bad, value)
     assert torch.equal(again, out) and torch.equal(again_lse, lse)
 
 
-@pytest.mark.parametrize("rep,head_dim", [(1, 128), (5, 128), (8, 128), (16, 128), (8, 64)])
+@pytest.mark.parametrize("rep,head_dim", [(1, 128), (2, 128), (4, 128), (4, 64), (9, 128), (5, 128), (8, 128), (16, 128), (8, 64)])
 @pytest.mark.parametrize("bits", [2, 4, 8, 16])
 @pytest.mark.parametrize("qscale,kscale", [(200.0, 100.0), (3.0e3, 2.0e3), (1.5e4, 1.5e4)])
 def test_logits_far_beyond_the_binary32_integers(rep, head_dim, bits, qscale, kscale):
