@@ -756,10 +756,19 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
     //   mode 2: rank r of group j becomes workgroup (r odd ? P/2 : 0) + j*k/2 + (r/2 + j) mod (k/2):
     //           SIMD mates are neighbouring ranks of one group.  Mode 3: mates are ranks r and r + k/2.
     // With twins the groups of a unit are dealt out so that the workers of a stripe are kXcds apart.
+    // Where a class has more than half of the workers, some have a mate of their own class, and of those the one dispatched first gets ahead
+    // of the other by a third of the call (128K tokens, 40 heads: INT2 next to INT2 ends at 77 and 105 us, every other worker
+    // between 88 and 97).  Every other rank of such groups trades places with its mate: each group then has both
+    // kinds, and its pool evens them out (107.5 -> 103.9 us per call).  One head per wave only: with four, a cache of FP16 alone got
+    // slower by it (32 q / 8 kv heads, 64K tokens: 51.4 -> 52.6 us; INT2 alone and INT4 alone the same).
     const int pair_mode = tune.pair_mode;
     const bool spread = pair_mode >= 2 && group_workers % 2 == 0 && P % group_workers == 0;
+    const bool trade = wrep == 1 && pool_percent > 0 && pair_mode == 0 && P % 2 == 0;
+    auto class_of = [&](int w) { return items[w].g0 < items[w].g1 ? segs[items[w].seg0].cls : -1; };
     for (int w = 0; w < P; ++w) {
       int id = w;
+      const int mate = (w + P / 2) % P;
+      if (trade && items[std::min(w, mate)].rank % 2 == 1 && class_of(w) == class_of(mate)) id = mate;
       if (spread) {
         const int hk = group_workers / 2, j = items[w].group, r = items[w].rank;
         id = pair_mode == 2 ? (r & 1) * (P / 2) + j * hk + ((r >> 1) + j) % hk

@@ -239,6 +239,25 @@ def test_work_split_of_random_small_shapes(seed):
         _check_work_split(plan, w, workers, seed)
 
 
+@pytest.mark.parametrize("mix,workers,trades", [((0.0, 0.0, 1.0), 64, True), ((0.0, 0.0, 1.0), 192, True), ((0.1, 0.1, 0.8), 128, True),
+                                                ((0.3, 0.35, 0.35), 128, False), ((0.0, 0.0, 1.0), 65, False)])
+def test_workers_next_to_one_of_their_own_class_trade_places(mix, workers, trades):
+    """One head per wave: where worker w and its mate w + P/2 stream the same class, every other rank runs in the place of its mate, so
+    that the pools of such groups are shared by both kinds; whatever runs where, every unit is read once."""
+    w = workloads.small(f"trade{workers}", 1, 4, 4, [64 * 300], 64, 32, mix=mix, seed_offset=901)
+    plan, _ = _plan(w, workers)
+    _check_work_split(plan, w, workers)
+    h, p = _parse(plan), int(plan.sizes.num_workers)
+    recs = _arr(plan.blob, h["off"]["worker_rec"], np.int32, 16 * p).reshape(p, 16)
+    order = recs[:, 0]                                        # first block of a workgroup's own range, by workgroup id
+    moved = [i for i in range(p) if order[i] != np.sort(order)[i]]
+    assert bool(moved) == trades
+    if trades:
+        assert all(recs[i, 6] == recs[(i + p // 2) % p, 6] for i in moved)
+        groups = [{i < p // 2 for i in range(p) if recs[i, 12] == g} for g in set(recs[moved, 12].tolist())]
+        assert all(len(g) == 2 for g in groups)
+
+
 def test_plan_is_the_same_whatever_the_buffer_it_is_written_to():
     """One pass into a buffer of any content and spare room gives the bytes of a size query followed by an exact fit."""
     import ctypes as C
