@@ -42,11 +42,17 @@ int check_shape(const cocktail_shape* s) {
 }
 
 constexpr int64_t kCostWeight[kNumClasses] = {1150, 1300, 1100, 530};
-// The same for the kernels on the matrix unit, fitted with four query heads per wave.  With eight the optimum is flat around
-// them (us; 4 x 128K at 8 heads | ragged at 16 | 8 x 16K at 8 and 300 appended): 132 | 52.8 | 51.9; INT2 at 1150 130.4 | 52.9 |
-// 51.8, at 1450 131.6 | 51.3 | 51.4; INT4 at 1100 132.4 | 52.3 | 52.4, at 1400 129.7 | 53.2 | 51.9; FP16 at 400 130.1 | 51.2 |
-// 51.1, at 500 132.5 | 52.9 | 51.9, at 550 134.2 | 54.6 | 51.8 (one run; two of the present weights differ by up to 1.3).
+// The same for the kernels on the matrix unit: two to four query heads per wave.
 constexpr int64_t kQuadCostWeight[kNumClasses] = {1300, 1250, 950, 450};
+// Five to eight heads per wave: the split is static, so nothing absorbs an error, and a byte of an INT2 or INT4 block carries twice the
+// vector work of the kernel above while one of an FP16 block only waits for memory.  FP16 at 450 | 420 | 400 | 380 | 360 (us):
+// 4 x 128K at 8 heads 134.6 | 131.4 | 130.5 | 129.8 | 132.3; one of 64K 30.7 | 30.0 | 29.7 | 29.8 | 30.7; 2 x 64K at 5 heads 41.1 | 40.4 | 40.3 |
+// 39.9 | 39.8; INT2 and INT4 5 % to either side of these figures differ by no more than two runs do.
+constexpr int64_t kTileCostWeight[kNumClasses] = {1300, 1250, 950, 390};
+// With several sets of heads per kv head (twins) all but the first read the blocks from the L2, so FP16 bytes are cheaper still.  FP16 at
+// 450 | 400 | 360 | 340 | 320 | 300 (us): 8 ragged contexts, 16 heads 52.8 | 51.4 | 50.8 | 50.5 | 50.1 | 50.9; 2 x 40K at 12 heads 42.7 | 40.6 | 40.7 |
+// 40.1 | 39.9 | 40.1; one of 128K at 16 60.5 | 60.7 | 58.3 | 58.4 | 57.9 | 58.3.
+constexpr int64_t kTwinCostWeight[kNumClasses] = {1300, 1250, 950, 330};
 // Workers per group.  Measured on MI355X: with one query head per kv head 4 to 8 are equal on long
 // ranges (8 a hair ahead at 128K), 5 to 6 clearly best on short ones (32K: 33.2 against 35.9 us); the
 // grouped-query kernel likes 4.
@@ -301,7 +307,8 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
   const int share = rep / wrep;                         // work heads that walk the blocks of one kv head
   const bool quads = uses_token_quads(wrep);
   if (quads && !tune.weight_set)
-    for (int c = 0; c < NC; ++c) tune.weight[c] = kQuadCostWeight[c];
+    for (int c = 0; c < NC; ++c)
+      tune.weight[c] = !uses_tiles(wrep) ? kQuadCostWeight[c] : share > 1 ? kTwinCostWeight[c] : kTileCostWeight[c];
   const int64_t* weight = tune.weight;
   if ((wrep > 1 && !(quads && !uses_tiles(wrep))) || reproducible) pool_percent = 0;
 
