@@ -66,6 +66,26 @@ __device__ __forceinline__ kparams_t kparams() {
   return reinterpret_cast<kparams_t>(p);
 }
 
+// What a worker needs of the arguments before it has its record.  The kernel argument segment is four lines of the scalar cache, all of
+// them cold when a kernel starts: one load from each, requested together with the fields below, makes the reads that follow one by
+// one (kparams) hits.  A worker of a 1K-token layer had its first loads on the way 2300 cycles after its start, with every line
+// a miss of its own; a quarter of its time.
+struct FirstParams {
+  const WorkerRec* recs;
+  int32_t num_workers, num_q_heads, rep;
+};
+__device__ __forceinline__ FirstParams first_params() {
+  const kparams_t kp = kparams();
+  const auto* words = reinterpret_cast<const __attribute__((address_space(4))) uint32_t*>(kp);
+  constexpr int kLine = 16;   // dwords
+  static_assert(sizeof(DecodeParams) > 3 * kLine * 4 && sizeof(DecodeParams) <= 4 * kLine * 4, "four lines");
+  FirstParams f;
+  f.recs = kp->recs, f.num_workers = kp->num_workers, f.num_q_heads = kp->num_q_heads, f.rep = kp->rep;
+  const uint32_t l1 = words[kLine], l2 = words[2 * kLine], l3 = words[3 * kLine];
+  asm volatile("" : "+s"(f.recs), "+s"(f.num_workers), "+s"(f.num_q_heads), "+s"(f.rep) : "s"(l1), "s"(l2), "s"(l3));
+  return f;
+}
+
 // A run of blocks is addressed through a buffer resource: every load is
 // buffer_load(resource, lane offset in a VGPR, unit/piece offset in an SGPR), so a lane needs
 // one address register per tensor kind, and reads past `bytes` return zero instead of faulting.
@@ -145,6 +165,13 @@ __device__ __forceinline__ float both_halves(float x, bool maximum) {
 __device__ __forceinline__ void swap_rows(float x, float y, float& even, float& odd) {
   const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, y), false, false);
   even = __builtin_bit_cast(float, uint32_t(r[0])), odd = __builtin_bit_cast(float, uint32_t(r[1]));
+}
+// Maximum over the wave; every lane gets it.
+__device__ __forceinline__ float wave_max(float x) {
+  float a, b;
+  x = row_max(x);
+  swap_rows(x, x, a, b);
+  return both_halves(fmaxf(a, b), true);
 }
 // Sum over the lanes that hold different tokens in the flushes: the 32 lanes of a half (UT = 32) or all 64.
 template <int UT>
@@ -269,15 +296,18 @@ struct QuantClass {
           ga[cb / GL][k] = dot2(q[cb / 2 + NPOS + k], w1 & mask, ga[cb / GL][k]);
         }
       }
+    // (which products are fused is spelled out: logits far beyond 2^24 have to come out alike for equal keys, also from the copies of
+    // this code for the units of an iteration, for which the compiler chooses one by one)
     float sum = 0.f;
 #pragma unroll
     for (int g = 0; g < NGH; ++g) {
       float t = ga[g][NPOS - 1];
 #pragma unroll
-      for (int k = NPOS - 2; k >= 0; --k) t = t * (1.0f / float(1 << BITS)) + ga[g][k];
+      for (int k = NPOS - 2; k >= 0; --k) t = __builtin_fmaf(t, 1.0f / float(1 << BITS), ga[g][k]);
       // t = sum_d q_d code_d * 2^-24 over the lane's channels of group g
       const h2 mz = as_h2(s.meta[g]);
-      sum += (static_cast<float>(mz.x) * kTwo24) * t + static_cast<float>(mz.y) * qsum[g];
+      sum = __builtin_fmaf(static_cast<float>(mz.y), qsum[g], sum);
+      sum = __builtin_fmaf(static_cast<float>(mz.x) * kTwo24, t, sum);
     }
     return sum;
   }
@@ -414,15 +444,18 @@ struct Stream {
 
   __device__ __forceinline__ void enter(const Segment& g, int index) {
     kparams_t kp = kparams();
+    enter(g, index, kp->num_q_heads, kp->rep);
+  }
+  __device__ __forceinline__ void enter(const Segment& g, int index, int num_q_heads, int rep) {
     s = index;
     cls = uni(g.cls), ntok = uni(g.ntok), blk0 = uni(g.blk0), nblk = uni(g.nblk), gu0 = UPB * uni(g.gblk0);
     pid = uni(g.pid0);   // whoever enters a segment from its start is its first visitor
-    qrow = uni(g.b) * kp->num_q_heads + uni(g.h) * kp->rep;
+    qrow = uni(g.b) * num_q_heads + uni(g.h) * rep;
   }
 
-  __device__ __forceinline__ void init(const WorkerRec& rec) {
+  __device__ __forceinline__ void init(const WorkerRec& rec, const FirstParams& fp) {
     u = UPB * uni(rec.g0), u1 = UPB * uni(rec.g1);
-    enter(rec.first, uni(rec.seg0));
+    enter(rec.first, uni(rec.seg0), fp.num_q_heads, fp.rep);
     pid = uni(rec.pid0);   // the first segment is usually entered somewhere in the middle
     if (u >= u1) s = -1;   // no own range: `first` describes nothing, the first pool piece enters its segment
     last_seg = -1;

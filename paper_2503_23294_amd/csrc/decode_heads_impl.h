@@ -50,9 +50,7 @@ __device__ __forceinline__ void softmax_step(const float (&s)[J], float (&p)[J],
   // number of rescales per state is that of one running maximum, not of 64 independent ones
   const bool grow = smax > st.m + kRescaleThreshold;
   if (__builtin_expect(__builtin_amdgcn_ballot_w64(grow) != 0, 0)) {
-    float mnew = fmaxf(smax, st.m);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mnew = fmaxf(mnew, __shfl_xor(mnew, o));
+    const float mnew = wave_max(fmaxf(smax, st.m));
     const float alpha = __builtin_amdgcn_exp2f(st.m - mnew);
     st.m = mnew;
     st.l *= alpha;
@@ -209,7 +207,7 @@ __device__ __forceinline__ void run_class(Stream<HD>& sm, Piece& cur, int r, int
 #pragma unroll
     for (int jj = 0; jj < J; ++jj) {
       float full = s[jj];
-      if constexpr (HD == 128) full += __shfl_xor(s[jj], 32);   // both halves of the token
+      if constexpr (HD == 128) full = both_halves(full, false);   // both halves of the token
       full *= scale_log2;
       s[jj] = (jj * UT + t < valid) ? full : -INFINITY;
     }
@@ -260,12 +258,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void de
 #ifdef COCKTAIL_TRACE
   const uint64_t t_start = __builtin_amdgcn_s_memrealtime();
 #endif
-  if (int(blockIdx.x) >= kparams()->num_workers) {
-    appended_tokens<HD, G, AUX>(int(blockIdx.x) - kparams()->num_workers, r, lane);
+  const FirstParams fp = first_params();
+  if (int(blockIdx.x) >= fp.num_workers) {
+    appended_tokens<HD, G, AUX>(int(blockIdx.x) - fp.num_workers, r, lane);
     return;
   }
   Stream<HD> sm;
-  sm.init(load_record(kparams()->recs + blockIdx.x));
+  sm.init(load_record(fp.recs + blockIdx.x), fp);
   Piece cur = sm.next(lane);
   while (cur.nu > 0) {
     if (cur.cls == 0) {

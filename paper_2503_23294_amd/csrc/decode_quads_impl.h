@@ -55,11 +55,6 @@ __device__ __forceinline__ f4 splat(float x) {
 }
 __device__ __forceinline__ float pick(f4 v, int i) { return i == 0 ? v[0] : i == 1 ? v[1] : i == 2 ? v[2] : v[3]; }
 __device__ __forceinline__ uint32_t pk_mul(uint32_t a, uint32_t b) { return as_u32(as_h2(a) * as_h2(b)); }
-__device__ __forceinline__ f4 shfl_xor4(f4 v, int o) {
-  f4 r;
-  r[0] = __shfl_xor(v[0], o), r[1] = __shfl_xor(v[1], o), r[2] = __shfl_xor(v[2], o), r[3] = __shfl_xor(v[3], o);
-  return r;
-}
 __device__ __forceinline__ f4 max4(f4 a, f4 b) {
   f4 r;
   r[0] = fmaxf(a[0], b[0]), r[1] = fmaxf(a[1], b[1]), r[2] = fmaxf(a[2], b[2]), r[3] = fmaxf(a[3], b[3]);
@@ -230,11 +225,10 @@ __device__ __forceinline__ void softmax_quads(const f4 (&s)[J], const float (&ev
   const bool grow = tmax[0] > st.m[0] + kTopExp || tmax[1] > st.m[1] + kTopExp || tmax[2] > st.m[2] + kTopExp ||
                     tmax[3] > st.m[3] + kTopExp;
   if (__builtin_expect(__builtin_amdgcn_ballot_w64(grow) != 0, 0)) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) tmax = max4(tmax, shfl_xor4(tmax, o));
     f4 alpha;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
+      tmax[i] = wave_max(tmax[i]);
       // (from 2^24 on binary32 holds no fractions: a reference below a logit is rounded to one 16 below it, for which fp16 has no
       // room; the logit itself leaves a weight of 1 and a V scale as the largest product)
       const float room = __builtin_fabsf(tmax[i]) < kFar ? kTopExp - kHeadroom : 0.f;
@@ -412,7 +406,9 @@ __device__ __forceinline__ void run_quads(Stream<HD>& sm, Piece& cur, int lane, 
 #pragma unroll
     for (int jj = 0; jj < J; ++jj) {
       f4 full = s[jj];
-      if constexpr (HD == 128) full += shfl_xor4(s[jj], 32);   // both halves of the token
+      if constexpr (HD == 128)   // both halves of the token
+#pragma unroll
+        for (int i = 0; i < 4; ++i) full[i] = both_halves(full[i], false);
       full *= scale_log2;
       s[jj] = (jj * UT + t < valid) ? full : splat(-INFINITY);
     }
@@ -467,12 +463,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void de
 #ifdef COCKTAIL_TRACE
   const uint64_t t_start = __builtin_amdgcn_s_memrealtime();
 #endif
-  if (int(blockIdx.x) >= kparams()->num_workers) {
-    appended_tokens_quads<HD, G, AUX>(int(blockIdx.x) - kparams()->num_workers, lane);
+  const FirstParams fp = first_params();
+  if (int(blockIdx.x) >= fp.num_workers) {
+    appended_tokens_quads<HD, G, AUX>(int(blockIdx.x) - fp.num_workers, lane);
     return;
   }
   Stream<HD> sm;
-  sm.init(load_record(kparams()->recs + blockIdx.x));
+  sm.init(load_record(fp.recs + blockIdx.x), fp);
   Piece cur = sm.next(lane);
   while (cur.nu > 0) {
     if (cur.cls == 0) {

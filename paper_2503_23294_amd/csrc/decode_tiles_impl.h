@@ -810,8 +810,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void de
 #ifdef COCKTAIL_TRACE
   const uint64_t t_start = __builtin_amdgcn_s_memrealtime();
 #endif
-  if (int(blockIdx.x) >= kparams()->num_workers) {
-    const AppendSlice a = append_slice(int(blockIdx.x) - kparams()->num_workers);
+  const FirstParams fp = first_params();
+  if (int(blockIdx.x) >= fp.num_workers) {
+    const AppendSlice a = append_slice(int(blockIdx.x) - fp.num_workers);
     if (a.tokens <= 0) {
       write_neutral_set<HD>(a.pid, lane);
       return;
@@ -823,7 +824,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void de
     return;
   }
   Stream<HD> sm;
-  sm.init(load_record(kparams()->recs + blockIdx.x));
+  sm.init(load_record(fp.recs + blockIdx.x), fp);
   sm.ngran = 0, sm.nps = 0;
   Piece cur = sm.next(lane);
   while (cur.nu > 0) {
