@@ -7,6 +7,8 @@
 #include <cstdlib>
 #include <algorithm>
 #include <cstring>
+#include <queue>
+#include <utility>
 #include <vector>
 
 #include "../../include/cocktail.h"
@@ -75,6 +77,19 @@ constexpr int kMinBlocksPerWorkerForPool = 4;
 constexpr int kShortRangeBlocks = 16;
 constexpr int kShortRangePoolPercent = 40;
 
+// Plans without pools whose ranges end where runs end (aligned_ranges).  A worker whose range crosses from one run into the next starts a second
+// partial state: another query, another flush, and across classes a pipeline that runs empty; and where a worker has few blocks, ranges cut
+// by cost to the nearest block differ by a block, i.e. by a whole iteration.  With up to this many blocks per worker on average that
+// costs more than the pools bring in; five to eight heads per wave never have pools.  By cost and with pools -> aligned (us; MIX 10 % FP16,
+// 30 % INT4, 60 % INT2): one head, 8 kv heads, 16K 16.1 -> 15.0, 24K 17.7 -> 16.4, 64K (4 blocks per worker) 25.5 -> 23.2, 32 x 32K (8)
+// 35.3 -> 34.4, 4 x 45K (11) 44.3 -> 43.7, but 40.2 -> 42.4 with 5 / 25 / 70 %, 40 x 128K (40) 104 -> 117; four heads, 24K 20.5 -> 18.5, 64K
+// 29.4 -> 25.2, 4 x 45K 48.6 -> 45.6, 4 x 64K (16) 68.5 -> 67.3, ragged up to 128K (36) 206 -> 210; eight heads, 24K 20.8 -> 18.3, 64K 28.8 ->
+// 25.0, 4 x 128K 130 -> 126.7, 8 x 16K with 300 appended 49.8 -> 47.6; sixteen, ragged up to 64K 50.3 -> 47.3.
+constexpr int kAlignedBlocks = 8, kAlignedBlocksQuads = 20;
+constexpr int kAlignedQuadsWorkers = 1024;   // kAlignedBlocksQuads was measured with a full chip: from a worker per SIMD on, kAlignedBlocks below
+// Fewer blocks per worker than this are rounded to whole iterations (INT2: four units): 24K, eight heads 20.2 -> 18.7.
+constexpr int kWholeIterationBlocks = 8;
+
 // The split parameters.  The defaults are what was measured best on MI355X; the environment variables
 // are tuning aids for experiments and are read once per cocktail_plan call.
 struct Tuning {
@@ -138,6 +153,72 @@ static Tuning read_tuning() {
   int_knob("COCKTAIL_MIN_POOL_BLOCKS", 1, 4096, t.min_pool_blocks);
   t.pair_speed = ps != 0;
   return t;
+}
+
+// Ranges that end where runs end.  `nblk` [kNumClasses][B] as [NC * b + c]: blocks of a run, the same for all `heads` heads; cost[c]: of a
+// block.  Finds the smallest cost a worker may be given such that `slots` workers are enough, cuts every run into equal parts of at most
+// that, and lets workers that are left over (beyond 1 in 40: they would bring nothing) cut the dearest parts once more.  Returns the first block of every worker's range
+// in class, sequence, head order (slots + 1 entries), or nothing if there are more runs than workers.
+static std::vector<int32_t> aligned_ranges(const std::vector<int32_t>& nblk, int B, int heads, int slots, const double (&cost)[kNumClasses],
+                                           int units_per_block) {
+  constexpr int NC = kNumClasses;
+  auto per_worker = [&](int c, double budget) {
+    int64_t n = static_cast<int64_t>(budget / cost[c]);
+    const int whole = std::max(1, kIterUnits[c] / units_per_block);
+    if (n < kWholeIterationBlocks) n = n / whole * whole;
+    return std::max<int64_t>(n, 1);
+  };
+  auto workers_for = [&](double budget) {
+    int64_t n = 0;
+    for (int c = 0; c < NC; ++c) {
+      const int64_t per = per_worker(c, budget);
+      for (int b = 0; b < B; ++b) n += (nblk[NC * b + c] + per - 1) / per;
+    }
+    return n * heads;
+  };
+  double total = 0;
+  for (int b = 0; b < B; ++b)
+    for (int c = 0; c < NC; ++c) total += cost[c] * heads * nblk[NC * b + c];
+  std::vector<int32_t> bound;
+  if (total == 0 || workers_for(2 * total) > slots) return bound;
+  double lo = 0, hi = total / slots;
+  while (workers_for(hi) > slots) lo = hi, hi *= 2;
+  for (int i = 0; i < 20; ++i) {
+    const double mid = 0.5 * (lo + hi);
+    (workers_for(mid) <= slots ? hi : lo) = mid;
+  }
+  std::vector<int32_t> parts(NC * B), extra(NC * B, 0);   // parts per run; in addition one more for the first `extra` heads
+  int64_t left = slots - slots / 40;
+  for (int c = 0; c < NC; ++c) {
+    const int64_t per = per_worker(c, hi);
+    for (int b = 0; b < B; ++b) {
+      parts[NC * b + c] = static_cast<int32_t>((nblk[NC * b + c] + per - 1) / per);
+      left -= int64_t(heads) * parts[NC * b + c];
+    }
+  }
+  std::priority_queue<std::pair<double, int>> dearest;   // cost of the largest part, run
+  auto offer = [&](int i) {
+    if (parts[i] > 0 && parts[i] < nblk[i]) dearest.push({(nblk[i] + parts[i] - 1) / parts[i] * cost[i % NC], i});
+  };
+  if (left > 0)
+    for (int i = 0; i < NC * B; ++i) offer(i);
+  while (left > 0 && !dearest.empty()) {
+    const int i = dearest.top().second;
+    dearest.pop();
+    if (left < heads) extra[i] = static_cast<int32_t>(left);
+    else ++parts[i], offer(i);
+    left -= heads;
+  }
+  bound.reserve(slots + 1);
+  int32_t at = 0;
+  for (int c = 0; c < NC; ++c)
+    for (int b = 0; b < B; ++b)
+      for (int h = 0; h < heads; ++h) {
+        const int i = NC * b + c, m = parts[i] + (h < extra[i]);
+        for (int k = 0; k < m; ++k) bound.push_back(at), at += nblk[i] / m + (k < nblk[i] % m);
+      }
+  bound.resize(slots + 1, at);   // the rest has no work
+  return bound;
 }
 
 static inline int64_t align16(int64_t x) { return (x + 15) & ~int64_t(15); }
@@ -363,6 +444,16 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
   const int layout = tune.layout;
   const int class_order[NC] = {layout ? 3 : 0, layout ? 0 : 1, layout ? 1 : 2, layout ? 2 : 3};
   std::vector<int64_t> cut[NC];
+  std::vector<int32_t> bound;   // aligned ranges of one set's workers
+  const bool tiles = quads && uses_tiles(wrep);
+  const int slots = twins ? NST * group_workers : P;
+  const int aligned_blocks = quads && P >= kAlignedQuadsWorkers ? kAlignedBlocksQuads : kAlignedBlocks;
+  if (!layout && !tune.pair_table_set && (tiles || (!tune.pool_percent_set && tot_blocks <= int64_t(aligned_blocks) * P))) {
+    double block_cost[NC];
+    for (int c = 0; c < NC; ++c) block_cost[c] = double(block_bytes[c]) * double(weight[c]);
+    bound = aligned_ranges(v_nblk, B, Hw / sets, slots, block_cost, units_per_block);
+    if (!bound.empty()) pool_percent = 0;
+  }
   {
     int64_t per[NC], tot = 0, start[NC];
     for (int c = 0; c < NC; ++c) {
@@ -409,6 +500,11 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
         }
       }
     }
+    if (!bound.empty())
+      for (int j = 0; j <= NST; ++j) {
+        int64_t at = bound[std::min(j * group_workers, slots)];
+        for (int c = 0; c < NC; ++c) cut[c][j] = std::min(std::max<int64_t>(at, 0), class_nblk[c]), at -= class_nblk[c];
+      }
     for (int c = 0; c < NC; ++c) cut[c][0] = 0, cut[c][NST] = class_nblk[c];
   }
   std::vector<Segment> segs;
@@ -542,6 +638,10 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
         int snb;
         if (r == k - 1) {
           nb = Gp, snb = sGp;
+        } else if (!bound.empty()) {
+          const int w = j / sets * group_workers;
+          nb = j < NST * sets ? G0 + (bound[w + r + 1] - bound[w]) : Gp;
+          snb = seg_of(nb, sprev);
         } else {
           nb = block_at(c0 + own_q * (r + 1) + own_r * (r + 1) / k, sc);   // c0 + (cp - c0) (r + 1) / k without 128-bit arithmetic
           snb = sc;

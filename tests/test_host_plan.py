@@ -244,7 +244,7 @@ def test_work_split_of_random_small_shapes(seed):
 def test_workers_next_to_one_of_their_own_class_trade_places(mix, workers, trades):
     """One head per wave: where worker w and its mate w + P/2 stream the same class, every other rank runs in the place of its mate, so
     that the pools of such groups are shared by both kinds; whatever runs where, every unit is read once."""
-    w = workloads.small(f"trade{workers}", 1, 4, 4, [64 * 300], 64, 32, mix=mix, seed_offset=901)
+    w = workloads.small(f"trade{workers}", 1, 4, 4, [64 * 600], 64, 32, mix=mix, seed_offset=901)
     plan, _ = _plan(w, workers)
     _check_work_split(plan, w, workers)
     h, p = _parse(plan), int(plan.sizes.num_workers)
@@ -256,6 +256,32 @@ def test_workers_next_to_one_of_their_own_class_trade_places(mix, workers, trade
         assert all(recs[i, 6] == recs[(i + p // 2) % p, 6] for i in moved)
         groups = [{i < p // 2 for i in range(p) if recs[i, 12] == g} for g in set(recs[moved, 12].tolist())]
         assert all(len(g) == 2 for g in groups)
+
+
+@pytest.mark.parametrize("rep,lens,workers,aligned", [
+    (1, [64 * 128], 64, True), (1, [64 * 129 + 64], 64, False), (4, [64 * 128], 64, True), (4, [64 * 1280], 2048, True), (4, [64 * 10300], 2048, False),
+    (8, [64 * 6000, 64 * 77 + 5], 2048, True), (16, [64 * 300], 256, True), (6, [64, 65, 1, 0, 640], 2048, True), (8, [40, 0, 3], 4, False)])
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_ranges_that_end_where_runs_end(rep, lens, workers, aligned, head_dim):
+    """Few blocks per worker, and five to eight heads per wave: every worker stays in one run, ranges of a run differ by a
+    block at most, at least 95 % of the workers have work, and there are no pools.  More runs than workers: the plain split."""
+    w = workloads.small(f"aligned{rep}", len(lens), 4 * rep, 4, lens, 64, 32, mix=(0.2, 0.3, 0.3, 0.2), head_dim=head_dim, seed_offset=903)
+    plan, _ = _plan(w, workers)
+    if aligned or head_dim == 128:
+        _check_work_split(plan, w, workers)                  # (it replays pools in units of half a block)
+    h, p = _parse(plan), int(plan.sizes.num_workers)
+    recs = _arr(plan.blob, h["off"]["worker_rec"], np.int32, 16 * p).reshape(p, 16)
+    segs = _arr(plan.blob, h["off"]["segments"], np.int32, 8 * h["segments"]).reshape(-1, 8)
+    busy = recs[recs[:, 0] < recs[:, 1]]
+    run = np.searchsorted(segs[:, 6], busy[:, 0], side="right") - 1
+    inside = busy[:, 1] <= segs[run, 6] + segs[run, 5]
+    assert (inside.all() and (recs[:, 14] == 0).all()) == aligned
+    if aligned:
+        size = {}
+        for r, s in zip(busy, segs[run]):
+            size.setdefault(tuple(s[:3]), []).append(int(r[1] - r[0]))
+        assert all(max(v) - min(v) <= 1 for v in size.values())
+        assert len(busy) >= 0.95 * min(p, h["gblocks"])
 
 
 def test_plan_is_the_same_whatever_the_buffer_it_is_written_to():
