@@ -158,12 +158,10 @@ extern "C" int cocktail_append_fp16(const cocktail_shape* shape, const void* k_n
     return fail(COCKTAIL_EINVAL, "position %d outside the append capacity %d", position, hd->append_capacity);
   const int num_bh = hd->batch * hd->num_kv_heads;
   const dim3 grid((num_bh * (shape->head_dim / 8) + 255) / 256, 2, 1);
-  hipLaunchKernelGGL(append_fp16_kernel, grid, dim3(256), 0, static_cast<hipStream_t>(stream),
-                     static_cast<const u32x4*>(k_new), static_cast<const u32x4*>(v_new),
-                     static_cast<char*>(cache->k_app), static_cast<char*>(cache->v_app), position, hd->append_blocks,
-                     num_bh, hd->v_layout, shape->head_dim, static_cast<const int32_t*>(nullptr),
-                     static_cast<const uint8_t*>(nullptr), hd->num_kv_heads, hd->append_capacity);
-  const hipError_t e = hipGetLastError();
+  const hipError_t e = launch(append_fp16_kernel, grid, dim3(256), static_cast<hipStream_t>(stream), static_cast<const u32x4*>(k_new),
+                              static_cast<const u32x4*>(v_new), static_cast<char*>(cache->k_app), static_cast<char*>(cache->v_app),
+                              position, hd->append_blocks, num_bh, hd->v_layout, shape->head_dim, nullptr, nullptr, hd->num_kv_heads,
+                              hd->append_capacity);
   if (e != hipSuccess) return fail(COCKTAIL_EHIP, "append launch failed: %s", hipGetErrorString(e));
   return COCKTAIL_OK;
 }

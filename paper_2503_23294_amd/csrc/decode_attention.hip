@@ -271,11 +271,9 @@ int decode_enqueue(const cocktail_shape* shape, const PlanHeader* hd, const void
     const hipError_t ev = hipEventRecord(static_cast<hipEvent_t>(event_between), st);
     if (ev != hipSuccess) return fail(COCKTAIL_EHIP, "recording the event between the two kernels failed: %s", hipGetErrorString(ev));
   }
-  if (shape->head_dim == 64)
-    hipLaunchKernelGGL(decode_merge_kernel<64>, dim3(shape->batch * shape->num_q_heads), dim3(16 * kMergeSlices), 0, st, p);
-  else
-    hipLaunchKernelGGL(decode_merge_kernel<128>, dim3(shape->batch * shape->num_q_heads), dim3(32 * kMergeSlices), 0, st, p);
-  const hipError_t e = hipGetLastError();
+  const hipError_t e = shape->head_dim == 64
+                           ? launch(decode_merge_kernel<64>, dim3(shape->batch * shape->num_q_heads), dim3(16 * kMergeSlices), st, p)
+                           : launch(decode_merge_kernel<128>, dim3(shape->batch * shape->num_q_heads), dim3(32 * kMergeSlices), st, p);
   if (e != hipSuccess)
     return fail(COCKTAIL_EHIP, "decode_merge launch failed: %s (the ticket counters in plan_dev were not reset: upload the plan again)",
                 hipGetErrorString(e));

@@ -310,8 +310,7 @@ hipError_t launch_decode_heads(const DecodeParams& p, int group_size, bool nt, b
   }
 #undef COCKTAIL_PICK
   if (!kern) return hipErrorInvalidValue;   // a group size larger than head_dim: refused by the shape check before
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(64), 0, st, p);
-  return hipGetLastError();
+  return launch(kern, dim3(grid), dim3(64), st, p);
 }
 
 }  // namespace cocktail

@@ -516,8 +516,7 @@ hipError_t launch_decode_quads(const DecodeParams& p, int group_size, bool non_t
 #undef COCKTAIL_PICK
 #undef COCKTAIL_PICK2
   if (!kern) return hipErrorInvalidValue;   // a group size larger than head_dim: refused by the shape check before
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(64), 0, st, p);
-  return hipGetLastError();
+  return launch(kern, dim3(grid), dim3(64), st, p);
 }
 
 }  // namespace cocktail
