@@ -56,12 +56,11 @@ def cocktail_plan(shape: Shape, seq_lens: Sequence[int], chunk_bits: Sequence[in
     cb = np.ascontiguousarray(np.asarray(chunk_bits, dtype=np.uint8).reshape(-1))
     if sl.shape != (shape.batch,):
         raise ValueError("seq_lens must have one entry per sequence")
-    need = int(sum(int(t) // shape.chunk_size for t in sl if t >= 0)) if shape.chunk_size > 0 else 0
+    lens, chunk = sl.tolist(), shape.chunk_size
+    need = sum(t // chunk for t in lens if t >= 0) if chunk > 0 else 0
     if cb.size != need:
         raise ValueError(f"chunk_bits has {cb.size} entries, {need} expected")
     sizes = Sizes()
-    slp = sl.ctypes.data_as(C.POINTER(C.c_int32))
-    cbp = cb.ctypes.data_as(C.POINTER(C.c_uint8)) if cb.size else None
     opt = _lib.PlanOptions(int(append_capacity), int(bool(reproducible)), int(bool(vector_alu_only)))
     if max_seq_lens is not None:
         ml = np.ascontiguousarray(np.asarray(max_seq_lens, dtype=np.int32))
@@ -72,17 +71,21 @@ def cocktail_plan(shape: Shape, seq_lens: Sequence[int], chunk_bits: Sequence[in
     # it not be, the library says how much it takes
     ct = np.zeros((shape.batch, _lib.NUM_CLASSES), dtype=np.int32)
     perm = np.zeros(max(cb.size, 1), dtype=np.int32)
-    longest = sl if max_seq_lens is None else np.maximum(sl, ml)
-    nbytes = _plan_bytes_bound(shape, int(longest.astype(np.int64).sum()) if sl.size else 0, cb.size, num_workers)
+    longest = lens if max_seq_lens is None else np.maximum(sl, ml).tolist()
+    nbytes = _plan_bytes_bound(shape, sum(longest), cb.size, num_workers)
     for _ in range(2):
         blob = np.empty(nbytes, dtype=np.uint8)
-        rc = lib().cocktail_plan_ex(C.byref(shape), slp, cbp, num_workers, C.byref(opt), C.byref(sizes), blob.ctypes.data,
-                                    blob.size, ct.ctypes.data_as(C.POINTER(C.c_int32)), perm.ctypes.data_as(C.POINTER(C.c_int32)))
+        rc = lib().cocktail_plan_ex(C.byref(shape), _address(sl), _address(cb) if cb.size else None, num_workers, C.byref(opt),
+                                    C.byref(sizes), _address(blob), nbytes, _address(ct), _address(perm))
         nbytes = int(sizes.plan_bytes)
         if rc != _lib.ENOSPACE:
             break
     check(rc)
     return Plan(shape, sizes, blob[:nbytes], ct, perm[:int(sizes.total_chunks)], sl)
+
+
+def _address(a: np.ndarray) -> int:
+    return a.__array_interface__["data"][0]
 
 
 def _plan_bytes_bound(shape: Shape, tokens: int, chunks: int, num_workers: int) -> int:
@@ -114,10 +117,10 @@ class PackedCache:
         self.plan_dev = torch.from_numpy(plan.blob).to(device)
         self.k: List[torch.Tensor] = []
         self.v: List[torch.Tensor] = []
-        for c in range(_lib.NUM_CLASSES):
-            n = int(plan.sizes.class_bytes[c])
-            self.k.append(torch.empty(n, dtype=torch.uint8, device=device))
-            self.v.append(torch.empty(n, dtype=torch.uint8, device=device))
+        new = self.plan_dev.new_empty   # bytes on the same device
+        for n in plan.sizes.class_bytes:
+            self.k.append(new(n))
+            self.v.append(new(n))
         self.desc = Cache()
         for c in range(_lib.NUM_CLASSES):
             self.desc.k[c] = self.k[c].data_ptr() if self.k[c].numel() else None
@@ -125,8 +128,8 @@ class PackedCache:
         self.desc.plan_host = plan.blob.ctypes.data
         self.desc.plan_dev = self.plan_dev.data_ptr()
         nb = int(plan.sizes.append_bytes)
-        self.k_app = torch.empty(nb, dtype=torch.uint8, device=device) if nb else None
-        self.v_app = torch.empty(nb, dtype=torch.uint8, device=device) if nb else None
+        self.k_app = new(nb) if nb else None
+        self.v_app = new(nb) if nb else None
         self.desc.k_app = self.k_app.data_ptr() if nb else None
         self.desc.v_app = self.v_app.data_ptr() if nb else None
         self.desc.num_appended = 0
@@ -134,7 +137,7 @@ class PackedCache:
         # lockstep batches count in desc.num_appended)
         self.appended = torch.zeros(plan.shape.batch, dtype=torch.int32, device=device) if nb else None
         self.desc.appended_dev = None
-        self.workspace = torch.empty(int(plan.sizes.workspace_bytes), dtype=torch.uint8, device=device)
+        self.workspace = new(int(plan.sizes.workspace_bytes))
 
 
 def _stream_ptr(stream: Optional[torch.cuda.Stream]) -> int:
@@ -264,7 +267,7 @@ def cocktail_decode_attention(cache: PackedCache, q: torch.Tensor, sm_scale: flo
     if out is None:
         out = torch.empty_like(q)
     if lse is None:
-        lse = torch.empty((sh.batch, sh.num_q_heads), dtype=torch.float32, device=q.device)
+        lse = q.new_empty((sh.batch, sh.num_q_heads), dtype=torch.float32)
     check(lib().cocktail_decode_attention(C.byref(sh), q.data_ptr(), C.byref(cache.desc), float(sm_scale),
                                           out.data_ptr(), lse.data_ptr(), cache.workspace.data_ptr(),
                                           cache.workspace.numel(), _stream_ptr(stream)))
@@ -331,9 +334,16 @@ def cocktail_chunk_bitwidths(query_emb: torch.Tensor, chunk_emb: torch.Tensor, n
     total = int(off[-1])
     if chunk_emb.shape != (total, e) or len(num_chunks) != batch:
         raise ValueError("chunk_emb must have shape [sum(num_chunks), E] and num_chunks one entry per sequence")
-    off_dev = torch.from_numpy(off).to(query_emb.device)
-    scores = torch.empty(total, dtype=torch.float32, device=query_emb.device)
-    bits = torch.empty(total, dtype=torch.uint8, device=query_emb.device)
+    if stream is None and query_emb.device.index == torch.cuda.current_device() and not torch.cuda.is_current_stream_capturing():
+        # from pinned memory and without waiting: the kernels follow on the same stream (a copy from pageable memory waits for all that
+        # is on the stream, in a series of requests the reorder+quantize of the one before)
+        staged = torch.empty(batch + 1, dtype=torch.int32, pin_memory=True)
+        staged.numpy()[:] = off
+        off_dev = staged.to(query_emb.device, non_blocking=True)
+    else:
+        off_dev = torch.from_numpy(off).to(query_emb.device)
+    scores = query_emb.new_empty(total)
+    bits = query_emb.new_empty(total, dtype=torch.uint8)
     check(lib().cocktail_chunk_bitwidths(batch, e, total, off_dev.data_ptr(), query_emb.data_ptr(),
                                          chunk_emb.data_ptr() if total else None, float(alpha), float(beta),
                                          scores.data_ptr() if total else None, bits.data_ptr() if total else None,

@@ -462,49 +462,51 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
       tot += class_nblk[c] * per[c];
       cut[c].assign(NGR + 1, 0);
     }
-    // Share of the total cost in front of every group.  Equal shares per worker to begin with; then,
-    // if the workgroups fill the chip twice (workgroup i and i + P/2 share a SIMD), a few rounds that
-    // scale every worker's share by the measured relative speed of its class next to its mate's class.
-    std::vector<double> wcap(P, 1.0), gfrac(NGR + 1, 0.0);
-    const bool pair_speed = pair_speed_on && !layout && P % 2 == 0 && P >= 2 * group_workers &&
-                            (wrep == 1 || (tune.pair_table_set && quads && !twins));
-    for (int round = 0; round < (pair_speed ? 4 : 1); ++round) {
-      double total_cap = 0.0;
-      for (int w = 0; w < P; ++w) total_cap += wcap[w];
-      double acc = 0.0;
-      for (int j = 0; j < NGR; ++j) {
-        gfrac[j] = acc / total_cap;
-        for (int w = j * group_workers; w < P && w < (j + 1) * group_workers; ++w) acc += wcap[w];
-      }
-      gfrac[NGR] = 1.0;
-      if (twins)
-        for (int j = 0; j <= NST; ++j) gfrac[j] = double(j) / NST;
-      if (!pair_speed || round == 3) break;
-      std::vector<int> wclass(P);
-      for (int w = 0; w < P; ++w) {
-        const int j = w / group_workers, k = (j + 1) * group_workers <= P ? group_workers : P - j * group_workers;
-        const double x = double(tot) * (gfrac[j] + (w - j * group_workers + 0.5) / k * (gfrac[j + 1] - gfrac[j]));
-        wclass[w] = x < double(start[1]) ? 0 : x < double(start[2]) ? 1 : x < double(start[3]) ? 2 : 3;
-      }
-      for (int w = 0; w < P; ++w) wcap[w] = tune.pair_table[wclass[w]][wclass[(w + P / 2) % P]];
-    }
-    for (int j = 0; j <= NST; ++j) {
-      for (int c = 0; c < NC; ++c) {
-        if (layout) {
-          const int w_lo = j * group_workers < P ? j * group_workers : P;
-          cut[c][j] = class_nblk[c] * w_lo / P;
-        } else {
-          const int64_t target = static_cast<int64_t>(double(tot) * gfrac[j]);
-          int64_t v = (target - start[c] + per[c] / 2) / per[c];
-          cut[c][j] = v < 0 ? 0 : (v > class_nblk[c] ? class_nblk[c] : v);
-        }
-      }
-    }
-    if (!bound.empty())
+    if (!bound.empty()) {
       for (int j = 0; j <= NST; ++j) {
         int64_t at = bound[std::min(j * group_workers, slots)];
         for (int c = 0; c < NC; ++c) cut[c][j] = std::min(std::max<int64_t>(at, 0), class_nblk[c]), at -= class_nblk[c];
       }
+    } else {
+      // Share of the total cost in front of every group.  Equal shares per worker to begin with; then,
+      // if the workgroups fill the chip twice (workgroup i and i + P/2 share a SIMD), a few rounds that
+      // scale every worker's share by the measured relative speed of its class next to its mate's class.
+      std::vector<double> wcap(P, 1.0), gfrac(NGR + 1, 0.0);
+      const bool pair_speed = pair_speed_on && !layout && P % 2 == 0 && P >= 2 * group_workers &&
+                              (wrep == 1 || (tune.pair_table_set && quads && !twins));
+      for (int round = 0; round < (pair_speed ? 4 : 1); ++round) {
+        double total_cap = 0.0;
+        for (int w = 0; w < P; ++w) total_cap += wcap[w];
+        double acc = 0.0;
+        for (int j = 0; j < NGR; ++j) {
+          gfrac[j] = acc / total_cap;
+          for (int w = j * group_workers; w < P && w < (j + 1) * group_workers; ++w) acc += wcap[w];
+        }
+        gfrac[NGR] = 1.0;
+        if (twins)
+          for (int j = 0; j <= NST; ++j) gfrac[j] = double(j) / NST;
+        if (!pair_speed || round == 3) break;
+        std::vector<int> wclass(P);
+        for (int w = 0; w < P; ++w) {
+          const int j = w / group_workers, k = (j + 1) * group_workers <= P ? group_workers : P - j * group_workers;
+          const double x = double(tot) * (gfrac[j] + (w - j * group_workers + 0.5) / k * (gfrac[j + 1] - gfrac[j]));
+          wclass[w] = x < double(start[1]) ? 0 : x < double(start[2]) ? 1 : x < double(start[3]) ? 2 : 3;
+        }
+        for (int w = 0; w < P; ++w) wcap[w] = tune.pair_table[wclass[w]][wclass[(w + P / 2) % P]];
+      }
+      for (int j = 0; j <= NST; ++j) {
+        for (int c = 0; c < NC; ++c) {
+          if (layout) {
+            const int w_lo = j * group_workers < P ? j * group_workers : P;
+            cut[c][j] = class_nblk[c] * w_lo / P;
+          } else {
+            const int64_t target = static_cast<int64_t>(double(tot) * gfrac[j]);
+            int64_t v = (target - start[c] + per[c] / 2) / per[c];
+            cut[c][j] = v < 0 ? 0 : (v > class_nblk[c] ? class_nblk[c] : v);
+          }
+        }
+      }
+    }
     for (int c = 0; c < NC; ++c) cut[c][0] = 0, cut[c][NST] = class_nblk[c];
   }
   std::vector<Segment> segs;
@@ -586,12 +588,25 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
       const int k = w1 - w0;
       const int32_t G0 = group_g0[j], G1 = group_g0[j + 1];
       const int sG0 = group_s0[j], sG1 = group_s0[j + 1];
-      const int64_t c0 = cost_at(G0, sG0), c1 = cost_at(G1, sG1);
       GroupRec gr;
       std::memset(&gr, 0, sizeof(gr));
       gr.nworkers = k;
       gr.counter = static_cast<int32_t>(groups.size());
       gr.pseg0 = static_cast<int32_t>(psegs.size());
+      if (!bound.empty()) {
+        const int w = std::min(j / sets * group_workers, slots - k);
+        int32_t prev = G0;
+        int sprev = sG0;
+        for (int r = 0; r < k; ++r) {
+          const int32_t nb = r < k - 1 && j < NST * sets ? G0 + (bound[w + r + 1] - bound[w]) : G1;
+          sprev = seg_of(prev, sprev);
+          items[w0 + r] = {prev, nb, sprev, 0, gr.counter, r};
+          prev = nb;
+        }
+        groups.push_back(gr);
+        continue;
+      }
+      const int64_t c0 = cost_at(G0, sG0), c1 = cost_at(G1, sG1);
       int32_t Gp = G1;
       int sGp = sG1;
       if (pool_percent > 0 && int64_t(G1 - G0) >= int64_t(tune.min_pool_blocks) * k) {
@@ -638,10 +653,6 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
         int snb;
         if (r == k - 1) {
           nb = Gp, snb = sGp;
-        } else if (!bound.empty()) {
-          const int w = j / sets * group_workers;
-          nb = j < NST * sets ? G0 + (bound[w + r + 1] - bound[w]) : Gp;
-          snb = seg_of(nb, sprev);
         } else {
           nb = block_at(c0 + own_q * (r + 1) + own_r * (r + 1) / k, sc);   // c0 + (cp - c0) (r + 1) / k without 128-bit arithmetic
           snb = sc;
