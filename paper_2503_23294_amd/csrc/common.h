@@ -24,18 +24,22 @@ __host__ __device__ inline h2 as_h2(uint32_t u) { return __builtin_bit_cast(h2, 
 __host__ __device__ inline uint32_t as_u32(h2 v) { return __builtin_bit_cast(uint32_t, v); }
 
 #ifdef __HIPCC__
-// Launches a kernel without dynamic shared memory.  hipLaunchKernel itself: the launch macro hands the configuration over through the
-// runtime first, 0.25 of 2.55 us, and a short decode call is as long as the host takes for its two launches.
+// Launches a kernel, with `lds` bytes of dynamic shared memory per workgroup.  hipLaunchKernel itself: the launch macro hands the
+// configuration over through the runtime first, 0.25 of 2.55 us, and a short decode call is as long as the host takes for its two launches.
 template <class T>
 struct Same {
   typedef T type;
 };
 template <class... A>
-inline hipError_t launch(void (*kernel)(A...), dim3 grid, dim3 block, hipStream_t stream, typename Same<A>::type... a) {
+inline hipError_t launch_lds(void (*kernel)(A...), dim3 grid, dim3 block, size_t lds, hipStream_t stream, typename Same<A>::type... a) {
   void* args[] = {const_cast<void*>(static_cast<const void*>(&a))...};
-  const hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, args, 0, stream);
+  const hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, args, lds, stream);
   if (e != hipSuccess) (void)hipGetLastError();   // not left for the caller's next call to find
   return e;
+}
+template <class... A>
+inline hipError_t launch(void (*kernel)(A...), dim3 grid, dim3 block, hipStream_t stream, typename Same<A>::type... a) {
+  return launch_lds(kernel, grid, block, 0, stream, a...);
 }
 
 // Reads a plan record through the scalar data path: the records are written by the host only, and

@@ -47,7 +47,7 @@ struct DecodeParams {
   float scale_log2;         // sm_scale * log2(e)
   int32_t rep, num_q_heads, num_kv_heads, num_groups;   // rep, num_kv_heads: of the work split (PlanHeader::work_rep, work_heads)
   int32_t kv_share;         // work heads that share one kv head of the cache (1, or Hq / Hkv with one wave per query head)
-  int32_t num_workers;      // workgroups behind these serve the appended tokens, app_slices per (sequence, kv head)
+  int32_t num_workers;      // waves behind these serve the appended tokens, app_slices per (sequence, kv head)
   int32_t num_appended, app_blocks;   // tokens appended to every sequence (used if `appended` is NULL), blocks per (b, kv head)
   const int32_t* appended;  // [B] tokens appended per sequence, or NULL
   int32_t app_capacity, app_slices;   // tokens per sequence the append buffers hold; workgroups per (b, kv head) for them
@@ -84,6 +84,20 @@ __device__ __forceinline__ FirstParams first_params() {
   const uint32_t l1 = words[kLine], l2 = words[2 * kLine], l3 = words[3 * kLine];
   asm volatile("" : "+s"(f.recs), "+s"(f.num_workers), "+s"(f.num_q_heads), "+s"(f.rep) : "s"(l1), "s"(l2), "s"(l3));
   return f;
+}
+
+// Which worker a wave is.  A workgroup is one wave, or (launch_workers) kCuWaves of them: the waves of a workgroup have the ids of
+// every CU-count-th worker, so that the worker's XCD is its id modulo 8 and its SIMD mate is P / 2 ids away in both cases.
+constexpr int kCuWaves = 8, kChipWorkers = 256 * kCuWaves;
+struct Place {
+  int wave, lane, worker;
+};
+__device__ __forceinline__ Place place(const FirstParams& fp) {
+  Place p;
+  p.wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+  p.lane = int(threadIdx.x) & 63;
+  p.worker = int(blockIdx.x) + p.wave * (fp.num_workers / kCuWaves);
+  return p;
 }
 
 // A run of blocks is addressed through a buffer resource: every load is
@@ -599,5 +613,23 @@ template <int HD>
 hipError_t launch_decode_quads(const DecodeParams& p, int group_size, bool non_temporal, bool int8, int grid, hipStream_t st);
 template <int HD>
 hipError_t launch_decode_tiles(const DecodeParams& p, int group_size, bool non_temporal, bool int8, int grid, hipStream_t st);
+
+// `grid` waves, each with `lds` bytes of shared memory.  Where the workers fill the chip with two waves per SIMD, in workgroups of a whole
+// compute unit.  Launched one by one, the waves are dealt out to the units in order, but which SIMD of its unit a wave gets depends on
+// what ran before: right behind the merge of the call before the fourth wave went to the SIMD of the first one on up to 6 %
+// of the SIMDs, behind a kernel that fills the chip on 15 %.  Those SIMDs then run two waves of the same half of the ids, two INT2 ranges
+// say, for 1.4 times as long as the rest, and the call ends with the slowest worker.  The waves of one workgroup go to the SIMDs in
+// turn (traced: worker w next to w + P / 2 on all 1024, whatever ran before).  One by one -> by compute units, us per call, each call behind an
+// elementwise kernel of 6 us, which is counted: 40 heads 128K 120.8 -> 108.7; 32 heads 32K 41.5 -> 39.7; ragged, 16 query heads per kv head
+// 60.6 -> 55.4; INT2-heavy (5 / 25 / 70 %) 4 x 64K at 8 heads 76.8 -> 63.2, 2 x 40K at 9 59.3 -> 48.5, 4 x 45K at 3 47.7 -> 42.5.  Back to back:
+// 35.7 -> 30.9 (2 x 64K at 5 heads), 53 -> 42, 42.3 -> 37.9, the same where the merge has one workgroup per unit or few.
+// Slices of appended tokens want to start where the first worker ends, not where the first compute unit does: then, and where the
+// workers are no multiple of the chip's, one by one.
+template <class... A>
+inline hipError_t launch_workers(void (*kern)(A...), const DecodeParams& p, int grid, size_t lds, hipStream_t st) {
+  const bool by_unit = grid == p.num_workers && p.num_workers % kChipWorkers == 0;
+  const int waves = by_unit ? kCuWaves : 1;
+  return launch_lds(kern, dim3(grid / waves), dim3(64 * waves), waves * lds, st, p);
+}
 
 }  // namespace cocktail

@@ -248,23 +248,24 @@ __device__ __forceinline__ void appended_tokens(int idx, int r, int lane) {
   if (cur.nu > 0) run_class<HD, HalfClass<HD, G>, kFp16Class, G, AUX>(sm, cur, r, lane, true);
 }
 
-// One single-wave workgroup per worker (Hq = Hkv: the query head of a kv head is that head).  INT8: the cache
+// One wave per worker (Hq = Hkv: the query head of a kv head is that head).  INT8: the cache
 // has an INT8 class; caches without one run a kernel without that code (a third less of it to fetch and
 // to allocate registers for, worth 1.5 us on a 32K-token layer).
 template <int HD, int G, int AUX, bool INT8>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void decode_attention_kernel(DecodeParams) {
-  const int lane = threadIdx.x;
+__global__ __launch_bounds__(64 * kCuWaves) __attribute__((amdgpu_waves_per_eu(2))) void decode_attention_kernel(DecodeParams) {
   constexpr int r = 0;             // query head inside the kv head's group
 #ifdef COCKTAIL_TRACE
   const uint64_t t_start = __builtin_amdgcn_s_memrealtime();
 #endif
   const FirstParams fp = first_params();
-  if (int(blockIdx.x) >= fp.num_workers) {
-    appended_tokens<HD, G, AUX>(int(blockIdx.x) - fp.num_workers, r, lane);
+  const Place me = place(fp);
+  const int lane = me.lane;
+  if (me.worker >= fp.num_workers) {
+    appended_tokens<HD, G, AUX>(me.worker - fp.num_workers, r, lane);
     return;
   }
   Stream<HD> sm;
-  sm.init(load_record(fp.recs + blockIdx.x), fp);
+  sm.init(load_record(fp.recs + me.worker), fp);
   Piece cur = sm.next(lane);
   while (cur.nu > 0) {
     if (cur.cls == 0) {
@@ -284,8 +285,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void de
     if (sm.rank < ps.nslots) write_neutral<HD>(ps.slot0 + sm.rank, r, lane);
   }
 #ifdef COCKTAIL_TRACE
-  if (threadIdx.x == 0) {
-    uint64_t* tr = kparams()->trace + blockIdx.x * 4;
+  if (lane == 0) {
+    uint64_t* tr = kparams()->trace + me.worker * 4;
     tr[0] = t_start;
     tr[1] = __builtin_amdgcn_s_memrealtime();
     tr[2] = __builtin_amdgcn_s_getreg((4) | (0 << 6) | (31 << 11));    // HW_ID
@@ -310,7 +311,7 @@ hipError_t launch_decode_heads(const DecodeParams& p, int group_size, bool nt, b
   }
 #undef COCKTAIL_PICK
   if (!kern) return hipErrorInvalidValue;   // a group size larger than head_dim: refused by the shape check before
-  return launch(kern, dim3(grid), dim3(64), st, p);
+  return launch_workers(kern, p, grid, 0, st);
 }
 
 }  // namespace cocktail

@@ -456,20 +456,21 @@ __device__ __forceinline__ void appended_tokens_quads(int idx, int lane) {
   if (cur.nu > 0) run_quads<HD, QuadHalf<HD, G>, kFp16Class, G, AUX>(sm, cur, lane, true);
 }
 
-// One single-wave workgroup per worker.
+// One wave per worker.
 template <int HD, int G, int AUX, bool INT8>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void decode_quads_kernel(DecodeParams) {
-  const int lane = threadIdx.x;
+__global__ __launch_bounds__(64 * kCuWaves) __attribute__((amdgpu_waves_per_eu(2))) void decode_quads_kernel(DecodeParams) {
 #ifdef COCKTAIL_TRACE
   const uint64_t t_start = __builtin_amdgcn_s_memrealtime();
 #endif
   const FirstParams fp = first_params();
-  if (int(blockIdx.x) >= fp.num_workers) {
-    appended_tokens_quads<HD, G, AUX>(int(blockIdx.x) - fp.num_workers, lane);
+  const Place me = place(fp);
+  const int lane = me.lane;
+  if (me.worker >= fp.num_workers) {
+    appended_tokens_quads<HD, G, AUX>(me.worker - fp.num_workers, lane);
     return;
   }
   Stream<HD> sm;
-  sm.init(load_record(fp.recs + blockIdx.x), fp);
+  sm.init(load_record(fp.recs + me.worker), fp);
   Piece cur = sm.next(lane);
   while (cur.nu > 0) {
     if (cur.cls == 0) {
@@ -488,8 +489,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void de
     if (sm.rank < ps.nslots) write_neutral_heads<HD>(ps.slot0 + sm.rank, lane);
   }
 #ifdef COCKTAIL_TRACE
-  if (threadIdx.x == 0) {
-    uint64_t* tr = kparams()->trace + blockIdx.x * 4;
+  if (lane == 0) {
+    uint64_t* tr = kparams()->trace + me.worker * 4;
     tr[0] = t_start;
     tr[1] = __builtin_amdgcn_s_memrealtime();
     tr[2] = __builtin_amdgcn_s_getreg((4) | (0 << 6) | (31 << 11));    // HW_ID
@@ -516,7 +517,7 @@ hipError_t launch_decode_quads(const DecodeParams& p, int group_size, bool non_t
 #undef COCKTAIL_PICK
 #undef COCKTAIL_PICK2
   if (!kern) return hipErrorInvalidValue;   // a group size larger than head_dim: refused by the shape check before
-  return launch(kern, dim3(grid), dim3(64), st, p);
+  return launch_workers(kern, p, grid, 0, st);
 }
 
 }  // namespace cocktail

@@ -679,9 +679,10 @@ __device__ __forceinline__ void wait_newest() {
 // Block `blk` of a run (out of range: zeros) to an image in shared memory.
 template <class T, int AUX>
 __device__ __forceinline__ void fetch_block(uint32_t lds, const LdsRsrc& rs, int blk, int lane) {
-  const uint32_t off = uint32_t(blk) * T::BLOCKB;
-  // what is still being read out of the image has been read; the wait states of the loads
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_nop 4" ::"s"(rs.w), "s"(off) : "memory");
+  uint32_t off = uint32_t(blk) * T::BLOCKB;
+  // What is still being read out of the image has been read; the wait states of the loads.  The offsets are changed as far as the compiler
+  // knows, so that it adds the constants behind this, with scalar instructions, and brings no sum back from a spill (v_readlane).
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_nop 4" : "+s"(off), "+s"(lds) : "s"(rs.w) : "memory");
 #pragma unroll
   for (int i = 0; i < T::BLOCKB / 1024; ++i) load_to_lds<AUX, true>(lds + i * 1024, rs, lane * 16, off + i * 1024);
 #pragma unroll
@@ -801,18 +802,20 @@ __device__ __forceinline__ void write_neutral_set(int slot, int lane) {
   for (int i = 0; i < rep; ++i) write_neutral<HD>(slot, i, lane);
 }
 
-// One single-wave workgroup per worker, then one per slice of the appended tokens.  The plans of these shapes have no
+// One wave per worker, then one per slice of the appended tokens.  The plans of these shapes have no
 // pools (a plan that had one would lose tokens, which the merge reports).
 template <int HD, int G, int AUX, bool INT8>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void decode_tiles_kernel(DecodeParams) {
-  __shared__ __attribute__((aligned(16))) char lds[kTileLds];
-  const int lane = threadIdx.x;
+__global__ __launch_bounds__(64 * kCuWaves) __attribute__((amdgpu_waves_per_eu(2))) void decode_tiles_kernel(DecodeParams) {
+  extern __shared__ __attribute__((aligned(16))) char all_lds[];   // kTileLds for every wave
 #ifdef COCKTAIL_TRACE
   const uint64_t t_start = __builtin_amdgcn_s_memrealtime();
 #endif
   const FirstParams fp = first_params();
-  if (int(blockIdx.x) >= fp.num_workers) {
-    const AppendSlice a = append_slice(int(blockIdx.x) - fp.num_workers);
+  const Place me = place(fp);
+  const int lane = me.lane;
+  char* const lds = all_lds + me.wave * kTileLds;
+  if (me.worker >= fp.num_workers) {
+    const AppendSlice a = append_slice(me.worker - fp.num_workers);
     if (a.tokens <= 0) {
       write_neutral_set<HD>(a.pid, lane);
       return;
@@ -824,7 +827,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void de
     return;
   }
   Stream<HD> sm;
-  sm.init(load_record(fp.recs + blockIdx.x), fp);
+  sm.init(load_record(fp.recs + me.worker), fp);
   sm.ngran = 0, sm.nps = 0;
   Piece cur = sm.next(lane);
   while (cur.nu > 0) {
@@ -839,8 +842,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void de
     }
   }
 #ifdef COCKTAIL_TRACE
-  if (threadIdx.x == 0) {
-    uint64_t* tr = kparams()->trace + blockIdx.x * 4;
+  if (lane == 0) {
+    uint64_t* tr = kparams()->trace + me.worker * 4;
     tr[0] = t_start;
     tr[1] = __builtin_amdgcn_s_memrealtime();
     tr[2] = __builtin_amdgcn_s_getreg((4) | (0 << 6) | (31 << 11));    // HW_ID
@@ -867,7 +870,7 @@ hipError_t launch_decode_tiles(const DecodeParams& p, int group_size, bool non_t
 #undef COCKTAIL_PICK
 #undef COCKTAIL_PICK2
   if (!kern) return hipErrorInvalidValue;   // a group size larger than head_dim: refused by the shape check before
-  return launch(kern, dim3(grid), dim3(64), st, p);
+  return launch_workers(kern, p, grid, kTileLds, st);
 }
 
 }  // namespace cocktail
