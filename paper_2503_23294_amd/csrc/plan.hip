@@ -85,8 +85,17 @@ constexpr int kShortRangePoolPercent = 40;
 // 35.3 -> 34.4, 4 x 45K (11) 44.3 -> 43.7, but 40.2 -> 42.4 with 5 / 25 / 70 %, 40 x 128K (40) 104 -> 117; four heads, 24K 20.5 -> 18.5, 64K
 // 29.4 -> 25.2, 4 x 45K 48.6 -> 45.6, 4 x 64K (16) 68.5 -> 67.3, ragged up to 128K (36) 206 -> 210; eight heads, 24K 20.8 -> 18.3, 64K 28.8 ->
 // 25.0, 4 x 128K 130 -> 126.7, 8 x 16K with 300 appended 49.8 -> 47.6; sixteen, ragged up to 64K 50.3 -> 47.3.
-constexpr int kAlignedBlocks = 8, kAlignedBlocksQuads = 20;
-constexpr int kAlignedQuadsWorkers = 1024;   // kAlignedBlocksQuads was measured with a full chip: from a worker per SIMD on, kAlignedBlocks below
+// With kInt2Stretch as well, one head, 10 and 12 blocks per worker: 42.8 -> 41.0 and 48.4 -> 45.9 at 5 / 25 / 70 %, 46.6 -> 45.6 and 52.0 ->
+// 51.4 at MIX; at 16 blocks 58.4 -> 57.0, but 64.7 -> 65.0.
+constexpr int kAlignedBlocks = 8, kAlignedBlocksHeads = 12, kAlignedBlocksQuads = 20;
+constexpr int kSimds = 1024;   // the larger two were measured with a full chip: from a worker per SIMD on, kAlignedBlocks below
+// Workers w and w + kSimds share a SIMD, and two INT2 ranges side by side, both bound by the vector ALU, take 1.4 times as long as one next to
+// another class (5 / 25 / 70 %, 2 x 60K, 12 heads: workers next to INT4 or FP16 end at 34 us, the later one of two INT2 workers at 47).
+// So INT2 gets no more than kSimds workers where its ranges need not become longer than this for it; those of the other classes become
+// shorter.  Without -> with (us, behind another kernel of 6): 32 heads 32K 39.6 -> 35.3, 4 x 64K at 8 heads 65.8 -> 61.9, 2 x 40K at 9 56.3 ->
+// 48.0, at 16 45.2 -> 37.1, 4 x 45K at 4 48.6 -> 46.9.  A limit of 1.15 misses some (2 x 64K at 5 heads 37.4 -> 35.3), 1.7 brings nothing more;
+// the same for INT4 (10 / 60 / 30 %, needs 1.4) 44.1 -> 48.
+constexpr double kInt2Stretch = 1.25;
 // Fewer blocks per worker than this are rounded to whole iterations (INT2: four units): 24K, eight heads 20.2 -> 18.7.
 constexpr int kWholeIterationBlocks = 8;
 
@@ -156,36 +165,50 @@ static Tuning read_tuning() {
 }
 
 // Ranges that end where runs end.  `nblk` [kNumClasses][B] as [NC * b + c]: blocks of a run, the same for all `heads` heads; cost[c]: of a
-// block.  Finds the smallest cost a worker may be given such that `slots` workers are enough, cuts every run into equal parts of at most
+// block; `most_int2`: workers INT2 may have (kInt2Stretch).  Finds the smallest cost a worker may be given such that `slots` workers are enough, cuts every run into equal parts of at most
 // that, and lets workers that are left over (beyond 1 in 40: they would bring nothing) cut the dearest parts once more.  Returns the first block of every worker's range
 // in class, sequence, head order (slots + 1 entries), or nothing if there are more runs than workers.
 static std::vector<int32_t> aligned_ranges(const std::vector<int32_t>& nblk, int B, int heads, int slots, const double (&cost)[kNumClasses],
-                                           int units_per_block) {
+                                           int units_per_block, int64_t most_int2) {
   constexpr int NC = kNumClasses;
+  int64_t int2_range = 0;   // blocks of a range of INT2, if not by cost
   auto per_worker = [&](int c, double budget) {
+    if (c == 0 && int2_range) return int2_range;
     int64_t n = static_cast<int64_t>(budget / cost[c]);
     const int whole = std::max(1, kIterUnits[c] / units_per_block);
     if (n < kWholeIterationBlocks) n = n / whole * whole;
     return std::max<int64_t>(n, 1);
   };
+  auto parts_of = [&](int c, int64_t per) {
+    int64_t n = 0;
+    for (int b = 0; b < B; ++b) n += (nblk[NC * b + c] + per - 1) / per;
+    return n * heads;
+  };
   auto workers_for = [&](double budget) {
     int64_t n = 0;
-    for (int c = 0; c < NC; ++c) {
-      const int64_t per = per_worker(c, budget);
-      for (int b = 0; b < B; ++b) n += (nblk[NC * b + c] + per - 1) / per;
-    }
-    return n * heads;
+    for (int c = 0; c < NC; ++c) n += parts_of(c, per_worker(c, budget));
+    return n;
   };
   double total = 0;
   for (int b = 0; b < B; ++b)
     for (int c = 0; c < NC; ++c) total += cost[c] * heads * nblk[NC * b + c];
   std::vector<int32_t> bound;
   if (total == 0 || workers_for(2 * total) > slots) return bound;
-  double lo = 0, hi = total / slots;
-  while (workers_for(hi) > slots) lo = hi, hi *= 2;
-  for (int i = 0; i < 20; ++i) {
-    const double mid = 0.5 * (lo + hi);
-    (workers_for(mid) <= slots ? hi : lo) = mid;
+  auto smallest_budget = [&] {
+    double lo = 0, hi = total / slots;
+    while (workers_for(hi) > slots) lo = hi, hi *= 2;
+    for (int i = 0; i < 20; ++i) {
+      const double mid = 0.5 * (lo + hi);
+      (workers_for(mid) <= slots ? hi : lo) = mid;
+    }
+    return hi;
+  };
+  double hi = smallest_budget();
+  if (most_int2 < slots && parts_of(0, per_worker(0, hi)) > most_int2) {
+    const int whole = std::max(1, kIterUnits[0] / units_per_block);
+    int64_t per = per_worker(0, hi);
+    while (per * cost[0] <= kInt2Stretch * hi && parts_of(0, per) > most_int2) per += per < kWholeIterationBlocks ? whole : 1;
+    if (per * cost[0] <= kInt2Stretch * hi) int2_range = per, hi = smallest_budget();
   }
   std::vector<int32_t> parts(NC * B), extra(NC * B, 0);   // parts per run; in addition one more for the first `extra` heads
   int64_t left = slots - slots / 40;
@@ -198,7 +221,7 @@ static std::vector<int32_t> aligned_ranges(const std::vector<int32_t>& nblk, int
   }
   std::priority_queue<std::pair<double, int>> dearest;   // cost of the largest part, run
   auto offer = [&](int i) {
-    if (parts[i] > 0 && parts[i] < nblk[i]) dearest.push({(nblk[i] + parts[i] - 1) / parts[i] * cost[i % NC], i});
+    if (parts[i] > 0 && parts[i] < nblk[i] && !(i % NC == 0 && int2_range)) dearest.push({(nblk[i] + parts[i] - 1) / parts[i] * cost[i % NC], i});
   };
   if (left > 0)
     for (int i = 0; i < NC * B; ++i) offer(i);
@@ -447,11 +470,11 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
   std::vector<int32_t> bound;   // aligned ranges of one set's workers
   const bool tiles = quads && uses_tiles(wrep);
   const int slots = twins ? NST * group_workers : P;
-  const int aligned_blocks = quads && P >= kAlignedQuadsWorkers ? kAlignedBlocksQuads : kAlignedBlocks;
+  const int aligned_blocks = P < kSimds ? kAlignedBlocks : quads ? kAlignedBlocksQuads : kAlignedBlocksHeads;
   if (!layout && !tune.pair_table_set && (tiles || (!tune.pool_percent_set && tot_blocks <= int64_t(aligned_blocks) * P))) {
     double block_cost[NC];
     for (int c = 0; c < NC; ++c) block_cost[c] = double(block_bytes[c]) * double(weight[c]);
-    bound = aligned_ranges(v_nblk, B, Hw / sets, slots, block_cost, units_per_block);
+    bound = aligned_ranges(v_nblk, B, Hw / sets, slots, block_cost, units_per_block, kSimds / sets);
     if (!bound.empty()) pool_percent = 0;
   }
   {

@@ -284,6 +284,23 @@ def test_ranges_that_end_where_runs_end(rep, lens, workers, aligned, head_dim):
         assert len(busy) >= 0.95 * min(p, h["gblocks"])
 
 
+@pytest.mark.parametrize("rep,lens,mix,workers,held", [
+    (1, [64 * 4000], (0.05, 0.25, 0.0, 0.7), 2048, True), (8, [64 * 3000, 64 * 2500 + 7], (0.05, 0.25, 0.0, 0.7), 2048, True),
+    (4, [64 * 9000], (0.05, 0.25, 0.0, 0.7), 2048, True), (16, [64 * 2500] * 2, (0.05, 0.25, 0.0, 0.7), 2048, True),
+    (8, [64 * 3000], (0.0, 0.0, 0.0, 1.0), 2048, False), (8, [64 * 3000], (0.0, 0.1, 0.0, 0.9), 2048, False), (8, [64 * 1500], (0.05, 0.25, 0.0, 0.7), 1000, True)])
+def test_no_two_workers_of_a_simd_on_int2(rep, lens, mix, workers, held):
+    """INT2 has more than half of the cost: it gets no more workers than there are SIMDs, where that does not make its ranges much
+    longer than the others; every block is still read once."""
+    w = workloads.small(f"held{rep}", len(lens), 4 * rep, 4, lens, 64, 32, mix=mix, seed_offset=905)
+    plan, _ = _plan(w, workers)
+    _check_work_split(plan, w, workers)
+    h, p = _parse(plan), int(plan.sizes.num_workers)
+    recs = _arr(plan.blob, h["off"]["worker_rec"], np.int32, 16 * p).reshape(p, 16)
+    busy = recs[:, 0] < recs[:, 1]
+    assert ((busy & (recs[:, 6] == 0)).sum() <= 1024) == held
+    assert busy.sum() >= 0.95 * p
+
+
 def test_plan_is_the_same_whatever_the_buffer_it_is_written_to():
     """One pass into a buffer of any content and spare room gives the bytes of a size query followed by an exact fit."""
     import ctypes as C
