@@ -266,7 +266,7 @@ int cocktail_reorder_quantize_paged(const cocktail_shape* shape, const cocktail_
  * the call after it finds the counters at zero again.  Which worker takes which pool piece differs from call to call, so
  * two calls on the same inputs agree to fp32 summation order, not bit for bit
  * (plans made with cocktail_plan_options::reproducible use no pools and are reproducible bit for bit, and so are
- * plans on matrix instructions whose workgroups serve five to eight query heads: Hq/Hkv of 5 to 8, and the larger
+ * plans with few blocks per worker, about 12 to 20 or fewer, which have no pools either, and plans on matrix instructions whose workgroups serve five to eight query heads: Hq/Hkv of 5 to 8, and the larger
  * ratios whose largest divisor up to 8 is at least 5, such as 10, 12 and 16 but not 9, 11 or 13).  Shapes with
  * Hq = Hkv run one query head per wave on the vector ALU; 2 <= Hq/Hkv <= 8 run all query heads of a kv head in one
  * wave on matrix instructions (4x4x4 up to four heads, 16x16x32 beyond; V in token quads), unless the plan asks for

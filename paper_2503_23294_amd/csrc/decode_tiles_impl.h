@@ -27,9 +27,9 @@
 // Bound by memory and, for the INT2 class, by the vector ALU (busy 90 % of a call on INT2 blocks of G 32): 190 vector and 22
 // matrix instructions per 32 INT2 tokens and eight heads at G 32 (151 and 19 at G 64; the loop of the built kernel without its
 // rescale), where a pair of waves with four heads each took 280 + 64.
-// 4 x 128K tokens, 64 query / 8 kv heads (759 MB): 182.5 -> 130 us per call; 8 ragged sequences, 64 q / 4 kv heads (two
-// sets per kv head): 92 -> 60 us, 52 with the sets as twins (plan.hip); 8 x 16K tokens and 300 appended, 64 q / 8 kv heads:
-// 66.5 -> 49.5 us.
+// 4 x 128K tokens, 64 query / 8 kv heads (759 MB): 182.5 -> 126.5 us per call; 8 ragged sequences, 64 q / 4 kv heads (two
+// sets per kv head): 92 -> 60 us, 47.5 with the sets as twins and ranges that end where runs end (plan.hip); 8 x 16K tokens and 300 appended, 64 q / 8 kv heads:
+// 66.5 -> 47.2 us.
 #pragma once
 #include <hip/hip_runtime.h>
 

@@ -888,13 +888,13 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
     put(hd.off_run_blocks, v_cap.data(), 4 * NC * size_t(B));
     put(hd.off_segments, segs.data(), sizeof(Segment) * size_t(S));
     put(hd.off_bh_off, bh_off.data(), 4 * bh_off.size());
-    // Which workgroup id runs which range.  Workgroup ids are handed to the compute units in order
-    // (round-robin over the XCDs), and when P fills the chip twice, workgroup i shares a SIMD with
-    // workgroup i + P/2, which was dispatched later and loses every issue arbitration against it.
-    //   mode 0 (default): range w runs as workgroup w.  With the class-major layout the INT2 ranges
+    // Which worker id runs which range.  Worker ids are handed to the compute units in order
+    // (round-robin over the XCDs), and when P fills the chip twice, worker i shares a SIMD with
+    // worker i + P/2, which was dispatched later and loses every issue arbitration against it.
+    //   mode 0 (default): range w runs as worker w.  With the class-major layout the INT2 ranges
     //           get INT4 / FP16 ranges as SIMD mates, the mix that keeps both the vector ALU and the
     //           memory pipeline busy.
-    //   mode 2: rank r of group j becomes workgroup (r odd ? P/2 : 0) + j*k/2 + (r/2 + j) mod (k/2):
+    //   mode 2: rank r of group j becomes worker (r odd ? P/2 : 0) + j*k/2 + (r/2 + j) mod (k/2):
     //           SIMD mates are neighbouring ranks of one group.  Mode 3: mates are ranks r and r + k/2.
     // With twins the groups of a unit are dealt out so that the workers of a stripe are kXcds apart.
     // Where a class has more than half of the workers, some have a mate of their own class, and of those the one dispatched first gets ahead
