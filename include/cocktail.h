@@ -453,7 +453,8 @@ int cocktail_selftest_arithmetic(uint64_t* mismatches, void* stream);
 /*
  * Debugging aid: value of one field of the plan header (the internal layout of the blob cocktail_plan writes),
  * by the name it has in the library's source, e.g. "off_counters", "num_groups", "class_blocks" (index =
- * class), plus a few constants of the layout ("counter_stride_bytes", "iter_units", "sizeof_worker_rec", ...).
+ * class), plus a few constants of the layout ("counter_stride_bytes", "iter_units", "sizeof_worker_rec", ...) and the waves
+ * per workgroup a decode call on the plan is launched with ("workgroup_waves").
  * Errors: EINVAL (not a plan of this library version, unknown name, index out of range).
  */
 int cocktail_plan_field(const void* plan_host, const char* name, int32_t index, int64_t* value);

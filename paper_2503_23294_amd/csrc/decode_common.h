@@ -88,7 +88,6 @@ __device__ __forceinline__ FirstParams first_params() {
 
 // Which worker a wave is.  A workgroup is one wave, or (launch_workers) kCuWaves of them: the waves of a workgroup have the ids of
 // every CU-count-th worker, so that the worker's XCD is its id modulo 8 and its SIMD mate is P / 2 ids away in both cases.
-constexpr int kCuWaves = 8, kChipWorkers = 256 * kCuWaves;
 struct Place {
   int wave, lane, worker;
 };
@@ -624,11 +623,10 @@ hipError_t launch_decode_tiles(const DecodeParams& p, int group_size, bool non_t
 // 60.6 -> 55.4; INT2-heavy (5 / 25 / 70 %) 4 x 64K at 8 heads 76.8 -> 63.2, 2 x 40K at 9 59.3 -> 48.5, 4 x 45K at 3 47.7 -> 42.5.  Back to back:
 // 35.7 -> 30.9 (2 x 64K at 5 heads), 53 -> 42, 42.3 -> 37.9, the same where the merge has one workgroup per unit or few.
 // Slices of appended tokens want to start where the first worker ends, not where the first compute unit does: then, and where the
-// workers are no multiple of the chip's, one by one.
+// workers do not fill the chip exactly once (workgroup_waves), one by one.
 template <class... A>
 inline hipError_t launch_workers(void (*kern)(A...), const DecodeParams& p, int grid, size_t lds, hipStream_t st) {
-  const bool by_unit = grid == p.num_workers && p.num_workers % kChipWorkers == 0;
-  const int waves = by_unit ? kCuWaves : 1;
+  const int waves = workgroup_waves(p.num_workers, grid - p.num_workers);
   return launch_lds(kern, dim3(grid / waves), dim3(64 * waves), waves * lds, st, p);
 }
 

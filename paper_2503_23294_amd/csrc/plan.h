@@ -34,6 +34,16 @@ constexpr int kMaxPoolSegments = 32;           // segments one pool may touch (a
 // The appended tokens of a (sequence, kv head) are attended to by one extra workgroup per this many 64-token
 // blocks of append capacity (one partial state each), so a long generation does not hang on a single wave.
 constexpr int kAppendSliceBlocks = 8;
+// The chip: 256 compute units of four SIMDs; the decode kernels run two waves per SIMD.
+constexpr int kCuWaves = 8, kChipWorkers = 256 * kCuWaves, kSimds = kChipWorkers / 2;
+// Waves per workgroup of a decode launch: a compute unit's where the workers fill the chip exactly once, else one.  With twice or three
+// times as many workers the next workgroup of a unit waits for the slowest of eight waves, where a single wave starts as soon as one
+// ends.  One by one | by unit (us per call, caches in turn): one head per wave, 4096 workers, 32K 32 heads 36.6 | 38.4, 128K 40 heads 117.7 |
+// 121.8, 6144 workers 40.1 | 42.6 and 122 | 132; eight heads, 4 x 32K 44.8 | 46.7 and 48.9 | 56.0.  (4 x 64K with four heads 76.3 | 74.4 and
+// 84 | 80.4, 4 x 128K with eight 148 | 138.5; but 2048 workers take 67 and 126 there.)  A call with append slices in its grid: launch_workers.
+__host__ __device__ inline int workgroup_waves(int num_workers, int append_slices) {
+  return num_workers == kChipWorkers && append_slices == 0 ? kCuWaves : 1;
+}
 constexpr int kCounterStride = 32;             // uint32 slots between two pool counters (one 128-byte line each)
 // Query heads per kv head for which one wave serves all of them with matrix instructions and V is stored in token quads.
 constexpr int kQuadMinRep = 2, kQuadMaxRep = 8;

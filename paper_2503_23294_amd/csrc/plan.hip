@@ -88,7 +88,7 @@ constexpr int kShortRangePoolPercent = 40;
 // With kInt2Stretch as well, one head, 10 and 12 blocks per worker: 42.8 -> 41.0 and 48.4 -> 45.9 at 5 / 25 / 70 %, 46.6 -> 45.6 and 52.0 ->
 // 51.4 at MIX; at 16 blocks 58.4 -> 57.0, but 64.7 -> 65.0.
 constexpr int kAlignedBlocks = 8, kAlignedBlocksHeads = 12, kAlignedBlocksQuads = 20;
-constexpr int kSimds = 1024;   // the larger two were measured with a full chip: from a worker per SIMD on, kAlignedBlocks below
+// (the larger two from a worker per SIMD on: measured with a full chip)
 // Workers w and w + kSimds share a SIMD, and two INT2 ranges side by side, both bound by the vector ALU, take 1.4 times as long as one next to
 // another class (5 / 25 / 70 %, 2 x 60K, 12 heads: workers next to INT4 or FP16 end at 34 us, the later one of two INT2 workers at 47).
 // So INT2 gets no more than kSimds workers where its ranges need not become longer than this for it; those of the other classes become
@@ -291,6 +291,7 @@ extern "C" int cocktail_plan_field(const void* plan_host, const char* name, int3
   if (std::strcmp(name, "counter_stride_bytes") == 0) return *value = 4 * kCounterStride, COCKTAIL_OK;
   if (std::strcmp(name, "partial_header_floats") == 0) return *value = kPartialFloats, COCKTAIL_OK;
   if (std::strcmp(name, "iter_units") == 0 && index >= 0 && index < kNumClasses) return *value = kIterUnits[index], COCKTAIL_OK;
+  if (std::strcmp(name, "workgroup_waves") == 0) return *value = workgroup_waves(hd->num_workers, hd->append_slices), COCKTAIL_OK;
   if (std::strcmp(name, "sizeof_segment") == 0) return *value = sizeof(Segment), COCKTAIL_OK;
   if (std::strcmp(name, "sizeof_worker_rec") == 0) return *value = sizeof(WorkerRec), COCKTAIL_OK;
   if (std::strcmp(name, "sizeof_group_rec") == 0) return *value = sizeof(GroupRec), COCKTAIL_OK;

@@ -932,13 +932,14 @@ def _sample_heads(w, n, seed):
 @pytest.mark.parametrize("workers", [2047, 2048, 4096])
 @pytest.mark.parametrize("rep,head_dim,group", [(1, 128, 32), (1, 64, 32), (3, 128, 64), (4, 64, 64), (5, 64, 32), (8, 128, 128), (16, 128, 32)])
 def test_waves_launched_one_by_one_and_by_compute_unit(rep, head_dim, group, workers):
-    """Workers that fill the chip are launched in workgroups of eight waves, a compute unit each (and 4096 in twice as many of
-    them); one worker less and every wave is a workgroup.  Every worker runs once in each case: all tokens are covered."""
+    """Workers that fill the chip once are launched in workgroups of eight waves, a compute unit each; one worker less, or twice
+    as many, and every wave is a workgroup.  Every worker runs once in each case: all tokens are covered."""
     w = workloads.small(f"unit{rep}_d{head_dim}", 2, 4 * rep, 4, [40000, 26001], 64, group, mix=(0.1, 0.2, 0.3, 0.4), head_dim=head_dim,
                         seed_offset=911 + rep)
     _announce(f"{w.name} workers={workers}")
     c = Case(w, workers=workers)
     assert int(c.plan.sizes.num_workers) == workers
+    assert ck.cocktail_plan_field(c.plan, "workgroup_waves") == (8 if workers == 2048 else 1)
     ck.cocktail_decode_check(c.cache)
     for b, h in _sample_heads(w, 2, rep):
         _announce(f"  head {b},{h}: {c.check_head(b, h):.2e}")

@@ -301,6 +301,18 @@ def test_no_two_workers_of_a_simd_on_int2(rep, lens, mix, workers, held):
     assert busy.sum() >= 0.95 * p
 
 
+@pytest.mark.parametrize("workers,capacity,waves", [(2048, 0, 8), (2048, 1, 1), (2047, 0, 1), (1024, 0, 1), (4096, 0, 1), (6144, 0, 1)])
+def test_workgroups_of_a_compute_unit_where_the_workers_fill_the_chip_once(workers, capacity, waves):
+    """Twice as many workers go out one by one again (a unit's next workgroup would wait for its slowest wave), and so do calls
+    with append slices."""
+    for rep in (1, 4, 8):
+        w = workloads.small(f"waves{rep}", 1, 8 * rep, 8, [64 * 900], 64, 32, seed_offset=921)
+        sh = ck.make_shape(w.batch, w.num_q_heads, w.num_kv_heads, w.head_dim, w.chunk_size, w.group_size)
+        plan = ck.cocktail_plan(sh, w.seq_lens, np.concatenate(workloads.chunk_bits(w)), workers, append_capacity=capacity)
+        assert int(plan.sizes.num_workers) == workers
+        assert ck.cocktail_plan_field(plan, "workgroup_waves") == waves
+
+
 def test_plan_is_the_same_whatever_the_buffer_it_is_written_to():
     """One pass into a buffer of any content and spare room gives the bytes of a size query followed by an exact fit."""
     import ctypes as C
