@@ -95,6 +95,9 @@ constexpr int kAlignedBlocks = 8, kAlignedBlocksHeads = 12, kAlignedBlocksQuads 
 // shorter.  Without -> with (us, behind another kernel of 6): 32 heads 32K 39.6 -> 35.3, 4 x 64K at 8 heads 65.8 -> 61.9, 2 x 40K at 9 56.3 ->
 // 48.0, at 16 45.2 -> 37.1, 4 x 45K at 4 48.6 -> 46.9.  A limit of 1.15 misses some (2 x 64K at 5 heads 37.4 -> 35.3), 1.7 brings nothing more;
 // the same for INT4 (10 / 60 / 30 %, needs 1.4) 44.1 -> 48.
+// Only where the launch goes by compute unit (workgroup_waves), which is what makes w and w + kSimds mates whatever ran before: one by one the
+// longer INT2 ranges still meet each other on some SIMDs.  Without -> with, 300 tokens appended, behind another kernel: 4 x 64K, four heads
+// 62.7 -> 69.9, eight 67.4 -> 75.9; 2 x 40K, nine 55.1 -> 58.7 (by cost 63.0, 66.8 and 56.2); 3072 workers, 32 heads 32K 35.6 -> 37.6.
 constexpr double kInt2Stretch = 1.25;
 // Fewer blocks per worker than this are rounded to whole iterations (INT2: four units): 24K, eight heads 20.2 -> 18.7.
 constexpr int kWholeIterationBlocks = 8;
@@ -475,7 +478,8 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
   if (!layout && !tune.pair_table_set && (tiles || (!tune.pool_percent_set && tot_blocks <= int64_t(aligned_blocks) * P))) {
     double block_cost[NC];
     for (int c = 0; c < NC; ++c) block_cost[c] = double(block_bytes[c]) * double(weight[c]);
-    bound = aligned_ranges(v_nblk, B, Hw / sets, slots, block_cost, units_per_block, kSimds / sets);
+    const bool mates = workgroup_waves(P, append_capacity) > 1;   // SIMD mates are known
+    bound = aligned_ranges(v_nblk, B, Hw / sets, slots, block_cost, units_per_block, mates ? kSimds / sets : slots);
     if (!bound.empty()) pool_percent = 0;
   }
   {
