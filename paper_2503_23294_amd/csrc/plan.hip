@@ -88,7 +88,8 @@ constexpr int kShortRangePoolPercent = 40;
 // With kInt2Stretch as well, one head, 10 and 12 blocks per worker: 42.8 -> 41.0 and 48.4 -> 45.9 at 5 / 25 / 70 %, 46.6 -> 45.6 and 52.0 ->
 // 51.4 at MIX; at 16 blocks 58.4 -> 57.0, but 64.7 -> 65.0.
 constexpr int kAlignedBlocks = 8, kAlignedBlocksHeads = 12, kAlignedBlocksQuads = 20;
-// (the larger two from a worker per SIMD on: measured with a full chip)
+// (the larger two with a full chip.  With one worker per SIMD the longest range decides: 1024 workers, behind another kernel, 4 x 40K with four
+// heads at 5 / 25 / 70 % (20 blocks) 61.5 -> 64.7; 1536, 32 heads 32K (11) 41.1 -> 43.5, but 4 x 40K with four heads (13) 51.1 -> 48.4.)
 // Workers w and w + kSimds share a SIMD, and two INT2 ranges side by side, both bound by the vector ALU, take 1.4 times as long as one next to
 // another class (5 / 25 / 70 %, 2 x 60K, 12 heads: workers next to INT4 or FP16 end at 34 us, the later one of two INT2 workers at 47).
 // So INT2 gets no more than kSimds workers where its ranges need not become longer than this for it; those of the other classes become
@@ -474,7 +475,7 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
   std::vector<int32_t> bound;   // aligned ranges of one set's workers
   const bool tiles = quads && uses_tiles(wrep);
   const int slots = twins ? NST * group_workers : P;
-  const int aligned_blocks = P < kSimds ? kAlignedBlocks : quads ? kAlignedBlocksQuads : kAlignedBlocksHeads;
+  const int aligned_blocks = P < kChipWorkers ? kAlignedBlocks : quads ? kAlignedBlocksQuads : kAlignedBlocksHeads;
   if (!layout && !tune.pair_table_set && (tiles || (!tune.pool_percent_set && tot_blocks <= int64_t(aligned_blocks) * P))) {
     double block_cost[NC];
     for (int c = 0; c < NC; ++c) block_cost[c] = double(block_bytes[c]) * double(weight[c]);

@@ -337,6 +337,17 @@ def test_int2_ranges_are_as_long_as_the_others_where_simd_mates_are_not_known(re
         assert (cls == 0).sum() <= 1024 and cost[cls == 0].max() > 1.03 * mean + 1.5 * block[0]
 
 
+@pytest.mark.parametrize("rep,blocks,workers,pools", [
+    (1, 5000, 2048, False), (1, 5000, 1536, True), (1, 3000, 1024, True), (1, 2000, 1024, False), (1, 9000, 3072, False),
+    (4, 9000, 2048, False), (4, 6000, 1536, True), (4, 5000, 1024, True), (4, 2000, 1024, False), (4, 11000, 3072, False), (4, 11000, 2048, True)])
+def test_limits_up_to_which_plans_have_no_pools(rep, blocks, workers, pools):
+    """Four kv heads of `blocks` blocks: up to 12 per worker with one head per wave, 20 with four, and 8 while the chip is not full."""
+    w = workloads.small(f"limits{rep}", 1, 4 * rep, 4, [64 * blocks], 64, 32, mix=(0.1, 0.2, 0.3, 0.4), seed_offset=907)
+    plan, _ = _plan(w, workers)
+    assert (int(_parse(plan)["pool_segs"]) > 0) == pools
+    _check_work_split(plan, w, workers)
+
+
 @pytest.mark.parametrize("workers,capacity,waves", [(2048, 0, 8), (2048, 1, 1), (2047, 0, 1), (1024, 0, 1), (4096, 0, 1), (6144, 0, 1)])
 def test_workgroups_of_a_compute_unit_where_the_workers_fill_the_chip_once(workers, capacity, waves):
     """Twice as many workers go out one by one again (a unit's next workgroup would wait for its slowest wave), and so do calls
