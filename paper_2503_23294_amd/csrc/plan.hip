@@ -100,6 +100,14 @@ constexpr int kAlignedBlocks = 8, kAlignedBlocksHeads = 12, kAlignedBlocksQuads 
 // longer INT2 ranges still meet each other on some SIMDs.  Without -> with, 300 tokens appended, behind another kernel: 4 x 64K, four heads
 // 62.7 -> 69.9, eight 67.4 -> 75.9; 2 x 40K, nine 55.1 -> 58.7 (by cost 63.0, 66.8 and 56.2); 3072 workers, 32 heads 32K 35.6 -> 37.6.
 constexpr double kInt2Stretch = 1.25;
+// Such ranges are taken where the longest is at most this many times the mean plus this many blocks of the dearest class, about what a second
+// partial state costs.  Beyond, the runs are too many for the workers: the longest ones cannot be cut further, and the whole call waits
+// for them (32 heads, 128K and 79 contexts of 1K: 9.2 times the mean).  By cost -> aligned (us; longest range over mean, blocks per worker):
+// eight heads, 48 x 16K 183 -> 207 (1.8, 48), 40 x 16K 163 -> 179 (1.4, 40), 64 x 4K 87.1 -> 82.2 (1.5, 16), 72 x 4K 96.3 -> 87.9 (1.6, 18); four heads,
+// 32K and 79 x 2K 71 -> 78 (2.3, 12), 32K and 48 x 2K 51.9 -> 44.5 (1.5, 8).  Of 132 such shapes these two figures keep 106, the worst of them 2 % slower
+// than by cost, and leave out ten that would have gained, up to 11 %; 1.25 and one block 22, up to 18 %, 1.4 and two keep one that lost 10 %.
+constexpr double kLongestRange = 1.25;
+constexpr int kLongestRangeBlocks = 2;
 // Fewer blocks per worker than this are rounded to whole iterations (INT2: four units): 24K, eight heads 20.2 -> 18.7.
 constexpr int kWholeIterationBlocks = 8;
 
@@ -171,7 +179,8 @@ static Tuning read_tuning() {
 // Ranges that end where runs end.  `nblk` [kNumClasses][B] as [NC * b + c]: blocks of a run, the same for all `heads` heads; cost[c]: of a
 // block; `most_int2`: workers INT2 may have (kInt2Stretch).  Finds the smallest cost a worker may be given such that `slots` workers are enough, cuts every run into equal parts of at most
 // that, and lets workers that are left over (beyond 1 in 40: they would bring nothing) cut the dearest parts once more.  Returns the first block of every worker's range
-// in class, sequence, head order (slots + 1 entries), or nothing if there are more runs than workers.
+// in class, sequence, head order (slots + 1 entries), or nothing if there are more runs than workers or the longest range is too long
+// (kLongestRange).
 static std::vector<int32_t> aligned_ranges(const std::vector<int32_t>& nblk, int B, int heads, int slots, const double (&cost)[kNumClasses],
                                            int units_per_block, int64_t most_int2) {
   constexpr int NC = kNumClasses;
@@ -236,6 +245,13 @@ static std::vector<int32_t> aligned_ranges(const std::vector<int32_t>& nblk, int
     else ++parts[i], offer(i);
     left -= heads;
   }
+  double longest = 0, dearest_block = 0;
+  for (int i = 0; i < NC * B; ++i)
+    if (parts[i] > 0) {
+      longest = std::max(longest, (nblk[i] + parts[i] - 1) / parts[i] * cost[i % NC]);
+      dearest_block = std::max(dearest_block, cost[i % NC]);
+    }
+  if (longest > kLongestRange * total / slots + kLongestRangeBlocks * dearest_block) return bound;
   bound.reserve(slots + 1);
   int32_t at = 0;
   for (int c = 0; c < NC; ++c)

@@ -337,6 +337,22 @@ def test_int2_ranges_are_as_long_as_the_others_where_simd_mates_are_not_known(re
         assert (cls == 0).sum() <= 1024 and cost[cls == 0].max() > 1.03 * mean + 1.5 * block[0]
 
 
+@pytest.mark.parametrize("hq,hkv,long,short,n,mix", [
+    (64, 8, 131072, 1024, 83, (0.15, 0.35, 0.5)), (64, 8, 131072, 4096, 62, (0.05, 0.15, 0.3, 0.5)), (64, 8, 16384, 16384, 63, (0.15, 0.35, 0.5)),
+    (64, 8, 131072, 4096, 85, (0.15, 0.35, 0.5)), (32, 8, 131072, 1024, 79, (0.15, 0.35, 0.5)), (32, 8, 32768, 2048, 79, (0.05, 0.15, 0.3, 0.5)),
+    (40, 40, 16384, 1024, 15, (0.15, 0.35, 0.5)), (64, 4, 131072, 1024, 84, (0.15, 0.35, 0.5)), (128, 8, 131072, 2048, 41, (0.1, 0.3, 0.6)),
+    (8, 8, 131072, 500, 200, (0.1, 0.3, 0.6)), (64, 8, 65536, 2048, 24, (0.15, 0.35, 0.5)), (32, 8, 65536, 65536, 3, (0.05, 0.15, 0.3, 0.5))])
+@pytest.mark.parametrize("workers", [2048, 1000])
+def test_no_worker_holds_up_the_call(hq, hkv, long, short, n, mix, workers):
+    """One long context among many short ones, up to as many runs as workers: no own range is much longer than the mean one,
+    whichever split is taken."""
+    w = workloads.small(f"long{hq}", n + 1, hq, hkv, [long] + [short] * n, 256, 32, mix=mix, seed_offset=909)
+    cls, cost, mean, block = _ranges(_plan(w, workers)[0])
+    # ends on runs: at most 1.25 of the mean and two blocks of the dearest class; by cost: to the nearest block, and with one head
+    # per wave up to 1.27 / 0.9 of the mean by the speed of the SIMD mate
+    assert cost.max() <= (1.25 if hq > hkv else 1.42) * mean + 2 * block.max()
+
+
 @pytest.mark.parametrize("rep,blocks,workers,pools", [
     (1, 5000, 2048, False), (1, 5000, 1536, True), (1, 3000, 1024, True), (1, 2000, 1024, False), (1, 9000, 3072, False),
     (4, 9000, 2048, False), (4, 6000, 1536, True), (4, 5000, 1024, True), (4, 2000, 1024, False), (4, 11000, 3072, False), (4, 11000, 2048, True)])
