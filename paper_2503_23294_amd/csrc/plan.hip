@@ -88,6 +88,15 @@ constexpr int kShortRangePoolPercent = 40;
 // With kInt2Stretch as well, one head, 10 and 12 blocks per worker: 42.8 -> 41.0 and 48.4 -> 45.9 at 5 / 25 / 70 %, 46.6 -> 45.6 and 52.0 ->
 // 51.4 at MIX; at 16 blocks 58.4 -> 57.0, but 64.7 -> 65.0.
 constexpr int kAlignedBlocks = 8, kAlignedBlocksHeads = 12, kAlignedBlocksQuads = 20;
+// The larger two do not hold for all caches (caches in turn, by cost and with pools -> aligned):
+// - one head per wave, INT2 on more than one worker per SIMD but fewer than kFewInt2Pairs (kInt2Stretch could not hold it): a few SIMDs have two
+//   INT2 workers, and without pools the call waits for those.  10 to 12 blocks per worker, 80 % INT2: 37.6 -> 38.9, 41.4 -> 44.2, 36.1 -> 37.6;
+//   85 %: 38.6 -> 40.1, 41.5 -> 43.2; with more of them it is the rule, not the exception: 90 % 36.9 -> 35.6, all INT2 33.1 -> 30.3.
+//   (Waves launched one by one meet by chance: 75 % INT2 and 300 tokens appended 41.5 -> 39.9, 39.5 -> 39.9.)
+// - two to four, nearly all bytes FP16 (kFp16Cache): bound by memory alone, whose differences between compute units are what the pools
+//   even out.  All FP16, 4 x 64K 162.0 -> 164.7, 4 x 78K 196.4 -> 200.2, 4 x 40K the same; 60 / 0 / 20 / 20 %, 4 x 48K 94.3 -> 96.3, 4 x 78K 147.7 ->
+//   152.9, 4 x 32K (8) 67.2 -> 65.8; but with half the chunks at FP16 and INT4 103.0 -> 101.0 (14), 111.4 -> 109.7 (16).
+constexpr double kFewInt2Pairs = 1.4, kFp16Cache = 0.8;
 // (the larger two with a full chip.  With one worker per SIMD the longest range decides: 1024 workers, behind another kernel, 4 x 40K with four
 // heads at 5 / 25 / 70 % (20 blocks) 61.5 -> 64.7; 1536, 32 heads 32K (11) 41.1 -> 43.5, but 4 x 40K with four heads (13) 51.1 -> 48.4.)
 // Workers w and w + kSimds share a SIMD, and two INT2 ranges side by side, both bound by the vector ALU, take 1.4 times as long as one next to
@@ -491,12 +500,19 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
   std::vector<int32_t> bound;   // aligned ranges of one set's workers
   const bool tiles = quads && uses_tiles(wrep);
   const int slots = twins ? NST * group_workers : P;
-  const int aligned_blocks = P < kChipWorkers ? kAlignedBlocks : quads ? kAlignedBlocksQuads : kAlignedBlocksHeads;
+  double all_bytes = 0;
+  for (int c = 0; c < NC; ++c) all_bytes += double(class_nblk[c]) * block_bytes[c];
+  const bool fp16_cache = double(class_nblk[kFp16Class]) * block_bytes[kFp16Class] >= kFp16Cache * all_bytes;
+  const int aligned_blocks = P < kChipWorkers || (quads && fp16_cache) ? kAlignedBlocks : quads ? kAlignedBlocksQuads : kAlignedBlocksHeads;
   if (!layout && !tune.pair_table_set && (tiles || (!tune.pool_percent_set && tot_blocks <= int64_t(aligned_blocks) * P))) {
     double block_cost[NC];
     for (int c = 0; c < NC; ++c) block_cost[c] = double(block_bytes[c]) * double(weight[c]);
     const bool mates = workgroup_waves(P, append_capacity) > 1;   // SIMD mates are known
     bound = aligned_ranges(v_nblk, B, Hw / sets, slots, block_cost, units_per_block, mates ? kSimds / sets : slots);
+    if (!bound.empty() && wrep == 1 && mates && tot_blocks > int64_t(kAlignedBlocks) * P) {
+      const int64_t int2_workers = std::lower_bound(bound.begin(), bound.end(), class_nblk[0]) - bound.begin();
+      if (int2_workers > kSimds && int2_workers < kFewInt2Pairs * kSimds) bound.clear();
+    }
     if (!bound.empty()) pool_percent = 0;
   }
   {

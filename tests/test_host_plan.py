@@ -353,15 +353,30 @@ def test_no_worker_holds_up_the_call(hq, hkv, long, short, n, mix, workers):
     assert cost.max() <= (1.25 if hq > hkv else 1.42) * mean + 2 * block.max()
 
 
-@pytest.mark.parametrize("rep,blocks,workers,pools", [
-    (1, 5000, 2048, False), (1, 5000, 1536, True), (1, 3000, 1024, True), (1, 2000, 1024, False), (1, 9000, 3072, False),
-    (4, 9000, 2048, False), (4, 6000, 1536, True), (4, 5000, 1024, True), (4, 2000, 1024, False), (4, 11000, 3072, False), (4, 11000, 2048, True)])
-def test_limits_up_to_which_plans_have_no_pools(rep, blocks, workers, pools):
-    """Four kv heads of `blocks` blocks: up to 12 per worker with one head per wave, 20 with four, and 8 while the chip is not full."""
-    w = workloads.small(f"limits{rep}", 1, 4 * rep, 4, [64 * blocks], 64, 32, mix=(0.1, 0.2, 0.3, 0.4), seed_offset=907)
+_FOUR = (0.1, 0.2, 0.3, 0.4)
+
+
+@pytest.mark.parametrize("rep,blocks,workers,mix,pools", [
+    (1, 5000, 2048, _FOUR, False), (1, 5000, 1536, _FOUR, True), (1, 3000, 1024, _FOUR, True), (1, 2000, 1024, _FOUR, False), (1, 9000, 3072, _FOUR, False),
+    (4, 9000, 2048, _FOUR, False), (4, 6000, 1536, _FOUR, True), (4, 5000, 1024, _FOUR, True), (4, 2000, 1024, _FOUR, False),
+    (4, 11000, 3072, _FOUR, False), (4, 11000, 2048, _FOUR, True),
+    # INT2 on a few more workers than there are SIMDs; held to one per SIMD; on nearly all; not more than eight blocks per worker
+    (1, 5000, 2048, (0.05, 0.15, 0.8), True), (1, 5000, 2048, (0.05, 0.25, 0.7), False), (1, 5000, 2048, (0.0, 0.05, 0.95), False),
+    (1, 4000, 2048, (0.05, 0.15, 0.8), False),
+    # nearly all bytes FP16
+    (4, 9000, 2048, (1.0, 0.0, 0.0), True), (3, 6000, 2048, (0.6, 0.2, 0.2), True), (4, 4000, 2048, (1.0, 0.0, 0.0), False),
+    (4, 9000, 2048, (0.4, 0.5, 0.1), False), (1, 5000, 2048, (1.0, 0.0, 0.0), False)])
+def test_limits_up_to_which_plans_have_no_pools(rep, blocks, workers, mix, pools):
+    """Four kv heads of `blocks` blocks: up to 12 per worker with one head per wave, 20 with two to four; 8 while the chip is not full,
+    where INT2 shares only a few SIMDs with itself, and where a cache is nearly all FP16."""
+    w = workloads.small(f"limits{rep}", 1, 4 * rep, 4, [64 * blocks], 64, 32, mix=mix, seed_offset=907)
     plan, _ = _plan(w, workers)
     assert (int(_parse(plan)["pool_segs"]) > 0) == pools
     _check_work_split(plan, w, workers)
+    if rep == 1 and mix == (0.05, 0.15, 0.8) and pools:       # launched one by one: no such SIMDs
+        sh = ck.make_shape(w.batch, w.num_q_heads, w.num_kv_heads, w.head_dim, w.chunk_size, w.group_size)
+        bits = np.concatenate(workloads.chunk_bits(w))
+        assert _parse(ck.cocktail_plan(sh, w.seq_lens, bits, workers, append_capacity=64))["pool_segs"] == 0
 
 
 @pytest.mark.parametrize("workers,capacity,waves", [(2048, 0, 8), (2048, 1, 1), (2047, 0, 1), (1024, 0, 1), (4096, 0, 1), (6144, 0, 1)])
