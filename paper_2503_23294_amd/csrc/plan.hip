@@ -51,7 +51,7 @@ constexpr int64_t kQuadCostWeight[kNumClasses] = {1300, 1250, 950, 450};
 // 4 x 128K at 8 heads 134.6 | 131.4 | 130.5 | 129.8 | 132.3; one of 64K 30.7 | 30.0 | 29.7 | 29.8 | 30.7; 2 x 64K at 5 heads 41.1 | 40.4 | 40.3 |
 // 39.9 | 39.8; INT2 and INT4 5 % to either side of these figures differ by no more than two runs do.
 constexpr int64_t kTileCostWeight[kNumClasses] = {1300, 1250, 950, 390};
-// With several sets of heads per kv head (twins) all but the first read the blocks from the L2, so FP16 bytes are cheaper still.  FP16 at
+// With the sets of heads of a kv head as twins all but the first read the blocks from the L2, so FP16 bytes are cheaper still.  FP16 at
 // 450 | 400 | 360 | 340 | 320 | 300 (us): 8 ragged contexts, 16 heads 52.8 | 51.4 | 50.8 | 50.5 | 50.1 | 50.9; 2 x 40K at 12 heads 42.7 | 40.6 | 40.7 |
 // 40.1 | 39.9 | 40.1; one of 128K at 16 60.5 | 60.7 | 58.3 | 58.4 | 57.9 | 58.3.
 constexpr int64_t kTwinCostWeight[kNumClasses] = {1300, 1250, 950, 330};
@@ -440,10 +440,6 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
   const int Hw = shape->num_q_heads / wrep;             // heads of the decode work split
   const int share = rep / wrep;                         // work heads that walk the blocks of one kv head
   const bool quads = uses_token_quads(wrep);
-  if (quads && !tune.weight_set)
-    for (int c = 0; c < NC; ++c)
-      tune.weight[c] = !uses_tiles(wrep) ? kQuadCostWeight[c] : share > 1 ? kTwinCostWeight[c] : kTileCostWeight[c];
-  const int64_t* weight = tune.weight;
   if ((wrep > 1 && !(quads && !uses_tiles(wrep))) || reproducible) pool_percent = 0;
 
   // ---- physical runs of the class buffers: (class, b, h) order, each a contiguous run of blocks ----
@@ -482,6 +478,10 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
   const bool twins = quads && share > 1 && !tune.layout && tune.pair_mode < 2 && kXcds % group_workers == 0 &&
                      P >= unit && int64_t(P % unit) * 32 <= P;
   const int sets = twins ? share : 1;
+  if (quads && !tune.weight_set)   // (sets that are not twins fetch their blocks from memory each)
+    for (int c = 0; c < NC; ++c)
+      tune.weight[c] = !uses_tiles(wrep) ? kQuadCostWeight[c] : twins ? kTwinCostWeight[c] : kTileCostWeight[c];
+  const int64_t* weight = tune.weight;
 
   // ---- global order and segments ----
   // The workers form groups of `group_workers`; group j works on one stripe [cut[c][j], cut[c][j+1]) of

@@ -353,6 +353,18 @@ def test_no_worker_holds_up_the_call(hq, hkv, long, short, n, mix, workers):
     assert cost.max() <= (1.25 if hq > hkv else 1.42) * mean + 2 * block.max()
 
 
+@pytest.mark.parametrize("hq,workers,twins", [(96, 64, False), (96, 720, True), (64, 512, True), (128, 24, False)])
+def test_weights_of_twins_are_for_plans_with_twins(hq, workers, twins):
+    """More than eight heads per kv head: sets that are not laid out as twins fetch every block themselves, and FP16 bytes count as much
+    as with one set."""
+    w = workloads.small(f"sets{hq}", 1, hq, 4, [64 * 4000], 64, 32, mix=(0.3, 0.3, 0.4), seed_offset=913)
+    plan, _ = _plan(w, workers)
+    cls, cost, _, block = _ranges(plan)                       # by the weights of twins
+    f16 = cost[cls == 3].mean() / cost[cls == 0].mean()
+    f16 *= 1.0 if twins else _WEIGHTS[8][3] / _WEIGHTS[16][3]
+    assert abs(f16 - 1) < 0.05
+
+
 _FOUR = (0.1, 0.2, 0.3, 0.4)
 
 
