@@ -112,7 +112,8 @@ typedef struct cocktail_sizes {
   int64_t plan_bytes;                          /* bytes of the plan blob                           */
   int64_t workspace_bytes;                     /* bytes of the decode-attention workspace          */
   int64_t packed_bytes;                        /* K+V bytes of codes + scale/zero, padding excluded */
-  int32_t num_workers;                         /* workgroups the decode kernel is launched with    */
+  int32_t num_workers;                         /* waves the decode kernel is launched with, without those
+                                                  of the append buffers                            */
   int32_t num_partials;                        /* partial softmax states written per call          */
   int32_t num_segments;
   int32_t append_capacity;                     /* tokens per sequence the append buffers can take  */
@@ -146,11 +147,11 @@ typedef struct cocktail_cache {
  * Computes the stable partition of every sequence's chunks by bitwidth, the token
  * count of every class (the FP16 class also receives the T_b mod C tail tokens,
  * Sec. III-A), the block layout of the packed cache and the static split of the
- * decode work over `num_workers` workgroups.
+ * decode work over `num_workers` workers (waves).
  *
  *   seq_lens     HOST [B]           context tokens T_b >= 0
  *   chunk_bits   HOST [sum_b N_b]   N_b = floor(T_b / C) values in {2, 4, 8, 16}, sequence after sequence
- *   num_workers  most workgroups the decode kernel may be launched with (> 0), normally
+ *   num_workers  most workers the decode kernel may be launched with (> 0), normally
  *                cocktail_default_workers(); a plan never has more workers than 32-token
  *                (head_dim 64: 64-token) units of work, rounded up to a multiple of 64:
  *                sizes->num_workers says how many it has
@@ -266,8 +267,9 @@ int cocktail_reorder_quantize_paged(const cocktail_shape* shape, const cocktail_
  * the call after it finds the counters at zero again.  Which worker takes which pool piece differs from call to call, so
  * two calls on the same inputs agree to fp32 summation order, not bit for bit
  * (plans made with cocktail_plan_options::reproducible use no pools and are reproducible bit for bit, and so are
- * plans with few blocks per worker, about 12 to 20 or fewer, which have no pools either, and plans on matrix instructions whose workgroups serve five to eight query heads: Hq/Hkv of 5 to 8, and the larger
- * ratios whose largest divisor up to 8 is at least 5, such as 10, 12 and 16 but not 9, 11 or 13).  Shapes with
+ * plans on matrix instructions whose waves serve five to eight query heads: Hq/Hkv of 5 to 8, and the larger
+ * ratios whose largest divisor up to 8 is at least 5, such as 10, 12 and 16 but not 9, 11 or 13.  Which other plans
+ * have pools is a matter of speed and no contract; cocktail_plan_field "num_pool_segs" is 0 for one without).  Shapes with
  * Hq = Hkv run one query head per wave on the vector ALU; 2 <= Hq/Hkv <= 8 run all query heads of a kv head in one
  * wave on matrix instructions (4x4x4 up to four heads, 16x16x32 beyond; V in token quads), unless the plan asks for
  * the vector ALU only; for larger ratios (up to COCKTAIL_MAX_Q_PER_KV) the query heads of a kv head are cut into equal
@@ -375,7 +377,7 @@ int cocktail_append_fp16_ragged(const cocktail_shape* shape, const void* k_new, 
  * append buffers into the packed cache, behind the FP16 rows of their (sequence, kv head) (they stay FP16 and keep
  * their place in the order of the tokens: the FP16 list of Alg. 1 grows at its end, nothing is quantized again), so
  * that the decode work split of a new plan covers them like any other token instead of leaving them to the few
- * workgroups that serve the append buffers.
+ * waves that serve the append buffers.
  *
  *   cache          the cache as it is: plan_host / plan_dev = the plan in use (made with append buffers and with
  *                  cocktail_plan_options::max_seq_lens), class and append buffers, appended_dev or num_appended
@@ -418,8 +420,8 @@ int cocktail_chunk_bitwidths(int32_t batch, int32_t embed_dim, int32_t total_chu
                              uint8_t* chunk_bits, void* stream);
 
 /*
- * Number of decode workgroups that fills the current HIP device for this shape
- * (compute units x resident waves per unit; a workgroup is one wave).  Needs a GPU: EHIP otherwise.
+ * Number of decode workers (waves) that fills the current HIP device for this shape
+ * (compute units x resident waves per unit).  Needs a GPU: EHIP otherwise.
  */
 int cocktail_default_workers(const cocktail_shape* shape, int32_t* num_workers);
 

@@ -659,6 +659,22 @@ def test_which_plans_have_no_pools(rep):
         assert (groups[:, 0] == 0).all() == static and (recs[:, 14] == 0).all() == static
 
 
+@pytest.mark.parametrize("hq,hkv,lens,workers,mix", [
+    (8, 8, [12800], 128, (0.1, 0.3, 0.6)), (32, 8, [12800], 128, (0.1, 0.3, 0.6)), (32, 32, [1024] * 32, 2048, (0.25, 0.25, 0.5)),
+    (128, 32, [512] * 32, 2048, (0.25, 0.25, 0.5))])
+def test_few_blocks_per_worker_are_no_promise_of_plans_without_pools(hq, hkv, lens, workers, mix):
+    """Fewer than 13 blocks per worker, and pools: calls may differ in their last bits unless `reproducible` is set.  The plan says which
+    it is, and the header makes no promise by the number of blocks."""
+    w = workloads.small("few", len(lens), hq, hkv, lens, 64, 32, mix=mix, seed_offset=919)
+    plan, bits = _plan(w, workers)
+    h = _parse(plan)
+    recs = _arr(plan.blob, h["off"]["worker_rec"], np.int32, 16 * h["workers"]).reshape(-1, 16)
+    assert h["gblocks"] < 13 * h["workers"] and h["pool_segs"] > 0 and (recs[:, 14] > 0).any()
+    fixed = _parse(ck.cocktail_plan(plan.shape, w.seq_lens, np.concatenate(bits), workers, reproducible=True))
+    assert fixed["pool_segs"] == 0
+    assert "blocks per worker" not in open(os.path.join(ROOT, "include", "cocktail.h")).read()
+
+
 def test_room_to_grow_keeps_the_cache_layout_from_plan_to_plan():
     """cocktail_plan_options::max_seq_lens: FP16 runs are laid out for the length a sequence may reach, so the plan
     of a longer context (more FP16 tokens at the end, Sec. III-A) describes the same buffers."""
