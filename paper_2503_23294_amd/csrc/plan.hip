@@ -88,15 +88,14 @@ constexpr int kShortRangePoolPercent = 40;
 // With kInt2Stretch as well, one head, 10 and 12 blocks per worker: 42.8 -> 41.0 and 48.4 -> 45.9 at 5 / 25 / 70 %, 46.6 -> 45.6 and 52.0 ->
 // 51.4 at MIX; at 16 blocks 58.4 -> 57.0, but 64.7 -> 65.0.
 constexpr int kAlignedBlocks = 8, kAlignedBlocksHeads = 12, kAlignedBlocksQuads = 20;
-// The larger two do not hold for all caches (caches in turn, by cost and with pools -> aligned):
-// - one head per wave, INT2 on more than one worker per SIMD but fewer than kFewInt2Pairs (kInt2Stretch could not hold it): a few SIMDs have two
-//   INT2 workers, and without pools the call waits for those.  10 to 12 blocks per worker, 80 % INT2: 37.6 -> 38.9, 41.4 -> 44.2, 36.1 -> 37.6;
-//   85 %: 38.6 -> 40.1, 41.5 -> 43.2; with more of them it is the rule, not the exception: 90 % 36.9 -> 35.6, all INT2 33.1 -> 30.3.
-//   (Waves launched one by one meet by chance: 75 % INT2 and 300 tokens appended 41.5 -> 39.9, 39.5 -> 39.9.)
-// - two to four, nearly all bytes FP16 (kFp16Cache): bound by memory alone, whose differences between compute units are what the pools
-//   even out.  All FP16, 4 x 64K 162.0 -> 164.7, 4 x 78K 196.4 -> 200.2, 4 x 40K the same; 60 / 0 / 20 / 20 %, 4 x 48K 94.3 -> 96.3, 4 x 78K 147.7 ->
-//   152.9, 4 x 32K (8) 67.2 -> 65.8; but with half the chunks at FP16 and INT4 103.0 -> 101.0 (14), 111.4 -> 109.7 (16).
-constexpr double kFewInt2Pairs = 1.4, kFp16Cache = 0.8;
+// One head per wave and more than kAlignedBlocks: not where INT2 has more than one worker per SIMD but fewer than kFewInt2Pairs (kInt2Stretch could
+// not hold it) and the runs are few (kFewRuns): some SIMDs have two INT2 workers, and without pools the call waits for those.  10 to 12 blocks
+// per worker, caches in turn, by cost and with pools -> aligned: 80 % INT2 37.6 -> 38.9, 41.4 -> 44.2, 36.1 -> 37.6, 85 % 38.6 -> 40.1, 41.5 -> 43.2,
+// 2.1 % in the mean of 28 such shapes (-8 to +10 %).  With more pairs they are the rule, not the exception: 90 % 36.9 -> 35.6, all INT2 33.1 -> 30.3;
+// with more runs pools need a partial state for each: 34 shapes -1.9 % in the mean (-17 to +7 %).  (Waves launched one by one meet by chance:
+// 75 % INT2 and 300 tokens appended 41.5 -> 39.9, 39.5 -> 39.9.)
+constexpr double kFewInt2Pairs = 1.4;
+constexpr int kFewRuns = 256;
 // (the larger two with a full chip.  With one worker per SIMD the longest range decides: 1024 workers, behind another kernel, 4 x 40K with four
 // heads at 5 / 25 / 70 % (20 blocks) 61.5 -> 64.7; 1536, 32 heads 32K (11) 41.1 -> 43.5, but 4 x 40K with four heads (13) 51.1 -> 48.4.)
 // Workers w and w + kSimds share a SIMD, and two INT2 ranges side by side, both bound by the vector ALU, take 1.4 times as long as one next to
@@ -109,13 +108,14 @@ constexpr double kFewInt2Pairs = 1.4, kFp16Cache = 0.8;
 // longer INT2 ranges still meet each other on some SIMDs.  Without -> with, 300 tokens appended, behind another kernel: 4 x 64K, four heads
 // 62.7 -> 69.9, eight 67.4 -> 75.9; 2 x 40K, nine 55.1 -> 58.7 (by cost 63.0, 66.8 and 56.2); 3072 workers, 32 heads 32K 35.6 -> 37.6.
 constexpr double kInt2Stretch = 1.25;
-// Such ranges are taken where the longest is at most this many times the mean plus this many blocks of the dearest class, about what a second
-// partial state costs.  Beyond, the runs are too many for the workers: the longest ones cannot be cut further, and the whole call waits
-// for them (32 heads, 128K and 79 contexts of 1K: 9.2 times the mean).  By cost -> aligned (us; longest range over mean, blocks per worker):
-// eight heads, 48 x 16K 183 -> 207 (1.8, 48), 40 x 16K 163 -> 179 (1.4, 40), 64 x 4K 87.1 -> 82.2 (1.5, 16), 72 x 4K 96.3 -> 87.9 (1.6, 18); four heads,
-// 32K and 79 x 2K 71 -> 78 (2.3, 12), 32K and 48 x 2K 51.9 -> 44.5 (1.5, 8).  Of 132 such shapes these two figures keep 106, the worst of them 2 % slower
-// than by cost, and leave out ten that would have gained, up to 11 %; 1.25 and one block 22, up to 18 %, 1.4 and two keep one that lost 10 %.
-constexpr double kLongestRange = 1.25;
+// Such ranges are taken where the longest is at most this many times the mean plus this many blocks of the dearest class.  Beyond, the runs are
+// too many for the workers: the longest ones cannot be cut further, and the whole call waits for them (32 heads, 128K and 79 contexts of 1K:
+// 9.2 times the mean).  By cost -> aligned (us; longest range over mean, blocks per worker): five heads and more, 48 x 16K 183 -> 207 (1.8, 48),
+// 40 x 16K 163 -> 179 (1.4, 40), 64 of up to 13K 68 -> 153 (6.7, 11), but 64 x 4K 87.1 -> 82.2 (1.5, 16).  Up to four, where the pools
+// need a partial state per run and rank, more: 32K and 79 x 2K 71 -> 78 (2.3, 12), 64 of up to 24K 98 -> 221 (8.6, 14), but 32K and 48 x 2K
+// 51.9 -> 44.5 (1.5, 8), at 70 % INT2 32K and 79 x 2K 59.8 -> 53.6 (1.75, 12).  Of 1324 random shapes (up to four heads | more) these keep 1090 | 181
+// with 24 | 4 that lose more than 4 %, at most 11, and leave out 17 | 3 that would have gained 3 % and more (1.25 for all: 68).
+constexpr double kLongestRange = 1.8, kLongestRangeTiles = 1.25;
 constexpr int kLongestRangeBlocks = 2;
 // Fewer blocks per worker than this are rounded to whole iterations (INT2: four units): 24K, eight heads 20.2 -> 18.7.
 constexpr int kWholeIterationBlocks = 8;
@@ -186,12 +186,12 @@ static Tuning read_tuning() {
 }
 
 // Ranges that end where runs end.  `nblk` [kNumClasses][B] as [NC * b + c]: blocks of a run, the same for all `heads` heads; cost[c]: of a
-// block; `most_int2`: workers INT2 may have (kInt2Stretch).  Finds the smallest cost a worker may be given such that `slots` workers are enough, cuts every run into equal parts of at most
+// block; `most_int2`: workers INT2 may have (kInt2Stretch); `longest_range`: kLongestRange.  Finds the smallest cost a worker may be given such that `slots` workers are enough, cuts every run into equal parts of at most
 // that, and lets workers that are left over (beyond 1 in 40: they would bring nothing) cut the dearest parts once more.  Returns the first block of every worker's range
 // in class, sequence, head order (slots + 1 entries), or nothing if there are more runs than workers or the longest range is too long
 // (kLongestRange).
 static std::vector<int32_t> aligned_ranges(const std::vector<int32_t>& nblk, int B, int heads, int slots, const double (&cost)[kNumClasses],
-                                           int units_per_block, int64_t most_int2) {
+                                           int units_per_block, int64_t most_int2, double longest_range) {
   constexpr int NC = kNumClasses;
   int64_t int2_range = 0;   // blocks of a range of INT2, if not by cost
   auto per_worker = [&](int c, double budget) {
@@ -260,7 +260,7 @@ static std::vector<int32_t> aligned_ranges(const std::vector<int32_t>& nblk, int
       longest = std::max(longest, (nblk[i] + parts[i] - 1) / parts[i] * cost[i % NC]);
       dearest_block = std::max(dearest_block, cost[i % NC]);
     }
-  if (longest > kLongestRange * total / slots + kLongestRangeBlocks * dearest_block) return bound;
+  if (longest > longest_range * total / slots + kLongestRangeBlocks * dearest_block) return bound;
   bound.reserve(slots + 1);
   int32_t at = 0;
   for (int c = 0; c < NC; ++c)
@@ -500,16 +500,14 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
   std::vector<int32_t> bound;   // aligned ranges of one set's workers
   const bool tiles = quads && uses_tiles(wrep);
   const int slots = twins ? NST * group_workers : P;
-  double all_bytes = 0;
-  for (int c = 0; c < NC; ++c) all_bytes += double(class_nblk[c]) * block_bytes[c];
-  const bool fp16_cache = double(class_nblk[kFp16Class]) * block_bytes[kFp16Class] >= kFp16Cache * all_bytes;
-  const int aligned_blocks = P < kChipWorkers || (quads && fp16_cache) ? kAlignedBlocks : quads ? kAlignedBlocksQuads : kAlignedBlocksHeads;
+  const int aligned_blocks = P < kChipWorkers ? kAlignedBlocks : quads ? kAlignedBlocksQuads : kAlignedBlocksHeads;
   if (!layout && !tune.pair_table_set && (tiles || (!tune.pool_percent_set && tot_blocks <= int64_t(aligned_blocks) * P))) {
     double block_cost[NC];
     for (int c = 0; c < NC; ++c) block_cost[c] = double(block_bytes[c]) * double(weight[c]);
     const bool mates = workgroup_waves(P, append_capacity) > 1;   // SIMD mates are known
-    bound = aligned_ranges(v_nblk, B, Hw / sets, slots, block_cost, units_per_block, mates ? kSimds / sets : slots);
-    if (!bound.empty() && wrep == 1 && mates && tot_blocks > int64_t(kAlignedBlocks) * P) {
+    bound = aligned_ranges(v_nblk, B, Hw / sets, slots, block_cost, units_per_block, mates ? kSimds / sets : slots,
+                           tiles ? kLongestRangeTiles : kLongestRange);
+    if (!bound.empty() && wrep == 1 && mates && runs.size() <= kFewRuns && tot_blocks > int64_t(kAlignedBlocks) * P) {
       const int64_t int2_workers = std::lower_bound(bound.begin(), bound.end(), class_nblk[0]) - bound.begin();
       if (int2_workers > kSimds && int2_workers < kFewInt2Pairs * kSimds) bound.clear();
     }

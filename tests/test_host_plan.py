@@ -348,9 +348,9 @@ def test_no_worker_holds_up_the_call(hq, hkv, long, short, n, mix, workers):
     whichever split is taken."""
     w = workloads.small(f"long{hq}", n + 1, hq, hkv, [long] + [short] * n, 256, 32, mix=mix, seed_offset=909)
     cls, cost, mean, block = _ranges(_plan(w, workers)[0])
-    # ends on runs: at most 1.25 of the mean and two blocks of the dearest class; by cost: to the nearest block, and with one head
-    # per wave up to 1.27 / 0.9 of the mean by the speed of the SIMD mate
-    assert cost.max() <= (1.25 if hq > hkv else 1.42) * mean + 2 * block.max()
+    # ends on runs: at most 1.25 of the mean and two blocks of the dearest class, 1.8 with up to four heads per wave; by cost: to the
+    # nearest block, and with one head per wave up to 1.27 / 0.9 of the mean by the speed of the SIMD mate
+    assert cost.max() <= (1.25 if hq > 4 * hkv else 1.8) * mean + 2 * block.max()
 
 
 @pytest.mark.parametrize("hq,workers,twins", [(96, 64, False), (96, 720, True), (64, 512, True), (128, 24, False)])
@@ -375,12 +375,11 @@ _FOUR = (0.1, 0.2, 0.3, 0.4)
     # INT2 on a few more workers than there are SIMDs; held to one per SIMD; on nearly all; not more than eight blocks per worker
     (1, 5000, 2048, (0.05, 0.15, 0.8), True), (1, 5000, 2048, (0.05, 0.25, 0.7), False), (1, 5000, 2048, (0.0, 0.05, 0.95), False),
     (1, 4000, 2048, (0.05, 0.15, 0.8), False),
-    # nearly all bytes FP16
-    (4, 9000, 2048, (1.0, 0.0, 0.0), True), (3, 6000, 2048, (0.6, 0.2, 0.2), True), (4, 4000, 2048, (1.0, 0.0, 0.0), False),
-    (4, 9000, 2048, (0.4, 0.5, 0.1), False), (1, 5000, 2048, (1.0, 0.0, 0.0), False)])
+    # a cache of FP16 alone
+    (4, 9000, 2048, (1.0, 0.0, 0.0), False), (1, 5000, 2048, (1.0, 0.0, 0.0), False), (4, 11000, 2048, (1.0, 0.0, 0.0), True)])
 def test_limits_up_to_which_plans_have_no_pools(rep, blocks, workers, mix, pools):
     """Four kv heads of `blocks` blocks: up to 12 per worker with one head per wave, 20 with two to four; 8 while the chip is not full,
-    where INT2 shares only a few SIMDs with itself, and where a cache is nearly all FP16."""
+    and where few runs of INT2 share only a few SIMDs with one another."""
     w = workloads.small(f"limits{rep}", 1, 4 * rep, 4, [64 * blocks], 64, 32, mix=mix, seed_offset=907)
     plan, _ = _plan(w, workers)
     assert (int(_parse(plan)["pool_segs"]) > 0) == pools
@@ -389,6 +388,8 @@ def test_limits_up_to_which_plans_have_no_pools(rep, blocks, workers, mix, pools
         sh = ck.make_shape(w.batch, w.num_q_heads, w.num_kv_heads, w.head_dim, w.chunk_size, w.group_size)
         bits = np.concatenate(workloads.chunk_bits(w))
         assert _parse(ck.cocktail_plan(sh, w.seq_lens, bits, workers, append_capacity=64))["pool_segs"] == 0
+        many = workloads.small("limits_runs", 24, 4, 4, [64 * 210] * 24, 64, 32, mix=mix, seed_offset=907)
+        assert _parse(_plan(many, workers)[0])["pool_segs"] == 0
 
 
 @pytest.mark.parametrize("workers,capacity,waves", [(2048, 0, 8), (2048, 1, 1), (2047, 0, 1), (1024, 0, 1), (4096, 0, 1), (6144, 0, 1)])
