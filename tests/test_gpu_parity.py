@@ -945,6 +945,29 @@ def test_waves_launched_one_by_one_and_by_compute_unit(rep, head_dim, group, wor
         _announce(f"  head {b},{h}: {c.check_head(b, h):.2e}")
 
 
+@pytest.mark.parametrize("mix", [(0.1, 0.2, 0.3, 0.4), (0.0, 0.0, 0.1, 0.9)])
+@pytest.mark.parametrize("rep,head_dim,group", [(1, 128, 32), (1, 128, 128), (1, 64, 32), (1, 64, 64), (2, 128, 32), (3, 64, 32), (4, 128, 64), (4, 64, 64)])
+def test_pools_with_workgroups_of_a_compute_unit(rep, head_dim, group, mix, monkeypatch):
+    """Pools (a small context only has them on request), eight waves to a workgroup: tickets, slots that stay neutral, and, with one head
+    per wave and mostly INT2, workers that trade places.  The counters are zero after every call."""
+    monkeypatch.setenv("COCKTAIL_POOL_PERCENT", "40")
+    monkeypatch.setenv("COCKTAIL_MIN_POOL_BLOCKS", "1")
+    w = workloads.small(f"unit_pools{rep}_d{head_dim}", 2, 4 * rep, 4, [50000, 36001], 64, group, mix=mix, head_dim=head_dim,
+                        seed_offset=931 + rep)
+    _announce(f"{w.name} g{group} mix={mix}")
+    c = Case(w, workers=2048)
+    cnt, pool_segs = _counters(c)
+    assert pool_segs > 0 and ck.cocktail_plan_field(c.plan, "workgroup_waves") == 8
+    assert (cnt == 0).all()
+    for _ in range(2):
+        out, lse = ck.cocktail_decode_attention(c.cache, c.q_dev)
+        ck.cocktail_decode_check(c.cache)
+        assert (_counters(c)[0] == 0).all()
+        c.out, c.lse = out.cpu().numpy(), lse.cpu().numpy()
+        for b, h in _sample_heads(w, 2, rep):
+            c.check_head(b, h)
+
+
 @pytest.mark.parametrize("layer", [0, 15, 31])
 def test_config2_layers(layer):
     w = workloads.config(2)

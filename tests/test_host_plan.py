@@ -227,16 +227,22 @@ def test_work_split_under_tuning_knobs(env, monkeypatch):
 
 
 @pytest.mark.parametrize("seed", range(6))
-def test_work_split_of_random_small_shapes(seed):
+def test_work_split_of_random_small_shapes(seed, monkeypatch):
     rng = np.random.default_rng(1000 + seed)
     batch = int(rng.integers(1, 5))
     hkv = int(rng.integers(1, 4))
     chunk = int(rng.choice([8, 16, 64, 128]))
     lens = [int(x) for x in rng.integers(0, 6000, size=batch)]
     w = workloads.small(f"rand{seed}", batch, hkv, hkv, lens, chunk, int(rng.choice([32, 64, 128])), seed_offset=seed)
-    for workers in (1, 3, 16, 40):
-        plan, _ = _plan(w, workers)
-        _check_work_split(plan, w, workers, seed)
+    with_pools = 0
+    for percent in (None, "25"):                             # with ranges that end where runs end, and never
+        if percent:
+            monkeypatch.setenv("COCKTAIL_POOL_PERCENT", percent)
+        for workers in (1, 3, 16, 40):
+            plan, _ = _plan(w, workers)
+            h, _, _ = _check_work_split(plan, w, workers, seed)
+            with_pools += percent is not None and h["pool_segs"] > 0
+    assert with_pools >= 2
 
 
 @pytest.mark.parametrize("mix,workers,trades", [((0.0, 0.0, 1.0), 64, True), ((0.0, 0.0, 1.0), 192, True), ((0.1, 0.1, 0.8), 128, True),
@@ -249,7 +255,7 @@ def test_workers_next_to_one_of_their_own_class_trade_places(mix, workers, trade
     _check_work_split(plan, w, workers)
     h, p = _parse(plan), int(plan.sizes.num_workers)
     recs = _arr(plan.blob, h["off"]["worker_rec"], np.int32, 16 * p).reshape(p, 16)
-    order = recs[:, 0]                                        # first block of a workgroup's own range, by workgroup id
+    order = recs[:, 0]                                        # first block of a worker's own range, by worker id
     moved = [i for i in range(p) if order[i] != np.sort(order)[i]]
     assert bool(moved) == trades
     if trades:
