@@ -139,13 +139,12 @@ extern "C" int cocktail_append_fp16_ragged(const cocktail_shape* shape, const vo
   const int num_bh = hd->batch * hd->num_kv_heads;
   const dim3 grid((num_bh * (shape->head_dim / 8) + 255) / 256, 2, 1);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  hipLaunchKernelGGL(append_fp16_kernel, grid, dim3(256), 0, st, static_cast<const u32x4*>(k_new),
-                     static_cast<const u32x4*>(v_new), static_cast<char*>(cache->k_app), static_cast<char*>(cache->v_app), 0,
-                     hd->append_blocks, num_bh, hd->v_layout, shape->head_dim, cache->appended_dev, active_dev,
-                     hd->num_kv_heads, hd->append_capacity);
-  hipLaunchKernelGGL(advance_appended_kernel, dim3((hd->batch + 255) / 256 < 64 ? (hd->batch + 255) / 256 : 64), dim3(256), 0, st,
-                     cache->appended_dev, active_dev, hd->batch, hd->append_capacity);
-  const hipError_t e = hipGetLastError();
+  hipError_t e = launch(append_fp16_kernel, grid, dim3(256), st, static_cast<const u32x4*>(k_new), static_cast<const u32x4*>(v_new),
+                        static_cast<char*>(cache->k_app), static_cast<char*>(cache->v_app), 0, hd->append_blocks, num_bh,
+                        hd->v_layout, shape->head_dim, cache->appended_dev, active_dev, hd->num_kv_heads, hd->append_capacity);
+  if (e == hipSuccess)
+    e = launch(advance_appended_kernel, dim3((hd->batch + 255) / 256 < 64 ? (hd->batch + 255) / 256 : 64), dim3(256), st,
+               cache->appended_dev, active_dev, hd->batch, hd->append_capacity);
   if (e != hipSuccess) return fail(COCKTAIL_EHIP, "append launch failed: %s", hipGetErrorString(e));
   return COCKTAIL_OK;
 }
