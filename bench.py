@@ -329,7 +329,7 @@ def main():
     ap.add_argument("--steps", type=int, default=30)
     ap.add_argument("--warmup", type=int, default=5)
     ap.add_argument("--config", type=int, default=4, help="workload: benchmark configuration 1..5 (headline: 4); 6..9 = extra shapes (8 query heads per kv head; head_dim 64; INT8 mixes)")
-    ap.add_argument("--workers", type=int, default=0, help="decode workgroups (0 = library default)")
+    ap.add_argument("--workers", type=int, default=0, help="decode workers, i.e. waves (0 = library default)")
     ap.add_argument("--cpu-heads", type=int, default=32, help="kv heads the CPU oracle is timed on (0 = skip)")
     ap.add_argument("--decode-only", action="store_true", help="steps run decode attention only (for profiling)")
     ap.add_argument("--tokens-per-step", type=int, default=128, help="decode calls per step (output tokens per request)")
@@ -351,8 +351,10 @@ def main():
     head, d = run_config(args.config, args.steps, args.warmup, ntok, args.workers, args.decode_only, args.cpu_heads,
                          args.calibrate_copy, args.vector_alu_only)
     w, plan = d["w"], d["plan"]
+    import paper_2503_23294_amd as ck
     stream_gbps = stream_read_ceiling(d["decode_bytes"])
     traffic, traffic_source = measured_traffic(w.name)
+    waves = ck.cocktail_plan_field(plan, "workgroup_waves")
     gbps = head["gbps"]
     configs = [head]
     if args.other_configs:
@@ -380,7 +382,7 @@ def main():
                    "head_dim": w.head_dim, "context": list(w.seq_lens), "chunk_size": w.chunk_size,
                    "group_size": w.group_size,
                    "class_tokens_int2_int4_int8_fp16": d["class_tokens"],
-                   "decode_workgroups": d["workers"], "decode_calls_per_step": ntok, "cache_copies": head["cache_copies"],
+                   "decode_workers": int(plan.sizes.num_workers), "decode_workgroups": int(plan.sizes.num_workers) // waves, "decode_calls_per_step": ntok, "cache_copies": head["cache_copies"],
                    "kernel_family": head["kernel_family"],
                    "step": "reorder+quantize once, then one decode-attention call per output token"
                    if not args.decode_only else "decode attention only"},

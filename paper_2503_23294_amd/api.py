@@ -34,7 +34,7 @@ class Plan:
 
 
 def cocktail_default_workers(shape: Shape, vector_alu_only: bool = False) -> int:
-    """Decode workgroups that fill the GPU for this shape (vector_alu_only: for a plan made with that option)."""
+    """Decode workers (waves) that fill the GPU for this shape (vector_alu_only: for a plan made with that option)."""
     n = C.c_int32(0)
     if vector_alu_only:
         shape = Shape(shape.batch, shape.num_q_heads, shape.num_q_heads, shape.head_dim, shape.chunk_size, shape.group_size)

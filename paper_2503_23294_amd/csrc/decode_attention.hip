@@ -122,7 +122,7 @@ extern "C" int cocktail_default_workers(const cocktail_shape* shape, int32_t* nu
     (void)hipGetLastError();
     return fail(COCKTAIL_EHIP, "no HIP device available");
   }
-  *num_workers = prop.multiProcessorCount * 8;   // one-wave workgroups, two waves per SIMD at <= 256 VGPRs
+  *num_workers = prop.multiProcessorCount * 8;   // two waves per SIMD at <= 256 VGPRs
   return COCKTAIL_OK;
 }
 
@@ -130,8 +130,8 @@ extern "C" int cocktail_default_workers(const cocktail_shape* shape, int32_t* nu
 // decode call.  In host code this name is only a handle; the device address comes from hipGetSymbolAddress.
 static __device__ __align__(256) unsigned char scratch[COCKTAIL_STATIC_WORKSPACE_BYTES_TILES];
 // What a plan may need of it.  The common limit holds the plans of the kernels with up to four heads per wave; two kinds of plans
-// have more partial states and may go as much beyond it: with eight heads per wave there are twice the workers of a kernel
-// with two waves per workgroup (up to 1024 more states of 8 x 132 floats, 4.3 MB), and where the sets of a kv head are
+// have more partial states and may go as much beyond it: with eight heads per wave there are twice the workers of the former
+// kernel, whose workgroups of two waves were a worker each (up to 1024 more states of 8 x 132 floats, 4.3 MB), and where the sets of a kv head are
 // planned as twins every set is cut where the others are (up to 4.6 MB more over some 400,000 random plans).
 size_t static_workspace_limit(const PlanHeader* hd) {
   const bool more = hd->v_layout == COCKTAIL_V_TOKEN_QUADS && (uses_tiles(hd->work_rep) || hd->work_rep < hd->rep);
@@ -245,15 +245,15 @@ int decode_enqueue(const cocktail_shape* shape, const PlanHeader* hd, const void
   if (hd->total_gblocks > 0 || app_groups > 0) {
     const bool quads = hd->v_layout == COCKTAIL_V_TOKEN_QUADS;
     const dim3 grid(hd->num_workers + app_groups, 1, 1);
-    // non-temporal K/V loads when nothing is read twice (one workgroup per kv head's blocks: the vector-ALU kernel
-    // with one query head per kv head, the matrix kernel with all query heads of a kv head in one workgroup) and the
+    // non-temporal K/V loads when nothing is read twice (one wave per kv head's blocks: the vector-ALU kernel
+    // with one query head per kv head, the matrix kernel with all query heads of a kv head in one wave) and the
     // cache is large enough that it cannot stay in the memory-side cache from one call to the next
     static const int nt_override = [] {   // tuning aid, read once: COCKTAIL_NON_TEMPORAL=0 | 1
       const char* e = std::getenv("COCKTAIL_NON_TEMPORAL");
       return e ? (std::atoi(e) != 0 ? 1 : 0) : -1;
     }();
     // (several work heads per kv head - one wave per query head of a grouped-query shape, or sets of eight at
-    // ratios above eight - read the same lines from different workgroups: default policy, the L2 serves the repeats)
+    // ratios above eight - read the same lines from different waves: default policy, the L2 serves the repeats)
     const bool nt = nt_override >= 0 ? nt_override == 1
                                      : (hd->work_rep == hd->rep && hd->packed_bytes >= kNonTemporalMinBytes);
     const bool int8 = hd->class_blocks[2] > 0;

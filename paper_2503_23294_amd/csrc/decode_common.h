@@ -50,7 +50,7 @@ struct DecodeParams {
   int32_t num_workers;      // waves behind these serve the appended tokens, app_slices per (sequence, kv head)
   int32_t num_appended, app_blocks;   // tokens appended to every sequence (used if `appended` is NULL), blocks per (b, kv head)
   const int32_t* appended;  // [B] tokens appended per sequence, or NULL
-  int32_t app_capacity, app_slices;   // tokens per sequence the append buffers hold; workgroups per (b, kv head) for them
+  int32_t app_capacity, app_slices;   // tokens per sequence the append buffers hold; waves per (b, kv head) for them
 #ifdef COCKTAIL_TRACE
   uint64_t* trace;          // [num_workers][4]: start, end (100 MHz ticks), hw id, xcc id
 #endif
@@ -108,7 +108,7 @@ __device__ __forceinline__ rsrc_t make_rsrc(const char* base, uint32_t bytes) {
 }
 // Cache policy of the K/V loads.  Every byte of a large cache is read exactly once per call, so the loads
 // are marked non-temporal (they do not displace anything in the L2 and the memory-side cache, which on
-// MI355X is worth 10 % of HBM throughput); shapes in which several workgroups walk the blocks of one kv head,
+// MI355X is worth 10 % of HBM throughput); shapes in which several waves walk the blocks of one kv head,
 // and small caches that stay resident between calls, use the default policy.
 constexpr int kAuxDefault = 0, kAuxNonTemporal = 2;
 constexpr int64_t kNonTemporalMinBytes = int64_t(64) << 20;   // packed K+V bytes of one call
@@ -572,7 +572,7 @@ __device__ __forceinline__ int appended_count(int b) {
   return min(max(n, 0), kp->app_capacity);
 }
 
-// The part of an append run that workgroup `idx` behind the regular workers attends to.
+// The part of an append run that wave `idx` behind the regular workers attends to.
 struct AppendSlice {
   int bh, tokens, first_block, blocks, qrow, pid;
 };
@@ -604,7 +604,7 @@ __device__ __forceinline__ void write_neutral(int slot, int r, int lane) {
 }
 
 // Launch the partial-state kernels for head_dim HD (one translation unit per head_dim and kernel family), `grid`
-// workgroups of one wave: one query head per wave on the vector ALU; 2 to 4 query heads per wave on 4x4x4 matrix
+// waves (launch_workers): one query head per wave on the vector ALU; 2 to 4 query heads per wave on 4x4x4 matrix
 // instructions, 5 to 8 on 16x16x32 ones.  int8: the cache has an INT8 class.
 template <int HD>
 hipError_t launch_decode_heads(const DecodeParams& p, int group_size, bool non_temporal, bool int8, int grid, hipStream_t st);
@@ -613,15 +613,18 @@ hipError_t launch_decode_quads(const DecodeParams& p, int group_size, bool non_t
 template <int HD>
 hipError_t launch_decode_tiles(const DecodeParams& p, int group_size, bool non_temporal, bool int8, int grid, hipStream_t st);
 
-// `grid` waves, each with `lds` bytes of shared memory.  Where the workers fill the chip with two waves per SIMD, in workgroups of a whole
+// `grid` waves, each with `lds` bytes of shared memory.  Where the workers fill the chip exactly once, two waves per SIMD, in workgroups of a whole
 // compute unit.  Launched one by one, the waves are dealt out to the units in order, but which SIMD of its unit a wave gets depends on
 // what ran before: right behind the merge of the call before the fourth wave went to the SIMD of the first one on up to 6 %
 // of the SIMDs, behind a kernel that fills the chip on 15 %.  Those SIMDs then run two waves of the same half of the ids, two INT2 ranges
 // say, for 1.4 times as long as the rest, and the call ends with the slowest worker.  The waves of one workgroup go to the SIMDs in
-// turn (traced: worker w next to w + P / 2 on all 1024, whatever ran before).  One by one -> by compute units, us per call, each call behind an
+// turn (traced: worker w next to w + P / 2 on all 1024 SIMDs, whatever ran before).  One by one -> by compute units, us per call, each call behind an
 // elementwise kernel of 6 us, which is counted: 40 heads 128K 120.8 -> 108.7; 32 heads 32K 41.5 -> 39.7; ragged, 16 query heads per kv head
 // 60.6 -> 55.4; INT2-heavy (5 / 25 / 70 %) 4 x 64K at 8 heads 76.8 -> 63.2, 2 x 40K at 9 59.3 -> 48.5, 4 x 45K at 3 47.7 -> 42.5.  Back to back:
 // 35.7 -> 30.9 (2 x 64K at 5 heads), 53 -> 42, 42.3 -> 37.9, the same where the merge has one workgroup per unit or few.
+// A workgroup starts where a whole unit is free.  With a second stream busy, one by one | by unit (us per call; per call and one kernel of the
+// other stream): an elementwise kernel of 4M numbers 37.8 | 37.2 (32 heads 32K) and 133 | 131 (4 x 128K at 8), a product of 2048^3 49.6 | 47.0 and
+// 148 | 138.5, a sort of 16 rows 39.2 | 39.0 and 133 | 132; a kernel that fills the chip for 85 us itself, both together: 108 | 120 and 236 | 233.
 // Slices of appended tokens want to start where the first worker ends, not where the first compute unit does: then, and where the
 // workers do not fill the chip exactly once (workgroup_waves), one by one.
 template <class... A>

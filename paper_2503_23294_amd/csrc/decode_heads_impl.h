@@ -3,7 +3,7 @@
 //
 // Design (gfx950, wave64):
 //  * The host planner puts all 64-token blocks of a layer into one global order and cuts it into
-//    groups of a few workers.  A worker (workgroup) streams its own block range and then takes
+//    groups of a few workers.  A worker (wave) streams its own block range and then takes
 //    pieces of the group's shared pool through an atomic ticket counter, so that the workers of a
 //    group finish together; it emits one partial softmax state per (sequence, kv head) segment it
 //    touches.
@@ -233,7 +233,7 @@ __device__ __forceinline__ void run_class(Stream<HD>& sm, Piece& cur, int r, int
 }
 
 // Workgroups behind the regular workers attend to the tokens appended during decoding (Sec. III-A): FP16 runs in
-// the append buffers, one workgroup per slice of a (sequence, kv head)'s run, each writing one of the last
+// the append buffers, one wave per slice of a (sequence, kv head)'s run, each writing one of the last
 // partials of that head's range.
 template <int HD, int G, int AUX>
 __device__ __forceinline__ void appended_tokens(int idx, int r, int lane) {

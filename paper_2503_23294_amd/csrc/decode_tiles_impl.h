@@ -1,4 +1,4 @@
-// Internal: the decode kernel for five to eight query heads per workgroup, as templates over head_dim; one
+// Internal: the decode kernel for five to eight query heads per wave, as templates over head_dim; one
 // translation unit per head_dim instantiates launch_decode_tiles<HD>.
 //
 // Decode side of Alg. 1 (Sec. III-C).  One wave serves all (up to eight) query heads of a set, so every K/V byte is

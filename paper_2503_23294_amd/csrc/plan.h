@@ -31,7 +31,7 @@ constexpr int kPartialFloats = 4;              // (m, l, tokens covered as int32
 #endif
 constexpr int kIterUnits[kNumClasses] = {COCKTAIL_J2, COCKTAIL_J4, COCKTAIL_J8, COCKTAIL_J16};
 constexpr int kMaxPoolSegments = 32;           // segments one pool may touch (a worker tracks them in a bit mask)
-// The appended tokens of a (sequence, kv head) are attended to by one extra workgroup per this many 64-token
+// The appended tokens of a (sequence, kv head) are attended to by one extra wave per this many 64-token
 // blocks of append capacity (one partial state each), so a long generation does not hang on a single wave.
 constexpr int kAppendSliceBlocks = 8;
 // The chip: 256 compute units of four SIMDs; the decode kernels run two waves per SIMD.
@@ -50,7 +50,7 @@ constexpr int kQuadMinRep = 2, kQuadMaxRep = 8;
 __host__ __device__ inline bool uses_token_quads(int rep) { return rep >= kQuadMinRep && rep <= kQuadMaxRep; }
 // Of these, 5 to 8 heads run on the kernel with eight heads per wave (16x16x32 instructions), 2 to 4 on the one with four.
 __host__ __device__ inline bool uses_tiles(int rep) { return rep > 4 && rep <= kQuadMaxRep; }
-// Query heads one workgroup serves when rep = Hq / Hkv heads share a kv head: all of them up to kQuadMaxRep; beyond
+// Query heads one wave serves when rep = Hq / Hkv heads share a kv head: all of them up to kQuadMaxRep; beyond
 // that the heads of a kv head are cut into equal sets (the largest divisor of rep that the matrix kernel takes),
 // each walking the kv head's blocks by itself; 1 (a wave per query head, vector ALU) if there is no such divisor
 // or the plan asks for it.
@@ -72,7 +72,7 @@ struct Segment {
   int32_t pid0;              // partial id of the first worker whose own range touches this segment
 };
 
-// Everything a decode workgroup needs to start streaming, in one 64-byte record.
+// Everything a decode worker (wave) needs to start streaming, in one 64-byte record.
 struct WorkerRec {
   int32_t g0, g1;            // its own block range [g0, g1) of the global order
   int32_t seg0;              // index of the segment holding g0
@@ -131,7 +131,7 @@ struct PlanHeader {
   int32_t work_heads;        // heads of the decode work split: Hkv, or Hq where every query head is served by a wave
                              // of its own (vector-ALU-only plans, and Hq / Hkv beyond what the matrix kernel takes):
                              // Segment::h and the (sequence, head) ranges of partial ids count in these
-  int32_t work_rep;          // query heads one workgroup serves: Hq / work_heads
+  int32_t work_rep;          // query heads one wave serves: Hq / work_heads
   int32_t num_workers, num_segments, num_partials;
   int32_t total_gblocks;
   int32_t v_layout;          // 0: V blocks hold token rows like K; 1: token quads (2 to 8 query heads per kv head)
@@ -166,7 +166,7 @@ struct PlanHeader {
   int32_t off_bh_off;         // int32 [B*Hkv + 1] prefix: (b, kv head) owns partial ids bh_off[bh] .. bh_off[bh+1]-1;
                               // with append buffers the last append_slices ids of each range are those of the appended tokens
   int32_t off_rq_items;       // RQItem [sum of class_blocks]
-  int32_t append_slices;      // workgroups (and partial ids) per (sequence, kv head) for the appended tokens
+  int32_t append_slices;      // waves (and partial ids) per (sequence, kv head) for the appended tokens
   int64_t ws_status_off;      // byte offset, inside the decode workspace, of int32 [B * Hq]: per (sequence, query
                               // head) tokens covered by the last call's partial states minus tokens of the sequence
                               // (0 = every token was attended to exactly once)

@@ -59,7 +59,7 @@ constexpr int64_t kTwinCostWeight[kNumClasses] = {1300, 1250, 950, 330};
 // ranges (8 a hair ahead at 128K), 5 to 6 clearly best on short ones (32K: 33.2 against 35.9 us); the
 // grouped-query kernel likes 4.
 constexpr int kGroupWorkers = 8, kGroupWorkersShort = 6, kQuadGroupWorkers = 4;
-constexpr int kXcds = 8;   // workgroups are handed to the XCDs round robin
+constexpr int kXcds = 8;   // workgroups (of one wave or a unit's eight, workgroup_waves) are handed to the XCDs round robin
 constexpr int kLongRangeBlocks = 24;   // average blocks per worker from which a range counts as long
 // The share of a group's cost that goes into its shared pool.
 constexpr int kPoolPercent = 25;
@@ -432,11 +432,11 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
   Tuning tune = read_tuning();
   int pool_percent = tune.pool_percent;
   const int rep = shape->num_q_heads / Hkv;
-  // Workgroups of five to eight query heads keep the purely static split: their calls are reproducible bit for bit.
-  // Up to eight query heads of a kv head are served by one workgroup.  Where more of them share a kv head they are
+  // Waves of five to eight query heads keep the purely static split: their calls are reproducible bit for bit.
+  // Up to eight query heads of a kv head are served by one wave.  Where more of them share a kv head they are
   // cut into equal sets, and with one wave per query head (the vector-ALU kernel, on request) every head is a set
   // of its own: each set walks the blocks of its kv head as if they were its own.
-  const int wrep = work_rep_of(rep, vector_alu_only);   // query heads a workgroup serves
+  const int wrep = work_rep_of(rep, vector_alu_only);   // query heads a wave serves
   const int Hw = shape->num_q_heads / wrep;             // heads of the decode work split
   const int share = rep / wrep;                         // work heads that walk the blocks of one kv head
   const bool quads = uses_token_quads(wrep);
@@ -460,8 +460,8 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
   for (int c = 0; c < NC; ++c) tot_blocks += class_nblk[c];
   if (tot_blocks >= (int64_t(1) << 31)) return fail(COCKTAIL_EINVAL, "more than 2^31 blocks in one call");
   // `num_workers` is an upper bound: a short context has fewer units of work than the chip has wave slots, and
-  // workgroups without work only lengthen the launch (8 heads x 2048 tokens on MI355X: 12.4 us per call with 2048
-  // workgroups, 11.5 us with 512).  At most one worker per unit, in multiples of 64.
+  // waves without work only lengthen the launch (8 heads x 2048 tokens on MI355X: 12.4 us per call with 2048
+  // of them, 11.5 us with 512).  At most one worker per unit, in multiples of 64.
   const int64_t unit_workers = (tot_blocks * units_per_block + 63) / 64 * 64;
   const int P = static_cast<int>(std::min<int64_t>(num_workers, std::max<int64_t>(unit_workers, 64)));
   const int group_workers = tune.group_workers > 0 ? tune.group_workers
@@ -469,7 +469,7 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
                             : tot_blocks >= int64_t(kLongRangeBlocks) * P ? kGroupWorkers : kGroupWorkersShort;
   // Where a kv head has several sets of query heads (ratios above eight on the matrix kernels), each set walks the same
   // blocks.  `sets` consecutive groups take the same stripe of blocks, one set each, worker by worker, and the workers
-  // of a stripe get workgroup ids that differ by multiples of kXcds: they run on one XCD, start together, and all but the first find
+  // of a stripe get worker ids that differ by multiples of kXcds: they run on one XCD, start together, and all but the first find
   // the blocks in its L2.  (In run order the sets lay half a class apart and every byte was fetched once per set:
   // 8 ragged contexts up to 64K, 64 q / 4 kv heads, 61 -> 52 us per call;
   // 4 x 128K, 128 q / 8 kv heads, 235 -> 167.)  Workers beyond whole units of kXcds * share stay without work: taken where
@@ -528,7 +528,7 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
       }
     } else {
       // Share of the total cost in front of every group.  Equal shares per worker to begin with; then,
-      // if the workgroups fill the chip twice (workgroup i and i + P/2 share a SIMD), a few rounds that
+      // if the workers fill the chip with two waves per SIMD (worker i and i + P/2 share a SIMD), a few rounds that
       // scale every worker's share by the measured relative speed of its class next to its mate's class.
       std::vector<double> wcap(P, 1.0), gfrac(NGR + 1, 0.0);
       const bool pair_speed = pair_speed_on && !layout && P % 2 == 0 && P >= 2 * group_workers &&

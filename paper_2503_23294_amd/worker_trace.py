@@ -1,4 +1,4 @@
-"""Tuning aid: when does every decode workgroup start and end inside one cocktail_decode_attention call?
+"""Tuning aid: when does every decode worker (wave) start and end inside one cocktail_decode_attention call?
 
 Needs a build of the library with per-worker time stamps, made on the build machine with
     python -m paper_2503_23294_amd.build --out paper_2503_23294_amd/libcocktail_trace.so -DCOCKTAIL_TRACE
@@ -75,7 +75,7 @@ def main():
         if m.any():
             print(f"  {name}: {int(m.sum())} workers, {np.median(own_blocks[m]):.0f} own blocks each, end min/median/max "
                   f"{en[m].min():.1f} / {np.median(en[m]):.1f} / {en[m].max():.1f} us")
-    # duration by own class and by the class of the SIMD mate (workgroup i shares a SIMD with workgroup i + P/2)
+    # duration by own class and by the class of the SIMD mate (worker i shares a SIMD with worker i + P/2)
     if workers % 2 == 0:
         mate = np.roll(cls, -workers // 2)
         names = ("INT2", "INT4", "INT8", "FP16")
