@@ -87,6 +87,9 @@ constexpr int kShortRangePoolPercent = 40;
 // 25.0, 4 x 128K 130 -> 126.7, 8 x 16K with 300 appended 49.8 -> 47.6; sixteen, ragged up to 64K 50.3 -> 47.3.
 // With kInt2Stretch as well, one head, 10 and 12 blocks per worker: 42.8 -> 41.0 and 48.4 -> 45.9 at 5 / 25 / 70 %, 46.6 -> 45.6 and 52.0 ->
 // 51.4 at MIX; at 16 blocks 58.4 -> 57.0, but 64.7 -> 65.0.
+// (One cache again and again.  With distinct caches in turn, as a model's layers are, 173 shapes of 8 to 20 blocks, six mixes, G 32 to 128: 4.1 % in the
+// mean; 4 x 64K, four heads, 5 % FP16, 15 % INT8, 30 % INT4, 50 % INT2 65.2 -> 63.6 at G 32 and 60.2 -> 59.1 at G 64, 32 heads 32K at MIX 35.1 ->
+// 34.4; losses of up to 3 % at 14 blocks and more, e.g. 4 x 64K at 15 / 35 / 50 %, G 64 63.7 -> 65.3, against 68.0 -> 66.6 at G 32.)
 constexpr int kAlignedBlocks = 8, kAlignedBlocksHeads = 12, kAlignedBlocksQuads = 20;
 // One head per wave and more than kAlignedBlocks: not where INT2 has more than one worker per SIMD but fewer than kFewInt2Pairs (kInt2Stretch could
 // not hold it) and the runs are few (kFewRuns): some SIMDs have two INT2 workers, and without pools the call waits for those.  10 to 12 blocks
