@@ -129,13 +129,8 @@ extern "C" int cocktail_default_workers(const cocktail_shape* shape, int32_t* nu
 // Scratch of the entry point that allocates nothing: the partial softmax states and the status words of one
 // decode call.  In host code this name is only a handle; the device address comes from hipGetSymbolAddress.
 static __device__ __align__(256) unsigned char scratch[COCKTAIL_STATIC_WORKSPACE_BYTES_TILES];
-// What a plan may need of it.  The common limit holds the plans of the kernels with up to four heads per wave; two kinds of plans
-// have more partial states and may go as much beyond it: with eight heads per wave there are twice the workers of the former
-// kernel, whose workgroups of two waves were a worker each (up to 1024 more states of 8 x 132 floats, 4.3 MB), and where the sets of a kv head are
-// planned as twins every set is cut where the others are (up to 4.6 MB more over some 400,000 random plans).
 size_t static_workspace_limit(const PlanHeader* hd) {
-  const bool more = hd->v_layout == COCKTAIL_V_TOKEN_QUADS && (uses_tiles(hd->work_rep) || hd->work_rep < hd->rep);
-  return more ? size_t(COCKTAIL_STATIC_WORKSPACE_BYTES_TILES) : size_t(COCKTAIL_STATIC_WORKSPACE_BYTES);
+  return static_cast<size_t>(static_workspace_limit(hd->v_layout, hd->work_rep, hd->rep));
 }
 
 namespace {

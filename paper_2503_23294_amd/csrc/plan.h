@@ -7,6 +7,8 @@
 #pragma once
 #include <stdint.h>
 
+#include "../../include/cocktail.h"
+
 namespace cocktail {
 
 constexpr uint32_t kPlanMagic = 0x434b544cu;  // "CKTL"
@@ -60,6 +62,15 @@ __host__ __device__ inline int work_rep_of(int rep, bool vector_alu_only) {
   for (int d = kQuadMaxRep; d >= kQuadMinRep; --d)
     if (rep % d == 0) return d;
   return 1;
+}
+
+// What a plan may need of the built-in workspace.  The common limit holds the plans of the kernels with up to four heads per wave; two
+// kinds of plans have more partial states and may go as much beyond it: with eight heads per wave there are twice the workers of the
+// former kernel, whose workgroups of two waves were a worker each (up to 1024 more states of 8 x 132 floats, 4.3 MB), and where the sets
+// of a kv head are planned as twins every set is cut where the others are (up to 4.6 MB more over some 400,000 random plans).
+inline int64_t static_workspace_limit(int v_layout, int work_rep, int rep) {
+  return v_layout == COCKTAIL_V_TOKEN_QUADS && (uses_tiles(work_rep) || work_rep < rep) ? COCKTAIL_STATIC_WORKSPACE_BYTES_TILES
+                                                                                        : COCKTAIL_STATIC_WORKSPACE_BYTES;
 }
 
 // One contiguous run of blocks of one (sequence, kv head, class): the part of it that one group works on.

@@ -189,12 +189,14 @@ static Tuning read_tuning() {
 }
 
 // Ranges that end where runs end.  `nblk` [kNumClasses][B] as [NC * b + c]: blocks of a run, the same for all `heads` heads; cost[c]: of a
-// block; `most_int2`: workers INT2 may have (kInt2Stretch); `longest_range`: kLongestRange.  Finds the smallest cost a worker may be given such that `slots` workers are enough, cuts every run into equal parts of at most
+// block; `most_int2`: workers INT2 may have (kInt2Stretch); `longest_range`: kLongestRange; `too_long`: whether it
+// is exceeded, which `any_length` allows.  Finds the smallest cost a worker may be given such that `slots` workers are enough, cuts every run into equal parts of at most
 // that, and lets workers that are left over (beyond 1 in 40: they would bring nothing) cut the dearest parts once more.  Returns the first block of every worker's range
 // in class, sequence, head order (slots + 1 entries), or nothing if there are more runs than workers or the longest range is too long
 // (kLongestRange).
 static std::vector<int32_t> aligned_ranges(const std::vector<int32_t>& nblk, int B, int heads, int slots, const double (&cost)[kNumClasses],
-                                           int units_per_block, int64_t most_int2, double longest_range) {
+                                           int units_per_block, int64_t most_int2, double longest_range,
+                                           bool any_length, bool* too_long) {
   constexpr int NC = kNumClasses;
   int64_t int2_range = 0;   // blocks of a range of INT2, if not by cost
   auto per_worker = [&](int c, double budget) {
@@ -263,7 +265,10 @@ static std::vector<int32_t> aligned_ranges(const std::vector<int32_t>& nblk, int
       longest = std::max(longest, (nblk[i] + parts[i] - 1) / parts[i] * cost[i % NC]);
       dearest_block = std::max(dearest_block, cost[i % NC]);
     }
-  if (longest > longest_range * total / slots + kLongestRangeBlocks * dearest_block) return bound;
+  if (longest > longest_range * total / slots + kLongestRangeBlocks * dearest_block) {
+    if (too_long) *too_long = true;
+    if (!any_length) return bound;
+  }
   bound.reserve(slots + 1);
   int32_t at = 0;
   for (int c = 0; c < NC; ++c)
@@ -339,9 +344,11 @@ extern "C" int cocktail_plan(const cocktail_shape* shape, const int32_t* seq_len
                           class_tokens, perm);
 }
 
-extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_lens, const uint8_t* chunk_bits,
-                                int32_t num_workers, const cocktail_plan_options* options, cocktail_sizes* sizes,
-                                void* plan_host, size_t plan_capacity, int32_t* class_tokens, int32_t* perm) {
+// cocktail_plan_ex with one of the two splits of the work where the longest range would be too long (kLongestRange); says in `too_long`
+// whether it would.
+static int make_plan(const cocktail_shape* shape, const int32_t* seq_lens, const uint8_t* chunk_bits, int32_t num_workers,
+                     const cocktail_plan_options* options, cocktail_sizes* sizes, void* plan_host, size_t plan_capacity,
+                     int32_t* class_tokens, int32_t* perm, bool any_length, bool* too_long) {
   if (int rc = check_shape(shape)) return rc;
   const int32_t append_capacity = options ? options->append_capacity : 0;
   const bool reproducible = options && options->reproducible != 0;
@@ -509,7 +516,7 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
     for (int c = 0; c < NC; ++c) block_cost[c] = double(block_bytes[c]) * double(weight[c]);
     const bool mates = workgroup_waves(P, append_capacity) > 1;   // SIMD mates are known
     bound = aligned_ranges(v_nblk, B, Hw / sets, slots, block_cost, units_per_block, mates ? kSimds / sets : slots,
-                           tiles ? kLongestRangeTiles : kLongestRange);
+                           tiles ? kLongestRangeTiles : kLongestRange, any_length, too_long);
     if (!bound.empty() && wrep == 1 && mates && runs.size() <= kFewRuns && tot_blocks > int64_t(kAlignedBlocks) * P) {
       const int64_t int2_workers = std::lower_bound(bound.begin(), bound.end(), class_nblk[0]) - bound.begin();
       if (int2_workers > kSimds && int2_workers < kFewInt2Pairs * kSimds) bound.clear();
@@ -973,4 +980,25 @@ extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_
   }
   g_err[0] = 0;
   return COCKTAIL_OK;
+}
+
+extern "C" int cocktail_plan_ex(const cocktail_shape* shape, const int32_t* seq_lens, const uint8_t* chunk_bits,
+                                int32_t num_workers, const cocktail_plan_options* options, cocktail_sizes* sizes,
+                                void* plan_host, size_t plan_capacity, int32_t* class_tokens, int32_t* perm) {
+  auto plan = [&](cocktail_sizes* to, bool write, bool any_length, bool* too_long) {
+    return make_plan(shape, seq_lens, chunk_bits, num_workers, options, to, write ? plan_host : nullptr, write ? plan_capacity : 0,
+                     class_tokens, perm, any_length, too_long);
+  };
+  bool too_long = false;
+  const int rc = plan(sizes, true, false, &too_long);
+  if (!too_long || (rc != COCKTAIL_OK && rc != COCKTAIL_ENOSPACE)) return rc;
+  // The split by cost of that many runs has a partial state for nearly each worker and run.  With more workers than the chip holds they
+  // may outgrow the built-in workspace where one state per worker does not: a slow plan that cocktail_decode_attention_static takes,
+  // rather than one it refuses.
+  const int rep = shape->num_q_heads / shape->num_kv_heads;
+  const int64_t limit = static_workspace_limit(sizes->v_layout, work_rep_of(rep, options && options->vector_alu_only != 0), rep);
+  if (sizes->workspace_bytes <= limit) return rc;
+  cocktail_sizes other;
+  const bool fits = plan(&other, false, true, nullptr) == COCKTAIL_OK && other.workspace_bytes <= limit;
+  return plan(sizes, true, fits, nullptr);
 }

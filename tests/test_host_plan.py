@@ -359,6 +359,34 @@ def test_no_worker_holds_up_the_call(hq, hkv, long, short, n, mix, workers):
     assert cost.max() <= (1.25 if hq > 4 * hkv else 1.8) * mean + 2 * block.max()
 
 
+@pytest.mark.parametrize("hq,hkv,n,tokens,workers,cut_by_cost", [(64, 8, 160, 1200, 4096, False), (128, 8, 85, 1200, 4096, False),
+                                                                 (40, 8, 160, 1200, 4096, True), (64, 8, 80, 1200, 2048, True)])
+def test_uneven_ranges_rather_than_a_plan_the_built_in_workspace_cannot_hold(hq, hkv, n, tokens, workers, cut_by_cost):
+    """So many runs that the longest range is too long.  The split by cost has a partial state for nearly each worker and run; where
+    only that makes a plan outgrow the built-in workspace, each worker stays in one run all the same.  Sizes asked for alone,
+    a buffer that is too small and the plan itself say the same."""
+    import ctypes as C
+    w = workloads.small("many", n, hq, hkv, [40000] + [tokens + 32 * (i % 7) for i in range(n - 1)], 32, 32, mix=(0.3, 0.3, 0.4), seed_offset=923)
+    plan, bits = _plan(w, workers)
+    _check_work_split(plan, w, workers)
+    h, (cls, cost, mean, block) = _parse(plan), _ranges(plan)
+    recs = _arr(plan.blob, h["off"]["worker_rec"], np.int32, 16 * workers).reshape(workers, 16)
+    segs = _arr(plan.blob, h["off"]["segments"], np.int32, 8 * h["segments"]).reshape(-1, 8)
+    run = np.searchsorted(segs[:, 6], recs[:, 0], side="right") - 1
+    one_run = (recs[:, 1] <= segs[run, 6] + segs[run, 5]) | (recs[:, 0] == recs[:, 1])
+    assert one_run.all() != cut_by_cost
+    assert plan.sizes.workspace_bytes <= 24 << 20
+    assert (cost.max() > 1.25 * mean + 2 * block.max()) != cut_by_cost
+    sl, flat, sizes = np.asarray(w.seq_lens, np.int32), np.concatenate(bits), _lib.Sizes()
+    args = (C.byref(plan.shape), sl.ctypes.data, flat.ctypes.data, workers, None, C.byref(sizes))
+    assert _lib.lib().cocktail_plan_ex(*args, None, 0, None, None) == 0 and bytes(sizes) == bytes(plan.sizes)
+    blob = np.full(plan.blob.size, 0xAB, np.uint8)
+    assert _lib.lib().cocktail_plan_ex(*args, blob.ctypes.data, blob.size - 1, None, None) == _lib.ENOSPACE
+    assert bytes(sizes) == bytes(plan.sizes) and b"plan buffer holds" in _lib.lib().cocktail_last_error()
+    assert _lib.lib().cocktail_plan_ex(*args, blob.ctypes.data, blob.size, None, None) == 0
+    assert np.array_equal(blob, plan.blob)
+
+
 @pytest.mark.parametrize("hq,workers,twins", [(96, 64, False), (96, 720, True), (64, 512, True), (128, 24, False)])
 def test_weights_of_twins_are_for_plans_with_twins(hq, workers, twins):
     """More than eight heads per kv head: sets that are not laid out as twins fetch every block themselves, and FP16 bytes count as much
