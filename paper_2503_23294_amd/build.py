@@ -16,6 +16,8 @@ FLAGS = [
     "-fhip-fp32-correctly-rounded-divide-sqrt",
     # packed-fp32 VALU forms are kept out of the generated code on purpose
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # leading scalar kernel arguments are in scalar registers when a wave starts
+    "-mllvm", "-amdgpu-kernarg-preload-count=8",
     "-Wall", "-Wno-unused-function",
 ]
 

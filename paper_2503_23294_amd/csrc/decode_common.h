@@ -56,34 +56,37 @@ struct DecodeParams {
 #endif
 };
 
+// The arguments of the partial-state kernels.  What a worker needs before it has its record comes first, as arguments of their own, which
+// are in scalar registers when a wave starts (build.py: kernarg preloading); the rest is read from memory (kparams).
+#define COCKTAIL_WORKER_ARGS const WorkerRec *recs, int32_t num_workers, int32_t num_q_heads, int32_t rep, DecodeParams
+typedef void (*worker_kernel)(COCKTAIL_WORKER_ARGS);
+constexpr int kParamsOffset = 24;   // of the DecodeParams in the kernel argument segment
+
 // The kernel keeps almost everything that describes its work in scalar registers.  To leave room
 // there, the kernel arguments are not held in registers for the whole kernel: code that needs one
 // of the rarely used pointers reads it from the kernel argument segment again.
 typedef const __attribute__((address_space(4))) DecodeParams* kparams_t;
 __device__ __forceinline__ kparams_t kparams() {
-  uint64_t p = reinterpret_cast<uint64_t>(__builtin_amdgcn_kernarg_segment_ptr());
+  uint64_t p = reinterpret_cast<uint64_t>(__builtin_amdgcn_kernarg_segment_ptr()) + kParamsOffset;
   asm volatile("" : "+s"(p));   // a fresh pointer every time: loads through it are not kept alive
   return reinterpret_cast<kparams_t>(p);
 }
 
-// What a worker needs of the arguments before it has its record.  The kernel argument segment is four lines of the scalar cache, all of
-// them cold when a kernel starts: one load from each, requested together with the fields below, makes the reads that follow one by
-// one (kparams) hits.  A worker of a 1K-token layer had its first loads on the way 2300 cycles after its start, with every line
-// a miss of its own; a quarter of its time.
+// What a worker needs of the arguments before it has its record.
 struct FirstParams {
   const WorkerRec* recs;
   int32_t num_workers, num_q_heads, rep;
 };
-__device__ __forceinline__ FirstParams first_params() {
-  const kparams_t kp = kparams();
-  const auto* words = reinterpret_cast<const __attribute__((address_space(4))) uint32_t*>(kp);
+// The kernel argument segment is four lines of the scalar cache, all of them cold when a kernel starts: one load from each, requested
+// together with the record, makes the reads that follow one by one (kparams) hits.  A worker of a 1K-token layer had its first loads on the
+// way 2300 cycles after its start, with every line a miss of its own; a quarter of its time.  (With the first fields in registers from the
+// start instead of read in front of the record, calls of small layers take another 0.1 to 0.2 us less: 13.8 -> 13.65, 16.4 -> 16.2.)
+__device__ __forceinline__ void touch_params(WorkerRec& rec) {
+  const auto* words = reinterpret_cast<const __attribute__((address_space(4))) uint32_t*>(reinterpret_cast<uint64_t>(__builtin_amdgcn_kernarg_segment_ptr()));
   constexpr int kLine = 16;   // dwords
-  static_assert(sizeof(DecodeParams) > 3 * kLine * 4 && sizeof(DecodeParams) <= 4 * kLine * 4, "four lines");
-  FirstParams f;
-  f.recs = kp->recs, f.num_workers = kp->num_workers, f.num_q_heads = kp->num_q_heads, f.rep = kp->rep;
-  const uint32_t l1 = words[kLine], l2 = words[2 * kLine], l3 = words[3 * kLine];
-  asm volatile("" : "+s"(f.recs), "+s"(f.num_workers), "+s"(f.num_q_heads), "+s"(f.rep) : "s"(l1), "s"(l2), "s"(l3));
-  return f;
+  static_assert(sizeof(DecodeParams) + kParamsOffset > 3 * kLine * 4 && sizeof(DecodeParams) + kParamsOffset <= 4 * kLine * 4, "four lines");
+  const uint32_t l0 = words[kLine / 2], l1 = words[kLine], l2 = words[2 * kLine], l3 = words[3 * kLine];
+  asm volatile("" : "+s"(rec.g0) : "s"(l0), "s"(l1), "s"(l2), "s"(l3));
 }
 
 // Which worker a wave is.  A workgroup is one wave, or (launch_workers) kCuWaves of them: the waves of a workgroup have the ids of
@@ -627,10 +630,9 @@ hipError_t launch_decode_tiles(const DecodeParams& p, int group_size, bool non_t
 // 148 | 138.5, a sort of 16 rows 39.2 | 39.0 and 133 | 132; a kernel that fills the chip for 85 us itself, both together: 108 | 120 and 236 | 233.
 // Slices of appended tokens want to start where the first worker ends, not where the first compute unit does: then, and where the
 // workers do not fill the chip exactly once (workgroup_waves), one by one.
-template <class... A>
-inline hipError_t launch_workers(void (*kern)(A...), const DecodeParams& p, int grid, size_t lds, hipStream_t st) {
+inline hipError_t launch_workers(worker_kernel kern, const DecodeParams& p, int grid, size_t lds, hipStream_t st) {
   const int waves = workgroup_waves(p.num_workers, grid - p.num_workers);
-  return launch_lds(kern, dim3(grid / waves), dim3(64 * waves), waves * lds, st, p);
+  return launch_lds(kern, dim3(grid / waves), dim3(64 * waves), waves * lds, st, p.recs, p.num_workers, p.num_q_heads, p.rep, p);
 }
 
 }  // namespace cocktail

@@ -252,12 +252,12 @@ __device__ __forceinline__ void appended_tokens(int idx, int r, int lane) {
 // has an INT8 class; caches without one run a kernel without that code (a third less of it to fetch and
 // to allocate registers for, worth 1.5 us on a 32K-token layer).
 template <int HD, int G, int AUX, bool INT8>
-__global__ __launch_bounds__(64 * kCuWaves) __attribute__((amdgpu_waves_per_eu(2))) void decode_attention_kernel(DecodeParams) {
+__global__ __launch_bounds__(64 * kCuWaves) __attribute__((amdgpu_waves_per_eu(2))) void decode_attention_kernel(COCKTAIL_WORKER_ARGS) {
   constexpr int r = 0;             // query head inside the kv head's group
 #ifdef COCKTAIL_TRACE
   const uint64_t t_start = __builtin_amdgcn_s_memrealtime();
 #endif
-  const FirstParams fp = first_params();
+  const FirstParams fp = {recs, num_workers, num_q_heads, rep};
   const Place me = place(fp);
   const int lane = me.lane;
   if (me.worker >= fp.num_workers) {
@@ -265,7 +265,9 @@ __global__ __launch_bounds__(64 * kCuWaves) __attribute__((amdgpu_waves_per_eu(2
     return;
   }
   Stream<HD> sm;
-  sm.init(load_record(fp.recs + me.worker), fp);
+  WorkerRec rec = load_record(fp.recs + me.worker);
+  touch_params(rec);
+  sm.init(rec, fp);
   Piece cur = sm.next(lane);
   while (cur.nu > 0) {
     if (cur.cls == 0) {
@@ -298,7 +300,7 @@ __global__ __launch_bounds__(64 * kCuWaves) __attribute__((amdgpu_waves_per_eu(2
 // Picks the instance for the group size, the cache policy and the classes present, and launches it.
 template <int HD>
 hipError_t launch_decode_heads(const DecodeParams& p, int group_size, bool nt, bool int8, int grid, hipStream_t st) {
-  void (*kern)(DecodeParams) = nullptr;
+  worker_kernel kern = nullptr;
 #define COCKTAIL_PICK(G)                                                                                                      \
   kern = int8 ? (nt ? decode_attention_kernel<HD, G, kAuxNonTemporal, true> : decode_attention_kernel<HD, G, kAuxDefault, true>) \
               : (nt ? decode_attention_kernel<HD, G, kAuxNonTemporal, false> : decode_attention_kernel<HD, G, kAuxDefault, false>)

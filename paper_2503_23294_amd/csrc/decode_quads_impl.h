@@ -458,11 +458,11 @@ __device__ __forceinline__ void appended_tokens_quads(int idx, int lane) {
 
 // One wave per worker.
 template <int HD, int G, int AUX, bool INT8>
-__global__ __launch_bounds__(64 * kCuWaves) __attribute__((amdgpu_waves_per_eu(2))) void decode_quads_kernel(DecodeParams) {
+__global__ __launch_bounds__(64 * kCuWaves) __attribute__((amdgpu_waves_per_eu(2))) void decode_quads_kernel(COCKTAIL_WORKER_ARGS) {
 #ifdef COCKTAIL_TRACE
   const uint64_t t_start = __builtin_amdgcn_s_memrealtime();
 #endif
-  const FirstParams fp = first_params();
+  const FirstParams fp = {recs, num_workers, num_q_heads, rep};
   const Place me = place(fp);
   const int lane = me.lane;
   if (me.worker >= fp.num_workers) {
@@ -470,7 +470,9 @@ __global__ __launch_bounds__(64 * kCuWaves) __attribute__((amdgpu_waves_per_eu(2
     return;
   }
   Stream<HD> sm;
-  sm.init(load_record(fp.recs + me.worker), fp);
+  WorkerRec rec = load_record(fp.recs + me.worker);
+  touch_params(rec);
+  sm.init(rec, fp);
   Piece cur = sm.next(lane);
   while (cur.nu > 0) {
     if (cur.cls == 0) {
@@ -501,7 +503,7 @@ __global__ __launch_bounds__(64 * kCuWaves) __attribute__((amdgpu_waves_per_eu(2
 
 template <int HD>
 hipError_t launch_decode_quads(const DecodeParams& p, int group_size, bool non_temporal, bool int8, int grid, hipStream_t st) {
-  void (*kern)(DecodeParams) = nullptr;
+  worker_kernel kern = nullptr;
 #define COCKTAIL_PICK2(G, I8) \
   kern = non_temporal ? decode_quads_kernel<HD, G, kAuxNonTemporal, I8> : decode_quads_kernel<HD, G, kAuxDefault, I8>
 #define COCKTAIL_PICK(G)             \

@@ -805,12 +805,12 @@ __device__ __forceinline__ void write_neutral_set(int slot, int lane) {
 // One wave per worker, then one per slice of the appended tokens.  The plans of these shapes have no
 // pools (a plan that had one would lose tokens, which the merge reports).
 template <int HD, int G, int AUX, bool INT8>
-__global__ __launch_bounds__(64 * kCuWaves) __attribute__((amdgpu_waves_per_eu(2))) void decode_tiles_kernel(DecodeParams) {
+__global__ __launch_bounds__(64 * kCuWaves) __attribute__((amdgpu_waves_per_eu(2))) void decode_tiles_kernel(COCKTAIL_WORKER_ARGS) {
   extern __shared__ __attribute__((aligned(16))) char all_lds[];   // kTileLds for every wave
 #ifdef COCKTAIL_TRACE
   const uint64_t t_start = __builtin_amdgcn_s_memrealtime();
 #endif
-  const FirstParams fp = first_params();
+  const FirstParams fp = {recs, num_workers, num_q_heads, rep};
   const Place me = place(fp);
   const int lane = me.lane;
   char* const lds = all_lds + me.wave * kTileLds;
@@ -827,7 +827,9 @@ __global__ __launch_bounds__(64 * kCuWaves) __attribute__((amdgpu_waves_per_eu(2
     return;
   }
   Stream<HD> sm;
-  sm.init(load_record(fp.recs + me.worker), fp);
+  WorkerRec rec = load_record(fp.recs + me.worker);
+  touch_params(rec);
+  sm.init(rec, fp);
   sm.ngran = 0, sm.nps = 0;
   Piece cur = sm.next(lane);
   while (cur.nu > 0) {
@@ -854,7 +856,7 @@ __global__ __launch_bounds__(64 * kCuWaves) __attribute__((amdgpu_waves_per_eu(2
 
 template <int HD>
 hipError_t launch_decode_tiles(const DecodeParams& p, int group_size, bool non_temporal, bool int8, int grid, hipStream_t st) {
-  void (*kern)(DecodeParams) = nullptr;
+  worker_kernel kern = nullptr;
 #define COCKTAIL_PICK2(G, I8) \
   kern = non_temporal ? decode_tiles_kernel<HD, G, kAuxNonTemporal, I8> : decode_tiles_kernel<HD, G, kAuxDefault, I8>
 #define COCKTAIL_PICK(G)             \

@@ -128,6 +128,20 @@ def _announce(msg):
     print(f"[parity] {msg}", flush=True)
 
 
+@pytest.mark.parametrize("rep,head_dim,rows,blocks", [
+    (1, 128, 1, 700), (5, 128, 2, 520), (2, 64, 1, 700), (1, 64, 1, 66), (3, 128, 1, 65), (1, 128, 130, 140), (1, 64, 130, 270), (4, 128, 33, 2)])
+def test_merge_of_many_and_of_few_partial_states(rep, head_dim, rows, blocks):
+    """A partial state per block: more of them than the merge holds at a time, with the channels of a row on one workgroup (more than
+    128 rows of query heads) and on several, one more than the threads of a workgroup take in one go, and two."""
+    lens = [64 * blocks] + [1 + 5 * i for i in range(rows - 1)]
+    w = workloads.small(f"merge_r{rep}", rows, rep, 1, lens, 64, 32, mix=(0.3, 0.3, 0.4), head_dim=head_dim, seed_offset=400 + rep)
+    _announce(f"{w.name} d{head_dim} {rows} x {blocks}")
+    c = Case(w, workers=2 * blocks + 2 * rows)
+    assert int(c.plan.sizes.num_partials) >= blocks
+    c.check_all()
+    ck.cocktail_decode_check(c.cache)
+
+
 @pytest.mark.parametrize("workers", [None, 1, 7, 64])
 def test_config1_all_heads(workers):
     _announce(f"config 1 workers={workers}")
