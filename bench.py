@@ -177,7 +177,8 @@ def run_config(cfg, steps, warmup, ntok, workers_arg, decode_only, cpu_heads, ca
     # The dominant kernel alone, live: an event recorded by the library between the partial-state kernel and the
     # merge (cocktail_decode_attention_marked), one event triple per call, outside the timed region above (the
     # extra record sits between the two kernels and delays the merge, so only start -> between is used: the
-    # partial-state kernel with its launch; the merge kernel's time is in the rocprofv3 summaries under profiles/).
+    # partial-state kernel with its launch; the merge kernel's time is in the rocprofv3 summaries under profiles/.
+    # Short contexts take one launch where nothing is recorded; the figure is then that of the two-launch path).
     nmark = min(ntok, 64)
     marks = [[torch.cuda.Event(enable_timing=True) for _ in range(3)] for _ in range(nmark)]
     for trip in marks:

@@ -130,7 +130,7 @@ typedef struct cocktail_cache {
   void* v[COCKTAIL_NUM_CLASSES]; /* DEVICE, same sizes                                                     */
   const void* plan_host;         /* HOST   plan blob written by cocktail_plan                              */
   void* plan_dev;                /* DEVICE byte-for-byte copy of the plan blob, 16-byte aligned; also holds
-                                    the decode kernel's ticket counters, the only part kernels write
+                                    the decode kernels' counters, the only part kernels write
                                     (see cocktail_decode_attention)                                        */
   void* k_app;                   /* DEVICE append_bytes each, 256-byte aligned: K/V rows of the tokens     */
   void* v_app;                   /*        generated during decoding; NULL iff append_capacity == 0         */
@@ -254,17 +254,19 @@ int cocktail_reorder_quantize_paged(const cocktail_shape* shape, const cocktail_
  * Decode side of Alg. 1: out[b,h] = softmax(sm_scale * q[b,h] . K^_b^T) V^_b over
  * all tokens of all classes of sequence b, K^/V^ being the dequantized
  * (or raw fp16) rows of kv head h / (Hq/Hkv).  Two launches: partial states per
- * worker, then the exact merge.  Workers that finish their own share early take
+ * worker, then the exact merge.  Contexts so short that a worker has a few 32-token units at most take one launch: the workgroups of a
+ * (sequence, kv head) count themselves in the device copy of the plan, and the last one merges.  Workers that finish their own share early take
  * further pieces from a pool shared by a few neighbouring workers; the pools are
- * handed out through ticket counters that live in the device copy of the plan.
- * The counters are zero in the blob cocktail_plan writes and every call leaves
+ * handed out through ticket counters that live in the device copy of the plan as well.
+ * All these counters are zero in the blob cocktail_plan writes and every call leaves
  * them zero again, so calls on the same plan_dev must not overlap in time (calls
  * on one stream never do), and a plan_dev whose call was aborted has to be
  * re-uploaded.  A call that breaks this rule is not silently wrong: every partial
  * state records how many tokens it covers, the merge compares their sum with the
  * token count of the sequence, and a (sequence, query head) row that does not add
  * up gets NaN in out and lse and a non-zero status word (cocktail_decode_check);
- * the call after it finds the counters at zero again.  Which worker takes which pool piece differs from call to call, so
+ * the call after it finds the ticket counters at zero again, and cocktail_decode_check
+ * puts those of the one launch back.  Which worker takes which pool piece differs from call to call, so
  * two calls on the same inputs agree to fp32 summation order, not bit for bit
  * (plans made with cocktail_plan_options::reproducible use no pools and are reproducible bit for bit, and so are
  * plans on matrix instructions whose waves serve five to eight query heads: Hq/Hkv of 5 to 8, and the larger
@@ -298,7 +300,8 @@ int cocktail_decode_attention(const cocktail_shape* shape, const void* q, const 
  * Measurement aid: cocktail_decode_attention that also records `event_between` (a hipEvent_t created by the
  * caller with timing enabled) on `stream` between its two kernels, so that the partial-state kernel (Alg. 1
  * decode phase, the kernel that streams the cache) and the merge can be timed apart with events on the launch
- * stream.  The record itself sits between the kernels: time whole calls with cocktail_decode_attention.
+ * stream.  The record itself sits between the kernels: time whole calls with cocktail_decode_attention, which
+ * takes one launch for short contexts where this call always takes two.
  * Errors: as cocktail_decode_attention; EINVAL if event_between is NULL; EHIP if the record fails.
  */
 int cocktail_decode_attention_marked(const cocktail_shape* shape, const void* q, const cocktail_cache* cache,
@@ -308,7 +311,7 @@ int cocktail_decode_attention_marked(const cocktail_shape* shape, const void* q,
 /*
  * cocktail_decode_attention for callers that cannot allocate device memory or hand over a workspace: code
  * that runs under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments,
- * same two kernels and same results, but the partial states go to a workspace built into the library: a
+ * same kernels and same results, but the partial states go to a workspace built into the library: a
  * static device array of COCKTAIL_STATIC_WORKSPACE_BYTES_TILES that every GPU the library runs on holds until the
  * process ends.  The call allocates and frees nothing, on the device or through any library.
  *
@@ -334,7 +337,7 @@ int cocktail_decode_attention_static(const cocktail_shape* shape, const void* q,
  *
  *   workspace  DEVICE, the workspace of that call; NULL = the built-in one of cocktail_decode_attention_static
  *
- * Returns COCKTAIL_OK if every word is zero, else COCKTAIL_ESTATE with a message naming the first bad row
+ * Counters of short contexts that are not zero are set to zero in plan_dev.  Returns COCKTAIL_OK if every word is zero, else COCKTAIL_ESTATE with a message naming the first bad row
  * (see cocktail_decode_attention for the causes).  Other errors: EINVAL, EHIP.
  */
 int cocktail_decode_check(const cocktail_shape* shape, const cocktail_cache* cache, const void* workspace,

@@ -1,12 +1,14 @@
 // Decode side of Alg. 1 (Sec. III-C): single-query attention over the INT2, INT4,
 // INT8 and FP16 classes of the packed cache.
 //
-// This file holds the exact merge of the partial softmax states and the host side of the decode entry points;
+// This file holds the exact merge of the partial softmax states and the host side of the decode entry points; short contexts run on kernels
+// that merge by themselves (decode_short_impl.h);
 // the partial-state kernels are templates (decode_heads_impl.h: one query head per kv head, vector ALU;
 // decode_quads_impl.h: two to four query heads per wave, 4x4x4 matrix instructions; decode_tiles_impl.h: five to eight,
 // 16x16x32 matrix instructions) instantiated per head_dim in their own translation units.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdlib>
 #include <mutex>
@@ -234,7 +236,7 @@ int check_plan_matches(const cocktail_shape* shape, const cocktail_cache* cache,
   return COCKTAIL_OK;
 }
 
-// Validates the arguments and enqueues the two kernels; `workspace` holds at least hd->workspace_bytes.
+// Validates the arguments and enqueues the kernels; `workspace` holds at least hd->workspace_bytes.
 int decode_enqueue(const cocktail_shape* shape, const PlanHeader* hd, const void* q, const cocktail_cache* cache,
                    float sm_scale, void* out, float* lse, void* workspace, void* stream, void* event_between = nullptr) {
   if (shape->head_dim != 64 && shape->head_dim != 128)
@@ -296,6 +298,21 @@ int decode_enqueue(const cocktail_shape* shape, const PlanHeader* hd, const void
   p.trace = reinterpret_cast<uint64_t*>(static_cast<char*>(workspace) + ((hd->workspace_bytes + 255) & ~int64_t(255)));
 #endif
   hipStream_t st = static_cast<hipStream_t>(stream);
+#ifdef COCKTAIL_TRACE
+  const bool one_launch = false;   // (the workers' records are what is traced)
+#else
+  // (between the two kernels: an event there wants two)
+  const bool one_launch = hd->short_groups > 0 && !event_between;
+#endif
+  if (one_launch) {
+    const ShortRec* recs = reinterpret_cast<const ShortRec*>(pd + hd->off_short);
+    const ShortGroup* place = reinterpret_cast<const ShortGroup*>(pd + short_group_offset(*hd));
+    const int counters = static_cast<int>(short_counters_offset(*hd) - short_group_offset(*hd));
+    const bool quads = hd->v_layout == COCKTAIL_V_TOKEN_QUADS, int8 = hd->class_blocks[2] > 0;
+    const hipError_t e = shape->head_dim == 64 ? launch_decode_short<64>(p, recs, place, counters, quads, shape->group_size, int8, hd->short_units == 1, hd->short_groups, st)
+                                               : launch_decode_short<128>(p, recs, place, counters, quads, shape->group_size, int8, hd->short_units == 1, hd->short_groups, st);
+    return e == hipSuccess ? COCKTAIL_OK : fail(COCKTAIL_EHIP, "decode launch failed: %s", hipGetErrorString(e));
+  }
   const int app_groups = hd->batch * hd->work_heads * hd->append_slices;   // 0 without append buffers
   if (hd->total_gblocks > 0 || app_groups > 0) {
     const bool quads = hd->v_layout == COCKTAIL_V_TOKEN_QUADS;
@@ -396,6 +413,20 @@ extern "C" int cocktail_decode_check(const cocktail_shape* shape, const cocktail
   if (e != hipSuccess) {
     (void)hipGetLastError();
     return fail(COCKTAIL_EHIP, "reading the status of the last decode call failed: %s", hipGetErrorString(e));
+  }
+  if (hd->short_groups > 0) {
+    // a counter that was not zero when a call started is not zero after it either
+    std::vector<uint32_t> counters(size_t(kShortCounterStride) * hd->batch * hd->work_heads);
+    char* const at = static_cast<char*>(cache->plan_dev) + short_counters_offset(*hd);
+    e = hipMemcpy(counters.data(), at, counters.size() * 4, hipMemcpyDeviceToHost);
+    if (e == hipSuccess && std::any_of(counters.begin(), counters.end(), [](uint32_t c) { return c != 0; })) {
+      std::fill(counters.begin(), counters.end(), 0u);
+      e = hipMemcpy(at, counters.data(), counters.size() * 4, hipMemcpyHostToDevice);
+    }
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      return fail(COCKTAIL_EHIP, "looking at the counters of the plan failed: %s", hipGetErrorString(e));
+    }
   }
   int bad = 0, first = -1;
   for (int i = 0; i < rows; ++i)

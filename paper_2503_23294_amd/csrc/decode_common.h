@@ -81,12 +81,12 @@ struct FirstParams {
 // together with the record, makes the reads that follow one by one (kparams) hits.  A worker of a 1K-token layer had its first loads on the
 // way 2300 cycles after its start, with every line a miss of its own; a quarter of its time.  (With the first fields in registers from the
 // start instead of read in front of the record, calls of small layers take another 0.1 to 0.2 us less: 13.8 -> 13.65, 16.4 -> 16.2.)
-__device__ __forceinline__ void touch_params(WorkerRec& rec) {
+__device__ __forceinline__ void touch_params(int32_t& first) {
   const auto* words = reinterpret_cast<const __attribute__((address_space(4))) uint32_t*>(reinterpret_cast<uint64_t>(__builtin_amdgcn_kernarg_segment_ptr()));
   constexpr int kLine = 16;   // dwords
   static_assert(sizeof(DecodeParams) + kParamsOffset > 3 * kLine * 4 && sizeof(DecodeParams) + kParamsOffset <= 4 * kLine * 4, "four lines");
   const uint32_t l0 = words[kLine / 2], l1 = words[kLine], l2 = words[2 * kLine], l3 = words[3 * kLine];
-  asm volatile("" : "+s"(rec.g0) : "s"(l0), "s"(l1), "s"(l2), "s"(l3));
+  asm volatile("" : "+s"(first) : "s"(l0), "s"(l1), "s"(l2), "s"(l3));
 }
 
 // Which worker a wave is.  A workgroup is one wave, or (launch_workers) kCuWaves of them: the waves of a workgroup have the ids of
@@ -114,7 +114,6 @@ __device__ __forceinline__ rsrc_t make_rsrc(const char* base, uint32_t bytes) {
 // MI355X is worth 10 % of HBM throughput); shapes in which several waves walk the blocks of one kv head,
 // and small caches that stay resident between calls, use the default policy.
 constexpr int kAuxDefault = 0, kAuxNonTemporal = 2;
-constexpr int64_t kNonTemporalMinBytes = int64_t(64) << 20;   // packed K+V bytes of one call
 template <int AUX>
 __device__ __forceinline__ u32x4 load16(rsrc_t rs, uint32_t voff, uint32_t soff) {
   return __builtin_amdgcn_raw_buffer_load_b128(rs, voff, soff, AUX);
@@ -571,7 +570,7 @@ struct Stream {
 // Tokens appended to sequence b so far (never more than the append buffers hold).
 __device__ __forceinline__ int appended_count(int b) {
   kparams_t kp = kparams();
-  const int n = kp->appended ? kp->appended[b] : kp->num_appended;
+  const int n = kp->appended ? load_record(kp->appended + b) : kp->num_appended;
   return min(max(n, 0), kp->app_capacity);
 }
 
@@ -596,6 +595,37 @@ __device__ __forceinline__ AppendSlice append_slice(int idx) {
   return a;
 }
 
+// Where a partial state goes: (m, l, tokens, unused, o[HD]) per query head, at byte offsets of its slot.  A slot of the workspace, or of the
+// workgroup's shared memory (short contexts).
+struct WorkspaceSlot {
+  float* p;
+};
+struct SharedSlot {
+  char* p;
+};
+template <class T>
+__device__ __forceinline__ void put(WorkspaceSlot s, int at, T v) { *reinterpret_cast<T*>(reinterpret_cast<char*>(s.p) + at) = v; }
+template <class T>
+__device__ __forceinline__ void put(SharedSlot s, int at, T v) { *reinterpret_cast<T*>(s.p + at) = v; }
+template <class S>
+__device__ __forceinline__ void put_header(S s, int at, float m, float l, int tokens) {
+  put(s, at, float4{m, l, __int_as_float(tokens), 0.f});
+}
+template <int HD>
+struct Workspace {
+  static constexpr bool kOne = false;   // a loop iteration is kIterUnits
+  __device__ __forceinline__ WorkspaceSlot slot(int pid) const {
+    kparams_t kp = kparams();
+    return {kp->ws + int64_t(pid) * kp->rep * (HD + kPartialFloats)};
+  }
+};
+template <bool ONE>
+struct SharedStates {
+  static constexpr bool kOne = ONE;     // a loop iteration is one unit
+  char* p;
+  __device__ __forceinline__ SharedSlot slot(int) const { return {p}; }
+};
+
 // The neutral partial state (weight zero in the merge) for a slot nobody had tokens for.
 template <int HD>
 __device__ __forceinline__ void write_neutral(int slot, int r, int lane) {
@@ -615,6 +645,10 @@ template <int HD>
 hipError_t launch_decode_quads(const DecodeParams& p, int group_size, bool non_temporal, bool int8, int grid, hipStream_t st);
 template <int HD>
 hipError_t launch_decode_tiles(const DecodeParams& p, int group_size, bool non_temporal, bool int8, int grid, hipStream_t st);
+
+// Short contexts (decode_short_impl.h): `groups` workgroups, which merge the partial states themselves.
+template <int HD>
+hipError_t launch_decode_short(const DecodeParams& p, const ShortRec* recs, const ShortGroup* place, int counters_offset, bool quads, int group_size, bool int8, bool one, int groups, hipStream_t st);
 
 // `grid` waves, each with `lds` bytes of shared memory.  Where the workers fill the chip exactly once, two waves per SIMD, in workgroups of a whole
 // compute unit.  Launched one by one, the waves are dealt out to the units in order, but which SIMD of its unit a wave gets depends on

@@ -66,25 +66,20 @@ __device__ __forceinline__ void softmax_step(const float (&s)[J], float (&p)[J],
   }
 }
 
-// Writes this wave's partial state `pid`: (m, l, o[HD]) summed over its lanes, and the number of tokens it covers.
+// Writes this wave's partial state: (m, l, o[HD]) summed over its lanes, and the number of tokens it covers.
 // The lanes share one reference m, so nothing is rescaled.  The sums over the token lanes halve the number of values a
 // lane holds step by step: 130 instructions in registers.  Through a shared-memory tile, sixteen channels at a time, a
 // flush took 1.5 us of a worker's 6 on a 2K-token layer (32K tokens, 32 heads: 36.3 -> 35.4 us per call; 128K, 40 heads:
 // 107.4 -> 106.3; four heads per wave, INT8 mix, 4 x 64K tokens: 62.2 -> 60.6, its other mixes gain 0.5 %).
-template <int HD, int NGH, int GL>
-__device__ __forceinline__ void flush_partial(const LaneState<NGH>& st, int pid, int r, int lane, int tokens) {
+template <int HD, int NGH, int GL, class SLOT>
+__device__ __forceinline__ void flush_partial(const LaneState<NGH>& st, SLOT out, int r, int lane, int tokens) {
   constexpr int UT = Geo<HD>::UT;       // lanes that hold different tokens
-  kparams_t prm = kparams();
   const float lw = token_sum<UT>(st.l);
   float z[NGH];
 #pragma unroll
   for (int g = 0; g < NGH; ++g) z[g] = token_sum<UT>(st.zacc[g]);
-  float* out = prm->ws + (int64_t(pid) * prm->rep + r) * (HD + kPartialFloats);
-  if (lane == 0) {
-    out[0] = st.m;
-    out[1] = lw;
-    out[2] = __int_as_float(tokens);
-  }
+  const int at = r * ((HD + kPartialFloats) * 4);
+  if (lane == 0) put_header(out, at, st.m, lw, tokens);
   // after the folds lane (bits b5 .. b0) holds channels 32 b4 + 16 b3 + 8 b2 + 4 b1 + 2 b0 + {0, 1} of its half (head_dim
   // 64: one channel, 32 b5 + 16 b4 + 8 b3 + 4 b2 + 2 b1 + b0); a channel's group is bit 4 (b4; b5) of 64 channels at G 32
   float v[32];
@@ -101,7 +96,7 @@ __device__ __forceinline__ void flush_partial(const LaneState<NGH>& st, int pid,
     for (int i = 0; i < 2; ++i) v[i] = fold2(v[i], v[i + 2], lane & 2);
     v[0] = fold1(v[0], v[1], lane & 1);
     const float zz = NGH == 2 ? (lane & 32 ? z[NGH - 1] : z[0]) : z[0];
-    out[kPartialFloats + lane] = v[0] + zz;
+    put(out, at + (kPartialFloats + lane) * 4, v[0] + zz);
   } else {
 #pragma unroll
     for (int i = 0; i < 32; ++i) v[i] = fold16(st.acc[i], st.acc[i + 32]);
@@ -114,7 +109,7 @@ __device__ __forceinline__ void flush_partial(const LaneState<NGH>& st, int pid,
 #pragma unroll
     for (int i = 0; i < 2; ++i) v[i] = fold1(v[i], v[i + 2], lane & 1);
     const float zz = NGH == 2 ? (lane & 16 ? z[NGH - 1] : z[0]) : z[0];
-    *reinterpret_cast<float2*>(out + kPartialFloats + 2 * lane) = float2{v[0] + zz, v[1] + zz};
+    put(out, at + (kPartialFloats + 2 * lane) * 4, float2{v[0] + zz, v[1] + zz});
   }
 }
 
@@ -154,13 +149,13 @@ __device__ __forceinline__ void begin_state(int qrow, int h, LaneState<NGH>& st,
 // which the buffer resource answers with zeros without touching memory, so the loop body has no
 // branches around the loads (the zeros are masked like padding).  The accumulators live and die inside this function, one
 // instance per class.
-template <int HD, class CLS, int CID, int G, int AUX>
-__device__ __forceinline__ void run_class(Stream<HD>& sm, Piece& cur, int r, int lane, bool app = false) {
+template <int HD, class CLS, int CID, int G, int AUX, class DEST = Workspace<HD>, class STREAM = Stream<HD>>
+__device__ __forceinline__ void run_class(STREAM& sm, Piece& cur, int r, int lane, bool app = false, DEST dest = {}) {
   constexpr int NGH = CLS::NGH;
   constexpr int GL = G < DH ? G : DH;
-  constexpr int J = CLS::J;
+  constexpr int J = DEST::kOne ? 1 : CLS::J;
   constexpr int UT = Geo<HD>::UT, UPB = Geo<HD>::UPB;
-  static_assert(J == kIterUnits[CID], "the planner cuts pool pieces to the kernel's iteration size");
+  static_assert(DEST::kOne || J == kIterUnits[CID], "the planner cuts pool pieces to the kernel's iteration size");
   const int t = lane % UT, h = lane / UT;
   const uint32_t vc = CLS::code_voff(t, h), vm = CLS::meta_voff(t, h);
   const char* const kbase = uni(app ? kparams()->k_app : kparams()->k[CID]);   // app: the append buffers
@@ -219,7 +214,7 @@ __device__ __forceinline__ void run_class(Stream<HD>& sm, Piece& cur, int r, int
       CLS::template load<AUX>(vs[jj], vrs, jj < rn ? ru + jj : roob, vc, vm);
       sched_fence();
     }
-    if (!more || nxt.fresh) flush_partial<HD, NGH, GL>(st, pid, r, lane, covered);
+    if (!more || nxt.fresh) flush_partial<HD, NGH, GL>(st, dest.slot(pid), r, lane, covered);
     if (!more) break;
     if (nxt.fresh) {
       pid = nxt.pid;
@@ -266,7 +261,7 @@ __global__ __launch_bounds__(64 * kCuWaves) __attribute__((amdgpu_waves_per_eu(2
   }
   Stream<HD> sm;
   WorkerRec rec = load_record(fp.recs + me.worker);
-  touch_params(rec);
+  touch_params(rec.g0);
   sm.init(rec, fp);
   Piece cur = sm.next(lane);
   while (cur.nu > 0) {

@@ -250,14 +250,13 @@ __device__ __forceinline__ void softmax_quads(const f4 (&s)[J], const float (&ev
   }
 }
 
-// Writes the partial states `pid` of the wave's query heads: (m, l, tokens, o[HD]) per head, summed over the lanes in
+// Writes the partial states of the wave's query heads: (m, l, tokens, o[HD]) per head, summed over the lanes in
 // registers (decode_common.h: the fold steps).
-template <int HD, class CLS, int NGH, int GL>
-__device__ __forceinline__ void flush_quads(const QuadState<NGH>& st, int pid, int lane, int tokens) {
+template <int HD, class CLS, int NGH, int GL, class SLOT>
+__device__ __forceinline__ void flush_quads(const QuadState<NGH>& st, SLOT out, int lane, int tokens) {
   constexpr int UT = Geo<HD>::UT;
   constexpr int STRIDE = HD + kPartialFloats;
-  kparams_t prm = kparams();
-  const int rep = prm->rep;
+  const int rep = kparams()->rep;
   // quantities kept per token lane: the lanes that hold different tokens (at head_dim 128 the 32 lanes of each half;
   // both halves hold the same p)
   f4 l, z[NGH];
@@ -267,12 +266,7 @@ __device__ __forceinline__ void flush_quads(const QuadState<NGH>& st, int pid, i
 #pragma unroll
     for (int g = 0; g < NGH; ++g) z[g][i] = token_sum<UT>(st.zacc[g][i]);
   }
-  float* out = prm->ws + int64_t(pid) * rep * STRIDE;
-  if (lane < rep) {
-    out[lane * STRIDE] = pick(st.m, lane);
-    out[lane * STRIDE + 1] = pick(l, lane);
-    out[lane * STRIDE + 2] = __int_as_float(tokens);
-  }
+  if (lane < rep) put_header(out, lane * (STRIDE * 4), pick(st.m, lane), pick(l, lane), tokens);
   // channel accumulators: lane 32h + 4b + j (head_dim 64: 4b + j) holds the sum over the tokens of quad b for its channels
   // e = 0..15.  The steps over the bits of b leave four consecutive channels e = 8 e3 + 4 e2 + {0..3} and two heads (one)
   // per lane; the factor of a channel depends on e % 4 only.
@@ -303,7 +297,7 @@ __device__ __forceinline__ void flush_quads(const QuadState<NGH>& st, int pid, i
     const float zh = pick(zz, head);
 #pragma unroll
     for (int e = 0; e < 4; ++e) o[0][e] = o[0][e] * CLS::fac(e) + zh;
-    if (head < rep) *reinterpret_cast<f4*>(out + head * STRIDE + kPartialFloats + ch) = o[0];
+    if (head < rep) put(out, (head * STRIDE + kPartialFloats + ch) * 4, o[0]);
   } else {
     const int head0 = 2 * ((lane >> 2) & 1), ch = 64 * (lane >> 5) + 32 * ((lane >> 4) & 1) + 8 * j + 4 * ((lane >> 3) & 1);
 #pragma unroll
@@ -311,7 +305,7 @@ __device__ __forceinline__ void flush_quads(const QuadState<NGH>& st, int pid, i
       const float zh = lane & 4 ? zz[2 + i] : zz[i];
 #pragma unroll
       for (int e = 0; e < 4; ++e) o[i][e] = o[i][e] * CLS::fac(e) + zh;
-      if (head0 + i < rep) *reinterpret_cast<f4*>(out + (head0 + i) * STRIDE + kPartialFloats + ch) = o[i];
+      if (head0 + i < rep) put(out, ((head0 + i) * STRIDE + kPartialFloats + ch) * 4, o[i]);
     }
   }
 }
@@ -351,13 +345,13 @@ __device__ __forceinline__ void begin_quads(int qrow, int h, int lane, QuadState
 }
 
 // The quad kernel's version of the one-head kernel's run_class: same pipeline, four heads per wave.
-template <int HD, class CLS, int CID, int G, int AUX>
-__device__ __forceinline__ void run_quads(Stream<HD>& sm, Piece& cur, int lane, bool app = false) {
+template <int HD, class CLS, int CID, int G, int AUX, class DEST = Workspace<HD>, class STREAM = Stream<HD>>
+__device__ __forceinline__ void run_quads(STREAM& sm, Piece& cur, int lane, bool app = false, DEST dest = {}) {
   constexpr int NGH = CLS::NGH;
   constexpr int GL = G < DH ? G : DH;
-  constexpr int J = CLS::J;
+  constexpr int J = DEST::kOne ? 1 : CLS::J;
   constexpr int UT = Geo<HD>::UT, UPB = Geo<HD>::UPB;
-  static_assert(J == kIterUnits[CID], "the planner cuts pool pieces to the kernel's iteration size");
+  static_assert(DEST::kOne || J == kIterUnits[CID], "the planner cuts pool pieces to the kernel's iteration size");
   const int t = lane % UT, h = lane / UT;
   const uint32_t vc = CLS::code_voff(t, h), vm = CLS::meta_voff(t, h);
   const char* const kbase = uni(app ? kparams()->k_app : kparams()->k[CID]);
@@ -423,7 +417,7 @@ __device__ __forceinline__ void run_quads(Stream<HD>& sm, Piece& cur, int lane, 
       CLS::template load<AUX>(vs[jj], vrs, jj < rn ? ru + jj : roob, vc, vm);
       sched_fence();
     }
-    if (!more || nxt.fresh) flush_quads<HD, CLS, NGH, GL>(st, pid, lane, covered);
+    if (!more || nxt.fresh) flush_quads<HD, CLS, NGH, GL>(st, dest.slot(pid), lane, covered);
     if (!more) break;
     if (nxt.fresh) {
       pid = nxt.pid;
@@ -471,7 +465,7 @@ __global__ __launch_bounds__(64 * kCuWaves) __attribute__((amdgpu_waves_per_eu(2
   }
   Stream<HD> sm;
   WorkerRec rec = load_record(fp.recs + me.worker);
-  touch_params(rec);
+  touch_params(rec.g0);
   sm.init(rec, fp);
   Piece cur = sm.next(lane);
   while (cur.nu > 0) {

@@ -111,7 +111,6 @@ struct TileClass {
 
   // INT2 and INT4 blocks are staged through shared memory (run_tiles_lds), as they lie in the cache
   static constexpr bool LDS = BITS <= 4;
-  static constexpr int JB = J / UPB;                       // blocks per iteration
   static constexpr int NI = BLOCKB / 1024 + BLOCKB % 1024 / 256;   // load instructions per block
 
   struct KStage {
@@ -496,15 +495,13 @@ __device__ __forceinline__ void tile_softmax(f4 (&p)[N], const float (&ev)[N], f
   }
 }
 
-// Writes the partial states `pid` of the set's query heads: (m, l, tokens, o[HD]) per head.
-template <int HD, class T>
-__device__ __forceinline__ void flush_tiles(const TileState<T>& st, int pid, int lane, int tokens) {
+// Writes the partial states of the set's query heads: (m, l, tokens, o[HD]) per head.
+template <int HD, class T, class SLOT>
+__device__ __forceinline__ void flush_tiles(const TileState<T>& st, SLOT out, int lane, int tokens) {
   constexpr int STRIDE = HD + kPartialFloats;
   constexpr float c0 = T::QUANT ? 0.5f * float((1 << (16 / T::PER)) - 1) : 0.f;
-  kparams_t prm = kparams();
-  const int rep = prm->rep;
+  const int rep = kparams()->rep;
   const int c = lane & 15, par = lane >> 5, head0 = 4 * ((lane >> 4) & 1);
-  float* out = prm->ws + (int64_t(pid) * rep + head0) * STRIDE;
   f4 l, z[T::NM];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -512,11 +509,7 @@ __device__ __forceinline__ void flush_tiles(const TileState<T>& st, int pid, int
 #pragma unroll
     for (int g = 0; g < T::NM; ++g) z[g][i] = T::QUANT ? both_halves(row_sum(st.zacc[g][i]), false) : 0.f;
   }
-  if (lane < 32 && c < 4 && head0 + c < rep) {
-    out[c * STRIDE] = pick(st.m, c);
-    out[c * STRIDE + 1] = pick(l, c);
-    out[c * STRIDE + 2] = __int_as_float(tokens);
-  }
+  if (lane < 32 && c < 4 && head0 + c < rep) put_header(out, (head0 + c) * (STRIDE * 4), pick(st.m, c), pick(l, c), tokens);
   const bool mine = (c >> 3) == par;   // not the columns of the other half
 #pragma unroll
   for (int a = 0; a < T::NA; ++a) {
@@ -530,7 +523,7 @@ __device__ __forceinline__ void flush_tiles(const TileState<T>& st, int pid, int
         f4 o;
 #pragma unroll
         for (int x = 0; x < 4; ++x) o[x] = st.acc[a][e + x][i] * T::fac(e + x) + base;
-        if (mine && head0 + i < rep) *reinterpret_cast<f4*>(out + i * STRIDE + kPartialFloats + ch + e) = o;
+        if (mine && head0 + i < rep) put(out, ((head0 + i) * STRIDE + kPartialFloats + ch + e) * 4, o);
       }
     }
   }
@@ -551,11 +544,11 @@ __device__ __forceinline__ void tile_select(int lane, u32x4 (&sel)[2]) {
 }
 
 // The eight-head version of run_class (decode_heads_impl.h): the same pipeline over the stream's pieces.
-template <int HD, int BITS, int CID, int G, int AUX>
-__device__ __forceinline__ void run_tiles(Stream<HD>& sm, Piece& cur, int lane, bool app = false) {
+template <int HD, int BITS, int CID, int G, int AUX, class DEST = Workspace<HD>, class STREAM = Stream<HD>>
+__device__ __forceinline__ void run_tiles(STREAM& sm, Piece& cur, int lane, bool app = false, DEST dest = {}) {
   typedef TileClass<HD, BITS, G> T;
-  constexpr int J = T::J, GR = T::GR, UT = T::UT, UPB = T::UPB;
-  static_assert(J == kIterUnits[CID], "the stream hands out pieces of the kernel's iteration size");
+  constexpr int J = DEST::kOne ? 1 : T::J, GR = T::GR, UT = T::UT, UPB = T::UPB;
+  static_assert(DEST::kOne || J == kIterUnits[CID], "the stream hands out pieces of the kernel's iteration size");
   const typename T::Lane off = T::lane_offsets(lane);
   const char* const kbase = uni(app ? kparams()->k_app : kparams()->k[CID]);
   const char* const vbase = uni(app ? kparams()->v_app : kparams()->v[CID]);
@@ -621,7 +614,7 @@ __device__ __forceinline__ void run_tiles(Stream<HD>& sm, Piece& cur, int lane, 
       T::template load_v<AUX>(vs[jj], vrs, jj < rn ? ru + jj : roob, off);
       sched_fence();
     }
-    if (!more || nxt.fresh) flush_tiles<HD, T>(st, pid, lane, covered);
+    if (!more || nxt.fresh) flush_tiles<HD, T>(st, dest.slot(pid), lane, covered);
     if (!more) break;
     if (nxt.fresh) {
       pid = nxt.pid;
@@ -698,11 +691,11 @@ __device__ __forceinline__ void fetch_block(uint32_t lds, const LdsRsrc& rs, int
 // compute unit's load path per 32 INT2 tokens (4-byte loads 16 bytes apart cost 32 cycles, 8-byte loads as much as
 // 16-byte ones: 16); contiguous 16-byte loads take 48.
 constexpr int kTileLds = 12 * 1024;
-template <int HD, int BITS, int CID, int G, int AUX>
-__device__ __forceinline__ void run_tiles_lds(Stream<HD>& sm, Piece& cur, char* lds, int lane) {
+template <int HD, int BITS, int CID, int G, int AUX, class DEST = Workspace<HD>, class STREAM = Stream<HD>>
+__device__ __forceinline__ void run_tiles_lds(STREAM& sm, Piece& cur, char* lds, int lane, DEST dest = {}) {
   typedef TileClass<HD, BITS, G> T;
-  constexpr int J = T::J, JB = T::JB, UPB = T::UPB, NG = 2 * JB;
-  static_assert(J == kIterUnits[CID], "the stream hands out pieces of the kernel's iteration size");
+  constexpr int UPB = T::UPB, J = DEST::kOne ? UPB : T::J, JB = J / UPB, NG = 2 * JB;   // blocks, granules per iteration
+  static_assert(DEST::kOne || J == kIterUnits[CID], "the stream hands out pieces of the kernel's iteration size");
   static_assert(2 * JB * T::BLOCKB <= kTileLds, "the images of an iteration fit");
   const typename T::Lane off = T::lane_offsets(lane);
   const char* const kbase = uni(kparams()->k[CID]);
@@ -781,7 +774,7 @@ __device__ __forceinline__ void run_tiles_lds(Stream<HD>& sm, Piece& cur, char* 
       fetch_block<T, AUX>(lds0 + vimg(j), vrs, j < rn ? rb + j : oob, lane);
       sched_fence();
     }
-    if (!more || nxt.fresh) flush_tiles<HD, T>(st, pid, lane, covered);
+    if (!more || nxt.fresh) flush_tiles<HD, T>(st, dest.slot(pid), lane, covered);
     if (!more) break;
     if (nxt.fresh) {
       pid = nxt.pid;
@@ -828,7 +821,7 @@ __global__ __launch_bounds__(64 * kCuWaves) __attribute__((amdgpu_waves_per_eu(2
   }
   Stream<HD> sm;
   WorkerRec rec = load_record(fp.recs + me.worker);
-  touch_params(rec);
+  touch_params(rec.g0);
   sm.init(rec, fp);
   sm.ngran = 0, sm.nps = 0;
   Piece cur = sm.next(lane);

@@ -36,6 +36,8 @@ constexpr int kMaxPoolSegments = 32;           // segments one pool may touch (a
 // The appended tokens of a (sequence, kv head) are attended to by one extra wave per this many 64-token
 // blocks of append capacity (one partial state each), so a long generation does not hang on a single wave.
 constexpr int kAppendSliceBlocks = 8;
+// Packed K+V bytes of a call from which its loads are non-temporal (decode_common.h).
+constexpr int64_t kNonTemporalMinBytes = int64_t(64) << 20;
 // The chip: 256 compute units of four SIMDs; the decode kernels run two waves per SIMD.
 constexpr int kCuWaves = 8, kChipWorkers = 256 * kCuWaves, kSimds = kChipWorkers / 2;
 // Waves per workgroup of a decode launch: a compute unit's where the workers fill the chip exactly once, else one.  With twice or three
@@ -107,6 +109,23 @@ struct GroupRec {
   int32_t pad[3];
 };
 static_assert(sizeof(GroupRec) == 32, "GroupRec layout");
+
+// Short contexts have a second split of the work, which leaves the merge to the workgroups themselves: a workgroup of kCuWaves waves works on one
+// row (sequence, work head), every wave on a range of units of one class, or of the row's appended tokens.
+struct ShortGroup {          // a workgroup
+  int32_t b, qrow;           // its row: sequence, index of the first query head
+  int32_t context;           // tokens of the sequence
+  uint32_t place;            // index among the workgroups of the row | their number << 8 | the row's counter << 20
+};
+struct ShortRec {            // one of its waves
+  int32_t cls;               // class, or kNumClasses: the appended tokens
+  uint32_t range;            // units u0 | u1 << 16 of the run (appended tokens: part u0 of u1 equal parts); u0 == u1: no work
+  int32_t ntok, blk0;        // tokens and first block of the run (appended tokens: 2^32 / u1 + 1, first block in the append buffers)
+};
+static_assert(sizeof(ShortGroup) == 16 && sizeof(ShortRec) == 16, "layout of the split for short contexts");
+constexpr int kShortCounterStride = 16;        // uint32 slots between two counters
+// States (of one query head each) of a row that the last of its workgroups may find: they are merged in shared memory.
+constexpr int kShortThreads = 64 * kCuWaves, kShortStates = 128;
 
 // The part of a pool that lies inside one segment.  Ticket t with gran0 <= t < gran0 + ceil(nunits / J)
 // stands for units [unit0 + (t - gran0) * J, + J) of the segment, J = kIterUnits[class].
@@ -181,7 +200,15 @@ struct PlanHeader {
   int64_t ws_status_off;      // byte offset, inside the decode workspace, of int32 [B * Hq]: per (sequence, query
                               // head) tokens covered by the last call's partial states minus tokens of the sequence
                               // (0 = every token was attended to exactly once)
+  int16_t short_groups;       // workgroups of the split for short contexts (ShortRec), 0 = the plan has none
+  int16_t short_units;        // 1: a loop iteration of its waves is one unit (or staged block) of any class; 0: kIterUnits
+  int32_t off_short;          // ShortRec [short_groups * kCuWaves], ShortGroup [short_groups], then (128-byte aligned) a counter per row, zero
+                              // between calls
 };
+static_assert(sizeof(PlanHeader) == 304, "the arrays start behind 304 bytes; the last two fields are zero in plans that were written before they existed");
+
+inline int64_t short_group_offset(const PlanHeader& hd) { return hd.off_short + int64_t(sizeof(ShortRec)) * kCuWaves * hd.short_groups; }
+inline int64_t short_counters_offset(const PlanHeader& hd) { return (short_group_offset(hd) + int64_t(sizeof(ShortGroup)) * hd.short_groups + 127) & ~int64_t(127); }
 
 // Token-quad form of a V block: byte offset, inside the block, of the half-word that holds token i
 // (0..63) of lane j's channels e .. e + per - 1 in the 64-channel half h, where per = 16 / bits values

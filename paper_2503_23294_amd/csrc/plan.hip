@@ -7,6 +7,7 @@
 #include <cstdlib>
 #include <algorithm>
 #include <cstring>
+#include <unistd.h>
 #include <queue>
 #include <utility>
 #include <vector>
@@ -65,6 +66,16 @@ constexpr int kLongRangeBlocks = 24;   // average blocks per worker from which a
 constexpr int kPoolPercent = 25;
 constexpr int kPairMode = 0;
 constexpr int kLayout = 0;
+// The split for short contexts is taken while no wave has more loop iterations than this: of one unit of any class (five heads and more: a staged block),
+// else of kIterUnits.  Calls on prepared arguments, as two launches -> one (us).  One unit, one to four heads: 8 heads 2K (1 unit) 9.6 -> 7.5, 32 heads
+// 5.3K (2) 12.9 -> 9.7, 4 ragged up to 7K at head_dim 64 (4) 12.5 -> 9.7, 3 x 32 heads 2.3K (6) 14.2 -> 11.3, 4 ragged up to 4.4K at 64 q / 32 kv heads
+// (8) 18.6 -> 16.4.  kIterUnits: the same up to 5K (3 iterations) 22.4 -> 20.2, 4 ragged at 80 q / 40 kv heads, 3.2K and 205 appended (6) 25.7 ->
+// 25.0.  With kIterUnits for all of them a wave with one unit runs the code of four: 10.3 instead of 8.9 on the first of these shapes.  Five heads and more,
+// where what is written and read per state is five to eight times as much: 3 x 1.4K at five heads (1 block) 10.3 -> 9.9, 4 x 1.4K at seven
+// (1) 10.9 -> 9.8, seven at head_dim 64 with appended tokens (3) 15.4 -> 13.0; with longer ranges 24.8K at six heads (6) 15.7 -> 18.9.
+constexpr int kShortUnits = 8, kShortIterations = 6, kShortUnitsTiles = 3;
+// A row that one workgroup finishes is done 2 us after its waves, one of several after 3: worth this many iterations.
+constexpr int kShortMergeIterations = 1;
 // Relative speed of a worker of class [self] whose SIMD mate works on class [mate] (INT2, INT4, INT8, FP16), traced
 // on MI355X at equal weighted cost: two bandwidth-bound or two ALU-bound waves on a SIMD get in each other's way,
 // an INT4 wave next to an FP16 wave runs well ahead.  (INT8 was not traced: neutral.)
@@ -137,10 +148,19 @@ struct Tuning {
   int min_pool_blocks = kMinBlocksPerWorkerForPool;   // COCKTAIL_MIN_POOL_BLOCKS  1..4096
   double pair_table[kNumClasses][kNumClasses];        // COCKTAIL_PAIR_TABLE="16 numbers, row = own class": replaces
   bool pair_table_set = false;                        // kPairSpeed, and switches the correction on for the matrix kernel too
+  bool changed = false;                 // any of these is set: no split for short contexts, which knows none of them
 };
 
 static Tuning read_tuning() {
   Tuning t;
+  for (int a = 0; a < kNumClasses; ++a)
+    for (int b = 0; b < kNumClasses; ++b) t.pair_table[a][b] = kPairSpeed[a][b];
+  // (one look for all of them: sixteen searches of the environment took 3 us of a short context's 11)
+  for (char** e = environ; e && *e; ++e)
+    if (std::strncmp(*e, "COCKTAIL_", 9) == 0)
+      for (const char* name : {"COST_WEIGHTS=", "POOL_PERCENT=", "GROUP_WORKERS=", "PAIR_SPEED=", "LAYOUT=", "PAIR_MODE=", "MIN_POOL_BLOCKS=", "PAIR_TABLE="})
+        t.changed = t.changed || std::strncmp(*e + 9, name, std::strlen(name)) == 0;
+  if (!t.changed) return t;
   if (const char* e = std::getenv("COCKTAIL_COST_WEIGHTS")) {
     long a = 0, b = 0, c = 0, d = 0;
     const int n = std::sscanf(e, "%ld,%ld,%ld,%ld", &a, &b, &c, &d);
@@ -155,8 +175,6 @@ static Tuning read_tuning() {
       if (v >= lo && v <= hi) out = v;
     }
   };
-  for (int a = 0; a < kNumClasses; ++a)
-    for (int b = 0; b < kNumClasses; ++b) t.pair_table[a][b] = kPairSpeed[a][b];
   if (const char* e = std::getenv("COCKTAIL_PAIR_TABLE")) {
     double v[16];
     int n = 0;
@@ -281,6 +299,143 @@ static std::vector<int32_t> aligned_ranges(const std::vector<int32_t>& nblk, int
   return bound;
 }
 
+// The split for short contexts (decode_short_impl.h).  Every row gets as many workgroups as it takes for no wave to have more than some number of loop
+// iterations, the smallest for which the chip's workgroups are enough; a run is cut into equal parts, one per wave.
+struct ShortSplit {
+  struct Run {
+    int cls, units, step, iters, parts;   // step: units a range is a multiple of
+  };
+  struct Sequence {
+    Run runs[kNumClasses + 1];            // the last one: appended tokens
+    int n = 0, groups = 0;                // runs, workgroups of a row
+  };
+  std::vector<Sequence> sequences;
+  int groups = 0, rows = 0;               // 0: no such split
+  bool one = false;                       // an iteration is one unit (or staged block)
+  bool shared = false;                    // some row has several workgroups
+};
+static ShortSplit short_split(const std::vector<int32_t>& ntok, int B, int heads, int head_dim, int append_capacity, int rep, bool one, int most_groups) {
+  constexpr int NC = kNumClasses, W = kCuWaves;
+  const bool tiles = uses_tiles(rep);   // which stage whole blocks of INT2 and INT4
+  const int most_iterations = tiles ? kShortUnitsTiles : one ? kShortUnits : kShortIterations;
+  const int units_per_block = head_dim == 64 ? 1 : 2, unit_tokens = kTB / units_per_block;
+  ShortSplit s;
+  const int64_t rows = int64_t(B) * heads;
+  if (rows > most_groups) return s;
+  s.sequences.resize(B);
+  for (int b = 0; b < B; ++b) {
+    ShortSplit::Sequence& q = s.sequences[b];
+    for (int cls = 0; cls <= NC; ++cls) {
+      const int64_t tokens = cls == NC ? append_capacity : ntok[NC * b + cls];
+      if (tokens <= 0) continue;
+      const int c = std::min(cls, kFp16Class), step = tiles && c < 2 ? units_per_block : 1, iteration = one ? step : kIterUnits[c];
+      const int64_t units = (tokens + unit_tokens * step - 1) / (unit_tokens * step) * step;
+      if (units > 0xffff && cls < NC) return s;   // (units are 16-bit fields)
+      q.runs[q.n++] = {cls, int(units), step, int((units + iteration - 1) / iteration), 0};
+    }
+  }
+  auto waves_for = [&](int b, int most) {
+    const ShortSplit::Sequence& q = s.sequences[b];
+    int64_t n = 0;
+    for (int i = 0; i < q.n; ++i) n += (q.runs[i].iters + most - 1) / most;
+    return n;
+  };
+  const int64_t most_of_row = kShortStates / rep / W * W;
+  auto groups_for = [&](int most, bool limit) {
+    int64_t n = 0;
+    for (int b = 0; b < B; ++b) {
+      const int64_t row = std::max<int64_t>((waves_for(b, most) + W - 1) / W, 1);
+      n += limit && row > most_of_row ? most_groups + 1 : row * heads;
+    }
+    return n;
+  };
+  if (groups_for(most_iterations, true) > most_groups) return s;
+  auto fewest = [&](bool limit) {
+    int lo = 0, hi = most_iterations;
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) / 2;
+      (groups_for(mid, limit) <= most_groups ? hi : lo) = mid;
+    }
+    return hi;
+  };
+  int hi = fewest(true);
+  // few rows: too many workgroups of one for a merge in shared memory, and those it may have leave a part of the chip idle
+  if (hi > fewest(false) + (tiles ? 0 : 1)) return s;
+  // rows that one workgroup finishes need no second merge
+  int whole = 1;
+  while (whole <= hi + kShortMergeIterations && whole <= most_iterations && groups_for(whole, true) > rows) ++whole;
+  if (whole <= hi + kShortMergeIterations && whole <= most_iterations) hi = whole;
+  s.one = one, s.groups = int(groups_for(hi, true)), s.rows = int(rows);
+  for (int b = 0; b < B; ++b) {
+    ShortSplit::Sequence& q = s.sequences[b];
+    q.groups = int(std::max<int64_t>((waves_for(b, hi) + W - 1) / W, 1));
+    s.shared = s.shared || q.groups > 1;
+    int left = q.groups * W;
+    for (int i = 0; i < q.n; ++i) q.runs[i].parts = (q.runs[i].iters + hi - 1) / hi, left -= q.runs[i].parts;
+    // spare waves go to the run whose ranges are longest
+    for (; left > 0; --left) {
+      int best = -1;
+      for (int i = 0; i < q.n; ++i) {
+        const ShortSplit::Run &r = q.runs[i], *p = best < 0 ? nullptr : &q.runs[best];
+        if (r.iters > r.parts && (!p || int64_t(r.iters) * p->parts > int64_t(p->iters) * r.parts)) best = i;
+      }
+      if (best < 0) break;
+      ++q.runs[best].parts;
+    }
+  }
+  return s;
+}
+
+// Its records (by copies, as everything in the blob: the caller's buffer need not be aligned).
+static void write_short_split(const ShortSplit& s, const std::vector<int32_t>& ntok, const std::vector<int32_t>& blk_base, const std::vector<int32_t>& cap,
+                              const int32_t* seq_lens, int heads, int share, int rep, int append_blocks, char* recs, char* place) {
+  constexpr int NC = kNumClasses, W = kCuWaves;
+  for (int b = 0; b < int(s.sequences.size()); ++b) {
+    const ShortSplit::Sequence& q = s.sequences[b];
+    for (int h = 0; h < heads; ++h, recs += sizeof(ShortRec) * W * q.groups) {
+      for (int g = 0; g < q.groups; ++g, place += sizeof(ShortGroup)) {
+        const ShortGroup p = {b, (b * heads + h) * rep, seq_lens[b], uint32_t(g) | uint32_t(q.groups) << 8 | uint32_t(b * heads + h) << 20};
+        std::memcpy(place, &p, sizeof(p));
+      }
+      if (h > 0) {   // the same ranges of the next head's runs
+        const size_t bytes = sizeof(ShortRec) * W * q.groups;
+        std::memcpy(recs, recs - bytes, bytes);
+        if (h % share == 0)
+          for (int i = 0; i < q.groups * W; ++i) {
+            ShortRec r;
+            std::memcpy(&r, recs + i * sizeof(r), sizeof(r));
+            r.blk0 += r.cls == NC ? append_blocks : cap[NC * b + r.cls];
+            std::memcpy(recs + i * sizeof(r), &r, sizeof(r));
+          }
+        continue;
+      }
+      // range after range, each on another workgroup: the waves of one work on all classes, and SIMD mates (four waves apart) on different ones
+      int g = 0, w = 0;
+      auto put = [&](const ShortRec& r) {
+        std::memcpy(recs + (g * W + w) * sizeof(r), &r, sizeof(r));
+        if (++g == q.groups) g = 0, ++w;
+      };
+      for (int i = 0; i < q.n; ++i) {
+        const ShortSplit::Run& r = q.runs[i];
+        if (r.cls == NC) {
+          const int32_t inverse = int32_t((uint64_t(1) << 32) / r.parts + 1), blk0 = b * (heads / share) * append_blocks;
+          for (int k = 0; k < r.parts; ++k) put({r.cls, uint32_t(k) | uint32_t(r.parts) << 16, inverse, blk0});
+          continue;
+        }
+        const int each = r.units / r.step / r.parts, more = r.units / r.step % r.parts;   // (the first `more` ranges have one more)
+        const int32_t tokens = ntok[NC * b + r.cls], blk0 = blk_base[NC * b + r.cls];
+        uint32_t at = 0;
+        for (int k = 0; k < r.parts; ++k) {
+          const uint32_t end = at + (each + (k < more)) * r.step;
+          put({r.cls, at | end << 16, tokens, blk0});
+          at = end;
+        }
+      }
+      while (w < W) put({0, 0, 0, 0});   // no work
+    }
+  }
+}
+
 static inline int64_t align16(int64_t x) { return (x + 15) & ~int64_t(15); }
 
 }  // namespace cocktail
@@ -321,7 +476,7 @@ extern "C" int cocktail_plan_field(const void* plan_host, const char* name, int3
   COCKTAIL_FIELD(off_worker_rec) COCKTAIL_FIELD(off_group_rec) COCKTAIL_FIELD(off_pool_seg)
   COCKTAIL_FIELD(off_counters) COCKTAIL_FIELD(num_groups) COCKTAIL_FIELD(num_pool_segs)
   COCKTAIL_FIELD(append_blocks) COCKTAIL_FIELD(append_slices) COCKTAIL_FIELD(off_bh_off) COCKTAIL_FIELD(off_rq_items)
-  COCKTAIL_FIELD(ws_status_off)
+  COCKTAIL_FIELD(ws_status_off) COCKTAIL_FIELD(short_groups) COCKTAIL_FIELD(short_units) COCKTAIL_FIELD(off_short)
 #undef COCKTAIL_FIELD
 #undef COCKTAIL_ARRAY
   // constants of the layout that are not stored in the header
@@ -333,6 +488,9 @@ extern "C" int cocktail_plan_field(const void* plan_host, const char* name, int3
   if (std::strcmp(name, "sizeof_worker_rec") == 0) return *value = sizeof(WorkerRec), COCKTAIL_OK;
   if (std::strcmp(name, "sizeof_group_rec") == 0) return *value = sizeof(GroupRec), COCKTAIL_OK;
   if (std::strcmp(name, "sizeof_pool_seg") == 0) return *value = sizeof(PoolSeg), COCKTAIL_OK;
+  if (hd->short_groups > 0 && std::strcmp(name, "off_short_place") == 0) return *value = short_group_offset(*hd), COCKTAIL_OK;
+  if (hd->short_groups > 0 && std::strcmp(name, "off_short_counters") == 0) return *value = short_counters_offset(*hd), COCKTAIL_OK;
+  if (std::strcmp(name, "short_counter_stride_bytes") == 0) return *value = 4 * kShortCounterStride, COCKTAIL_OK;
   if (std::strcmp(name, "sizeof_rq_item") == 0) return *value = sizeof(RQItem), COCKTAIL_OK;
   return fail(COCKTAIL_EINVAL, "unknown plan field %s[%d]", name, index);
 }
@@ -652,6 +810,7 @@ static int make_plan(const cocktail_shape* shape, const int32_t* seq_lens, const
   std::vector<GroupRec> groups;
   std::vector<PoolSeg> psegs;
   {
+    groups.reserve((P + group_workers - 1) / group_workers), psegs.reserve(2 * groups.capacity());
     for (int w0 = 0, j = 0; w0 < P; w0 += group_workers, ++j) {
       const int w1 = w0 + group_workers < P ? w0 + group_workers : P;
       const int k = w1 - w0;
@@ -723,7 +882,7 @@ static int make_plan(const cocktail_shape* shape, const int32_t* seq_lens, const
         if (r == k - 1) {
           nb = Gp, snb = sGp;
         } else {
-          nb = block_at(c0 + own_q * (r + 1) + own_r * (r + 1) / k, sc);   // c0 + (cp - c0) (r + 1) / k without 128-bit arithmetic
+          nb = block_at(c0 + own_q * (r + 1) + int32_t(own_r) * (r + 1) / k, sc);   // c0 + (cp - c0) (r + 1) / k without 128-bit arithmetic
           snb = sc;
           if (nb > Gp) nb = Gp, snb = sGp;
           if (nb < prev) nb = prev, snb = sprev;
@@ -845,6 +1004,15 @@ static int make_plan(const cocktail_shape* shape, const int32_t* seq_lens, const
       }
   };
 
+  // ---- the split for short contexts ----
+  ShortSplit quick;
+  if (!tune.changed && packed < kNonTemporalMinBytes)
+    for (const bool one : {true, false}) {
+      if (quick.groups > 0 || (tiles && !one)) break;
+      quick = short_split(v_ct, B, Hw, D, append_capacity, wrep, one, std::min(num_workers, kChipWorkers) / kCuWaves);
+    }
+  if (quick.shared && quick.groups > npart) quick = ShortSplit();   // (their states share the workspace with those of the other split)
+
   // ---- sizes and blob layout ----
   PlanHeader hd;
   std::memset(&hd, 0, sizeof(hd));
@@ -890,6 +1058,13 @@ static int make_plan(const cocktail_shape* shape, const int32_t* seq_lens, const
   place(hd.off_rq_items, int64_t(sizeof(RQItem)) * num_items);
   off = (off + 127) & ~int64_t(127);
   place(hd.off_counters, int64_t(4 * kCounterStride) * NG);
+  if (quick.groups > 0) {
+    place(hd.off_short, int64_t(sizeof(ShortRec) * kCuWaves + sizeof(ShortGroup)) * quick.groups);
+    hd.short_groups = int16_t(quick.groups), hd.short_units = quick.one;
+    int32_t counters;
+    off = short_counters_offset(hd);
+    place(counters, int64_t(4 * kShortCounterStride) * quick.rows);
+  }
   if (too_large || off >= (int64_t(1) << 31)) return fail(COCKTAIL_EUNSUPPORTED, "plan larger than 2 GiB");
   hd.plan_bytes = off;
 
@@ -934,6 +1109,8 @@ static int make_plan(const cocktail_shape* shape, const int32_t* seq_lens, const
     put(hd.off_run_blocks, v_cap.data(), 4 * NC * size_t(B));
     put(hd.off_segments, segs.data(), sizeof(Segment) * size_t(S));
     put(hd.off_bh_off, bh_off.data(), 4 * bh_off.size());
+    if (quick.groups > 0)
+      write_short_split(quick, v_ct, v_blk_base, v_cap, seq_lens, Hw, share, wrep, append_blocks, p + hd.off_short, p + short_group_offset(hd));
     // Which worker id runs which range.  Worker ids are handed to the compute units in order
     // (round-robin over the XCDs), and when P fills the chip twice, worker i shares a SIMD with
     // worker i + P/2, which was dispatched later and loses every issue arbitration against it.

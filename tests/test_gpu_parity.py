@@ -142,6 +142,69 @@ def test_merge_of_many_and_of_few_partial_states(rep, head_dim, rows, blocks):
     ck.cocktail_decode_check(c.cache)
 
 
+def _short_counters(c):
+    """The counters of the split for short contexts inside the device copy of the plan."""
+    off, n = ck.cocktail_plan_field(c.plan, "off_short_counters"), c.w.batch * ck.cocktail_plan_field(c.plan, "work_heads")
+    return c.cache.plan_dev[off:off + ck.cocktail_plan_field(c.plan, "short_counter_stride_bytes") * n].view(torch.int32)
+
+
+@pytest.mark.parametrize("rep,head_dim,group", [(1, 128, 32), (1, 64, 64), (2, 64, 32), (3, 128, 64), (4, 128, 128), (5, 64, 64), (8, 128, 32), (16, 128, 64)])
+def test_short_contexts_in_one_launch(rep, head_dim, group):
+    """Rows on one workgroup, on a few, on more than the last of them folds in one go (one row of 30K tokens), several iterations per wave (32
+    workers), empty and one-token sequences: results, the same bits again, counters back at zero, and the two-launch path's results."""
+    for lens, workers, mix in (([300, 1, 0, 65], 2048, (0.25, 0.25, 0.25, 0.25)), ([1437, 888], 2048, (0.1, 0.3, 0.6)), ([30000], 2048, (0.05, 0.25, 0.7)),
+                               ([700, 650], 32, (0.2, 0.2, 0.3, 0.3)), ([2600, 2500], 32, (0.1, 0.3, 0.6))):
+        w = workloads.small(f"short_r{rep}", len(lens), rep, 1, lens, 32, group, mix=mix, head_dim=head_dim, seed_offset=300 + rep)
+        _announce(f"{w.name} d{head_dim} {lens} workers={workers}")
+        c = Case(w, workers=workers)
+        c.check_all()
+        ck.cocktail_decode_check(c.cache)
+        if ck.cocktail_plan_field(c.plan, "short_groups") == 0:
+            assert rep >= 5 and lens[0] > 700
+            continue
+        for _ in range(3):
+            out, lse = ck.cocktail_decode_attention(c.cache, c.q_dev)
+            assert torch.equal(out, c.out_dev) and torch.equal(lse, c.lse_dev)
+        assert not _short_counters(c).any()
+        ev = torch.cuda.Event(enable_timing=True)
+        ev.record()
+        ck.cocktail_decode_attention_marked(c.cache, c.q_dev, ev, out, lse)
+        ck.cocktail_decode_check(c.cache)
+        rows = torch.tensor([t > 0 for t in lens], device=out.device)
+        a, b = out[rows].double(), c.out_dev[rows].double()
+        assert ((a - b).abs().amax(dim=2) <= TOL * b.abs().amax(dim=2)).all() and (lse[rows] - c.lse_dev[rows]).abs().max() <= 1e-4 * 20
+
+
+@pytest.mark.parametrize("rep", [1, 4, 8])
+def test_stale_counter_of_a_short_context_is_reported(rep):
+    """A counter that is not zero when a call starts lets a workgroup merge too early.  States that are missing then cover no tokens: the row is NaN
+    and reported, or (if all had been written by then) right; no other row is touched, and cocktail_decode_check puts the counters back."""
+    w = workloads.small(f"stale_short{rep}", 2, 2 * rep, 2, [1437, 888], 32, 32, mix=(0.2, 0.4, 0.4), seed_offset=340 + rep)
+    c = Case(w, workers=2048)
+    counters = _short_counters(c)
+    groups = int(np.frombuffer(c.plan.blob.tobytes(), np.int32, 4, ck.cocktail_plan_field(c.plan, "off_short_place"))[3]) >> 8 & 0xfff
+    assert groups > 1
+    for stale in (1, groups - 1, groups, 3 * groups + 1):
+        counters[0] = stale                                  # of the first row
+        for _ in range(2):
+            out, lse = ck.cocktail_decode_attention(c.cache, c.q_dev)
+            torch.cuda.synchronize()
+        bad = torch.isnan(lse)
+        assert torch.equal(torch.isnan(out).all(dim=2), bad) and not bad[0, rep:].any() and not bad[1].any()
+        assert torch.equal(out[~bad], c.out_dev[~bad]) and torch.equal(lse[~bad], c.lse_dev[~bad])
+        if bad.any():
+            with pytest.raises(ck.CocktailError) as e:
+                ck.cocktail_decode_check(c.cache)
+            assert e.value.code == -6
+        else:
+            ck.cocktail_decode_check(c.cache)
+        assert not counters.any()
+        for _ in range(2):
+            out, lse = ck.cocktail_decode_attention(c.cache, c.q_dev)
+            ck.cocktail_decode_check(c.cache)
+            assert torch.equal(out, c.out_dev) and torch.equal(lse, c.lse_dev)
+
+
 @pytest.mark.parametrize("workers", [None, 1, 7, 64])
 def test_config1_all_heads(workers):
     _announce(f"config 1 workers={workers}")

@@ -850,3 +850,64 @@ def test_the_sets_of_a_kv_head_have_twin_workers(rep, sets, workers, capacity):
             other = pieces(recs[i + 8 * k])
             assert [x[0] for x in other] == [x[0] for x in first] and all(x[1] == k for x in other)
     assert work > 0
+
+
+@pytest.mark.parametrize("rep,head_dim", [(1, 128), (1, 64), (3, 128), (8, 128), (8, 64), (16, 128), (11, 64)])
+@pytest.mark.parametrize("lens,capacity,workers", [([1437, 888, 1], 0, 2048), ([0, 64, 63], 0, 2048), ([5000], 70, 2048), ([2049, 0], 600, 2048), ([15251, 300], 0, 1600), ([20000, 20011], 0, 288)])
+def test_the_split_for_short_contexts_covers_every_unit_once(rep, head_dim, lens, capacity, workers):
+    """Workgroups of eight waves on one row each: together the waves of a row's workgroups have every unit of its runs, whole blocks where
+    the kernel stages those, and every part of its appended tokens; no more waves than were asked for."""
+    w = workloads.small(f"short{rep}", len(lens), 2 * rep, 2, lens, 32, 32, mix=(0.2, 0.2, 0.3, 0.3), head_dim=head_dim, seed_offset=930 + rep)
+    shape = ck.make_shape(w.batch, w.num_q_heads, w.num_kv_heads, w.head_dim, w.chunk_size, w.group_size)
+    plan = ck.cocktail_plan(shape, w.seq_lens, np.concatenate(workloads.chunk_bits(w)), workers, append_capacity=capacity)
+    f = lambda n, i=0: ck.cocktail_plan_field(plan, n, i)
+    h, groups = _parse(plan), f("short_groups")
+    if h["work_rep"] > 4 and lens[0] > 15000 or rep == 11 and workers == 288:   # three staged blocks per wave at most; too many rows
+        assert groups == 0
+        return
+    assert 0 < 8 * groups <= workers and f("short_units") == (0 if workers == 288 and head_dim == 128 else 1)
+    recs = _arr(plan.blob, f("off_short"), np.int32, 4 * 8 * groups).reshape(groups, 8, 4)
+    recs = np.stack([recs[..., 0], recs[..., 1] & 0xffff, recs[..., 1].view(np.uint32) >> 16, recs[..., 2], recs[..., 3]], axis=2).astype(np.int64)
+    place = _arr(plan.blob, f("off_short_place"), np.int32, 4 * groups).reshape(groups, 4)
+    rows = w.batch * h["work_heads"]
+    counters = plan.blob[f("off_short_counters"):f("off_short_counters") + f("short_counter_stride_bytes") * rows]
+    assert counters.size == f("short_counter_stride_bytes") * rows and not counters.any()
+    assert f("off_short_counters") % 128 == 0 and f("off_short_place") == f("off_short") + 128 * groups
+    upb, heads, share = 1 if head_dim == 64 else 2, h["work_heads"], h["work_heads"] // 2
+    blk_base = _arr(plan.blob, f("off_blk_base"), np.int32, 4 * (w.batch + 1)).reshape(-1, 4)
+    g = 0
+    for b in range(w.batch):
+        for hd in range(heads):
+            n = place[g, 3] >> 8 & 0xfff
+            assert n >= 1 and g + n <= groups and (n == 1 or groups <= max(h["partials"], 1))
+            for k in range(n):
+                assert place[g + k].tolist() == [b, (b * heads + hd) * h["work_rep"], w.seq_lens[b], k | n << 8 | (b * heads + hd) << 20]
+            own = recs[g:g + n].reshape(-1, 5)
+            for c in range(4):
+                tokens = int(plan.class_tokens[b, c])
+                mine = sorted((int(x[1]), int(x[2])) for x in own if x[0] == c and x[1] < x[2])
+                blocks = -(-tokens // 64)
+                end = blocks * upb if h["work_rep"] > 4 and c < 2 else -(-tokens * upb // 64)
+                assert [x for r in mine for x in r] == ([0] + [x for r in mine[:-1] for x in (r[1], r[1])] + [end] if tokens else [])
+                for x in own:
+                    if x[0] == c and x[1] < x[2]:
+                        assert x[3] == tokens and x[4] == blk_base[b, c] + (hd // share) * blocks
+                        assert not (h["work_rep"] > 4 and c < 2) or (x[1] % upb == 0 and x[2] % upb == 0)
+            app = [x for x in own if x[0] == 4]
+            if capacity:
+                m = len(app)
+                assert sorted(int(x[1]) for x in app) == list(range(m)) and all(x[2] == m and x[4] == (2 * b + hd // share) * f("append_blocks") for x in app)
+                for units in (0, 1, 2, m, -(-capacity * upb // 64)):          # the kernel's division by multiplication
+                    each = units if m == 1 else ((units + m - 1) * (int(app[0][3]) & 0xffffffff)) >> 32
+                    assert each == -(-units // m)
+            else:
+                assert not app
+            g += n
+    assert g == groups
+
+
+def test_contexts_without_a_split_for_short_ones():
+    """Long contexts, more rows than workgroups, fewer than eight workers: the plan has only the split by workers."""
+    for w, workers in ((workloads.config(2), 2048), (workloads.small("rows", 40, 8, 8, [64] * 40, 64, 32), 2048), (workloads.config(1), 7)):
+        plan, _ = _plan(w, workers)
+        assert ck.cocktail_plan_field(plan, "short_groups") == 0
