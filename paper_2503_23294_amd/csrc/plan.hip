@@ -72,8 +72,12 @@ constexpr int kLayout = 0;
 // (8) 18.6 -> 16.4.  kIterUnits: the same up to 5K (3 iterations) 22.4 -> 20.2, 4 ragged at 80 q / 40 kv heads, 3.2K and 205 appended (6) 25.7 ->
 // 25.0.  With kIterUnits for all of them a wave with one unit runs the code of four: 10.3 instead of 8.9 on the first of these shapes.  Five heads and more,
 // where what is written and read per state is five to eight times as much: 3 x 1.4K at five heads (1 block) 10.3 -> 9.9, 4 x 1.4K at seven
-// (1) 10.9 -> 9.8, seven at head_dim 64 with appended tokens (3) 15.4 -> 13.0; with longer ranges 24.8K at six heads (6) 15.7 -> 18.9.
-constexpr int kShortUnits = 8, kShortIterations = 6, kShortUnitsTiles = 3;
+// (1) 10.9 -> 9.8, seven at head_dim 64 with appended tokens (3) 15.4 -> 13.0; 3 ragged up to 17K at five heads, 476 appended (4) 27.2 -> 22.4, 8 x
+// 7.3K at seven (4) 22.1 -> 19.5, 3 x 13.4K at six (4) 20.3 -> 19.8; with longer ranges 24.8K at six (6) 15.7 -> 18.9.  At head_dim 64, where a
+// block has half the bytes: 8 x 6.4K at eight heads (4) 16.6 -> 13.4, 3 x 23.4K at five (5) 21.0 -> 16.5, 3 ragged up to 49K (6) 18.8 -> 18.3.  Sets
+// of heads, which as twins find each other's blocks in the L2: 3 blocks, as four and more gain and lose (3 x 7K at sixteen heads 16.3 -> 16.5, 25K
+// 19.8 -> 22.2, 8 x 7.3K at ten (5) 19.0 -> 20.3, but 2 x 14K at twelve 17.9 -> 17.1).
+constexpr int kShortUnits = 8, kShortIterations = 6, kShortUnitsSets = 3, kShortUnitsTiles = 4, kShortUnitsTilesD64 = 6;
 // A row that one workgroup finishes is done 2 us after its waves, one of several after 3: worth this many iterations.
 constexpr int kShortMergeIterations = 1;
 // Relative speed of a worker of class [self] whose SIMD mate works on class [mate] (INT2, INT4, INT8, FP16), traced
@@ -314,10 +318,11 @@ struct ShortSplit {
   bool one = false;                       // an iteration is one unit (or staged block)
   bool shared = false;                    // some row has several workgroups
 };
-static ShortSplit short_split(const std::vector<int32_t>& ntok, int B, int heads, int head_dim, int append_capacity, int rep, bool one, int most_groups) {
+static ShortSplit short_split(const std::vector<int32_t>& ntok, int B, int heads, int head_dim, int append_capacity, int rep, int share, bool one,
+                              int most_groups) {
   constexpr int NC = kNumClasses, W = kCuWaves;
   const bool tiles = uses_tiles(rep);   // which stage whole blocks of INT2 and INT4
-  const int most_iterations = tiles ? kShortUnitsTiles : one ? kShortUnits : kShortIterations;
+  const int most_iterations = tiles ? share > 1 ? kShortUnitsSets : head_dim == 64 ? kShortUnitsTilesD64 : kShortUnitsTiles : one ? kShortUnits : kShortIterations;
   const int units_per_block = head_dim == 64 ? 1 : 2, unit_tokens = kTB / units_per_block;
   ShortSplit s;
   const int64_t rows = int64_t(B) * heads;
@@ -1009,7 +1014,7 @@ static int make_plan(const cocktail_shape* shape, const int32_t* seq_lens, const
   if (!tune.changed && packed < kNonTemporalMinBytes)
     for (const bool one : {true, false}) {
       if (quick.groups > 0 || (tiles && !one)) break;
-      quick = short_split(v_ct, B, Hw, D, append_capacity, wrep, one, std::min(num_workers, kChipWorkers) / kCuWaves);
+      quick = short_split(v_ct, B, Hw, D, append_capacity, wrep, share, one, std::min(num_workers, kChipWorkers) / kCuWaves);
     }
   if (quick.shared && quick.groups > npart) quick = ShortSplit();   // (their states share the workspace with those of the other split)
 

@@ -862,7 +862,8 @@ def test_the_split_for_short_contexts_covers_every_unit_once(rep, head_dim, lens
     plan = ck.cocktail_plan(shape, w.seq_lens, np.concatenate(workloads.chunk_bits(w)), workers, append_capacity=capacity)
     f = lambda n, i=0: ck.cocktail_plan_field(plan, n, i)
     h, groups = _parse(plan), f("short_groups")
-    if h["work_rep"] > 4 and lens[0] > 15000 or rep == 11 and workers == 288:   # three staged blocks per wave at most; too many rows
+    blocks_of_a_wave = h["work_rep"] > 4 and lens[0] > 15000 and (rep, head_dim, workers) != (8, 64, 288)
+    if blocks_of_a_wave or rep == 11 and workers == 288:   # more staged blocks per wave than allowed; too many rows
         assert groups == 0
         return
     assert 0 < 8 * groups <= workers and f("short_units") == (0 if workers == 288 and head_dim == 128 else 1)
