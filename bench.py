@@ -375,6 +375,10 @@ def main():
     head["frac_of_stream_read"] = gbps / stream_gbps
     paged = paged_reorder_quantize(args.config, (16, 256)) if args.other_configs and not args.decode_only else None
 
+    # a short context's call is one launch of its own kernel (the partial-state kernel ran in the marked calls only)
+    short_kernel = {"decode_attention_kernel": "decode_short_heads_kernel", "decode_quads_kernel": "decode_short_quads_kernel",
+                    "decode_tiles_kernel": "decode_short_tiles_kernel"}[head["kernel"]]
+
     result = {
         "metric": METRIC, "value": head["decode_us"], "unit": "us/layer", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": d["wall"] / args.steps * 1e3, "higher_is_better": False,
@@ -402,7 +406,7 @@ def main():
                      "traffic": traffic, "traffic_source": traffic_source,
                      "kernel": head["kernel"], "kernel_avg_us": head["partial_state_kernel_us"],
                      "whole_call": {"us": head["decode_us"], "achieved": gbps, "frac": gbps / HBM_PEAK_GBPS,
-                                    "kernels": head["kernel"] + " + decode_merge_kernel"}},
+                                    "kernels": short_kernel if ck.cocktail_plan_field(plan, "short_groups") > 0 else head["kernel"] + " + decode_merge_kernel"}},
         "configs": configs,
     }
     if d["cpu_baseline"] is not None:
