@@ -265,8 +265,10 @@ int cocktail_reorder_quantize_paged(const cocktail_shape* shape, const cocktail_
  * state records how many tokens it covers, the merge compares their sum with the
  * token count of the sequence, and a (sequence, query head) row that does not add
  * up gets NaN in out and lse and a non-zero status word (cocktail_decode_check);
- * the call after it finds the ticket counters at zero again, and cocktail_decode_check
- * puts those of the one launch back.  Which worker takes which pool piece differs from call to call, so
+ * the call after it finds the ticket counters at zero again.  The workgroups of the one
+ * launch notice a counter that was not zero, or that another call adds to, and put it back
+ * to zero: calls one behind the other are right whatever it was, and of calls that overlap
+ * a row may end up merged by nobody, which is NaN and reported like the above.  Which worker takes which pool piece differs from call to call, so
  * two calls on the same inputs agree to fp32 summation order, not bit for bit
  * (plans made with cocktail_plan_options::reproducible use no pools and are reproducible bit for bit, and so are
  * plans on matrix instructions whose waves serve five to eight query heads: Hq/Hkv of 5 to 8, and the larger

@@ -4,7 +4,7 @@
 // second launch, and its own chain over the partial states of the first.  Here a workgroup of eight waves works on one row (sequence,
 // work head) and merges its eight states in shared memory; a row that one workgroup holds is finished there, and otherwise
 // the last workgroup of a row merges what the others have written through to memory (a state per workgroup, counted by one
-// atomic each).  One launch instead of two.
+// atomic each: short_count.h).  One launch instead of two.
 //
 // Measured (us, two launches -> one; calls back to back, device time alone in brackets): 8 heads 2K 10.0 -> 7.5 [9.6 -> 7.5], 32 heads 5.3K
 // [12.9 -> 9.7], appended tokens at 1 to 2K [16.4 -> 9.4, 15.9 -> 11.0]; 64 random shapes 0.905 in the geometric mean.  Of the 7.5: launch, record
@@ -18,6 +18,7 @@
 
 #include "decode_heads_impl.h"
 #include "decode_tiles_impl.h"
+#include "short_count.h"
 
 namespace cocktail {
 
@@ -78,6 +79,25 @@ struct ShortStream {
   }
 };
 
+// Other XCDs see the store, and no L2 holds it back to write it later.
+template <class T>
+__device__ __forceinline__ void write_through(T* p, T x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// Counts this workgroup of a row (short_count.h); true if it is the one that merges.  For one lane.
+__device__ __forceinline__ bool short_arrives(__attribute__((address_space(1))) uint64_t* word, uint64_t step, uint32_t groups) {
+  auto add = [&] { return __hip_atomic_fetch_add(word, step, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+  auto to_zero = [&](uint64_t& from) { return __hip_atomic_compare_exchange_strong(word, &from, uint64_t(0), __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+  uint64_t all = groups * step, old = add();
+  if (__builtin_expect(old + step != all && !short_own(old, step), 0)) {
+    uint64_t now = old + step;
+    for (int i = 0; i < kShortHealTries && !short_own(now, step) && !to_zero(now); ++i);
+    old = add();
+  }
+  if (old + step != all) return false;
+  to_zero(all);
+  return true;
+}
+
 // A state without tokens.
 template <int HD>
 __device__ __forceinline__ void short_empty(char* slot, int rep, int lane) {
@@ -104,6 +124,8 @@ __device__ __forceinline__ void short_finish(char* states, const ShortWave& w, u
   const char* from = states;
   int count = kCuWaves;
   bool last = groups == 1;
+  const uint64_t step = short_step(reinterpret_cast<uint64_t>(__builtin_amdgcn_dispatch_ptr()));
+  auto* const word = reinterpret_cast<__attribute__((address_space(1))) uint64_t*>(reinterpret_cast<uint64_t>(counters + counter * kShortCounterStride));
 #pragma unroll 1
   while (true) {
     __syncthreads();
@@ -133,9 +155,6 @@ __device__ __forceinline__ void short_finish(char* states, const ShortWave& w, u
       }
     }
     if (last) {
-      // copied by all waves: a state that is read again without having been written covers no tokens
-      if (groups > 1)
-        for (int i = tid; i < groups * rep; i += kShortThreads) __builtin_amdgcn_raw_buffer_store_b32(0u, rs, i * STRIDE + 8, 0, kAuxDefault);
       if (!mine) return;
       kparams_t kp = kparams();
       const bool empty = !(l > 0.f), sound = covered == expected;
@@ -156,19 +175,20 @@ __device__ __forceinline__ void short_finish(char* states, const ShortWave& w, u
       const f4 hd = {m, l, __int_as_float(covered), 0.f};
       if (quad == 0) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, hd), rs, at, 0, kAuxWriteThrough);
       __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), rs, at + 16 + quad * 16, 0, kAuxWriteThrough);
+      if (index == 0) {   // until the row is merged
+        kparams_t kp = kparams();
+        const int row = w.group.qrow + head;
+        write_through(reinterpret_cast<uint64_t*>(kp->out + int64_t(row) * HD + quad * 4), uint64_t(0x7e007e007e007e00));
+        if (quad == 0) {
+          write_through(kp->status + row, short_pending(expected));
+          if (kp->lse) write_through(kp->lse + row, __builtin_nanf(""));
+        }
+      }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // written through: other XCDs see it
     if (rep * QUADS > 64) __syncthreads();             // by more than the first wave
     int* const flag = reinterpret_cast<int*>(states + kShortBytes<HD>) - 4;
-    if (w.wave == 0) {
-      // one more state of the row is in memory (only lane 0's offset is in range and performs the add)
-      uint32_t* const c = counters + counter * kShortCounterStride;
-      const rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(c, 0, 4, 0x00020000);
-      const int now = uni(__builtin_amdgcn_raw_ptr_buffer_atomic_add_i32(1, rc, w.lane * 4, 0, kAuxWriteThrough)) + 1;
-      const bool all = now >= groups && now % groups == 0;   // (more than there are: the counter was not zero)
-      if (all) __builtin_amdgcn_raw_ptr_buffer_atomic_add_i32(-groups, rc, w.lane * 4, 0, kAuxWriteThrough);
-      if (w.lane == 0) *flag = all;
-    }
+    if (tid == 0) *flag = short_arrives(word, step, groups);
     __syncthreads();
     if (!uni(*flag)) return;
     asm volatile("" ::: "memory");
