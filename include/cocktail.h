@@ -335,11 +335,12 @@ int cocktail_decode_attention_static(const cocktail_shape* shape, const void* q,
  * Diagnostic: waits for `stream`, then reads the status words the last decode call on `workspace` left
  * (the only entry point that synchronises and copies).  The softmax of Alg. 1's decode phase runs over the
  * concatenation of all classes, i.e. over every token of the sequence exactly once; the status word
- * of a (sequence, query head) is the number of tokens its partial states covered minus the sequence length.
+ * of a (sequence, query head) is the number of tokens its partial states covered minus the sequence length (a row
+ * that was not merged at all: one less than if they had covered none).
  *
  *   workspace  DEVICE, the workspace of that call; NULL = the built-in one of cocktail_decode_attention_static
  *
- * Counters of short contexts that are not zero are set to zero in plan_dev.  Returns COCKTAIL_OK if every word is zero, else COCKTAIL_ESTATE with a message naming the first bad row
+ * Nothing is written.  Returns COCKTAIL_OK if every word is zero, else COCKTAIL_ESTATE with a message naming the first bad row
  * (see cocktail_decode_attention for the causes).  Other errors: EINVAL, EHIP.
  */
 int cocktail_decode_check(const cocktail_shape* shape, const cocktail_cache* cache, const void* workspace,

@@ -8,7 +8,6 @@
 // 16x16x32 matrix instructions) instantiated per head_dim in their own translation units.
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
 #include <cmath>
 #include <cstdlib>
 #include <mutex>
@@ -414,20 +413,6 @@ extern "C" int cocktail_decode_check(const cocktail_shape* shape, const cocktail
     (void)hipGetLastError();
     return fail(COCKTAIL_EHIP, "reading the status of the last decode call failed: %s", hipGetErrorString(e));
   }
-  if (hd->short_groups > 0) {
-    // a counter that was not zero when a call started is not zero after it either
-    std::vector<uint32_t> counters(size_t(kShortCounterStride) * hd->batch * hd->work_heads);
-    char* const at = static_cast<char*>(cache->plan_dev) + short_counters_offset(*hd);
-    e = hipMemcpy(counters.data(), at, counters.size() * 4, hipMemcpyDeviceToHost);
-    if (e == hipSuccess && std::any_of(counters.begin(), counters.end(), [](uint32_t c) { return c != 0; })) {
-      std::fill(counters.begin(), counters.end(), 0u);
-      e = hipMemcpy(at, counters.data(), counters.size() * 4, hipMemcpyHostToDevice);
-    }
-    if (e != hipSuccess) {
-      (void)hipGetLastError();
-      return fail(COCKTAIL_EHIP, "looking at the counters of the plan failed: %s", hipGetErrorString(e));
-    }
-  }
   int bad = 0, first = -1;
   for (int i = 0; i < rows; ++i)
     if (status[i] != 0) {
@@ -436,7 +421,7 @@ extern "C" int cocktail_decode_check(const cocktail_shape* shape, const cocktail
     }
   if (bad)
     return fail(COCKTAIL_ESTATE, "the last decode call covered %d tokens too %s for sequence %d, query head %d (%d of %d rows "
-                "affected; their out and lse are NaN): the ticket counters in plan_dev were not zero when the call "
+                "affected; their out and lse are NaN): the counters in plan_dev were not zero when the call "
                 "started, calls on this cache overlapped, or plan_dev was modified; upload the plan again",
                 status[first] < 0 ? -status[first] : status[first], status[first] < 0 ? "few" : "many",
                 first / hd->num_q_heads, first % hd->num_q_heads, bad, rows);
