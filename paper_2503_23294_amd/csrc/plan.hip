@@ -152,7 +152,7 @@ struct Tuning {
   int min_pool_blocks = kMinBlocksPerWorkerForPool;   // COCKTAIL_MIN_POOL_BLOCKS  1..4096
   double pair_table[kNumClasses][kNumClasses];        // COCKTAIL_PAIR_TABLE="16 numbers, row = own class": replaces
   bool pair_table_set = false;                        // kPairSpeed, and switches the correction on for the matrix kernel too
-  bool changed = false;                 // any of these is set: no split for short contexts, which knows none of them
+  bool changed = false;                 // any of these is set to a value it takes: no split for short contexts, which knows none of them
 };
 
 static Tuning read_tuning() {
@@ -160,11 +160,12 @@ static Tuning read_tuning() {
   for (int a = 0; a < kNumClasses; ++a)
     for (int b = 0; b < kNumClasses; ++b) t.pair_table[a][b] = kPairSpeed[a][b];
   // (one look for all of them: sixteen searches of the environment took 3 us of a short context's 11)
+  bool any = false;
   for (char** e = environ; e && *e; ++e)
     if (std::strncmp(*e, "COCKTAIL_", 9) == 0)
       for (const char* name : {"COST_WEIGHTS=", "POOL_PERCENT=", "GROUP_WORKERS=", "PAIR_SPEED=", "LAYOUT=", "PAIR_MODE=", "MIN_POOL_BLOCKS=", "PAIR_TABLE="})
-        t.changed = t.changed || std::strncmp(*e + 9, name, std::strlen(name)) == 0;
-  if (!t.changed) return t;
+        any = any || std::strncmp(*e + 9, name, std::strlen(name)) == 0;
+  if (!any) return t;
   if (const char* e = std::getenv("COCKTAIL_COST_WEIGHTS")) {
     long a = 0, b = 0, c = 0, d = 0;
     const int n = std::sscanf(e, "%ld,%ld,%ld,%ld", &a, &b, &c, &d);
@@ -172,11 +173,12 @@ static Tuning read_tuning() {
       t.weight[0] = a, t.weight[1] = b, t.weight[2] = c, t.weight[3] = d, t.weight_set = true;
     else if (n == 3 && a > 0 && b > 0 && c > 0)
       t.weight[0] = a, t.weight[1] = b, t.weight[3] = c, t.weight_set = true;
+    t.changed = t.weight_set;
   }
-  auto int_knob = [](const char* name, int lo, int hi, int& out) {
+  auto int_knob = [&](const char* name, int lo, int hi, int& out) {
     if (const char* e = std::getenv(name)) {
       const int v = std::atoi(e);
-      if (v >= lo && v <= hi) out = v;
+      if (v >= lo && v <= hi) out = v, t.changed = true;
     }
   };
   if (const char* e = std::getenv("COCKTAIL_PAIR_TABLE")) {
@@ -195,7 +197,7 @@ static Tuning read_tuning() {
     for (int i = 0; ok && i < 16; ++i) ok = v[i] > 0.25 && v[i] < 4.0;
     if (ok) {
       for (int i = 0; i < 16; ++i) t.pair_table[i / 4][i % 4] = v[i];
-      t.pair_table_set = true;
+      t.pair_table_set = t.changed = true;
     }
   }
   int ps = 1;

@@ -912,3 +912,16 @@ def test_contexts_without_a_split_for_short_ones():
     for w, workers in ((workloads.config(2), 2048), (workloads.small("rows", 40, 8, 8, [64] * 40, 64, 32), 2048), (workloads.config(1), 7)):
         plan, _ = _plan(w, workers)
         assert ck.cocktail_plan_field(plan, "short_groups") == 0
+
+
+@pytest.mark.parametrize("name,refused,taken", [
+    ("COST_WEIGHTS", "64,0,64,64", "64,64,64,64"), ("POOL_PERCENT", "101", "10"), ("GROUP_WORKERS", "0", "4"), ("PAIR_SPEED", "2", "0"),
+    ("LAYOUT", "-1", "1"), ("PAIR_MODE", "4", "2"), ("MIN_POOL_BLOCKS", "0", "2"), ("PAIR_TABLE", "1,1", ",".join(["1.1"] * 16))])
+def test_a_tuning_value_that_is_refused_leaves_the_split_for_short_contexts(name, refused, taken, monkeypatch):
+    """The split knows none of the tuning variables and makes way for the one by workers where one is set, not where its value is refused."""
+    w = workloads.config(1)
+    groups = ck.cocktail_plan_field(_plan(w, 2048)[0], "short_groups")
+    assert groups > 0
+    for value, expected in ((refused, groups), (taken, 0)):
+        monkeypatch.setenv("COCKTAIL_" + name, value)
+        assert ck.cocktail_plan_field(_plan(w, 2048)[0], "short_groups") == expected
