@@ -110,7 +110,7 @@ int check_append(const cocktail_shape* shape, const void* k_new, const void* v_n
   if (int rc = check_shape(shape)) return rc;
   if (!cache || !cache->plan_host) return fail(COCKTAIL_EINVAL, "cache or its plan is NULL");
   const PlanHeader* hd = static_cast<const PlanHeader*>(cache->plan_host);
-  if (hd->magic != kPlanMagic || hd->version != kPlanVersion)
+  if (hd->magic != kPlanMagic || !known_version(hd->version))
     return fail(COCKTAIL_EINVAL, "plan_host is not a plan written by this library version");
   if (hd->batch != shape->batch || hd->num_kv_heads != shape->num_kv_heads || hd->head_dim != shape->head_dim ||
       hd->chunk_size != shape->chunk_size || hd->group_size != shape->group_size ||
@@ -172,7 +172,7 @@ extern "C" int cocktail_fold_appended(const cocktail_shape* shape, const cocktai
   if (!new_plan_host || !new_plan_dev) return fail(COCKTAIL_EINVAL, "new_plan_host and new_plan_dev must not be NULL");
   const PlanHeader* h0 = static_cast<const PlanHeader*>(cache->plan_host);
   const PlanHeader* h1 = static_cast<const PlanHeader*>(new_plan_host);
-  if (h0->magic != kPlanMagic || h0->version != kPlanVersion || h1->magic != kPlanMagic || h1->version != kPlanVersion)
+  if (h0->magic != kPlanMagic || !known_version(h0->version) || h1->magic != kPlanMagic || !known_version(h1->version))
     return fail(COCKTAIL_EINVAL, "plan_host or new_plan_host is not a plan written by this library version");
   for (const PlanHeader* hd : {h0, h1})
     if (hd->batch != shape->batch || hd->num_kv_heads != shape->num_kv_heads || hd->head_dim != shape->head_dim ||

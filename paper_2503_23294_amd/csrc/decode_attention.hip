@@ -92,7 +92,7 @@ __global__ __launch_bounds__(kMergeThreads) void decode_merge_kernel(const int32
   const int expected = context + min(max(appended, 0), capacity);
   // every worker has drawn its last ticket: put the counters back to zero for the next call
   if (bh == 0 && r == 0 && part == 0)
-    for (int i = tid; i < prm->num_groups; i += kMergeThreads) prm->counters[i * kCounterStride] = 0u;
+    for (int i = tid; i < prm->num_groups; i += kMergeThreads) prm->counters[i * kPoolCounterStride] = 0u;
   sched_fence();
   float m = -INFINITY, l = 0.f;
   f4 o = {0.f, 0.f, 0.f, 0.f};
@@ -225,7 +225,7 @@ int check_plan_matches(const cocktail_shape* shape, const cocktail_cache* cache,
   if (int rc = check_shape(shape)) return rc;
   if (!cache || !cache->plan_host || !cache->plan_dev) return fail(COCKTAIL_EINVAL, "cache or its plan is NULL");
   const PlanHeader* hd = static_cast<const PlanHeader*>(cache->plan_host);
-  if (hd->magic != kPlanMagic || hd->version != kPlanVersion)
+  if (hd->magic != kPlanMagic || !known_version(hd->version))
     return fail(COCKTAIL_EINVAL, "plan_host is not a plan written by this library version");
   if (hd->batch != shape->batch || hd->num_kv_heads != shape->num_kv_heads || hd->head_dim != shape->head_dim ||
       hd->chunk_size != shape->chunk_size || hd->group_size != shape->group_size ||
@@ -253,7 +253,7 @@ int decode_enqueue(const cocktail_shape* shape, const PlanHeader* hd, const void
   p.psegs = reinterpret_cast<const PoolSeg*>(pd + hd->off_pool_seg);
   p.counters = reinterpret_cast<uint32_t*>(pd + hd->off_counters);
   p.seq_len = reinterpret_cast<const int32_t*>(pd + hd->off_seq_len);
-  p.num_groups = hd->num_groups;
+  p.num_groups = hd->num_pool_segs > 0 ? hd->num_groups : 0;   // whose counters the merge puts back
   p.num_workers = hd->num_workers;
   p.k_app = p.v_app = nullptr;
   p.num_appended = 0, p.app_blocks = hd->append_blocks;

@@ -32,7 +32,7 @@ struct DecodeParams {
   const WorkerRec* recs;    // [num_workers]
   const Segment* segs;      // [num_segments]
   const PoolSeg* psegs;     // [num_pool_segs]
-  uint32_t* counters;       // [num_groups * kCounterStride] ticket counters, zero between calls
+  uint32_t* counters;       // [num_groups * kPoolCounterStride] ticket counters, zero between calls
   const int32_t* bh_off;    // [B*Hkv + 1] (sequence, kv head) owns the partial ids bh_off[bh] .. bh_off[bh+1]-1
   const int32_t* seq_len;   // [B] context tokens per sequence
   int32_t* status;          // [B*Hq] written by the merge: 0, or how far the tokens covered by the partials are off
@@ -45,7 +45,7 @@ struct DecodeParams {
   _Float16* out;            // [B][Hq][head_dim]
   float* lse;               // [B][Hq] or NULL
   float scale_log2;         // sm_scale * log2(e)
-  int32_t rep, num_q_heads, num_kv_heads, num_groups;   // rep, num_kv_heads: of the work split (PlanHeader::work_rep, work_heads)
+  int32_t rep, num_q_heads, num_kv_heads, num_groups;   // rep, num_kv_heads: of the work split (PlanHeader::work_rep, work_heads); num_groups: 0 without pools
   int32_t kv_share;         // work heads that share one kv head of the cache (1, or Hq / Hkv with one wave per query head)
   int32_t num_workers;      // waves behind these serve the appended tokens, app_slices per (sequence, kv head)
   int32_t num_appended, app_blocks;   // tokens appended to every sequence (used if `appended` is NULL), blocks per (b, kv head)
@@ -434,7 +434,7 @@ __device__ __forceinline__ int iter_units(int cls) { return cls == 0 ? J2 : cls 
 // The add is a buffer atomic over a 4-byte resource with one offset per lane, so only lane 0 is in
 // range and performs it (out-of-range lanes are dropped by the bounds check): no divergent branch.
 __device__ __forceinline__ uint32_t request_ticket(int counter, int lane) {
-  uint32_t* c = kparams()->counters + counter * kCounterStride;
+  uint32_t* c = kparams()->counters + counter * kPoolCounterStride;
   const rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(c, 0, 4, 0x00020000);
   return uint32_t(__builtin_amdgcn_raw_ptr_buffer_atomic_add_i32(1, rs, lane * 4, 0, /*sc1: device scope*/ 16));
 }

@@ -12,7 +12,9 @@
 namespace cocktail {
 
 constexpr uint32_t kPlanMagic = 0x434b544cu;  // "CKTL"
-constexpr uint32_t kPlanVersion = 15;
+constexpr uint32_t kPlanVersion = 16;
+// (15 keeps its ticket counters a line apart in plans without pools too, where no kernel looks at them)
+constexpr bool known_version(uint32_t version) { return version == 15 || version == kPlanVersion; }
 constexpr int kTB = 64;                        // tokens per block
 constexpr int kNumClasses = 4;                 // INT2, INT4, INT8, FP16: the order of the concatenation
 constexpr int kFp16Class = kNumClasses - 1;
@@ -48,7 +50,11 @@ constexpr int kCuWaves = 8, kChipWorkers = 256 * kCuWaves, kSimds = kChipWorkers
 __host__ __device__ inline int workgroup_waves(int num_workers, int append_slices) {
   return num_workers == kChipWorkers && append_slices == 0 ? kCuWaves : 1;
 }
-constexpr int kCounterStride = 32;             // uint32 slots between two pool counters (one 128-byte line each)
+// uint32 slots between two ticket counters: a 128-byte line each where there are pools (half a line each: ragged contexts up to 130K, four heads
+// per kv head, 205.1 -> 205.25 us per call; 128K, 40 heads 102.4 -> 102.5).  In plans without pools nobody draws a ticket, and a line each would be an
+// eighth of what a request uploads (2 contexts up to 32K, 8 kv heads: 485 -> 428 KB).
+constexpr int kPoolCounterStride = 32, kCounterStride = 4;
+inline int counter_stride(int num_pool_segs) { return num_pool_segs > 0 ? kPoolCounterStride : kCounterStride; }
 // Query heads per kv head for which one wave serves all of them with matrix instructions and V is stored in token quads.
 constexpr int kQuadMinRep = 2, kQuadMaxRep = 8;
 __host__ __device__ inline bool uses_token_quads(int rep) { return rep >= kQuadMinRep && rep <= kQuadMaxRep; }
@@ -105,7 +111,7 @@ struct GroupRec {
   int32_t pseg0;             // index of its first PoolSeg
   int32_t nps;               // number of PoolSegs (<= kMaxPoolSegments)
   int32_t nworkers;
-  int32_t counter;           // index of its ticket counter (times kCounterStride)
+  int32_t counter;           // index of its ticket counter (times counter_stride)
   int32_t pad[3];
 };
 static_assert(sizeof(GroupRec) == 32, "GroupRec layout");
@@ -190,7 +196,7 @@ struct PlanHeader {
   int32_t off_worker_rec;     // WorkerRec [num_workers]
   int32_t off_group_rec;      // GroupRec [num_groups]
   int32_t off_pool_seg;       // PoolSeg [num_pool_segs]
-  int32_t off_counters;       // uint32 [num_groups * kCounterStride], zero; the only part kernels write
+  int32_t off_counters;       // uint32 [num_groups * counter_stride], zero; the only part kernels write
   int32_t num_groups, num_pool_segs;
   int32_t append_blocks;      // blocks per (sequence, kv head) in the append buffers
   int32_t off_bh_off;         // int32 [B*Hkv + 1] prefix: (b, kv head) owns partial ids bh_off[bh] .. bh_off[bh+1]-1;

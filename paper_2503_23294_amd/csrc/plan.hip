@@ -457,7 +457,7 @@ extern "C" int cocktail_version(void) { return (0 << 16) | 5; }
 extern "C" int cocktail_plan_field(const void* plan_host, const char* name, int32_t index, int64_t* value) {
   if (!plan_host || !name || !value) return fail(COCKTAIL_EINVAL, "plan_host, name and value must not be NULL");
   const PlanHeader* hd = static_cast<const PlanHeader*>(plan_host);
-  if (hd->magic != kPlanMagic || hd->version != kPlanVersion)
+  if (hd->magic != kPlanMagic || !known_version(hd->version))
     return fail(COCKTAIL_EINVAL, "plan_host is not a plan written by this library version");
 #define COCKTAIL_FIELD(f)                                                                            \
   if (std::strcmp(name, #f) == 0) {                                                                  \
@@ -487,7 +487,7 @@ extern "C" int cocktail_plan_field(const void* plan_host, const char* name, int3
 #undef COCKTAIL_FIELD
 #undef COCKTAIL_ARRAY
   // constants of the layout that are not stored in the header
-  if (std::strcmp(name, "counter_stride_bytes") == 0) return *value = 4 * kCounterStride, COCKTAIL_OK;
+  if (std::strcmp(name, "counter_stride_bytes") == 0) return *value = 4 * counter_stride(hd->num_pool_segs), COCKTAIL_OK;
   if (std::strcmp(name, "partial_header_floats") == 0) return *value = kPartialFloats, COCKTAIL_OK;
   if (std::strcmp(name, "iter_units") == 0 && index >= 0 && index < kNumClasses) return *value = kIterUnits[index], COCKTAIL_OK;
   if (std::strcmp(name, "workgroup_waves") == 0) return *value = workgroup_waves(hd->num_workers, hd->append_slices), COCKTAIL_OK;
@@ -1067,7 +1067,7 @@ static int make_plan(const cocktail_shape* shape, const int32_t* seq_lens, const
   place(hd.off_pool_seg, int64_t(sizeof(PoolSeg)) * NPS);
   place(hd.off_rq_items, int64_t(sizeof(RQItem)) * num_items);
   off = (off + 127) & ~int64_t(127);
-  place(hd.off_counters, int64_t(4 * kCounterStride) * NG);
+  place(hd.off_counters, int64_t(4 * counter_stride(NPS)) * NG);
   if (quick.groups > 0) {
     place(hd.off_short, int64_t(sizeof(ShortRec) * kCuWaves + sizeof(ShortGroup)) * quick.groups);
     hd.short_groups = int16_t(quick.groups), hd.short_units = quick.one;

@@ -499,7 +499,7 @@ int plan_of(const cocktail_shape* shape, const cocktail_cache* cache, const Plan
   if (int rc = check_shape(shape)) return rc;
   if (!cache || !cache->plan_host || !cache->plan_dev) return fail(COCKTAIL_EINVAL, "cache or its plan is NULL");
   const PlanHeader* hd = static_cast<const PlanHeader*>(cache->plan_host);
-  if (hd->magic != kPlanMagic || hd->version != kPlanVersion)
+  if (hd->magic != kPlanMagic || !known_version(hd->version))
     return fail(COCKTAIL_EINVAL, "plan_host is not a plan written by this library version");
   if (hd->batch != shape->batch || hd->num_kv_heads != shape->num_kv_heads || hd->head_dim != shape->head_dim ||
       hd->chunk_size != shape->chunk_size || hd->group_size != shape->group_size ||

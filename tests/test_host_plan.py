@@ -925,3 +925,20 @@ def test_a_tuning_value_that_is_refused_leaves_the_split_for_short_contexts(name
     for value, expected in ((refused, groups), (taken, 0)):
         monkeypatch.setenv("COCKTAIL_" + name, value)
         assert ck.cocktail_plan_field(_plan(w, 2048)[0], "short_groups") == expected
+
+
+def test_plans_without_pools_carry_no_lines_of_counters_and_older_ones_are_taken():
+    """Counters nobody draws from take little of what a request uploads; a plan written with a line for each (version 15) is still one."""
+    for w, pools in ((workloads.config(1), False), (workloads.config(5), True)):
+        plan, _ = _plan(w, 2048)
+        f = lambda n: ck.cocktail_plan_field(plan, n)
+        assert (f("num_pool_segs") > 0) == pools and f("counter_stride_bytes") == (128 if pools else 16)
+        head = plan.blob[:8].view(np.uint32)
+        assert head[1] == 16
+        for version, known in ((15, True), (14, False), (17, False), (16, True)):
+            head[1] = version
+            if known:
+                assert f("batch") == w.batch
+            else:
+                with pytest.raises(ck.CocktailError):
+                    f("batch")
