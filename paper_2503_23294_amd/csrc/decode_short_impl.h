@@ -270,9 +270,10 @@ __global__ __launch_bounds__(kShortThreads) __attribute__((amdgpu_waves_per_eu(2
   short_finish<HD>(shared, w, counters_of(place, counters_offset), rep);
 }
 
-// five to eight
-template <int HD, int G, bool INT8, bool ONE>
+// five to eight: a staged block per iteration only
+template <int HD, int G, bool INT8>
 __global__ __launch_bounds__(kShortThreads) __attribute__((amdgpu_waves_per_eu(2))) void decode_short_tiles_kernel(COCKTAIL_SHORT_ARGS) {
+  constexpr bool ONE = true;
   COCKTAIL_SHORT_BEGIN(true)
   char* const lds = shared + kCuWaves * rep * ((HD + kPartialFloats) * 4) + w.wave * kTileLds;   // (free when the states of a row come in)
   if (cur.nu <= 0) short_empty<HD>(dest.p, rep, w.lane);
@@ -290,8 +291,9 @@ hipError_t launch_decode_short(const DecodeParams& p, const ShortRec* recs, cons
                                int groups, hipStream_t st) {
   short_kernel kern = nullptr;
   const bool tiles = quads && uses_tiles(p.rep);
+  if (tiles && !one) return hipErrorInvalidValue;   // not a split the planner makes
 #define COCKTAIL_PICK3(G, I8, ONE)                                       \
-  kern = tiles ? decode_short_tiles_kernel<HD, G, I8, ONE>               \
+  kern = tiles ? decode_short_tiles_kernel<HD, G, I8>                    \
          : quads ? decode_short_quads_kernel<HD, G, I8, ONE> : decode_short_heads_kernel<HD, G, I8, ONE>
 #define COCKTAIL_PICK2(G, I8)            \
   if (one) COCKTAIL_PICK3(G, I8, true);  \

@@ -54,3 +54,15 @@ def test_wait_states_and_m0_of_the_loads_to_shared_memory(tmp_path):
                 if prev.startswith("v_"):
                     assert not _scalars(prev.split(None, 1)[1].split(",")[0]) & uses, (prev, line)
     assert loads > 0
+
+
+def test_no_kernel_for_short_contexts_that_no_plan_asks_for():
+    """Five to eight heads per wave take a staged block per iteration and nothing else; the others one unit or several: group sizes 32, 64 and (at
+    head_dim 128) 128, with and without INT8."""
+    tool = shutil.which("llvm-nm") or next((p for p in ("/opt/rocm/llvm/bin/llvm-nm",) if os.path.exists(p)), None) or shutil.which("nm")
+    if not tool:
+        pytest.skip("nm is needed to list the kernels")
+    names = subprocess.run([tool, "-C", _lib.LIB_PATH], check=True, capture_output=True, text=True).stdout
+    kernels = set(re.findall(r"cocktail::(?:__device_stub__)?(decode_short_\w+_kernel<[^>]*>)", names))
+    count = {kind: sum(k.startswith(f"decode_short_{kind}_") for k in kernels) for kind in ("heads", "quads", "tiles")}
+    assert count == {"heads": 5 * 2 * 2, "quads": 5 * 2 * 2, "tiles": 5 * 2}
