@@ -42,10 +42,11 @@ template hipError_t launch_decode_heads<128>(const DecodeParams&, int, bool, boo
 // status array.
 constexpr int kSplitMergeRows = 128;
 constexpr int kMergeThreads = 512, kMergeWaves = kMergeThreads / 64;
-constexpr int kMergeParamsOffset = 32;   // of the DecodeParams in the merge's kernel argument segment
+#define COCKTAIL_MERGE_ARGS const int32_t *bh_off, const float *ws, const int32_t *seq_len, int32_t rep, int32_t num_kv_heads, DecodeParams
+typedef void (*merge_kernel)(COCKTAIL_MERGE_ARGS);
+constexpr int kMergeParamsOffset = LastArgument<merge_kernel>::offset();   // of the DecodeParams in the merge's kernel argument segment
 template <int D, int PARTS>
-__global__ __launch_bounds__(kMergeThreads) void decode_merge_kernel(const int32_t* bh_off, const float* ws, const int32_t* seq_len,
-                                                                     int32_t rep, int32_t num_kv_heads, DecodeParams) {
+__global__ __launch_bounds__(kMergeThreads) void decode_merge_kernel(COCKTAIL_MERGE_ARGS) {
   constexpr int CH = D / PARTS, QUADS = CH / 4, SLICES = kMergeThreads / QUADS;
   static_assert(QUADS >= 8 && QUADS <= 32, "the slices of a wave are 8, 16 or 32 lanes apart");
   constexpr int STRIDE = D + kPartialFloats;
@@ -343,7 +344,7 @@ int decode_enqueue(const cocktail_shape* shape, const PlanHeader* hd, const void
     if (ev != hipSuccess) return fail(COCKTAIL_EHIP, "recording the event between the two kernels failed: %s", hipGetErrorString(ev));
   }
   const bool split = int64_t(hd->batch) * hd->num_q_heads <= kSplitMergeRows;
-  auto merge = [&](auto kernel, int parts) {
+  auto merge = [&](merge_kernel kernel, int parts) {
     return launch(kernel, dim3(hd->batch * hd->work_heads, hd->work_rep, parts), dim3(kMergeThreads), st, p.bh_off, p.ws, p.seq_len, p.rep, p.num_kv_heads, p);
   };
   const hipError_t e = shape->head_dim == 64 ? split ? merge(decode_merge_kernel<64, 2>, 2) : merge(decode_merge_kernel<64, 1>, 1)

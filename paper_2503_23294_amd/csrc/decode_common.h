@@ -60,7 +60,18 @@ struct DecodeParams {
 // are in scalar registers when a wave starts (build.py: kernarg preloading); the rest is read from memory (kparams).
 #define COCKTAIL_WORKER_ARGS const WorkerRec *recs, int32_t num_workers, int32_t num_q_heads, int32_t rep, DecodeParams
 typedef void (*worker_kernel)(COCKTAIL_WORKER_ARGS);
-constexpr int kParamsOffset = 24;   // of the DecodeParams in the kernel argument segment
+// Where the last argument of a kernel is in its argument segment (which is laid out like a struct of the arguments).
+template <class>
+struct LastArgument;
+template <class... A>
+struct LastArgument<void (*)(A...)> {
+  static constexpr int offset() {
+    size_t at = 0, last = 0;
+    ((last = (at + alignof(A) - 1) / alignof(A) * alignof(A), at = last + sizeof(A)), ...);
+    return int(last);
+  }
+};
+constexpr int kParamsOffset = LastArgument<worker_kernel>::offset();   // of the DecodeParams in the kernel argument segment
 
 // The kernel keeps almost everything that describes its work in scalar registers.  To leave room
 // there, the kernel arguments are not held in registers for the whole kernel: code that needs one

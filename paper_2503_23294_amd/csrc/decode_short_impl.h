@@ -27,6 +27,7 @@ constexpr int kAuxWriteThrough = 16;   // sc1: device scope
 // The arguments are laid out like those of the other decode kernels (kparams).
 #define COCKTAIL_SHORT_ARGS const ShortRec *recs, const ShortGroup *place, int32_t rep, int32_t counters_offset, DecodeParams
 typedef void (*short_kernel)(COCKTAIL_SHORT_ARGS);
+static_assert(LastArgument<short_kernel>::offset() == kParamsOffset, "kparams finds them where the other kernels have them");
 
 // Shared memory for the states of a row (in whole batches of the fold), those of the slices they are folded in where they are more than
 // kShortDirect, and a flag.
