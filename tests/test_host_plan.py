@@ -942,3 +942,15 @@ def test_plans_without_pools_carry_no_lines_of_counters_and_older_ones_are_taken
             else:
                 with pytest.raises(ck.CocktailError):
                     f("batch")
+
+
+@pytest.mark.parametrize("rep,head_dim,lens,capacity,taken", [
+    (16, 128, [15584], 0, False), (16, 128, [14346, 896], 0, False), (12, 128, [11113], 0, False), (10, 128, [9891, 2875, 11508], 0, False),
+    (16, 128, [10250, 3416], 0, True), (16, 128, [6000], 0, True), (16, 128, [14586], 362, True), (16, 64, [11181], 0, True), (8, 128, [9600, 9600], 0, True), (10, 128, [5000, 5000, 5000], 0, True)])
+def test_long_rows_of_sets_of_heads_keep_two_launches(rep, head_dim, lens, capacity, taken):
+    """Sets of heads at head_dim 128: more than eight workgroups per row whose waves have two staged blocks and more lose by one launch while they do not fill the chip.  One block per
+    wave, appended tokens, head_dim 64, no sets, shorter rows gain."""
+    w = workloads.small(f"sets{rep}", len(lens), 8 * rep, 8, lens, 32, 64, mix=(0.15, 0.35, 0.5), head_dim=head_dim, seed_offset=970 + rep)
+    shape = ck.make_shape(w.batch, w.num_q_heads, w.num_kv_heads, w.head_dim, w.chunk_size, w.group_size)
+    plan = ck.cocktail_plan(shape, w.seq_lens, np.concatenate(workloads.chunk_bits(w)), 2048, append_capacity=capacity)
+    assert (ck.cocktail_plan_field(plan, "short_groups") > 0) == taken
