@@ -254,8 +254,8 @@ int cocktail_reorder_quantize_paged(const cocktail_shape* shape, const cocktail_
  * Decode side of Alg. 1: out[b,h] = softmax(sm_scale * q[b,h] . K^_b^T) V^_b over
  * all tokens of all classes of sequence b, K^/V^ being the dequantized
  * (or raw fp16) rows of kv head h / (Hq/Hkv).  Two launches: partial states per
- * worker, then the exact merge.  Contexts so short that a worker has a few 32-token units at most take one launch: the workgroups of a
- * (sequence, kv head) count themselves in the device copy of the plan, and the last one merges.  Workers that finish their own share early take
+ * worker, then the exact merge.  Short contexts take one launch (plans whose cocktail_plan_field "short_groups" is not 0): the workgroups of a
+ * (sequence, set of query heads that a wave serves) count themselves in the device copy of the plan, and the last one merges.  Workers that finish their own share early take
  * further pieces from a pool shared by a few neighbouring workers; the pools are
  * handed out through ticket counters that live in the device copy of the plan as well.
  * All these counters are zero in the blob cocktail_plan writes and every call leaves

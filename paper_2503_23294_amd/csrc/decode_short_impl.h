@@ -7,8 +7,9 @@
 // atomic each: short_count.h).  One launch instead of two.
 //
 // Measured (us, two launches -> one; calls back to back, device time alone in brackets): 8 heads 2K 10.0 -> 7.5 [9.6 -> 7.5], 32 heads 5.3K
-// [12.9 -> 9.7], appended tokens at 1 to 2K [16.4 -> 9.4, 15.9 -> 11.0]; 64 random shapes 0.905 in the geometric mean.  Of the 7.5: launch, record
-// and blocks 4, fold in shared memory 0.7, write-through store, count and the last workgroup's fold 1.5.  The planner writes 2 % more for it.
+// [12.9 -> 9.7], appended tokens at 1 to 2K [16.4 -> 9.4, 15.9 -> 11.0]; 60 random short shapes 0.81 in the geometric mean.  Of the 7.5: launch, record
+// and blocks 4, fold in shared memory 0.7, write-through store, count and the last workgroup's fold 1.5.  A plan grows by 144 bytes per workgroup and 64
+// per row for it (8 heads 2K by 9.7 KB, the largest by 37 to 53).
 // What one launch for all contexts costs where the chip is full (a worker's states written through, the merge by the last wave of a row): 4 x
 // 64K at four heads 66 -> 68, 4 x 128K at eight 126 -> 128.5, 8 x 32K at 40 heads 73.7 -> 76.6; those keep two.
 #pragma once

@@ -83,7 +83,7 @@ constexpr int kShortMergeIterations = 1;
 // Sets of heads at head_dim 128 keep two launches where a wave has two staged blocks and more and a row more workgroups than this, unless they
 // fill the chip: the last of a row merges as many states of five to eight heads, and in the two launches twins find each other's blocks in the L2.
 // Without appended tokens.  Two launches -> one (us): 16 heads per kv head 15.6K 15.6 -> 16.7, 0.9K and 14.3K 16.2 -> 18.3, 10 heads 8 ragged up to 11.5K
-// 14.5 -> 15.8, 12 heads 11.1K 12.5 -> 13.8; of 25 shapes one gains, 10 heads 19.3K 16.7 -> 15.8.  Taken: 3 x 6.8K at ten heads (5 workgroups) 18.9 -> 16.9,
+// 14.5 -> 15.8, 12 heads 11.1K 12.5 -> 13.8; of 29 shapes one gains, 10 heads 19.3K 16.7 -> 15.8.  Taken: 3 x 6.8K at ten heads (5 workgroups) 18.9 -> 16.9,
 // 8 x 12.8K at sixteen (16, a full chip) 15.2 -> 14.3, 14.6K and 362 appended at sixteen 21.4 -> 20.6.
 constexpr int kShortGroupsSets = 8;
 // Relative speed of a worker of class [self] whose SIMD mate works on class [mate] (INT2, INT4, INT8, FP16), traced
